@@ -98,7 +98,8 @@ size_t nm_mask_bytes(int64_t O, int64_t K);
  * possibly 0).  The product kernels consume the weight in matrix-core operand order, which
  * depends on the kernel the token count selects; whenever the packed layout is not already
  * that order the call first rewrites the packed weight into the scratch (large layers: always).
- * 0 if the level or shape is illegal. */
+ * Where K is no multiple of 64 the scratch is optional: without it a slower kernel reads the
+ * packed layout.  0 if the level or shape is illegal. */
 size_t nm_spmm_workspace_bytes(int64_t O, int64_t K, int32_t N, int32_t M, int64_t T);
 
 /*
@@ -220,9 +221,11 @@ int32_t nm_pack_ranked_batched(const nm_pack_ranked_desc* descs, int32_t count, 
  *                    kernel reads the packed format itself (Fig. 2: values + positions, decoded on the fly;
  *                    slower than the workspace path, nothing to prepare).  Every other shape reports
  *                    NM_ERR_WORKSPACE.
- * The matrix-core kernels need K % 64 == 0, 16-byte aligned X, values and Y and ldx, ldy
- * multiples of 8; other shapes run a slower general kernel with the same results.  Rows of X and Y
- * that start on 128-byte boundaries (ldx, ldy multiples of 64) are fastest.
+ * The fastest matrix-core kernels need K % 64 == 0, 16-byte aligned X, values and Y and ldx, ldy
+ * multiples of 8; any other K above 64 and any other alignment of X and Y runs a matrix-core kernel that
+ * stages X through registers (it needs the workspace); what is left (K < 64, no workspace) runs a slower
+ * general kernel with the same results.  Rows of X and Y that start on 128-byte boundaries (ldx, ldy multiples
+ * of 64) are fastest.
  */
 int32_t nm_spmm(const nm_bf16* values, const uint32_t* indices, int64_t O, int64_t K,
                 int32_t N, int32_t M, const nm_bf16* X, int64_t T, int64_t ldx,

@@ -551,9 +551,10 @@ def nm_linear_forward(values, indices, K: int, N: int, M: int, X, bias=None, out
         raise ValueError("out must be [T, O]")
     need = 0 if from_packed else nm_spmm_workspace_bytes(O, K, N, M, T)
     if workspace is None and need:
-        if _prepared:
+        if not _prepared:
+            workspace = _workspace(need, X.device, stream)
+        elif K % 64 == 0:  # (a ragged reduction can do without one)
             raise ValueError("a prepared call needs the workspace nm_spmm_prepare filled")
-        workspace = _workspace(need, X.device, stream)
     ws_ptr = workspace.data_ptr() if workspace is not None else None
     ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
     bias_ptr = None

@@ -354,8 +354,10 @@ nm_tgemm_kernel(const TGemmArgs a) {
       write_wave_tile_pieces<IT, JT, 2>(smem + wave * wave_tile_slice_bytes<IT, 2>(), lane, get, a.out, a.ldo, row0, col0, a.J, a.I);
     else
       write_wave_tile_pieces<IT, JT, 4>(smem + wave * wave_tile_slice_bytes<IT, 4>(), lane, get, a.out, a.ldo, row0, col0, a.J, a.I);
+  } else if (a.out_bf16) {
+    write_wave_tile_rows<IT, JT, 2>(smem + wave * wave_tile_slice_bytes<IT, 4>(), lane, get, a.out, a.ldo, row0, col0, a.J, a.I);
   } else {
-    write_wave_tile_elements<IT, JT>(lane, get, a.out, a.ldo, row0, col0, a.J, a.I, a.out_bf16 != 0);
+    write_wave_tile_rows<IT, JT, 4>(smem + wave * wave_tile_slice_bytes<IT, 4>(), lane, get, a.out, a.ldo, row0, col0, a.J, a.I);
   }
 }
 

@@ -103,24 +103,31 @@ __device__ __forceinline__ void write_wave_tile_pieces(unsigned char* slice, int
   }
 }
 
-// Any alignment: element by element.
-template <int OT, int TT, typename Get>
-__device__ __forceinline__ void write_wave_tile_elements(int lane, Get get, void* Y, int64_t ldy, int64_t row0, int64_t col0,
-                                                         int64_t n_rows, int64_t n_cols, bool to_bf16) {
+// Any alignment, any row length: 16 rows at a time through the wave's LDS slice (wave_tile_slice_bytes<OT, 4>) as
+// 32-bit patterns, then one element per lane, consecutive lanes on consecutive columns of a row, so that a store
+// instruction covers one contiguous row segment (or two) instead of 64 scattered elements.
+template <int OT, int TT, int ES, typename Get>
+__device__ __forceinline__ void write_wave_tile_rows(unsigned char* slice, int lane, Get get, void* Y, int64_t ldy,
+                                                     int64_t row0, int64_t col0, int64_t n_rows, int64_t n_cols) {
+  constexpr int OW = OT * 16;
+  static_assert(OW <= 64 && 64 % OW == 0, "whole rows per store");
+  constexpr int RS = OW * 4 + 16;       // padded LDS row
+  constexpr int ROWS = 64 / OW;         // rows per store instruction
   const int r16 = lane & 15, kb = lane >> 4;
+  const int col = lane % OW;
+  const bool col_ok = col0 + col < n_cols;
 #pragma unroll
   for (int j = 0; j < TT; ++j) {
-    const int64_t r = row0 + j * 16 + r16;
-    if (r >= n_rows) continue;
 #pragma unroll
-    for (int i = 0; i < OT; ++i) {
-      const int64_t c = col0 + i * 16 + kb * 4;
-      const u32x4_t v = get(i, j);
+    for (int i = 0; i < OT; ++i) *reinterpret_cast<u32x4_t*>(slice + r16 * RS + (i * 16 + kb * 4) * 4) = get(i, j);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if (c + e >= n_cols) break;
-        if (to_bf16) reinterpret_cast<bf16_t*>(Y)[r * ldy + c + e] = (bf16_t)f32_to_bf16_rne(__uint_as_float(v[e]));
-        else reinterpret_cast<uint32_t*>(Y)[r * ldy + c + e] = v[e];
+    for (int q = 0; q < 16 / ROWS; ++q) {
+      const int row = q * ROWS + lane / OW;
+      const uint32_t v = *reinterpret_cast<const uint32_t*>(slice + row * RS + col * 4);
+      const int64_t r = row0 + j * 16 + row;
+      if (r < n_rows && col_ok) {
+        if constexpr (ES == 2) reinterpret_cast<bf16_t*>(Y)[r * ldy + col0 + col] = (bf16_t)f32_to_bf16_rne(__uint_as_float(v));
+        else reinterpret_cast<uint32_t*>(Y)[r * ldy + col0 + col] = v;
       }
     }
   }

@@ -41,87 +41,98 @@ namespace nm {
 // kept value of the run goes to slot 2q with selector = its offset in the run, a second one to slot 2q+1; free slots
 // hold +0 with selector 0 (the matrix instruction is a plain multiplexer per slot, so any selector of a zero slot
 // is harmless).
-// ---------------------------------------------------------------------------------------------
-
+//
+// One lane per 16 consecutive weights of a row (one 16-byte piece of the 2:4 form, two of the dense form).  K need
+// not be a whole number of steps: K_pad is K rounded up to one, and what lies past K is zero.  The kept values go to
+// their places through 32 bytes of LDS per lane: a 2-byte LDS write per value instead of a comparison with every
+// place it could have.
 template <int N, int M>
 __global__ void __launch_bounds__(256)
-recode_stream_kernel(const bf16_t* __restrict__ values, const uint32_t* __restrict__ indices, int64_t O, int64_t O_pad,
-                     int64_t K, unsigned char* __restrict__ vals_s, unsigned char* __restrict__ sel_s) {
+operand_stream_kernel(const bf16_t* __restrict__ values, const uint32_t* __restrict__ indices, int64_t O, int64_t O_pad,
+                      int64_t K, int64_t K_pad, int wide, unsigned char* __restrict__ vals_s,
+                      unsigned char* __restrict__ sel_s) {
   constexpr int B = log2_of(M);
-  constexpr int G = 32 / M;
-  constexpr int RUNS = M / 4;
-  const int64_t per_row = K / 32;
+  constexpr int VPC = 16 / M * N;  // kept values of a chunk
+  constexpr bool SPARSE = N <= 2 && N < M;
+  constexpr int BYTES = SPARSE ? 16 : 32, STRIDE = BYTES + 16;
+  __shared__ __attribute__((aligned(16))) unsigned char places[256 * STRIDE];
+  const int64_t per_row = K_pad / 16;
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (id >= O_pad * per_row) return;
-  const int64_t o = id / per_row, blk = id % per_row;
-  uint32_t out[8];
+  int64_t o, kc;
+  if (O_pad * per_row < (int64_t)1 << 31) {  // the 32-bit division is a fifth of the 64-bit one
+    o = (uint32_t)id / (uint32_t)per_row;
+    kc = (uint32_t)id % (uint32_t)per_row;
+  } else {
+    o = id / per_row;
+    kc = id % per_row;
+  }
+  unsigned char* mine = places + threadIdx.x * STRIDE;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) out[i] = 0;
+  for (int i = 0; i < BYTES / 16; ++i) reinterpret_cast<uint4*>(mine)[i] = make_uint4(0, 0, 0, 0);
   uint32_t sel = 0;
-  if (o < O) {
-    const int64_t nf = K / M * N;
+  const int64_t nf = K / M * N, f0 = kc * VPC;
+  if (o < O && f0 < nf) {
     const int64_t nw = (nf * B + 31) / 32;
-    const int64_t f0 = blk * G * N;
-    const uint32_t fields = stream_bits(indices + o * nw, nw, f0 * B, G * N * B);
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      uint32_t prev_run = 0xFFFFFFFFu;
-#pragma unroll
-      for (int j = 0; j < N; ++j) {
-        const uint32_t p = (fields >> ((g * N + j) * B)) & (M - 1);
-        const uint32_t v = values[o * nf + f0 + g * N + j];
-        const uint32_t run = p >> 2, within = p & 3u;
-        const uint32_t second = (run == prev_run) ? 1u : 0u;
-        prev_run = run;
-#pragma unroll
-        for (int r = 0; r < RUNS; ++r) out[g * RUNS + r] |= (run == (uint32_t)r) ? (v << (16 * second)) : 0u;
-        sel |= within << (4 * (g * RUNS + run) + 2 * second);
-      }
-    }
-  }
-  // 32 weights = 16 slots = chunks 2*half, 2*half+1 of step blk/2
-  const int64_t nk = K / 64, ks = blk >> 1;
-  const int half = (int)(blk & 1);
-  *reinterpret_cast<uint4*>(vals_s + stream_piece_offset(o, ks, 2 * half, nk)) = make_uint4(out[0], out[1], out[2], out[3]);
-  *reinterpret_cast<uint4*>(vals_s + stream_piece_offset(o, ks, 2 * half + 1, nk)) = make_uint4(out[4], out[5], out[6], out[7]);
-  // selectors: per (tile, step) a 2 KiB block; rows r and r+16 of a 32-row pair share the word of a lane
-  // (r mod 16, kb): low half = the first row's 16 bits, high half = the second row's, which is what the
-  // matrix instruction's ABID modifier selects
-  *reinterpret_cast<uint16_t*>(sel_s + stream_selector_offset(o, ks, 2 * half, nk)) = (uint16_t)sel;
-  *reinterpret_cast<uint16_t*>(sel_s + stream_selector_offset(o, ks, 2 * half + 1, nk)) = (uint16_t)(sel >> 16);
-}
-
-// dense form: one lane per 8 consecutive weights (one 16-byte piece)
-__global__ void __launch_bounds__(256)
-expand_stream_kernel(const bf16_t* __restrict__ values, const uint32_t* __restrict__ indices, int64_t O, int64_t O_pad,
-                     int64_t K, int N, int M, unsigned char* __restrict__ dense_s) {
-  const int64_t per_row = K / 8;
-  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= O_pad * per_row) return;
-  const int64_t o = id / per_row, pc = id % per_row;
-  uint32_t w[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) w[i] = 0;
-  if (o < O) {
-    const int b = log2_of(M);
-    const int64_t nf = K / M * N;
-    const int64_t nw = (nf * b + 31) / 32;
     const uint32_t* row = indices + o * nw;
-    const int64_t k0 = pc * 8;
-    const int64_t g_first = k0 / M, g_last = (k0 + 7) / M;
-    for (int64_t g = g_first; g <= g_last; ++g) {
-      for (int j = 0; j < N; ++j) {
-        const int64_t f = g * N + j;
-        const int64_t k = g * M + stream_bits(row, nw, f * b, b);
-        const uint32_t v = values[o * nf + f];
+    const int64_t w0 = (f0 * B) >> 5;
+    const int sh = (int)((f0 * B) & 31);
+    uint64_t fields = row[w0];
+    if (sh + VPC * B > 32 && w0 + 1 < nw) fields |= (uint64_t)row[w0 + 1] << 32;
+    fields >>= sh;
+    if (VPC * B > 32 && sh && w0 + 2 < nw) fields |= (uint64_t)row[w0 + 2] << (64 - sh);
+    uint32_t v[VPC];
+    const bf16_t* src = values + o * nf + f0;
+    if (wide) {  // whole chunks at aligned addresses
+      if constexpr (VPC % 8 == 0) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) w[i] = (k == k0 + i) ? v : w[i];
+        for (int j = 0; j < VPC; j += 8) {
+          const uint4 q = *reinterpret_cast<const uint4*>(src + j);
+          v[j] = q.x & 0xFFFFu; v[j + 1] = q.x >> 16; v[j + 2] = q.y & 0xFFFFu; v[j + 3] = q.y >> 16;
+          v[j + 4] = q.z & 0xFFFFu; v[j + 5] = q.z >> 16; v[j + 6] = q.w & 0xFFFFu; v[j + 7] = q.w >> 16;
+        }
+      } else if constexpr (VPC % 2 == 0) {
+#pragma unroll
+        for (int j = 0; j < VPC; j += 2) {
+          const uint32_t q = *reinterpret_cast<const uint32_t*>(src + j);
+          v[j] = q & 0xFFFFu; v[j + 1] = q >> 16;
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < VPC; ++j) v[j] = src[j];
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < VPC; ++j) v[j] = f0 + j < nf ? src[j] : 0u;
+    }
+    uint32_t prev_run = 0xFFFFFFFFu;
+#pragma unroll
+    for (int j = 0; j < VPC; ++j) {
+      if (!wide && f0 + j >= nf) break;
+      const uint32_t pos = (uint32_t)(j / N * M) + ((uint32_t)(fields >> (B * j)) & (uint32_t)(M - 1));
+      if constexpr (SPARSE) {
+        const uint32_t run = pos >> 2;
+        const uint32_t second = run == prev_run ? 1u : 0u;
+        prev_run = run;
+        *reinterpret_cast<uint16_t*>(mine + 4 * run + 2 * second) = (uint16_t)v[j];
+        sel |= (pos & 3u) << (4 * run + 2 * second);
+      } else {
+        *reinterpret_cast<uint16_t*>(mine + 2 * pos) = (uint16_t)v[j];
       }
     }
   }
-  const int64_t nk = K / 32, ks = pc >> 2;
-  *reinterpret_cast<uint4*>(dense_s + stream_piece_offset(o, ks, (int)(pc & 3), nk)) =
-      make_uint4(w[0] | (w[1] << 16), w[2] | (w[3] << 16), w[4] | (w[5] << 16), w[6] | (w[7] << 16));
+  if constexpr (SPARSE) {
+    const int64_t nk = K_pad / 64;
+    *reinterpret_cast<uint4*>(vals_s + stream_piece_offset(o, kc >> 2, (int)(kc & 3), nk)) = *reinterpret_cast<const uint4*>(mine);
+    // rows r and r+16 of a 32-row pair share the selector word of a lane (r mod 16, chunk): low half = the first
+    // row's 16 bits, high half = the second row's, which is what the matrix instruction's ABID modifier selects
+    *reinterpret_cast<uint16_t*>(sel_s + stream_selector_offset(o, kc >> 2, (int)(kc & 3), nk)) = (uint16_t)sel;
+  } else {
+    const int64_t nk = K_pad / 32, ks = kc >> 1;
+    const int c0 = (int)(kc & 1) * 2;
+    *reinterpret_cast<uint4*>(vals_s + stream_piece_offset(o, ks, c0, nk)) = reinterpret_cast<const uint4*>(mine)[0];
+    *reinterpret_cast<uint4*>(vals_s + stream_piece_offset(o, ks, c0 + 1, nk)) = reinterpret_cast<const uint4*>(mine)[1];
+  }
 }
 
 // dense form of a TRANSPOSED weight: the operand rows are the columns of Ws [R, I] (row-major, ld ldw), the
@@ -168,6 +179,7 @@ struct GemmArgs {
   uint8_t stream_form;  // A (and sel) lie in stream order (the pre-pass's output), else row-major as packed
   uint8_t splits;       // ranges the reduction is cut into (tiled kernel only; 1 = the whole K in one block)
   uint8_t rot;          // tiled kernel: XCD x takes the layer's share number (x + rot) mod 8
+  uint8_t x_align;      // bytes every X row start is a multiple of: 16, 8, 4 or 2 (read by the register-staged form only)
 };
 
 template <bool SPARSE, int WO, int WT, int OT, int TT, int STAGES_>
@@ -221,7 +233,9 @@ __device__ __forceinline__ f32x4_t bias_init(const float* bias, int64_t o, int64
 // STREAM: the weight lies in stream order (the pre-pass's output: every 16-row x K-step slice one contiguous,
 // already swizzled kilobyte; selector words interleaved per 32-row pair), else row-major (the packed 2:4 layout
 // or a dense level's values, read as they lie).
-template <bool SPARSE, int WO, int WT, int OT, int TT, int STAGES, bool STREAM>
+// X_REGS: X travels through registers instead of by asynchronous copies, so that its rows may start anywhere and K
+// may end anywhere (see the loop); two stages.
+template <bool SPARSE, int WO, int WT, int OT, int TT, int STAGES, bool STREAM, bool X_REGS = false>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned block, unsigned char* smem) {
   using C = GemmCfg<SPARSE, WO, WT, OT, TT, STAGES>;
   static_assert(!STREAM || (OT % 2 == 0 && C::BO % 32 == 0 && 256 % C::BO == 0), "stream order: whole 32-row pairs inside one 256-row tile");
@@ -266,7 +280,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned block, uns
     x_voff[i] = (uint32_t)((row * a.ldx + c * 8) * 2);
     x_dst[i] = (uint32_t)(j * 1024);
   }
-  const int nk_all = (int)(a.K / C::KC);               // K steps of the layer
+  const int nk_all = (int)((a.K + C::KC - 1) / C::KC);  // K steps of the layer
   const int per_split = (nk_all + n_splits - 1) / n_splits;
   const int ks0 = split * per_split;                    // this block's steps: ks0 .. ks0 + nk - 1
   const int nk = nk_all - ks0 < per_split ? nk_all - ks0 : per_split;
@@ -278,7 +292,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned block, uns
       // first (h = 0) or second (h = 1) 32-wide step (dense form, two stream steps per stage)
       constexpr int GROUPS = C::BO / 16;
       const int rg = j % GROUPS, h = j / GROUPS;
-      a_voff[i] = (uint32_t)((((o0 >> 4) + rg) * (int64_t)(SPARSE ? nk_all : 2 * nk_all) + h) << 10) + (uint32_t)(lane * 16);
+      a_voff[i] = ((uint32_t)(rg * (SPARSE ? nk_all : 2 * nk_all) + h) << 10) + (uint32_t)(lane * 16);
       a_dst[i] = (uint32_t)(C::X_BYTES + h * (C::BO * 64) + rg * 1024);
     } else {
       int64_t row;
@@ -296,7 +310,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned block, uns
       const int j = (wave + i * C::NW) % C::S_LOADS;
       if constexpr (STREAM) {
         // the tile's share of the (256-row tile, step) selector block: 256 bytes per 32-row pair
-        s_voff[i] = (uint32_t)(((o0 >> 8) * (int64_t)nk_all << 11) + (((o0 & 255) >> 5) + j) * 256 + lane * 4);
+        s_voff[i] = (uint32_t)((((o0 & 255) >> 5) + j) * 256 + lane * 4);
       } else {
         int64_t row = 32 * j + (lane >> 1);
         if (row > o_last) row = o_last;
@@ -309,8 +323,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned block, uns
   constexpr int A_STEP = STREAM ? (SPARSE ? 512 : 1024) : (SPARSE ? 32 : 64);
   constexpr int S_STEP = STREAM ? 512 : 2;
   const bf16_t* x_base = a.X + t0 * a.ldx + (int64_t)ks0 * 64;
-  const bf16_t* a_base = (STREAM ? a.A : a.A + o0 * a_ld) + (int64_t)ks0 * A_STEP;
-  const uint32_t* s_base = SPARSE ? (STREAM ? a.sel : a.sel + o0 * (a.K >> 5)) + (int64_t)ks0 * S_STEP : nullptr;
+  const bf16_t* a_base = a.A + (STREAM ? (o0 >> 4) * (int64_t)nk_all * A_STEP : o0 * a_ld) + (int64_t)ks0 * A_STEP;
+  const uint32_t* s_base =
+      SPARSE ? a.sel + (STREAM ? (o0 >> 8) * (int64_t)nk_all * S_STEP : o0 * (a.K >> 5)) + (int64_t)ks0 * S_STEP : nullptr;
   // where the block's sums go: the output, or its range's partial sums (plain fp32 rows of O, no bias yet)
   void* out_ptr = a.Y;
   int64_t out_ld = a.ldy;
@@ -442,43 +457,121 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned block, uns
     else wait_loads_outstanding<0>();
   };
 
+  if constexpr (X_REGS) {
+    // Ragged operands.  A lane loads its 16-byte pieces of X with as many loads as the rows' alignment asks for and
+    // writes them to LDS where the asynchronous copies of the other form would put them; past K the piece is zero
+    // (so is the weight there: what lies behind a row's end never enters a sum).  The loads of step ks + 1 leave
+    // before step ks is multiplied and are written to the other buffer after it.  One stage is in flight and a
+    // step drains everything at its barrier, but the two small stages leave room for three blocks per compute unit.
+    static_assert(!X_REGS || (STAGES == 2 && STREAM), "register-staged form");
+    u32x4_t xr[C::X_PW];
+    const bf16_t* x_row_ptr[C::X_PW];
+    int x_k[C::X_PW];  // the piece's first k inside a step
 #pragma unroll
-  for (int s = 0; s < STAGES; ++s)
-    if (s < STAGES - 1 && s < nk) issue_stage(s);
-
-  // One barrier per stage; the buffer multiplied in the previous step is refilled right after the barrier,
-  // STAGES-1 stages ahead.  A wave issues one instruction at a time, so whatever the step spends on addresses and
-  // conditions its matrix instructions do not get: the steady state (every step has a stage to load) runs STAGES
-  // steps at a time, which makes every LDS buffer a constant and leaves the step without branches; the last steps
-  // run the general form.
-  int ks = 0;
-  for (; ks + 2 * STAGES - 2 < nk; ks += STAGES) {
-    [&]<int... B>(std::integer_sequence<int, B...>) {
-      ([&] {
-        constexpr int buf = B, nbuf = (B + STAGES - 1) % STAGES;
-        wait_stage(STAGES == 3 ? 1 : 0);
-        __builtin_amdgcn_s_barrier();
+    for (int i = 0; i < C::X_PW; ++i) {
+      const int j = (wave + i * C::NW) % C::X_LOADS;
+      int64_t row = 8 * j + (lane >> 3);
+      x_k[i] = ((lane & 7) ^ (int)(row & 7)) * 8;
+      if (row > t_last) row = t_last;
+      x_row_ptr[i] = a.X + (t0 + row) * a.ldx + x_k[i];
+    }
+    auto fetch_x = [&](int ks) {
+      const int64_t left = a.K - (int64_t)ks * 64;  // elements of the rows from this step on
 #pragma unroll
-        for (int h = 0; h < H; ++h) {
-          read_frags(buf, h);
-          multiply(h == 0, nbuf);
+      for (int i = 0; i < C::X_PW; ++i) {
+        const bf16_t* src = x_row_ptr[i] + (int64_t)ks * 64;
+        const int n = left - x_k[i] >= 8 ? 8 : (left - x_k[i] > 0 ? (int)(left - x_k[i]) : 0);  // a multiple of 4: K is one
+        u32x4_t v = u32x4_t{0, 0, 0, 0};
+        if (a.x_align == 16) {
+          if (n == 8) v = *reinterpret_cast<const u32x4_t*>(src);
+          else if (n == 4) { const uint2 h = *reinterpret_cast<const uint2*>(src); v[0] = h.x; v[1] = h.y; }
+        } else if (a.x_align == 8) {
+          if (n >= 4) { const uint2 h = *reinterpret_cast<const uint2*>(src); v[0] = h.x; v[1] = h.y; }
+          if (n == 8) { const uint2 h = *reinterpret_cast<const uint2*>(src + 4); v[2] = h.x; v[3] = h.y; }
+        } else if (a.x_align == 4) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (2 * e < n) v[e] = *reinterpret_cast<const uint32_t*>(src + 2 * e);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (2 * e < n) v[e] = (uint32_t)src[2 * e] | ((uint32_t)src[2 * e + 1] << 16);
         }
-      }(), ...);
-    }(std::make_integer_sequence<int, STAGES>{});
-  }
-  {
-    int buf = 0;  // ks is a multiple of STAGES here
-    for (; ks < nk; ++ks) {
-      wait_stage((STAGES == 3 && ks + 1 < nk) ? 1 : 0);
+        xr[i] = v;
+      }
+    };
+    auto put_x = [&](int buf) {
+#pragma unroll
+      for (int i = 0; i < C::X_PW; ++i)
+        *reinterpret_cast<u32x4_t*>(smem + buf * C::STAGE + x_dst[i] + lane * 16) = xr[i];
+    };
+    auto issue_weight = [&](int buf) {
+      [&]<int... D>(std::integer_sequence<int, D...>) {
+        (issue_one(std::integral_constant<int, C::X_PW + D>{}, buf), ...);
+      }(std::make_integer_sequence<int, C::LPW - C::X_PW>{});
+    };
+    auto stage_done = [&]() {
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
       __builtin_amdgcn_s_barrier();
-      int nbuf = buf + STAGES - 1;
-      if (nbuf >= STAGES) nbuf -= STAGES;
+      asm volatile("" ::: "memory");
+    };
+    issue_weight(0);
+    fetch_x(0);
+    put_x(0);
+    stage_done();
+    for (int ks = 0; ks < nk; ++ks) {
+      const int buf = ks & 1;
+      if (ks + 1 < nk) {
+        issue_weight(buf ^ 1);
+        fetch_x(ks + 1);
+      }
 #pragma unroll
       for (int h = 0; h < H; ++h) {
         read_frags(buf, h);
-        multiply(h == 0 && ks + STAGES - 1 < nk, nbuf);
+        multiply(false, 0);
       }
-      if (++buf == STAGES) buf = 0;
+      if (ks + 1 < nk) put_x(buf ^ 1);
+      stage_done();
+    }
+  } else {
+#pragma unroll
+    for (int s = 0; s < STAGES; ++s)
+      if (s < STAGES - 1 && s < nk) issue_stage(s);
+
+    // One barrier per stage; the buffer multiplied in the previous step is refilled right after the barrier,
+    // STAGES-1 stages ahead.  A wave issues one instruction at a time, so whatever the step spends on addresses and
+    // conditions its matrix instructions do not get: the steady state (every step has a stage to load) runs STAGES
+    // steps at a time, which makes every LDS buffer a constant and leaves the step without branches; the last steps
+    // run the general form.
+    int ks = 0;
+    for (; ks + 2 * STAGES - 2 < nk; ks += STAGES) {
+      [&]<int... B>(std::integer_sequence<int, B...>) {
+        ([&] {
+          constexpr int buf = B, nbuf = (B + STAGES - 1) % STAGES;
+          wait_stage(STAGES == 3 ? 1 : 0);
+          __builtin_amdgcn_s_barrier();
+#pragma unroll
+          for (int h = 0; h < H; ++h) {
+            read_frags(buf, h);
+            multiply(h == 0, nbuf);
+          }
+        }(), ...);
+      }(std::make_integer_sequence<int, STAGES>{});
+    }
+    {
+      int buf = 0;  // ks is a multiple of STAGES here
+      for (; ks < nk; ++ks) {
+        wait_stage((STAGES == 3 && ks + 1 < nk) ? 1 : 0);
+        __builtin_amdgcn_s_barrier();
+        int nbuf = buf + STAGES - 1;
+        if (nbuf >= STAGES) nbuf -= STAGES;
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+          read_frags(buf, h);
+          multiply(h == 0 && ks + STAGES - 1 < nk, nbuf);
+        }
+        if (++buf == STAGES) buf = 0;
+      }
     }
   }
 
@@ -495,8 +588,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned block, uns
       write_wave_tile_pieces<OT, TT, 2>(smem + wave * wave_tile_slice_bytes<OT, 2>(), lane, get, out_ptr, out_ld, row0, col0, a.T, a.O);
     else
       write_wave_tile_pieces<OT, TT, 4>(smem + wave * wave_tile_slice_bytes<OT, 4>(), lane, get, out_ptr, out_ld, row0, col0, a.T, a.O);
+  } else if (out_bf16) {
+    write_wave_tile_rows<OT, TT, 2>(smem + wave * wave_tile_slice_bytes<OT, 4>(), lane, get, out_ptr, out_ld, row0, col0, a.T, a.O);
   } else {
-    write_wave_tile_elements<OT, TT>(lane, get, out_ptr, out_ld, row0, col0, a.T, a.O, out_bf16);
+    write_wave_tile_rows<OT, TT, 4>(smem + wave * wave_tile_slice_bytes<OT, 4>(), lane, get, out_ptr, out_ld, row0, col0, a.T, a.O);
   }
 }
 
@@ -508,6 +603,14 @@ nm_gemm_kernel(const GemmArgs a) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   if (a.stream_form) gemm_tile<SPARSE, WO, WT, OT, TT, STAGES, true>(a, blockIdx.x, smem);
   else gemm_tile<SPARSE, WO, WT, OT, TT, STAGES, false>(a, blockIdx.x, smem);
+}
+
+// Any K, any alignment of X and Y: the weight in stream order (K padded with zeros to whole steps), X through registers.
+template <bool SPARSE, int WO, int WT, int OT, int TT>
+__global__ void __launch_bounds__(WO * WT * 64)
+nm_gemm_ragged_kernel(const GemmArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  gemm_tile<SPARSE, WO, WT, OT, TT, 2, true, true>(a, blockIdx.x, smem);
 }
 
 // The tiles of many small layers in one launch, whatever their operand form and weight order: products of a few
@@ -1275,21 +1378,30 @@ static int pick_tile(int64_t O, int64_t K, int64_t T, bool sparse_form) {
   return pick_tile(O, T, sparse_form ? K / 64 : K / 32, K / 64, sparse_form ? 0.34 : 0.5);
 }
 
+// A reduction that is no whole number of 64-wide steps: the ragged form of the tiled kernel multiplies it from stream
+// order padded with zeros.  The workspace it needs is optional (without it the gather kernel reads the packed layout);
+// a reduction shorter than one step is left to the gather kernel and asks for none.
+static bool ragged_shape(int64_t O, int64_t K, int64_t T) {
+  return (K % 64) != 0 && K > 64 && O <= (1 << 24) && T < (1ll << 31) && K <= (1 << 22);
+}
+static int64_t padded_k(int64_t K) { return (K + 63) / 64 * 64; }
+
 // The form in which the product kernels read a layer's weight at T tokens.
-//   FORM_PACKED  as packed: the gather kernel (K % 64 != 0), or the tiled kernel at 2:4 and at N = M, whose packed
-//                layouts already are the row-major 2:4 / dense operands
-//   FORM_STREAM  stream order in the workspace (2:4 form for N <= 2, dense form otherwise): every other level, and
-//                every level on the persistent kernel
+//   FORM_PACKED  as packed: the gather kernel, or the tiled kernel at 2:4 and at N = M, whose packed layouts already
+//                are the row-major 2:4 / dense operands
+//   FORM_STREAM  stream order in the workspace (2:4 form for N <= 2, dense form otherwise): every other level, every
+//                level on the persistent kernel, and every level where K is no whole number of steps
 enum { FORM_PACKED = 0, FORM_STREAM = 1 };
 static int operand_form(int64_t O, int64_t K, int64_t T, int N, int M, bool* sparse_form) {
   *sparse_form = N <= 2 && N < M;
-  if (K % 64) return FORM_PACKED;
+  if (K % 64) return ragged_shape(O, K, T) ? FORM_STREAM : FORM_PACKED;
   const bool as_packed = (N == 2 && M == 4) || N == M;
   return (pick_tile(O, K, T, *sparse_form) != 0 && as_packed) ? FORM_PACKED : FORM_STREAM;
 }
 
+// whether the layer's weight lies in stream order without padding along K (what a packing kernel can write as it goes)
 bool spmm_stream_order(int64_t O, int64_t K, int64_t T, int N, int M, bool* sparse_form) {
-  return operand_form(O, K, T, N, M, sparse_form) == FORM_STREAM;
+  return K % 64 == 0 && operand_form(O, K, T, N, M, sparse_form) == FORM_STREAM;
 }
 
 // Ranges the reduction of a layer on the tiled kernel is cut into: a layer with far fewer tiles than the chip has
@@ -1314,12 +1426,14 @@ static int split_count(int64_t O, int64_t K, int64_t T, bool sparse_form) {
 static size_t operand_bytes(int64_t O, int64_t K, int N, int M, int64_t T, bool* sparse_form) {
   if (operand_form(O, K, T, N, M, sparse_form) != FORM_STREAM) return 0;
   const size_t o_pad = (size_t)((O + 255) / 256) * 256;  // whole 256-row tiles
-  return *sparse_form ? o_pad * (size_t)K + o_pad * (size_t)K / 8 : o_pad * (size_t)K * 2;
+  const size_t k_pad = (size_t)padded_k(K);
+  return *sparse_form ? o_pad * k_pad + o_pad * k_pad / 8 : o_pad * k_pad * 2;
 }
 
 // The part of the workspace a product cannot do without: the operand-order copy.  With no more than that the
-// reduction stays in one piece.
+// reduction stays in one piece.  (A ragged reduction can do without: the gather kernel takes it then.)
 size_t spmm_operand_workspace_bytes(int64_t O, int64_t K, int N, int M, int64_t T) {
+  if (K % 64) return 0;
   bool sparse_form = false;
   return operand_bytes(O, K, N, M, T, &sparse_form);
 }
@@ -1541,6 +1655,29 @@ static hipError_t dispatch_gemm(const GemmArgs& g, int pick, hipStream_t s) {
   }
 }
 
+// The ragged form of the tiled kernel: 128 x 128 tiles once there is one for every compute unit, else 64 x 64.  A call
+// on 1579 tokens x 1000 -> 1001 out-features at 2:8 (pre-pass and product) takes 20.8 us; the gather kernel, which
+// took such shapes before and still takes them when there is no workspace, 1096 us.
+template <bool SPARSE>
+static hipError_t launch_ragged(GemmArgs g, hipStream_t s) {
+  auto go = [&](auto kern, int bo, int bt, int threads, int lds, PerDeviceOnce& once) {
+    if (hipError_t e = raise_dynamic_lds_limit(kern, lds, once); e != hipSuccess) return e;
+    g.n_o_tiles = (int)((g.O + bo - 1) / bo);
+    g.n_t_tiles = (int)((g.T + bt - 1) / bt);
+    const int64_t grid = (((int64_t)g.n_o_tiles * g.n_t_tiles + 7) / 8) * 8;
+    if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), lds, s, g);
+    return hipGetLastError();
+  };
+  static PerDeviceOnce once_mid, once_small;
+  if (((g.O + 127) / 128) * ((g.T + 127) / 128) >= 256) {
+    using C = GemmCfg<SPARSE, 2, 2, 4, 4, 2>;
+    return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 4, 4>, C::BO, C::BT, C::NT, C::LDS_BYTES, once_mid);
+  }
+  using C = GemmCfg<SPARSE, 2, 2, 2, 2, 2>;
+  return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 2, 2>, C::BO, C::BT, C::NT, C::LDS_BYTES, once_small);
+}
+
 static hipError_t launch_general(const SpmmArgs& a, hipStream_t s) {
   const int64_t n_o_tiles = (a.O + 15) / 16, n_t_tiles = (a.T + 15) / 16;
   if (n_o_tiles * n_t_tiles > 0x7FFFFFFF) return hipErrorInvalidValue;
@@ -1583,28 +1720,30 @@ hipError_t launch_dense_transposed(const bf16_t* Ws, int64_t R, int64_t I, int64
   return dispatch_gemm<false>(g, 0, s);
 }
 
+#define NM_FOR_EACH_LEVEL(X)                                                                         \
+  X(1, 4) X(2, 4) X(3, 4) X(4, 4)                                                                    \
+  X(1, 8) X(2, 8) X(3, 8) X(4, 8) X(5, 8) X(6, 8) X(7, 8) X(8, 8)                                    \
+  X(1, 16) X(2, 16) X(3, 16) X(4, 16) X(5, 16) X(6, 16) X(7, 16) X(8, 16) X(9, 16) X(10, 16)         \
+  X(11, 16) X(12, 16) X(13, 16) X(14, 16) X(15, 16) X(16, 16)
+
 // The stream-order pre-pass of a layer into its workspace.
 static hipError_t launch_stream_prepass(const SpmmArgs& a, bool sparse_form, hipStream_t s) {
   unsigned char* ws = reinterpret_cast<unsigned char*>(a.workspace);
-  const int64_t o_pad = ((a.O + 255) / 256) * 256;
-  if (sparse_form) {
-    unsigned char* sel_s = ws + (size_t)o_pad * (size_t)a.K;
-    const int64_t n = o_pad * (a.K / 32);
-    const dim3 grid((unsigned)((n + 255) / 256));
-    switch (a.N * 32 + a.M) {
-#define X(n_, m_)                                                                                              \
-  case n_ * 32 + m_:                                                                                           \
-    hipLaunchKernelGGL((recode_stream_kernel<n_, m_>), grid, dim3(256), 0, s, a.values, a.indices, a.O, o_pad, a.K, \
-                       ws, sel_s);                                                                             \
+  const int64_t o_pad = ((a.O + 255) / 256) * 256, k_pad = padded_k(a.K);
+  unsigned char* sel_s = sparse_form ? ws + (size_t)o_pad * (size_t)k_pad : nullptr;
+  const int64_t n = o_pad * (k_pad / 16);
+  if ((n + 255) / 256 > 0x7FFFFFFF) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)((n + 255) / 256));
+  const int wide = (a.K % 16 == 0) && aligned_to(a.values, 16);  // every 16-weight chunk is whole and its values aligned
+  switch (a.N * 32 + a.M) {
+#define X(n_, m_)                                                                                                  \
+  case n_ * 32 + m_:                                                                                               \
+    hipLaunchKernelGGL((operand_stream_kernel<n_, m_>), grid, dim3(256), 0, s, a.values, a.indices, a.O, o_pad, a.K, \
+                       k_pad, wide, ws, sel_s);                                                                    \
     break;
-      X(1, 4) X(2, 4) X(1, 8) X(2, 8) X(1, 16) X(2, 16)
+    NM_FOR_EACH_LEVEL(X)
 #undef X
-      default: return hipErrorInvalidValue;
-    }
-  } else {
-    const int64_t n = o_pad * (a.K / 8);
-    hipLaunchKernelGGL(expand_stream_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.values, a.indices,
-                       a.O, o_pad, a.K, a.N, a.M, ws);
+    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
@@ -1616,6 +1755,10 @@ static void fill_gemm_args(const SpmmArgs& a, int form, bool sparse_form, GemmAr
   g->out_bf16 = a.out_bf16;
   g->n_o_tiles = g->n_t_tiles = 0;
   g->rot = 0;
+  {
+    const uintptr_t at = (uintptr_t)a.X | (uintptr_t)(a.ldx * 2);
+    g->x_align = (at & 15) == 0 ? 16 : (at & 7) == 0 ? 8 : (at & 3) == 0 ? 4 : 2;
+  }
   // 16-byte pieces of Y rows: every row start and the row end fall on a piece boundary
   const int per_piece = a.out_bf16 ? 8 : 4;
   g->vec_store = (a.ldy % per_piece == 0) && aligned_to(a.Y, 16) && (a.O % per_piece == 0) &&
@@ -1638,7 +1781,7 @@ static void fill_gemm_args(const SpmmArgs& a, int form, bool sparse_form, GemmAr
     const int64_t o_pad = ((a.O + 255) / 256) * 256;
     unsigned char* ws = reinterpret_cast<unsigned char*>(a.workspace);
     g->A = reinterpret_cast<const bf16_t*>(ws);
-    g->sel = sparse_form ? reinterpret_cast<const uint32_t*>(ws + (size_t)o_pad * (size_t)a.K) : nullptr;
+    g->sel = sparse_form ? reinterpret_cast<const uint32_t*>(ws + (size_t)o_pad * (size_t)padded_k(a.K)) : nullptr;
   } else {
     g->A = a.values;  // 2:4: values + index words are the row-major 2:4 operand; N = M: the dense weight
     g->sel = sparse_form ? a.indices : nullptr;
@@ -1657,12 +1800,28 @@ static bool packed_path(const SpmmArgs& a) {
 hipError_t launch_spmm(const SpmmArgs& a, hipStream_t s, bool* workspace_short, int phases) {
   *workspace_short = false;
   const bool prepare = phases & SPMM_PREPARE, product = phases & SPMM_PRODUCT;
-  if (!tiles_ok(a.K, a.X, a.ldx, a.values, a.indices, a.O, a.T)) {
-    if (!product) return hipSuccess;  // the gather kernel reads the packed layout itself
-    return launch_general(a, s);
-  }
   bool sparse_form = false;
   const int form = operand_form(a.O, a.K, a.T, a.N, a.M, &sparse_form);
+  // The ragged form of the tiled kernel: stream order in the workspace, any X and Y.  For K % 64 == 0 (an X that the
+  // other kernels cannot take) the weight has to be one that the prepare call, which does not see X, has written.
+  auto ragged_product = [&]() {
+    GemmArgs g;
+    fill_gemm_args(a, form, sparse_form, &g);
+    g.splits = 1; g.partial = nullptr;
+    return sparse_form ? launch_ragged<true>(g, s) : launch_ragged<false>(g, s);
+  };
+  const bool copy_fits = form == FORM_STREAM && a.workspace != nullptr && aligned_to(a.workspace, 256) &&
+                         a.workspace_bytes >= operand_bytes(a.O, a.K, a.N, a.M, a.T, &sparse_form);
+  if (!tiles_ok(a.K, a.X, a.ldx, a.values, a.indices, a.O, a.T)) {
+    // without the workspace the gather kernel reads the packed layout itself
+    const bool ragged = copy_fits && (a.K % 64 != 0 || tiles_ok(a.K, nullptr, a.K, a.values, a.indices, a.O, a.T));
+    if (ragged && prepare) {
+      hipError_t e = launch_stream_prepass(a, sparse_form, s);
+      if (e != hipSuccess) return e;
+    }
+    if (!product) return hipSuccess;
+    return ragged ? ragged_product() : launch_general(a, s);
+  }
   const size_t need = spmm_operand_workspace_bytes(a.O, a.K, a.N, a.M, a.T);
   if (need && (a.workspace == nullptr || a.workspace_bytes < need || !aligned_to(a.workspace, 256))) {
     // no workspace: few tokens can still be multiplied straight from the packed format
@@ -1676,15 +1835,13 @@ hipError_t launch_spmm(const SpmmArgs& a, hipStream_t s, bool* workspace_short, 
   const int pick = pick_tile(a.O, a.K, a.T, sparse_form);
   GemmArgs g;
   fill_gemm_args(a, form, sparse_form, &g);
-  // the persistent kernel writes Y in 16-byte pieces only; other outputs go to the gather kernel, which reads the
-  // packed layout itself
-  const bool gather = pick == 0 && (!g.vec_store || a.ldy > 0x7FFFFFFF);
-  if (prepare && form == FORM_STREAM && !(gather && product)) {
+  if (prepare && form == FORM_STREAM) {
     hipError_t e = launch_stream_prepass(a, sparse_form, s);
     if (e != hipSuccess) return e;
   }
   if (!product) return hipSuccess;
-  if (gather) return launch_general(a, s);
+  // the persistent kernel writes Y in 16-byte pieces only; other outputs take the ragged form of the tiled kernel
+  if (pick == 0 && (!g.vec_store || a.ldy > 0x7FFFFFFF)) return ragged_product();
   return sparse_form ? dispatch_gemm<true>(g, pick, s) : dispatch_gemm<false>(g, pick, s);
 }
 

@@ -1,0 +1,82 @@
+"""GPU parity of products whose operands fit no tile: a reduction that is no multiple of 64, rows of X that start at any
+element, outputs whose rows are not whole 16-byte pieces."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2409_09708_amd as nm
+from oracle import nm_oracle as orc
+from paper_2409_09708_amd import workloads as wl
+from gpu_util import check_output, dev_bf16, host_output
+
+pytestmark = pytest.mark.gpu
+
+
+def layer(seed, T, K, O, N, M):
+    rng = np.random.default_rng(seed)
+    X, W = wl.draw_activations(rng, T, K), wl.draw_weights(rng, O, K)
+    bias = rng.standard_normal(O).astype(np.float32)
+    Yref, B = orc.nm_linear_from_bits(X, W, N, M, bias=bias)
+    v, i = nm.nm_pack(dev_bf16(W), N, M)
+    return X, v, i, torch.from_numpy(bias).cuda(), Yref, B + np.abs(bias)[None, :]
+
+
+# K just above one step, half a step, a step but four, one group past a step; O and T off every tile edge; a few tiles
+# (64 x 64) and enough for the 128 x 128 ones
+@pytest.mark.parametrize("N,M", [(1, 4), (2, 4), (3, 4), (4, 4), (2, 8), (4, 8), (8, 8), (1, 16), (2, 16), (4, 16), (16, 16)])
+@pytest.mark.parametrize("T,K,O", [(1, 80, 1), (67, 96, 65), (130, 176, 131), (197, 1072, 77), (2049, 144, 2047)])
+def test_reductions_off_the_step(T, K, O, N, M):
+    X, v, i, bias, Yref, B = layer(11000 + N * 17 + M + T + K, T, K, O, N, M)
+    Xd = dev_bf16(X)
+    y = nm.nm_linear_forward(v, i, K, N, M, Xd, bias=bias)
+    check_output(host_output(y), Yref, B, K // M * N + 1, True, (T, K, O, N, M))
+    y16 = nm.nm_linear_forward(v, i, K, N, M, Xd, bias=bias, out_dtype=torch.bfloat16)
+    check_output(host_output(y16), Yref, B, K // M * N + 1, False, (T, K, O, N, M))
+    ws = nm.nm_spmm_prepare(v, i, K, N, M, T)
+    assert ws is not None
+    assert torch.equal(y, nm.nm_linear_forward_prepared(v, i, K, N, M, Xd, ws, bias=bias))
+
+
+@pytest.mark.parametrize("K", [68, 100, 124, 132, 252])  # multiples of 4 only
+def test_reductions_that_end_inside_a_piece(K):
+    T, O, N, M = 70, 66, 2, 4
+    X, v, i, bias, Yref, B = layer(11500 + K, T, K, O, N, M)
+    y = nm.nm_linear_forward(v, i, K, N, M, dev_bf16(X), bias=bias)
+    check_output(host_output(y), Yref, B, K // M * N + 1, True, K)
+
+
+# X and Y as views: rows that start on 16-, 8-, 4- and 2-byte boundaries; what lies beside the view (NaN around X, a
+# guard value around Y) is neither read into a sum nor written
+@pytest.mark.parametrize("offset,pad", [(0, 8), (4, 12), (2, 6), (1, 7), (3, 1)])
+@pytest.mark.parametrize("K,N,M", [(104, 2, 8), (192, 4, 8), (192, 1, 4)])
+@pytest.mark.parametrize("T", [75, 4200])
+def test_views_of_any_alignment(offset, pad, K, N, M, T):
+    O = 263 if T < 4000 else 2051
+    X, v, i, bias, Yref, B = layer(11700 + K + N + T, T, K, O, N, M)
+    wide = torch.full((T, K + offset + pad), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wide[:, offset:offset + K] = dev_bf16(X)
+    out = torch.full((T, O + 2), 7.0, dtype=torch.bfloat16, device="cuda")
+    nm.nm_linear_forward(v, i, K, N, M, wide[:, offset:offset + K], bias=bias, out=out[:, 1:O + 1])
+    check_output(host_output(out[:, 1:O + 1].contiguous()), Yref, B, K // M * N + 1, False, (offset, pad, K, N, M, T))
+    assert bool((out[:, 0] == 7).all()) and bool((out[:, O + 1] == 7).all())
+
+
+def test_without_a_workspace_the_same_product():
+    T, K, O, N, M = 50, 200, 40, 2, 8
+    X, v, i, bias, Yref, B = layer(11900, T, K, O, N, M)
+    y = nm.nm_linear_forward(v, i, K, N, M, dev_bf16(X), bias=bias, from_packed=True)
+    check_output(host_output(y), Yref, B, K // M * N + 1, True, "gather kernel")
+    y = nm.nm_linear_forward_prepared(v, i, K, N, M, dev_bf16(X), None, bias=bias)
+    check_output(host_output(y), Yref, B, K // M * N + 1, True, "prepared, no workspace")
+    y = nm.nm_linear_forward_static(v, i, K, N, M, dev_bf16(X), bias=bias)
+    check_output(host_output(y), Yref, B, K // M * N + 1, True, "fixed scratch")
+
+
+def test_ragged_layers_packed_and_prepared_in_one_call():
+    rng = np.random.default_rng(11950)
+    specs = [(100, 96, 256, 2, 8), (100, 160, 512, 4, 8), (70, 72, 30, 1, 4), (64, 128, 256, 1, 8)]
+    Ws = [dev_bf16(wl.draw_weights(rng, O, K)) for _, K, O, _, _ in specs]
+    packed, wss = nm.nm_pack_prepare_batched([(W, N, M, T) for W, (T, _, _, N, M) in zip(Ws, specs)])
+    for W, (v, i), ws, (T, K, O, N, M) in zip(Ws, packed, wss, specs):
+        alone = nm.nm_spmm_prepare(v, i, K, N, M, T)
+        assert torch.equal(ws, alone), (T, K, O, N, M)
