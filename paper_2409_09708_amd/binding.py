@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from ctypes import c_char_p, c_int32, c_int64, c_size_t, c_void_p
 from typing import List, Optional, Sequence, Tuple
 
@@ -41,17 +42,32 @@ class NmError(RuntimeError):
 class PackDesc(ctypes.Structure):
     _fields_ = [("W", c_void_p), ("values", c_void_p), ("indices", c_void_p),
                 ("O", c_int64), ("K", c_int64), ("N", c_int32), ("M", c_int32)]
+    packer = struct.Struct("QQQqqii")
 
 
 class PackRankedDesc(ctypes.Structure):
     _fields_ = [("W", c_void_p), ("rank", c_void_p), ("values", c_void_p), ("indices", c_void_p),
                 ("O", c_int64), ("K", c_int64), ("N", c_int32), ("M", c_int32)]
+    packer = struct.Struct("QQQQqqii")
 
 
 class LayerDesc(ctypes.Structure):
     _fields_ = [("W", c_void_p), ("values", c_void_p), ("indices", c_void_p),
                 ("O", c_int64), ("K", c_int64), ("N", c_int32), ("M", c_int32),
                 ("T", c_int64), ("workspace", c_void_p), ("workspace_bytes", c_size_t)]
+    packer = struct.Struct("QQQqqiiqQQ")
+
+
+class RankDesc(ctypes.Structure):
+    _fields_ = [("W", c_void_p), ("rank", c_void_p), ("O", c_int64), ("K", c_int64), ("M", c_int32),
+                ("reserved", c_int32)]
+    packer = struct.Struct("QQqqii")
+
+
+def _desc_array(kind, rows):
+    """Host array of descriptors of one kind from their packed rows (a quarter of the time of building the structures
+    one by one, and these calls describe a whole model)."""
+    return (kind * len(rows)).from_buffer_copy(b"".join(rows))
 
 
 class ForwardDesc(ctypes.Structure):
@@ -59,11 +75,6 @@ class ForwardDesc(ctypes.Structure):
                 ("M", c_int32), ("X", c_void_p), ("T", c_int64), ("ldx", c_int64), ("bias", c_void_p), ("Y", c_void_p),
                 ("ldy", c_int64), ("out_dtype", c_int32), ("reserved", c_int32), ("workspace", c_void_p),
                 ("workspace_bytes", c_size_t)]
-
-
-class RankDesc(ctypes.Structure):
-    _fields_ = [("W", c_void_p), ("rank", c_void_p), ("O", c_int64), ("K", c_int64), ("M", c_int32),
-                ("reserved", c_int32)]
 
 
 def library_path() -> str:
@@ -217,15 +228,25 @@ def nm_spmm_workspace_bytes(O: int, K: int, N: int, M: int, T: int) -> int:
 # ------------------------------------------------------------------------------------------------
 # tensor marshalling
 # ------------------------------------------------------------------------------------------------
+# A call on a small layer costs the host more than the device (one image through a 384 x 384 projection: 4 us of kernel,
+# 3 us of launch), so what every call does is kept short: torch is imported once, the current stream is asked for as
+# a raw handle (0.1 us; building a Stream object takes 2.9), and a tensor's sizes and strides are read once.
+_TORCH = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _TORCH
+    if _TORCH is None:
+        import torch
+        _TORCH = torch
+    return _TORCH
 
 
 def _stream_handle(stream) -> int:
-    torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    c = _torch()._C
+    return c._cuda_getCurrentRawStream(c._cuda_getDevice())
 
 
 def _need(t, dtype, what: str) -> None:
@@ -237,18 +258,66 @@ def _need(t, dtype, what: str) -> None:
 
 def _rows(t, what: str) -> Tuple[int, int, int]:
     """(rows, cols, leading dimension) of a 2-D tensor whose rows are contiguous."""
-    if t.dim() != 2 or (t.shape[1] > 1 and t.stride(1) != 1):
-        raise ValueError(f"{what} must be 2-D with unit stride along its rows")
-    return int(t.shape[0]), int(t.shape[1]), int(t.stride(0)) if t.shape[0] > 1 else int(t.shape[1])
+    shape = t.shape
+    if len(shape) == 2:
+        rows, cols = shape
+        ld, step = t.stride()
+        if step == 1 or cols <= 1:
+            return rows, cols, ld if rows > 1 else cols
+    raise ValueError(f"{what} must be 2-D with unit stride along its rows")
 
 
-def _empty_packed(O: int, K: int, N: int, M: int, device):
+def _contiguous_weight(W, caller: str) -> Tuple[int, int]:
+    """(out-features, in-features) of a bfloat16 weight of a batched call."""
+    _need(W, _torch().bfloat16, "W")
+    if not W.is_contiguous():
+        raise ValueError(f"{caller} needs contiguous weights")
+    O, K = W.shape
+    return O, K
+
+
+def _packed(values, indices, dtype) -> int:
+    """Out-features of a packed weight whose tensors have been checked."""
+    _need(values, dtype, "values")
+    _need(indices, _torch().int32, "indices")
+    if not values.is_contiguous() or not indices.is_contiguous():
+        raise ValueError("packed tensors must be contiguous")
+    return values.shape[0]
+
+
+def _per_feature(t, O: int, name: str):
+    """Device pointer of an optional float32 [O] tensor."""
+    if t is None:
+        return None
+    _need(t, _torch().float32, name)
+    if t.numel() != O or not t.is_contiguous():
+        raise ValueError(f"{name} must be contiguous [O]")
+    return t.data_ptr()
+
+
+def _mask_words(mask, O: int, K: int):
+    _need(mask, _torch().int32, "mask")
+    if mask.shape != (O, (K + 31) // 32) or not mask.is_contiguous():
+        raise ValueError("mask must be contiguous [O, ceil(K/32)] words")
+    return mask.data_ptr()
+
+
+def _scratch(workspace):
+    """(pointer, bytes) of an optional workspace tensor."""
+    if workspace is None:
+        return None, 0
+    return workspace.data_ptr(), workspace.nbytes
+
+
+def _empty_packed(O: int, K: int, N: int, M: int, W):
+    """Uninitialised packed tensors of a weight on W's device."""
     torch = _torch()
-    vb, ib = nm_values_bytes(O, K, N, M), nm_index_bytes(O, K, N, M)
+    lib = load_library()
+    vb = lib.nm_values_bytes(O, K, N, M)
     if vb == 0:  # illegal level or shape: let the library name the error (it returns before touching a pointer)
-        _check(load_library().nm_pack(16, O, K, K, N, M, None, 16, 16, None))
-    values = torch.empty((O, vb // (2 * O)), dtype=torch.bfloat16, device=device)
-    indices = torch.empty((O, ib // (4 * O)), dtype=torch.int32, device=device)
+        _check(lib.nm_pack(16, O, K, K, N, M, None, 16, 16, None))
+    values = W.new_empty((O, vb // (2 * O)))
+    indices = W.new_empty((O, lib.nm_index_bytes(O, K, N, M) // (4 * O)), dtype=torch.int32)
     return values, indices
 
 
@@ -257,7 +326,7 @@ def nm_prune(W, N: int, M: int, W_masked=None, stream=None):
     torch = _torch()
     _need(W, torch.bfloat16, "W")
     O, K, ldw = _rows(W, "W")
-    mask = torch.empty((O, (K + 31) // 32), dtype=torch.int32, device=W.device)
+    mask = W.new_empty((O, (K + 31) // 32), dtype=torch.int32)
     wm_ptr = None
     if W_masked is not None:
         _need(W_masked, torch.bfloat16, "W_masked")
@@ -273,7 +342,7 @@ def nm_prune_scored(score, N: int, M: int, stream=None):
     torch = _torch()
     _need(score, torch.float32, "score")
     O, K, lds = _rows(score, "score")
-    mask = torch.empty((O, (K + 31) // 32), dtype=torch.int32, device=score.device)
+    mask = score.new_empty((O, (K + 31) // 32), dtype=torch.int32)
     _check(load_library().nm_prune_scored(score.data_ptr(), O, K, lds, N, M, mask.data_ptr(), _stream_handle(stream)))
     return mask
 
@@ -327,24 +396,21 @@ def nm_rank(W, M: int, stream=None):
 def nm_rank_batched(layers: Sequence[Tuple[object, int]], stream=None, out=None):
     """One launch for many (W, M); returns the rank tensors."""
     torch = _torch()
-    descs = (RankDesc * len(layers))()
+    descs = []
     outs = []
     for i, (W, M) in enumerate(layers):
-        _need(W, torch.bfloat16, "W")
-        if not W.is_contiguous():
-            raise ValueError("nm_rank_batched needs contiguous weights")
-        O, K = int(W.shape[0]), int(W.shape[1])
-        rank = out[i] if out is not None else torch.empty((O, K // 2), dtype=torch.uint8, device=W.device)
+        O, K = _contiguous_weight(W, "nm_rank_batched")
+        rank = out[i] if out is not None else W.new_empty((O, K // 2), dtype=torch.uint8)
         outs.append(rank)
-        descs[i] = RankDesc(W.data_ptr(), rank.data_ptr(), O, K, M, 0)
-    _check(load_library().nm_rank_batched(descs, len(layers), _stream_handle(stream)))
+        descs.append(RankDesc.packer.pack(W.data_ptr(), rank.data_ptr(), O, K, M, 0))
+    _check(load_library().nm_rank_batched(_desc_array(RankDesc, descs), len(descs), _stream_handle(stream)))
     return outs
 
 
 def _need_rank(rank, O: int, K: int) -> None:
     torch = _torch()
     _need(rank, torch.uint8, "rank")
-    if tuple(rank.shape) != (O, K // 2) or not rank.is_contiguous():
+    if rank.shape != (O, K // 2) or not rank.is_contiguous():
         raise ValueError("rank must be contiguous [O, K/2]")
 
 
@@ -364,7 +430,7 @@ def nm_pack_ranked(W, rank, N: int, M: int, stream=None):
     _need(W, torch.bfloat16, "W")
     O, K, ldw = _rows(W, "W")
     _need_rank(rank, O, K)
-    values, indices = _empty_packed(O, K, N, M, W.device)
+    values, indices = _empty_packed(O, K, N, M, W)
     _check(load_library().nm_pack_ranked(W.data_ptr(), rank.data_ptr(), O, K, ldw, N, M, values.data_ptr(),
                                          indices.data_ptr(), _stream_handle(stream)))
     return values, indices
@@ -372,19 +438,15 @@ def nm_pack_ranked(W, rank, N: int, M: int, stream=None):
 
 def nm_pack_ranked_batched(layers: Sequence[Tuple[object, object, int, int]], stream=None, out=None):
     """One launch for many (W, rank, N, M); returns [(values, indices), ...]."""
-    torch = _torch()
-    descs = (PackRankedDesc * len(layers))()
+    descs = []
     outs: List[Tuple[object, object]] = []
     for i, (W, rank, N, M) in enumerate(layers):
-        _need(W, torch.bfloat16, "W")
-        if not W.is_contiguous():
-            raise ValueError("nm_pack_ranked_batched needs contiguous weights")
-        O, K = int(W.shape[0]), int(W.shape[1])
+        O, K = _contiguous_weight(W, "nm_pack_ranked_batched")
         _need_rank(rank, O, K)
-        values, indices = out[i] if out is not None else _empty_packed(O, K, N, M, W.device)
+        values, indices = out[i] if out is not None else _empty_packed(O, K, N, M, W)
         outs.append((values, indices))
-        descs[i] = PackRankedDesc(W.data_ptr(), rank.data_ptr(), values.data_ptr(), indices.data_ptr(), O, K, N, M)
-    _check(load_library().nm_pack_ranked_batched(descs, len(layers), _stream_handle(stream)))
+        descs.append(PackRankedDesc.packer.pack(W.data_ptr(), rank.data_ptr(), values.data_ptr(), indices.data_ptr(), O, K, N, M))
+    _check(load_library().nm_pack_ranked_batched(_desc_array(PackRankedDesc, descs), len(descs), _stream_handle(stream)))
     return outs
 
 
@@ -393,13 +455,8 @@ def nm_pack(W, N: int, M: int, mask=None, stream=None):
     torch = _torch()
     _need(W, torch.bfloat16, "W")
     O, K, ldw = _rows(W, "W")
-    values, indices = _empty_packed(O, K, N, M, W.device)
-    mask_ptr = None
-    if mask is not None:
-        _need(mask, torch.int32, "mask")
-        if tuple(mask.shape) != (O, (K + 31) // 32) or not mask.is_contiguous():
-            raise ValueError("mask must be contiguous [O, ceil(K/32)]")
-        mask_ptr = mask.data_ptr()
+    values, indices = _empty_packed(O, K, N, M, W)
+    mask_ptr = None if mask is None else _mask_words(mask, O, K)
     _check(load_library().nm_pack(W.data_ptr(), O, K, ldw, N, M, mask_ptr, values.data_ptr(), indices.data_ptr(),
                                   _stream_handle(stream)))
     return values, indices
@@ -407,42 +464,37 @@ def nm_pack(W, N: int, M: int, mask=None, stream=None):
 
 def nm_pack_batched(layers: Sequence[Tuple[object, int, int]], stream=None, out=None):
     """One launch for many (W, N, M); returns [(values, indices), ...]."""
-    torch = _torch()
-    descs = (PackDesc * len(layers))()
+    descs = []
     outs: List[Tuple[object, object]] = []
     for i, (W, N, M) in enumerate(layers):
-        _need(W, torch.bfloat16, "W")
-        if not W.is_contiguous():
-            raise ValueError("nm_pack_batched needs contiguous weights")
-        O, K = int(W.shape[0]), int(W.shape[1])
-        values, indices = out[i] if out is not None else _empty_packed(O, K, N, M, W.device)
+        O, K = _contiguous_weight(W, "nm_pack_batched")
+        values, indices = out[i] if out is not None else _empty_packed(O, K, N, M, W)
         outs.append((values, indices))
-        descs[i] = PackDesc(W.data_ptr(), values.data_ptr(), indices.data_ptr(), O, K, N, M)
-    _check(load_library().nm_pack_batched(descs, len(layers), _stream_handle(stream)))
+        descs.append(PackDesc.packer.pack(W.data_ptr(), values.data_ptr(), indices.data_ptr(), O, K, N, M))
+    _check(load_library().nm_pack_batched(_desc_array(PackDesc, descs), len(descs), _stream_handle(stream)))
     return outs
 
 
 def nm_pack_prepare_batched(layers: Sequence[Tuple[object, int, int, int]], stream=None, out=None, workspaces=None):
     """nm_pack + nm_spmm_prepare for many (W, N, M, T); returns ([(values, indices), ...], [workspace or None, ...])."""
     torch = _torch()
-    descs = (LayerDesc * len(layers))()
+    descs = []
     outs: List[Tuple[object, object]] = []
     wss: List[object] = []
     for i, (W, N, M, T) in enumerate(layers):
-        _need(W, torch.bfloat16, "W")
-        if not W.is_contiguous():
-            raise ValueError("nm_pack_prepare_batched needs contiguous weights")
-        O, K = int(W.shape[0]), int(W.shape[1])
-        values, indices = out[i] if out is not None else _empty_packed(O, K, N, M, W.device)
-        need = nm_spmm_workspace_bytes(O, K, N, M, T)
-        ws = workspaces[i] if workspaces is not None else (
-            torch.empty((need,), dtype=torch.uint8, device=W.device) if need else None)
+        O, K = _contiguous_weight(W, "nm_pack_prepare_batched")
+        values, indices = out[i] if out is not None else _empty_packed(O, K, N, M, W)
+        if workspaces is not None:
+            ws = workspaces[i]
+        else:
+            need = nm_spmm_workspace_bytes(O, K, N, M, T)
+            ws = W.new_empty((need,), dtype=torch.uint8) if need else None
         outs.append((values, indices))
         wss.append(ws)
-        descs[i] = LayerDesc(W.data_ptr(), values.data_ptr(), indices.data_ptr(), O, K, N, M, T,
-                             ws.data_ptr() if ws is not None else None,
-                             ws.numel() * ws.element_size() if ws is not None else 0)
-    _check(load_library().nm_pack_prepare_batched(descs, len(layers), _stream_handle(stream)))
+        ws_ptr, ws_bytes = _scratch(ws)
+        descs.append(LayerDesc.packer.pack(W.data_ptr(), values.data_ptr(), indices.data_ptr(), O, K, N, M, T, ws_ptr or 0,
+                                      ws_bytes))
+    _check(load_library().nm_pack_prepare_batched(_desc_array(LayerDesc, descs), len(descs), _stream_handle(stream)))
     return outs, wss
 
 
@@ -450,8 +502,8 @@ def nm_unpack(values, indices, K: int, N: int, M: int, stream=None):
     torch = _torch()
     _need(values, torch.bfloat16, "values")
     _need(indices, torch.int32, "indices")
-    O = int(values.shape[0])
-    Wd = torch.empty((O, K), dtype=torch.bfloat16, device=values.device)
+    O = values.shape[0]
+    Wd = values.new_empty((O, K))
     _check(load_library().nm_unpack(values.data_ptr(), indices.data_ptr(), O, K, N, M, Wd.data_ptr(), K,
                                     _stream_handle(stream)))
     return Wd
@@ -511,8 +563,7 @@ def nm_spmm_prepare(values, indices, K: int, N: int, M: int, T: int, workspace=N
     need = nm_spmm_workspace_bytes(O, K, N, M, T)
     if workspace is None and need:
         workspace = torch.empty((need,), dtype=torch.uint8, device=values.device)
-    ws_ptr = workspace.data_ptr() if workspace is not None else None
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    ws_ptr, ws_bytes = _scratch(workspace)
     _check(load_library().nm_spmm_prepare(values.data_ptr(), indices.data_ptr(), O, K, N, M, T, ws_ptr, ws_bytes,
                                           _stream_handle(stream)))
     return workspace
@@ -530,52 +581,23 @@ def nm_linear_forward(values, indices, K: int, N: int, M: int, X, bias=None, out
     from_packed: hand the library no workspace, so that a product of up to 208 tokens runs straight from the packed
     format (the library reports a missing workspace for shapes that path does not take)."""
     torch = _torch()
-    _need(values, torch.bfloat16, "values")
-    _need(indices, torch.int32, "indices")
+    lib = load_library()
+    O = _packed(values, indices, torch.bfloat16)
     _need(X, torch.bfloat16, "X")
-    O = int(values.shape[0])
     T, KX, ldx = _rows(X, "X")
     if KX != K:
         raise ValueError("X must be [T, K]")
-    if not values.is_contiguous() or not indices.is_contiguous():
-        raise ValueError("packed tensors must be contiguous")
-    if out is not None:
-        out_dtype = out.dtype
-    out_dtype = out_dtype or torch.float32
-    if out_dtype not in (torch.float32, torch.bfloat16):
-        raise ValueError("out dtype must be float32 or bfloat16")
-    if out is None:
-        out = torch.empty((T, O), dtype=out_dtype, device=X.device)
-    TY, OY, ldy = _rows(out, "out")
-    if (TY, OY) != (T, O):
-        raise ValueError("out must be [T, O]")
-    need = 0 if from_packed else nm_spmm_workspace_bytes(O, K, N, M, T)
-    if workspace is None and need:
-        if not _prepared:
+    out, ldy, code = _out_matrix(out, out_dtype, T, O, X, "out")
+    if workspace is None and not from_packed:
+        need = lib.nm_spmm_workspace_bytes(O, K, N, M, T)
+        if need and not _prepared:
             workspace = _workspace(need, X.device, stream)
-        elif K % 64 == 0:  # (a ragged reduction can do without one)
+        elif need and K % 64 == 0:  # (a ragged reduction can do without one)
             raise ValueError("a prepared call needs the workspace nm_spmm_prepare filled")
-    ws_ptr = workspace.data_ptr() if workspace is not None else None
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    bias_ptr = None
-    if bias is not None:
-        _need(bias, torch.float32, "bias")
-        if bias.numel() != O or not bias.is_contiguous():
-            raise ValueError("bias must be contiguous [O]")
-        bias_ptr = bias.data_ptr()
-    code = NM_OUT_F32 if out_dtype == torch.float32 else NM_OUT_BF16
-    lib = load_library()
-    if _prepared:
-        st = lib.nm_linear_forward_prepared(values.data_ptr(), indices.data_ptr(), O, K, N, M, X.data_ptr(), T, ldx,
-                                            bias_ptr, out.data_ptr(), ldy, code, ws_ptr, ws_bytes,
-                                            _stream_handle(stream))
-    elif bias_ptr is None:
-        st = lib.nm_spmm(values.data_ptr(), indices.data_ptr(), O, K, N, M, X.data_ptr(), T, ldx, out.data_ptr(), ldy,
-                         code, ws_ptr, ws_bytes, _stream_handle(stream))
-    else:
-        st = lib.nm_linear_forward(values.data_ptr(), indices.data_ptr(), O, K, N, M, X.data_ptr(), T, ldx, bias_ptr,
-                                   out.data_ptr(), ldy, code, ws_ptr, ws_bytes, _stream_handle(stream))
-    _check(st)
+    ws_ptr, ws_bytes = _scratch(workspace)
+    fn = lib.nm_linear_forward_prepared if _prepared else lib.nm_linear_forward
+    _check(fn(values.data_ptr(), indices.data_ptr(), O, K, N, M, X.data_ptr(), T, ldx, _per_feature(bias, O, "bias"),
+              out.data_ptr(), ldy, code, ws_ptr, ws_bytes, _stream_handle(stream)))
     return out
 
 
@@ -587,24 +609,15 @@ def nm_linear_forward_static(values, indices, K: int, N: int, M: int, X, bias=No
                              stream=None):
     """nm_linear_forward on the library's own fixed scratch: the call itself allocates nothing (pass `out`)."""
     torch = _torch()
-    _need(values, torch.bfloat16, "values")
-    _need(indices, torch.int32, "indices")
+    O = _packed(values, indices, torch.bfloat16)
     _need(X, torch.bfloat16, "X")
-    if not values.is_contiguous() or not indices.is_contiguous():
-        raise ValueError("packed tensors must be contiguous")
-    O = int(values.shape[0])
     T, KX, ldx = _rows(X, "X")
     if KX != K:
         raise ValueError("X must be [T, K]")
-    out, ldy, code = _out_matrix(out, out_dtype, T, O, X.device, "out")
-    bias_ptr = None
-    if bias is not None:
-        _need(bias, torch.float32, "bias")
-        if bias.numel() != O or not bias.is_contiguous():
-            raise ValueError("bias must be contiguous [O]")
-        bias_ptr = bias.data_ptr()
+    out, ldy, code = _out_matrix(out, out_dtype, T, O, X, "out")
     _check(load_library().nm_linear_forward_static(values.data_ptr(), indices.data_ptr(), O, K, N, M, X.data_ptr(), T,
-                                                   ldx, bias_ptr, out.data_ptr(), ldy, code, _stream_handle(stream)))
+                                                   ldx, _per_feature(bias, O, "bias"), out.data_ptr(), ldy, code,
+                                                   _stream_handle(stream)))
     return out
 
 
@@ -628,19 +641,25 @@ def nm_probe_copy(src, dst, stream=None):
     return dst
 
 
-def _out_matrix(out, out_dtype, rows: int, cols: int, device, name: str):
+def _out_matrix(out, out_dtype, rows: int, cols: int, like, name: str, i32: bool = False):
+    """(output tensor, its leading dimension, its type code); allocated on `like`'s device when not given."""
     torch = _torch()
     if out is not None:
         out_dtype = out.dtype
-    out_dtype = out_dtype or torch.float32
-    if out_dtype not in (torch.float32, torch.bfloat16):
-        raise ValueError("out dtype must be float32 or bfloat16")
+    if out_dtype == torch.bfloat16:
+        code = NM_OUT_BF16
+    elif out_dtype is None or out_dtype == torch.float32:
+        code, out_dtype = NM_OUT_F32, torch.float32
+    elif i32 and out_dtype == torch.int32:
+        code = NM_OUT_I32
+    else:
+        raise ValueError("out dtype must be float32, bfloat16 or int32" if i32 else "out dtype must be float32 or bfloat16")
     if out is None:
-        out = torch.empty((rows, cols), dtype=out_dtype, device=device)
+        return like.new_empty((rows, cols), dtype=out_dtype), cols, code
     r, c, ld = _rows(out, name)
     if (r, c) != (rows, cols):
         raise ValueError(f"{name} must be [{rows}, {cols}]")
-    return out, ld, (NM_OUT_F32 if out_dtype == torch.float32 else NM_OUT_BF16)
+    return out, ld, code
 
 
 def nm_backward_input_workspace_bytes(O: int, K: int, T: int) -> int:
@@ -656,12 +675,12 @@ def nm_linear_backward_input(Ws, dY, out_dtype=None, out=None, workspace=None, s
     T, OY, ldy = _rows(dY, "dY")
     if OY != O:
         raise ValueError("dY must be [T, O]")
-    out, ldx, code = _out_matrix(out, out_dtype, T, K, dY.device, "dX")
-    need = nm_backward_input_workspace_bytes(O, K, T)
-    if workspace is None and need:
-        workspace = _workspace(need, dY.device, stream)
-    ws_ptr = workspace.data_ptr() if workspace is not None else None
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    out, ldx, code = _out_matrix(out, out_dtype, T, K, dY, "dX")
+    if workspace is None:
+        need = nm_backward_input_workspace_bytes(O, K, T)
+        if need:
+            workspace = _workspace(need, dY.device, stream)
+    ws_ptr, ws_bytes = _scratch(workspace)
     _check(load_library().nm_linear_backward_input(Ws.data_ptr(), O, K, ldw, dY.data_ptr(), T, ldy, out.data_ptr(), ldx,
                                                    code, ws_ptr, ws_bytes, _stream_handle(stream)))
     return out
@@ -680,18 +699,13 @@ def nm_linear_backward_weight(dY, X, mask=None, out_dtype=None, out=None, worksp
     TX, K, ldx = _rows(X, "X")
     if TX != T:
         raise ValueError("dY and X must have the same number of rows")
-    mask_ptr = None
-    if mask is not None:
-        _need(mask, torch.int32, "mask")
-        if tuple(mask.shape) != (O, (K + 31) // 32) or not mask.is_contiguous():
-            raise ValueError("mask must be contiguous [O, ceil(K/32)] words")
-        mask_ptr = mask.data_ptr()
-    out, lddw, code = _out_matrix(out, out_dtype, O, K, dY.device, "dW")
-    need = nm_backward_weight_workspace_bytes(O, K, T)
-    if workspace is None and need:
-        workspace = _workspace(need, dY.device, stream)
-    ws_ptr = workspace.data_ptr() if workspace is not None else None
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    mask_ptr = None if mask is None else _mask_words(mask, O, K)
+    out, lddw, code = _out_matrix(out, out_dtype, O, K, dY, "dW")
+    if workspace is None:
+        need = nm_backward_weight_workspace_bytes(O, K, T)
+        if need:
+            workspace = _workspace(need, dY.device, stream)
+    ws_ptr, ws_bytes = _scratch(workspace)
     _check(load_library().nm_linear_backward_weight(dY.data_ptr(), T, O, ldy, X.data_ptr(), K, ldx, mask_ptr,
                                                     out.data_ptr(), lddw, code, ws_ptr, ws_bytes, _stream_handle(stream)))
     return out
@@ -746,8 +760,7 @@ def _i8_weight(Wq, mask):
     _need(Wq, torch.int8, "Wq")
     _need(mask, torch.int32, "mask")
     O, K, ldw = _rows(Wq, "Wq")
-    if tuple(mask.shape) != (O, (K + 31) // 32) or not mask.is_contiguous():
-        raise ValueError("mask must be contiguous [O, ceil(K/32)] words")
+    _mask_words(mask, O, K)
     return O, K, ldw
 
 
@@ -759,8 +772,7 @@ def nm_i8_prepare(Wq, mask, N: int, M: int, T: int, workspace=None, stream=None)
     need = nm_i8_workspace_bytes(O, K, N, M, T)
     if workspace is None and need:
         workspace = torch.empty((need,), dtype=torch.uint8, device=Wq.device)
-    ws_ptr = workspace.data_ptr() if workspace is not None else None
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    ws_ptr, ws_bytes = _scratch(workspace)
     _check(load_library().nm_i8_prepare(Wq.data_ptr(), O, K, ldw, mask.data_ptr(), N, M, T, ws_ptr, ws_bytes,
                                         _stream_handle(stream)))
     return workspace
@@ -776,38 +788,25 @@ def nm_linear_forward_i8(Wq, mask, N: int, M: int, Xq, x_scale: float = 1.0, w_s
     T, KX, ldx = _rows(Xq, "Xq")
     if KX != K:
         raise ValueError("Xq must be [T, K]")
-    if out is not None:
-        out_dtype = out.dtype
-    out_dtype = out_dtype or torch.float32
-    codes = {torch.float32: NM_OUT_F32, torch.bfloat16: NM_OUT_BF16, torch.int32: NM_OUT_I32}
-    if out_dtype not in codes:
-        raise ValueError("out dtype must be float32, bfloat16 or int32")
-    if out is None:
-        out = torch.empty((T, O), dtype=out_dtype, device=Xq.device)
-    TY, OY, ldy = _rows(out, "out")
-    if (TY, OY) != (T, O):
-        raise ValueError("out must be [T, O]")
-    ptrs = []
-    for t, name in ((w_scale, "w_scale"), (bias, "bias")):
-        if t is None:
-            ptrs.append(None)
-            continue
-        _need(t, torch.float32, name)
-        if t.numel() != O or not t.is_contiguous():
-            raise ValueError(f"{name} must be contiguous [O]")
-        ptrs.append(t.data_ptr())
-    need = nm_i8_workspace_bytes(O, K, N, M, T)
-    if workspace is None and need:
-        if _prepared:
-            raise ValueError("a prepared call needs the workspace nm_i8_prepare filled")
-        workspace = _workspace(need, Xq.device, stream)
-    ws_ptr = workspace.data_ptr() if workspace is not None else None
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    out, ldy, code = _out_matrix(out, out_dtype, T, O, Xq, "out", i32=True)
     lib = load_library()
+    workspace = _i8_scratch(lib, workspace, O, K, N, M, T, Xq, stream, _prepared, "nm_i8_prepare")
+    ws_ptr, ws_bytes = _scratch(workspace)
     fn = lib.nm_linear_forward_i8_prepared if _prepared else lib.nm_linear_forward_i8
-    _check(fn(Wq.data_ptr(), O, K, ldw, mask.data_ptr(), N, M, Xq.data_ptr(), T, ldx, float(x_scale), ptrs[0], ptrs[1],
-              out.data_ptr(), ldy, codes[out_dtype], ws_ptr, ws_bytes, _stream_handle(stream)))
+    _check(fn(Wq.data_ptr(), O, K, ldw, mask.data_ptr(), N, M, Xq.data_ptr(), T, ldx, float(x_scale),
+              _per_feature(w_scale, O, "w_scale"), _per_feature(bias, O, "bias"), out.data_ptr(), ldy, code, ws_ptr,
+              ws_bytes, _stream_handle(stream)))
     return out
+
+
+def _i8_scratch(lib, workspace, O: int, K: int, N: int, M: int, T: int, Xq, stream, prepared: bool, filler: str):
+    if workspace is None:
+        need = lib.nm_i8_workspace_bytes(O, K, N, M, T)
+        if need:
+            if prepared:
+                raise ValueError(f"a prepared call needs the workspace {filler} filled")
+            workspace = _workspace(need, Xq.device, stream)
+    return workspace
 
 
 def nm_linear_forward_i8_prepared(Wq, mask, N: int, M: int, Xq, workspace, x_scale: float = 1.0, w_scale=None, bias=None,
@@ -830,12 +829,7 @@ def nm_pack_i8(Wq, mask, N: int, M: int, stream=None):
 
 
 def _i8_packed(values, indices):
-    torch = _torch()
-    _need(values, torch.int8, "values")
-    _need(indices, torch.int32, "indices")
-    if not values.is_contiguous() or not indices.is_contiguous():
-        raise ValueError("packed tensors must be contiguous")
-    return int(values.shape[0])
+    return _packed(values, indices, _torch().int8)
 
 
 def nm_unpack_i8(values, indices, K: int, N: int, M: int, stream=None):
@@ -854,8 +848,7 @@ def nm_i8_prepare_packed(values, indices, K: int, N: int, M: int, T: int, worksp
     need = nm_i8_workspace_bytes(O, K, N, M, T)
     if workspace is None and need:
         workspace = torch.empty((need,), dtype=torch.uint8, device=values.device)
-    ws_ptr = workspace.data_ptr() if workspace is not None else None
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    ws_ptr, ws_bytes = _scratch(workspace)
     _check(load_library().nm_i8_prepare_packed(values.data_ptr(), indices.data_ptr(), O, K, N, M, T, ws_ptr, ws_bytes,
                                                _stream_handle(stream)))
     return workspace
@@ -870,37 +863,14 @@ def nm_linear_forward_i8_packed(values, indices, K: int, N: int, M: int, Xq, x_s
     T, KX, ldx = _rows(Xq, "Xq")
     if KX != K:
         raise ValueError("Xq must be [T, K]")
-    if out is not None:
-        out_dtype = out.dtype
-    out_dtype = out_dtype or torch.float32
-    codes = {torch.float32: NM_OUT_F32, torch.bfloat16: NM_OUT_BF16, torch.int32: NM_OUT_I32}
-    if out_dtype not in codes:
-        raise ValueError("out dtype must be float32, bfloat16 or int32")
-    if out is None:
-        out = torch.empty((T, O), dtype=out_dtype, device=Xq.device)
-    TY, OY, ldy = _rows(out, "out")
-    if (TY, OY) != (T, O):
-        raise ValueError("out must be [T, O]")
-    ptrs = []
-    for t, name in ((w_scale, "w_scale"), (bias, "bias")):
-        if t is None:
-            ptrs.append(None)
-            continue
-        _need(t, torch.float32, name)
-        if t.numel() != O or not t.is_contiguous():
-            raise ValueError(f"{name} must be contiguous [O]")
-        ptrs.append(t.data_ptr())
-    need = nm_i8_workspace_bytes(O, K, N, M, T)
-    if workspace is None and need:
-        if _prepared:
-            raise ValueError("a prepared call needs the workspace nm_i8_prepare_packed filled")
-        workspace = _workspace(need, Xq.device, stream)
-    ws_ptr = workspace.data_ptr() if workspace is not None else None
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    out, ldy, code = _out_matrix(out, out_dtype, T, O, Xq, "out", i32=True)
     lib = load_library()
+    workspace = _i8_scratch(lib, workspace, O, K, N, M, T, Xq, stream, _prepared, "nm_i8_prepare_packed")
+    ws_ptr, ws_bytes = _scratch(workspace)
     fn = lib.nm_linear_forward_i8_packed_prepared if _prepared else lib.nm_linear_forward_i8_packed
-    _check(fn(values.data_ptr(), indices.data_ptr(), O, K, N, M, Xq.data_ptr(), T, ldx, float(x_scale), ptrs[0], ptrs[1],
-              out.data_ptr(), ldy, codes[out_dtype], ws_ptr, ws_bytes, _stream_handle(stream)))
+    _check(fn(values.data_ptr(), indices.data_ptr(), O, K, N, M, Xq.data_ptr(), T, ldx, float(x_scale),
+              _per_feature(w_scale, O, "w_scale"), _per_feature(bias, O, "bias"), out.data_ptr(), ldy, code, ws_ptr,
+              ws_bytes, _stream_handle(stream)))
     return out
 
 
