@@ -734,19 +734,19 @@ __global__ void __launch_bounds__(256) splitk_reduce_kernel(const SplitGroup g) 
 // ---------------------------------------------------------------------------------------------
 // Persistent streamed product for large layers.
 //
-// One block of 8 waves (4 along O x 2 along T, 64 x 128 outputs each) per CU walks over its share of
-// the 256 x 256 output tiles; the LDS stage ring and the load pipeline run across tile boundaries,
+// One block of 8 waves (4 along O x 2 along T, 64 x 16 TT outputs each) per CU walks over its share of
+// the output tiles, 256 out-features x 32 TT tokens; the LDS stage ring and the load pipeline run across tile boundaries,
 // so the first stages of the next tile are already in flight (and its first fragments in registers)
 // while the current tile is being written out, and the stores of one tile drain while the next one
-// is multiplied.  A K step is 32 matrix instructions per wave for both operand forms: K = 64 of
+// is multiplied.  A K step is 4 TT matrix instructions per wave for both operand forms: K = 64 of
 // the 2:4 form through v_smfmac_f32_16x16x64_bf16, K = 32 of the dense form through
 // v_mfma_f32_16x16x32_bf16.
-// Per step a wave keeps its 4 W fragments in registers and streams the 8 X fragments through a ring
-// of four, three ahead of the instructions that consume them; the fragments of the next step are
-// fetched during the last groups of the current one.  Before anything of stage g+1 is read (group
-// TT-3 of stage g) every wave has issued all its reads of stage g: it drains them, makes sure its
+// Per step a wave keeps its 4 W fragments in registers and reads the TT X fragments three groups or more ahead
+// of the four instructions that consume each; the fragments of the next step are
+// fetched during the last groups of the current one.  Before anything of stage g+1 is read (group BAR of stage g) every wave
+// has issued all its reads of stage g: it drains them, makes sure its
 // share of stage g+1 has landed, meets the others at the step's only barrier and then refills the
-// buffer of stage g with stage g+3, two full steps ahead of its use.
+// buffer of stage g with stage g+STAGES, two full steps or more ahead of its use.
 // The tiles that share X rows (same tokens, other out-features) run on one XCD at the same time; each
 // walks K from its own starting step and wraps around, so that they do not miss on the same lines together.
 // The weight arrives in stream order (see the pre-pass above): every W load is one contiguous
@@ -754,19 +754,19 @@ __global__ void __launch_bounds__(256) splitk_reduce_kernel(const SplitGroup g) 
 // neighbour but stores only its own) and the weight is zero-padded to whole tiles, so every tile is
 // full and lane offsets never change.
 // ---------------------------------------------------------------------------------------------
-template <bool SPARSE, int WO_, int WT_, int STAGES_, bool I8 = false>
+template <bool SPARSE, int TT_, bool I8 = false>
 struct StreamCfg {
-  // Tiles are 256 out-features x 256 tokens on 8 waves (one block per CU, two waves per SIMD), three stages (four
-  // for the dense form, whose stages are 32 KiB); a wave holds 32 accumulator blocks of 16 x 16.  The layout in
-  // use is WO 4, WT 2 (64 out-features x 128 tokens per wave, 20 KiB of fragment reads per wave and step).
+  // Tiles are 256 out-features x 32 TT tokens on 8 waves (one block per CU, two waves per SIMD); a wave holds 64
+  // out-features x 16 TT tokens (WO 4, WT 2), 4 TT accumulator blocks of 16 x 16.  The height
+  // is chosen per launch (stream_height): 256 tokens move the fewest operand bytes per product, but 12608 tokens x 768
+  // out-features are 150 such tiles on 256 compute units, and 198 of 192 tokens are done sooner.
   // Measured and no faster on transformer-sized layers: WO 2, WT 4 (128 x 64 per wave: a fifth fewer fragment
   // bytes, the same time in the 2:4 form and 4 % more in the dense form), 4 waves of 128 x 128 (one per SIMD
   // with the 512-register budget: a lone wave does not hide its own LDS and issue latency), and 256 x 128 tiles
   // with two stages (two blocks of 4 waves per CU).
-  static constexpr int WO = WO_, WT = WT_, BO = 256, OT = BO / (WO * 16), TT = 32 / OT;  // 32 accumulator blocks per wave
+  static constexpr int WO = 4, WT = 2, BO = 256, OT = BO / (WO * 16), TT = TT_;
   static constexpr int TW = TT * 16, BT = TW * WT;       // tokens per wave, per tile
-  static constexpr int NW = WO * WT, NT = NW * 64, STAGES = STAGES_;
-  static constexpr int PER_CU = (NW == 4 && STAGES == 2) ? 2 : 1;  // co-resident blocks
+  static constexpr int NW = WO * WT, NT = NW * 64;
   static constexpr int OW = OT * 16;                     // out-features per wave
   // The int8 forms (v_smfmac_i32_16x16x128_i8, v_mfma_i32_16x16x64_i8) have the same geometry in bytes with
   // twice the K per step; only the selectors differ: a lane's 16 compressed values need a whole 32-bit word,
@@ -780,18 +780,33 @@ struct StreamCfg {
   static constexpr int S_ROWB = I8 ? 16 : 8;
   static constexpr int S_BYTES = SPARSE ? BO * S_ROWB : 0;
   static constexpr int STAGE = X_BYTES + A_BYTES + S_BYTES;
+  // as many stages as fit: three of the 2:4 form's, four of the smaller ones
+  static constexpr int STAGES = 4 * STAGE + 4 * BO * 4 <= 160 * 1024 ? 4 : 3;
   // Per-out-feature constants of a tile travel through LDS: the bias (one slice of BO floats per stage buffer,
   // read when the tile starts), or for int8 the weight scales and the bias (read when the tile ends, so the
   // slices alternate with the tile's parity instead: two pairs)
   static constexpr int BIAS0 = STAGES * STAGE;
   static constexpr int LDS_BYTES = BIAS0 + (I8 ? 4 : STAGES) * BO * 4;
-  static constexpr int X_PW = X_BYTES / 1024 / NW;
+  static constexpr int X_LOADS = X_BYTES / 1024;         // wave-wide loads of a stage
+  static constexpr int X_PW = (X_LOADS + NW - 1) / NW;   // of a wave; waves from X_FULL on have one less
+  static constexpr int X_FULL = X_LOADS % NW == 0 ? NW : X_LOADS % NW;
   static constexpr int A_PW = A_BYTES / 1024 / NW;
   static constexpr int S_PW = SPARSE ? S_BYTES / 256 / NW : 0;
   static constexpr int LPW = X_PW + A_PW + S_PW;
-  static_assert(WO == 2 || WO == 4, "wave layouts");
+  // Schedule of a step of TT groups (4 matrix instructions each): the barrier stands before group BAR.  After it the
+  // weight fragments of the next stage are read in two groups from W_GROUP on and its first PRE X fragments one per
+  // group; the other X fragments are read in their own step, before the barrier.  Where the registers allow it
+  // (everywhere but in the highest 2:4-form tile) the last of those reads is two groups before the barrier, which
+  // drains them, and the weight comes first after it: 3 - 8 % on the dense form of 160 to 224 tokens, nothing on the
+  // 2:4 form.
+  static constexpr bool ROOMY = !(SPARSE && TT == 8);
+  static constexpr int BAR = TT == 4 ? 1 : (ROOMY ? TT - 4 : TT - 3), PRE = TT - BAR;
+  static constexpr int W_GROUP = ROOMY ? BAR : TT - 2;
+  static constexpr int read_group(int f) {               // group that reads X fragment f (PRE <= f < TT) of its own step
+    return !ROOMY ? f - PRE : TT == 8 ? (f == 4 ? 0 : f == 7 ? 2 : 1) : (TT == 7 && f == 6 ? 1 : 0);
+  }
   static_assert(BO * 4 == 1024, "the bias slice of a tile is one wave-load");
-  static_assert(LDS_BYTES * PER_CU <= 160 * 1024 && STAGES * (LPW + 2) < 64, "LDS budget and vmcnt range");
+  static_assert(LDS_BYTES <= 160 * 1024 && STAGES * (LPW + 2) < 64, "LDS budget and vmcnt range");
 };
 
 // One launch serves a list of layers of the same operand form: their tiles form one list (layer after layer),
@@ -812,7 +827,6 @@ struct StreamLayer {
   int32_t out_kind;     // NM_OUT_F32 / NM_OUT_BF16 / NM_OUT_I32 (int8 only)
   int32_t reserved;
 };
-constexpr int kStreamWO = 4, kStreamWT = 2;  // wave layout of the bfloat16 launches
 constexpr int kStreamLayersMax = 44;
 struct StreamGroup {
   int32_t count, n_tiles;
@@ -820,10 +834,10 @@ struct StreamGroup {
 };
 static_assert(sizeof(StreamGroup) <= 4096, "the table must fit the kernel argument segment");
 
-template <bool SPARSE, int WO_, int WT_, int STAGES_, bool I8 = false>
-__global__ void __launch_bounds__(WO_ * WT_ * 64, (WO_ * WT_ == 4 && STAGES_ == 2) ? 2 : (WO_ * WT_) / 4)
+template <bool SPARSE, int TT_, bool I8 = false>
+__global__ void __launch_bounds__(512, 2)
 nm_stream_kernel(const StreamGroup g) {
-  using C = StreamCfg<SPARSE, WO_, WT_, STAGES_, I8>;
+  using C = StreamCfg<SPARSE, TT_, I8>;
   constexpr int OT = C::OT, TT = C::TT, STAGES = C::STAGES;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
@@ -938,10 +952,10 @@ nm_stream_kernel(const StreamGroup g) {
     ld_bias_voff = (uint32_t)((ob + 4 <= L.O ? ob : L.O - 4) * 4);
     ld_consts = (wave == 0 && (ld_bias != nullptr || (I8 && ld_scale != nullptr))) ? 1 : 0;
     // The tiles that share the tile's X rows (same tokens, other out-features) run on the same XCD at the
-    // same time, and so do a few that share its W rows (same out-features, other tokens); each starts at its
-    // own K step and wraps around, so they ask for different slices of those rows at any moment and find the
-    // others' slices in L2 instead of missing on them together.
-    ld_wrap = ld_nk - (int)((unsigned)(o_tile + (int)(t_lo / C::BT)) % (unsigned)ld_nk);  // steps until the walk wraps to K step 0
+    // same time; each starts at its own K step and wraps around, so they ask for different slices of those rows
+    // at any moment and find the others' slices in L2 instead of missing on them together.  The start depends on
+    // the out-features alone, so that a sum is added up in the same order whatever the tile height.
+    ld_wrap = ld_nk - (int)((unsigned)o_tile % (unsigned)ld_nk);  // steps until the walk wraps to K step 0
     const int64_t k0 = ld_nk - ld_wrap;
     ld_x += k0 * C::X_ROWB;
     ld_w += k0 * 1024;
@@ -982,7 +996,8 @@ nm_stream_kernel(const StreamGroup g) {
       }
     }
     if constexpr (d < C::X_PW) {
-      dma16_at(make_uniform(ld_x), x_voff[d], lds, __builtin_amdgcn_readfirstlane(x_dst[d]));
+      if (d + 1 < C::X_PW || C::X_FULL == C::NW || wave < C::X_FULL)
+        dma16_at(make_uniform(ld_x), x_voff[d], lds, __builtin_amdgcn_readfirstlane(x_dst[d]));
     } else if constexpr (d < C::X_PW + C::A_PW) {
       constexpr int q = d - C::X_PW;
       dma16_at(make_uniform(ld_w), w_voff[q], lds, __builtin_amdgcn_readfirstlane(a_dst[q]));
@@ -991,10 +1006,12 @@ nm_stream_kernel(const StreamGroup g) {
       dma4_at(make_uniform(ld_s), s_voff[q], lds, __builtin_amdgcn_readfirstlane(s_dst[q]));
     }
   };
-  auto wait_stage = [&](int younger) {
-    if (younger >= 2) wait_loads_outstanding<2 * C::LPW>();
-    else if (younger == 1) wait_loads_outstanding<C::LPW>();
-    else wait_loads_outstanding<0>();
+  // at most this wave's loads of STAGES - 2 whole stages, and HEADS of the one after, outstanding
+  auto wait_younger = [&](auto heads_tag) {
+    constexpr int HEADS = decltype(heads_tag)::value;
+    constexpr int LESS = HEADS >= C::X_PW ? 1 : 0;  // the load the later waves do not have is the last X load of a stage
+    if (C::X_FULL == C::NW || wave < C::X_FULL) wait_loads_outstanding<(STAGES - 2) * C::LPW + HEADS>();
+    else wait_loads_outstanding<(STAGES - 2) * (C::LPW - 1) + HEADS - LESS>();
   };
 
   // ---- fragment readers (the XOR undoes the swizzle applied by the loads).  A lane's four fragment
@@ -1042,7 +1059,7 @@ nm_stream_kernel(const StreamGroup g) {
   constexpr int LPG = (C::LPW + C::TT - 1) / C::TT;                     // loads that leave together
   constexpr int SLOTS = (C::LPW + LPG - 1) / LPG;
   constexpr int SPREAD = 2 * SLOTS <= C::TT ? 2 : 1;
-  constexpr int HEAD = ((3 + SPREAD - 1) / SPREAD) * LPG < C::LPW ? ((3 + SPREAD - 1) / SPREAD) * LPG : C::LPW;
+  constexpr int HEAD = ((C::PRE + SPREAD - 1) / SPREAD) * LPG < C::LPW ? ((C::PRE + SPREAD - 1) / SPREAD) * LPG : C::LPW;
   static_assert((SLOTS - 1) * SPREAD < C::TT, "the last load must be out before the next step's wait");
   cursor_tile(0);
 #pragma unroll
@@ -1056,20 +1073,21 @@ nm_stream_kernel(const StreamGroup g) {
       [&]<int... D>(std::integer_sequence<int, D...>) {
         (issue_one(std::integral_constant<int, D>{}, (uint32_t)(s * C::STAGE)), ...);
       }(std::make_integer_sequence<int, HEAD>{});
+      if constexpr (HEAD == C::LPW) cursor_advance();
     }
   }
-  wait_loads_outstanding<(STAGES - 2) * C::LPW + HEAD>();
+  wait_younger(std::integral_constant<int, HEAD>{});
   __builtin_amdgcn_s_barrier();
 
   u32x4_t afr[2][OT];  // W fragments of the current step and of the next one; the roles alternate
   int sfr[2][OT / 2 * SV];
   FragAddr at[2];      // likewise the fragment addresses in the current and in the next buffer
-  bfrag_t bq[4];
+  bfrag_t bq[TT];
   at[0] = at0;
 #pragma unroll
   for (int ip = 0; ip < OT / 2; ++ip) read_a2(at[0], ip, afr[0][2 * ip], afr[0][2 * ip + 1], &sfr[0][ip * SV]);
 #pragma unroll
-  for (int j = 0; j < 3; ++j) read_b(at[0], j, bq[j]);
+  for (int j = 0; j < C::PRE; ++j) read_b(at[0], j, bq[j]);
 
   uint32_t cur_off = 0;  // LDS offset of the buffer that holds the current stage
   using acc_t = std::conditional_t<I8, i32x4_t, f32x4_t>;
@@ -1079,7 +1097,6 @@ nm_stream_kernel(const StreamGroup g) {
   // instruction of the step is time its matrix instructions do not get.  PP names the fragment and address
   // set the step multiplies with.  Every step refills the buffer it has consumed and prefetches fragments
   // of the next stage, also past the block's last stage.
-  constexpr int AG = OT > 4 ? 3 : 2;  // groups that fetch the next step's W fragments (all after the barrier)
   auto step = [&](auto pp_tag) {
     constexpr int PP = decltype(pp_tag)::value;
     uint32_t nxt_off = cur_off + C::STAGE;
@@ -1089,50 +1106,56 @@ nm_stream_kernel(const StreamGroup g) {
     [&]<int... J>(std::integer_sequence<int, J...>) {
       ([&] {
         constexpr int j = J;
-        if constexpr (j == TT - 3) {
+        if constexpr (j == C::BAR) {
           asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // all this wave's reads of the stage are back
-          wait_loads_outstanding<(STAGES - 2) * C::LPW>();    // this wave's share of the next stage has landed
+          wait_younger(std::integral_constant<int, 0>{});     // this wave's share of the next stage has landed
           __builtin_amdgcn_s_barrier();
         }
-        if constexpr (j + 3 < TT) read_b(at[PP], j + 3, bq[(j + 3) & 3]);
-        else read_b(at[PP ^ 1], j + 3 - TT, bq[(j + 3) & 3]);
-        if constexpr (j >= TT - AG) {
-          // the next step's W fragments, a share in each of the last AG groups
-          constexpr int part = j - (TT - AG);
+        if constexpr (j < C::BAR) {
+          [&]<int... F>(std::integer_sequence<int, F...>) {
+            ([&] {
+              if constexpr (C::PRE + F < TT && C::read_group(C::PRE + F) == j) read_b(at[PP], C::PRE + F, bq[C::PRE + F]);
+            }(), ...);
+          }(std::make_integer_sequence<int, TT>{});
+        } else {
+          if constexpr (j >= C::W_GROUP && j < C::W_GROUP + 2) {
+            constexpr int part = j - C::W_GROUP;
 #pragma unroll
-          for (int ip = part * (OT / 2) / AG; ip < (part + 1) * (OT / 2) / AG; ++ip)
-            read_a2(at[PP ^ 1], ip, afr[PP ^ 1][2 * ip], afr[PP ^ 1][2 * ip + 1], &sfr[PP ^ 1][ip * SV]);
+            for (int ip = part * (OT / 2) / 2; ip < (part + 1) * (OT / 2) / 2; ++ip)
+              read_a2(at[PP ^ 1], ip, afr[PP ^ 1][2 * ip], afr[PP ^ 1][2 * ip + 1], &sfr[PP ^ 1][ip * SV]);
+          }
+          read_b(at[PP ^ 1], j - C::BAR, bq[j - C::BAR]);
         }
         [&]<int... I>(std::integer_sequence<int, I...>) {
           ([&] {
             constexpr int i = I;
             if constexpr (SPARSE && I8)
               acc[i][j] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(__builtin_bit_cast(i32x4_t, afr[PP][i]),
-                                                                   __builtin_bit_cast(i32x8_t, bq[j & 3]), acc[i][j],
+                                                                   __builtin_bit_cast(i32x8_t, bq[j]), acc[i][j],
                                                                    sfr[PP][i], 0, 0);
             else if constexpr (I8)
               acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4_t, afr[PP][i]),
-                                                                __builtin_bit_cast(i32x4_t, bq[j & 3]), acc[i][j], 0, 0, 0);
+                                                                __builtin_bit_cast(i32x4_t, bq[j]), acc[i][j], 0, 0, 0);
             else if constexpr (SPARSE)
               acc[i][j] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(__builtin_bit_cast(bf16x8_t, afr[PP][i]),
-                                                                    __builtin_bit_cast(bf16x16_t, bq[j & 3]),
+                                                                    __builtin_bit_cast(bf16x16_t, bq[j]),
                                                                     acc[i][j], sfr[PP][i / 2], 0, i & 1);
             else
               acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, afr[PP][i]),
-                                                                  __builtin_bit_cast(bf16x8_t, bq[j & 3]), acc[i][j],
+                                                                  __builtin_bit_cast(bf16x8_t, bq[j]), acc[i][j],
                                                                   0, 0, 0);
           }(), ...);
         }(std::make_integer_sequence<int, OT>{});
         {
           // the load that leaves after this group, if any: into the buffer this step has consumed (free since the
           // barrier), or the rest of the stage begun in the previous step into the buffer consumed there
-          constexpr int since = (j - (TT - 3) + TT) % TT;  // groups since the barrier
+          constexpr int since = (j - C::BAR + TT) % TT;  // groups since the barrier
           if constexpr (since % SPREAD == 0 && since / SPREAD < SLOTS) {
             [&]<int... Q>(std::integer_sequence<int, Q...>) {
               ([&] {
                 constexpr int d = since / SPREAD * LPG + Q;
                 if constexpr (d < C::LPW) {
-                  issue_one(std::integral_constant<int, d>{}, j >= TT - 3 ? cur_off : prev_off);
+                  issue_one(std::integral_constant<int, d>{}, j >= C::BAR ? cur_off : prev_off);
                   if constexpr (d == C::LPW - 1) cursor_advance();
                 }
               }(), ...);
@@ -1355,27 +1378,52 @@ static bool tiles_ok(int64_t K, const void* X, int64_t ldx, const void* values, 
   return true;
 }
 
-// Which product kernel a layer of O out-features runs at T tokens: 0 = the persistent 256 x 256 kernel, 2 = the
-// tiled kernel with 128 x 128 tiles, 3 = with 64 x 64 tiles.  The choice is the smaller of two estimated durations
-// (microseconds), a model fitted to measured launches on DeiT- and Swin-shaped layers (28 shapes from 197 to 50176
-// tokens; it picks the faster kernel on 27 of them and loses 19 % on the other):
-//   persistent: one block per compute unit walks ceil(tiles / 256) tiles of `stream_steps` K steps each, about
-//               0.7 us per step plus 4.5 us to write a tile out, plus the launch;
+// Estimated durations (microseconds) of the product kernels: models fitted to measured launches on DeiT- and Swin-shaped
+// and generic layers.
+//   persistent: one block per compute unit walks ceil(tiles / 256) tiles of 256 x 32 TT; a tile takes `nk` steps of
+//               step0 + step1 TT and epi0 + epi1 TT to write out, and everything takes up to 1 + busy times as long
+//               when the whole chip works on it (memory and power are shared: at 3072 -> 768 a step of the highest
+//               2:4 tile takes 0.63 us on 30 compute units and 0.95 on 255).  Fitted on 35 shapes from 1576 to 200704
+//               tokens in every height; the height it picks is within 5 % of the best one on all of them (0.3 % on
+//               average) and 12 % (2:4 form), 18 % (dense), 7 % and 12 % (int8) faster than always 256 tokens.
 //   tiled:      a compute unit works through ceil(tiles / 256) tiles of 128 x 128 (one after the other or two at
 //               a time, the rate per unit is the same), `tiled_step_us` per K step of 64 (0.34 us in the 2:4
 //               form, 0.5 us in the dense form, whose step holds twice the matrix instructions).
-// A layer with fewer than 64 tiles of 128 x 128 takes 64 x 64 tiles: the few tiles there are finish sooner.
-static int pick_tile(int64_t O, int64_t T, int64_t stream_steps, int64_t tiled_steps, double tiled_step_us) {
-  const int64_t tiles_big = ((O + 255) / 256) * ((T + 255) / 256);
+struct StreamModel {
+  double step0, step1, epi0, epi1, start, busy;
+  double tile(int64_t nk, int tt) const { return (double)nk * (step0 + step1 * tt) + epi0 + epi1 * tt; }
+};
+constexpr StreamModel kStreamModel[2][2] = {  // [int8][2:4 form]
+    {{0.082, 0.050, 0.02, 0.447, 3.4, 0.48}, {0.168, 0.046, 0.06, 0.388, 4.0, 0.60}},
+    {{0.092, 0.044, 0.17, 0.476, 3.9, 0.51}, {0.116, 0.035, 0.02, 0.296, 4.9, 1.32}}};
+constexpr int kStreamHeights[] = {8, 7, 6, 5, 4};
+constexpr double kModelUnits = 256.0;  // compute units of the chip the models were fitted on
+
+// Duration of one layer's launch with tiles of 32 tt tokens.
+static double stream_estimate(const StreamModel& m, int64_t O, int64_t T, int64_t nk, int tt) {
+  const double tiles = (double)((O + 255) / 256) * (double)((T + 32 * tt - 1) / (32 * tt));
+  const double full = (double)(int64_t)(tiles / kModelUnits), rest = tiles - full * kModelUnits;
+  return m.start + m.tile(nk, tt) * (full * (1.0 + m.busy) + (rest > 0 ? 1.0 + m.busy * rest / kModelUnits : 0.0));
+}
+static double stream_estimate(const StreamModel& m, int64_t O, int64_t T, int64_t nk) {
+  double best = 0;
+  for (int tt : kStreamHeights)
+    if (const double e = stream_estimate(m, O, T, nk, tt); tt == kStreamHeights[0] || e < best) best = e;
+  return best;
+}
+
+// Which product kernel a layer of O out-features runs at T tokens: 0 = the persistent kernel, 2 = the tiled kernel with
+// 128 x 128 tiles, 3 = with 64 x 64 tiles: the smaller estimate.  A layer with fewer than 64 tiles of 128 x 128 takes
+// 64 x 64 tiles: the few tiles there are finish sooner.
+static int pick_tile(int64_t O, int64_t T, int64_t stream_steps, const StreamModel& m, int64_t tiled_steps, double tiled_step_us) {
   const int64_t tiles_mid = ((O + 127) / 128) * ((T + 127) / 128);
   if (tiles_mid < 64) return 3;
   if (T < 256) return 2;
-  const double est_stream = (double)((tiles_big + 255) / 256) * ((double)stream_steps * 0.7 + 4.5) + 4.0;
   const double est_tiled = (double)((tiles_mid + 255) / 256) * ((double)tiled_steps * tiled_step_us + 1.5) + 3.0;
-  return est_stream <= est_tiled ? 0 : 2;
+  return stream_estimate(m, O, T, stream_steps) <= est_tiled ? 0 : 2;
 }
 static int pick_tile(int64_t O, int64_t K, int64_t T, bool sparse_form) {
-  return pick_tile(O, T, sparse_form ? K / 64 : K / 32, K / 64, sparse_form ? 0.34 : 0.5);
+  return pick_tile(O, T, sparse_form ? K / 64 : K / 32, kStreamModel[0][sparse_form], K / 64, sparse_form ? 0.34 : 0.5);
 }
 
 // A reduction that is no whole number of 64-wide steps: the ragged form of the tiled kernel multiplies it from stream
@@ -1573,28 +1621,75 @@ static hipError_t launch_gemm_group(TileGroup& grp, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <bool SPARSE, bool I8 = false>
-static hipError_t launch_stream_group(const StreamGroup& grp, hipStream_t s) {
-  constexpr int WO = I8 ? 4 : kStreamWO, WT = I8 ? 2 : kStreamWT;
-  using C = StreamCfg<SPARSE, WO, WT, SPARSE ? 3 : 4, I8>;  // dense stages are half the size: four fit
-  auto kern = nm_stream_kernel<SPARSE, WO, WT, SPARSE ? 3 : 4, I8>;
+// The tile height of a launch: the smallest estimate.  The tiles of several layers form one list, which ends in one
+// partial round.
+template <bool SPARSE, bool I8>
+static int stream_height(const StreamGroup& grp) {
+  const StreamModel& m = kStreamModel[I8][SPARSE];
+  int best_tt = kStreamHeights[0];
+  double best = 0;
+  for (int tt : kStreamHeights) {
+    if (I8 && grp.layer[0].nk < (tt > 6 ? StreamCfg<SPARSE, 8, I8>::STAGES : tt > 5 ? StreamCfg<SPARSE, 6, I8>::STAGES
+                                                                                   : StreamCfg<SPARSE, 4, I8>::STAGES))
+      continue;  // the per-tile constants alternate between two LDS slices: a tile has to have as many steps as stages
+    double e = 0;
+    if (grp.count == 1) {
+      e = stream_estimate(m, grp.layer[0].O, grp.layer[0].T, grp.layer[0].nk, tt);
+    } else {
+      double longest = 0;
+      for (int i = 0; i < grp.count; ++i) {
+        const StreamLayer& L = grp.layer[i];
+        const double tile = m.tile(L.nk, tt);
+        e += (double)L.n_o_tiles * (double)(((int64_t)L.T + 32 * tt - 1) / (32 * tt)) * tile / kModelUnits;
+        longest = tile > longest ? tile : longest;
+      }
+      e = (e < longest ? longest : e) + longest / 2;
+    }
+    if (tt == kStreamHeights[0] || e < best) { best = e; best_tt = tt; }
+  }
+  return best_tt;
+}
+
+template <bool SPARSE, int TT, bool I8>
+static hipError_t launch_stream_kernel(StreamGroup& grp, hipStream_t s) {
+  using C = StreamCfg<SPARSE, TT, I8>;
+  auto kern = nm_stream_kernel<SPARSE, TT, I8>;
   static PerDeviceOnce lds_limit;
   if (hipError_t e = raise_dynamic_lds_limit(kern, C::LDS_BYTES, lds_limit); e != hipSuccess) return e;
   int cus = 0;
   if (hipError_t e = compute_units(&cus); e != hipSuccess) return e;
   const int n_cu = cus > 8 ? (cus / 8) * 8 : 8;
-  const int64_t want = (((int64_t)grp.n_tiles + 7) / 8) * 8;
-  const int64_t resident = (int64_t)n_cu * C::PER_CU;  // persistent blocks: as many as fit at once
-  const unsigned grid = (unsigned)(want < resident ? want : resident);
+  int64_t tiles = 0;
+  for (int i = 0; i < grp.count; ++i) {
+    StreamLayer& L = grp.layer[i];
+    const int64_t n = (int64_t)L.n_o_tiles * (((int64_t)L.T + C::BT - 1) / C::BT);
+    L.n_tiles = (int32_t)n;
+    tiles += n;
+  }
+  if (tiles > 0x7FFFFFF0) return hipErrorInvalidValue;
+  grp.n_tiles = (int32_t)tiles;
+  const int64_t want = ((tiles + 7) / 8) * 8;
+  const unsigned grid = (unsigned)(want < n_cu ? want : n_cu);  // persistent blocks: one per compute unit
   hipLaunchKernelGGL(kern, dim3(grid), dim3(C::NT), C::LDS_BYTES, s, grp);
   return hipGetLastError();
+}
+
+template <bool SPARSE, bool I8 = false>
+static hipError_t launch_stream_group(StreamGroup& grp, hipStream_t s) {
+  switch (stream_height<SPARSE, I8>(grp)) {
+    case 4: return launch_stream_kernel<SPARSE, 4, I8>(grp, s);
+    case 5: return launch_stream_kernel<SPARSE, 5, I8>(grp, s);
+    case 6: return launch_stream_kernel<SPARSE, 6, I8>(grp, s);
+    case 7: return launch_stream_kernel<SPARSE, 7, I8>(grp, s);
+    default: return launch_stream_kernel<SPARSE, 8, I8>(grp, s);
+  }
 }
 
 // Appends a layer to the table of a launch; false when its tiles would overflow the list.
 template <bool SPARSE>
 static bool group_append(StreamGroup& grp, const GemmArgs& g) {
-  using C = StreamCfg<SPARSE, kStreamWO, kStreamWT, SPARSE ? 3 : 4>;
-  const int64_t n_o = (g.O + C::BO - 1) / C::BO, n_t = (g.T + C::BT - 1) / C::BT;
+  using C = StreamCfg<SPARSE, 8>;
+  const int64_t n_o = (g.O + C::BO - 1) / C::BO, n_t = (g.T + 127) / 128;  // of the lowest tiles
   const int64_t end = (int64_t)grp.n_tiles + n_o * n_t;
   if (grp.count >= kStreamLayersMax || end > 0x7FFFFFF0) return false;
   StreamLayer& L = grp.layer[grp.count++];
@@ -1620,8 +1715,9 @@ static hipError_t launch_stream(const GemmArgs& g, hipStream_t s) {
 bool stream_i8_takes(int64_t O, int64_t K, int64_t T, int N, int M) {
   const bool sparse_form = N <= 2 && N < M;
   const int64_t kstep = sparse_form ? 128 : 64;
-  // the per-tile constants alternate between two LDS slices, which needs tiles of at least three steps
-  return pick_tile(O, T, K / kstep, K / 128, sparse_form ? 0.5 : 1.0) == 0 && K % kstep == 0 && K / kstep >= 3 && O <= (1 << 24) && T < (1ll << 31) && K <= (1 << 22);
+  // the per-tile constants alternate between two LDS slices, which needs tiles of at least three steps (the highest
+  // tiles have three stages)
+  return pick_tile(O, T, K / kstep, kStreamModel[1][sparse_form], K / 128, sparse_form ? 0.5 : 1.0) == 0 && K % kstep == 0 && K / kstep >= 3 && O <= (1 << 24) && T < (1ll << 31) && K <= (1 << 22);
 }
 
 hipError_t launch_stream_i8(const StreamI8Args& a, hipStream_t s) {
@@ -1688,7 +1784,7 @@ static hipError_t launch_general(const SpmmArgs& a, hipStream_t s) {
 
 // Out[t, i] = sum_r Q[t, r] * Ws[r, i] on the persistent dense kernel: the weight is written transposed into
 // stream order first (a pass over the weight only), then it is an ordinary product with I out-features and a
-// reduction of R.  Shapes: enough 256 x 256 tiles, R % 64 == 0, Out rows in whole aligned 16-byte pieces.
+// reduction of R.  Shapes: enough tiles, R % 64 == 0, Out rows in whole aligned 16-byte pieces.
 size_t dense_transposed_workspace_bytes(int64_t R, int64_t I, int64_t T) {
   if ((R % 64) || pick_tile(I, R, T, false) != 0) return 0;
   return (size_t)(((I + 255) / 256) * 256) * (size_t)R * 2;

@@ -1,0 +1,61 @@
+"""The tile heights of the persistent product kernel (128 to 256 tokens): shapes that take each of them, with tokens off
+the tile edge, odd and even step counts, a bias and every output type; the same bytes alone and inside a batched call,
+whose launch may use another height."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2409_09708_amd as nm
+from oracle import nm_oracle as orc
+from paper_2409_09708_amd import workloads as wl
+from gpu_util import check_output, dev_bf16, dev_words, host_output
+
+pytestmark = pytest.mark.gpu
+
+# (T, K, O): chosen so that 256-row tiles number just above a multiple of the compute units and lower ones do not
+SHAPES = [(12001, 192, 768), (15873, 128, 768), (6301, 64, 2560), (5500, 320, 3072), (8200, 192, 2048), (16384, 128, 1024)]
+
+
+@pytest.mark.parametrize("N,M", [(2, 4), (1, 8), (4, 8), (8, 8)])
+@pytest.mark.parametrize("T,K,O", SHAPES)
+def test_products(T, K, O, N, M):
+    rng = np.random.default_rng(12000 + N * 17 + M + T)
+    X, W = wl.draw_activations(rng, T, K), wl.draw_weights(rng, O, K)
+    bias = rng.standard_normal(O).astype(np.float32)
+    Yref, B = orc.nm_linear_from_bits(X, W, N, M, bias=bias)
+    B = B + np.abs(bias)[None, :]
+    v, i = nm.nm_pack(dev_bf16(W), N, M)
+    Xd, bd = dev_bf16(X), torch.from_numpy(bias).cuda()
+    y = nm.nm_linear_forward(v, i, K, N, M, Xd, bias=bd)
+    check_output(host_output(y), Yref, B, K // M * N + 1, True, (T, K, O, N, M))
+    out = torch.full((T + 1, O), 7.0, dtype=torch.bfloat16, device="cuda")
+    ws = nm.nm_spmm_prepare(v, i, K, N, M, T)
+    nm.nm_linear_forward_prepared(v, i, K, N, M, Xd, ws, bias=bd, out=out[:T])
+    check_output(host_output(out[:T]), Yref, B, K // M * N + 1, False, (T, K, O, N, M))
+    assert bool((out[T] == 7).all())
+    # beside a layer with many more tiles: another height, the same sums
+    T2 = 40000
+    X2 = dev_bf16(wl.draw_activations(rng, T2, K))
+    ws2 = nm.nm_spmm_prepare(v, i, K, N, M, T2)
+    y2 = torch.empty((T2, O), dtype=torch.bfloat16, device="cuda")
+    both = torch.zeros((T, O), dtype=torch.float32, device="cuda")
+    nm.nm_linear_forward_prepared_batched([(v, i, K, N, M, Xd, ws, bd, both), (v, i, K, N, M, X2, ws2, None, y2)])
+    assert torch.equal(both, y)
+
+
+@pytest.mark.parametrize("N,M", [(2, 4), (4, 8)])
+@pytest.mark.parametrize("T,K,O", [(12001, 384, 768), (15873, 512, 768), (6301, 640, 2560), (8200, 1024, 2048)])
+def test_int8_products(T, K, O, N, M):
+    rng = np.random.default_rng(12500 + N + T)
+    xq, wq = wl.draw_int8(rng, T, K), wl.draw_int8(rng, O, K)
+    mask = orc.nm_mask(wl.f32_to_bf16_bits(wq.astype(np.float32)), N, M)
+    words = dev_words(orc.mask_to_words(mask))
+    acc = nm.nm_linear_forward_i8(torch.from_numpy(wq).cuda(), words, N, M, torch.from_numpy(xq).cuda(), out_dtype=torch.int32)
+    ref = xq.astype(np.float32) @ (wq * mask).astype(np.float32).T  # exact: |sums| < 1024 * 127 * 127 < 2^24
+    assert K * 127 * 127 < 2 ** 24 and np.array_equal(acc.cpu().numpy(), ref.astype(np.int32))
+    scale = torch.from_numpy(rng.random(O).astype(np.float32)).cuda()
+    bias = torch.from_numpy(rng.standard_normal(O).astype(np.float32)).cuda()
+    y = nm.nm_linear_forward_i8(torch.from_numpy(wq).cuda(), words, N, M, torch.from_numpy(xq).cuda(), x_scale=0.02,
+                                w_scale=scale, bias=bias)
+    expect = torch.addcmul(bias.double(), acc.double(), (0.02 * scale).double())  # one rounding of the fused multiply-add
+    assert (y.double() - expect).abs().max().item() <= 2.0 ** -23 * expect.abs().max().item()
