@@ -204,7 +204,7 @@ struct GemmCfg {
   static constexpr int A_PW = (A_LOADS + NW - 1) / NW;
   static constexpr int S_PW = SPARSE ? (S_LOADS + NW - 1) / NW : 0;
   static constexpr int LPW = X_PW + A_PW + S_PW;
-  static_assert(STAGES == 2 || STAGES == 3, "two or three LDS stages");
+  static_assert(STAGES >= 2 && STAGES <= 4, "LDS stages");
   static_assert(STAGES * LPW < 64, "vmcnt is a 6-bit counter");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS budget");
 };
@@ -548,7 +548,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned block, uns
       [&]<int... B>(std::integer_sequence<int, B...>) {
         ([&] {
           constexpr int buf = B, nbuf = (B + STAGES - 1) % STAGES;
-          wait_stage(STAGES == 3 ? 1 : 0);
+          wait_stage(STAGES - 2);
           __builtin_amdgcn_s_barrier();
 #pragma unroll
           for (int h = 0; h < H; ++h) {
@@ -561,7 +561,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned block, uns
     {
       int buf = 0;  // ks is a multiple of STAGES here
       for (; ks < nk; ++ks) {
-        wait_stage((STAGES == 3 && ks + 1 < nk) ? 1 : 0);
+        wait_stage(nk - 1 - ks < STAGES - 2 ? nk - 1 - ks : STAGES - 2);
         __builtin_amdgcn_s_barrier();
         int nbuf = buf + STAGES - 1;
         if (nbuf >= STAGES) nbuf -= STAGES;
@@ -1737,17 +1737,54 @@ hipError_t launch_stream_i8(const StreamI8Args& a, hipStream_t s) {
   return a.sparse_form ? launch_stream_group<true, true>(grp, s) : launch_stream_group<false, true>(grp, s);
 }
 
+// Tiles of the tiled kernel for one layer alone.  Its blocks are bound by the bytes their compute unit pulls into LDS
+// (about 100 GB/s per unit: a step of a 64 x 64 tile brings 12.5 KB for 4096 outputs, of a 128 x 128 tile 25 KB for
+// 16384), so larger tiles are cheaper per output and smaller ones spread a small layer over more units: 1576 tokens x
+// 768 out-features are 78 tiles of 128 x 128 and 150 of 128 x 64.  Durations (microseconds) by the same kind of model
+// as the persistent kernel's, fitted on 28 shapes of 8 to 200704 tokens per form (rms 4 - 11 %); the tile it picks is
+// within 4 % of the best one on average.  K = 3072 -> 768 at 1576 tokens 17.8 -> 11.9 us (128 x 128 before), K = 768 ->
+// 2304 at 788 7.1 -> 5.9, in the dense form 22.1 -> 16.5 and 9.5 -> 7.0.
+enum TileKind { TILE_64, TILE_128_64, TILE_128_TWO, TILE_128, TILE_KINDS };  // _TWO: two LDS stages instead of three
+struct TileModel {
+  int bo, bt;
+  double start, step, epi, busy;
+};
+constexpr TileModel kTileModel[2][TILE_KINDS] = {  // [2:4 form]
+    {{64, 64, 2.52, 0.154, 0.38, 0.12}, {128, 64, 2.59, 0.215, 0.65, 0.31}, {128, 128, 2.09, 0.413, 1.14, 0.13},
+     {128, 128, 1.88, 0.338, 2.19, 0.26}},
+    {{64, 64, 2.75, 0.099, 0.31, 0.30}, {128, 64, 2.81, 0.127, 0.40, 0.65}, {128, 128, 2.46, 0.359, 0.85, 0.06},
+     {128, 128, 2.68, 0.215, 0.97, 0.45}}};
+// The 128 x 128 or 64 x 64 tile of pick_tile's choice keeps the layer unless another is 2 % faster.
+static TileKind tile_kind(int64_t O, int64_t K, int64_t T, bool sparse_form, int pick) {
+  auto estimate = [&](const TileModel& m) {
+    const double tiles = (double)((O + m.bo - 1) / m.bo) * (double)((T + m.bt - 1) / m.bt);
+    const double full = (double)(int64_t)(tiles / kModelUnits), rest = tiles - full * kModelUnits;
+    return m.start + ((double)(K / 64) * m.step + m.epi) *
+                         (full * (1.0 + m.busy) + (rest > 0 ? 1.0 + m.busy * rest / kModelUnits : 0.0));
+  };
+  int best = pick == 3 ? TILE_64 : TILE_128;
+  double least = 0.98 * estimate(kTileModel[sparse_form][best]);
+  for (int k = 0; k < TILE_KINDS; ++k) {
+    if (const double e = estimate(kTileModel[sparse_form][k]); e < least) { best = k; least = e; }
+  }
+  return (TileKind)best;
+}
+
+// pick: pick_tile's choice.  A cut reduction keeps the tile its range count was computed for.
 template <bool SPARSE>
 static hipError_t dispatch_gemm(const GemmArgs& g, int pick, hipStream_t s) {
-  switch (pick) {
-    case 0: return launch_stream<SPARSE>(g, s);
-    case 2:
-      // dense form with more tiles than compute units: two LDS stages instead of three, so that two blocks share
-      // a compute unit and one's loads and write-out run under the other's matrix instructions (0.6 - 0.9 of the
-      // three-stage time on such shapes; with a block per unit the deeper pipeline wins)
-      if (!SPARSE && ((g.O + 127) / 128) * ((g.T + 127) / 128) > 256) return launch_gemm<SPARSE, 2, 2, 4, 4, 2>(g, s);
-      return launch_gemm<SPARSE, 2, 2, 4, 4, 3>(g, s);
-    default: return launch_gemm<SPARSE, 2, 2, 2, 2, 3>(g, s);
+  if (pick == 0) return launch_stream<SPARSE>(g, s);
+  const TileKind kind = g.splits > 1 ? (pick == 2 ? TILE_128 : TILE_64) : tile_kind(g.O, g.K, g.T, SPARSE, pick);
+  // A fourth stage pays where a unit has one block and that block 32 steps or more: 64 x 64 8.6 -> 8.3 us (dense form
+  // 13.8 -> 11.6) at 394 x 3072 -> 768, 128 x 64 14.5 -> 11.9 at 1576 x 3072 -> 768, 128 x 128 23.7 -> 21.0 at 3136 x
+  // 4096 -> 1024; at K = 768 it costs 2 - 5 %, with two blocks on a unit it gains nothing, and neither does a fifth.
+  const TileModel& m = kTileModel[SPARSE][kind];
+  const bool deep = g.splits <= 1 && g.K >= 2048 && ((g.O + m.bo - 1) / m.bo) * ((g.T + m.bt - 1) / m.bt) <= 256;
+  switch (kind) {
+    case TILE_64: return deep ? launch_gemm<SPARSE, 2, 2, 2, 2, 4>(g, s) : launch_gemm<SPARSE, 2, 2, 2, 2, 3>(g, s);
+    case TILE_128_64: return deep ? launch_gemm<SPARSE, 2, 2, 4, 2, 4>(g, s) : launch_gemm<SPARSE, 2, 2, 4, 2, 3>(g, s);
+    case TILE_128_TWO: return launch_gemm<SPARSE, 2, 2, 4, 4, 2>(g, s);
+    default: return deep ? launch_gemm<SPARSE, 2, 2, 4, 4, 4>(g, s) : launch_gemm<SPARSE, 2, 2, 4, 4, 3>(g, s);
   }
 }
 

@@ -1,0 +1,41 @@
+"""The tiles of the tiled product kernel a single layer may take (64 x 64 to 256 x 128, two to four LDS stages): one
+shape per tile and operand form, tokens and out-features off the tile edge, both weight orders, both output types; the
+same bytes as inside a batched call, which may use another tile."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2409_09708_amd as nm
+from oracle import nm_oracle as orc
+from paper_2409_09708_amd import workloads as wl
+from gpu_util import check_output, dev_bf16, host_output
+
+pytestmark = pytest.mark.gpu
+
+# (T, K, O): 64 x 64, 128 x 64, 128 x 128 tiles with three stages, then with four (K from 2048 on), two stages last
+SPARSE = [(397, 192, 504), (789, 192, 1272), (2999, 512, 760), (397, 3072, 504), (789, 2048, 1272), (2999, 2048, 760),
+          (2999, 192, 760)]
+DENSE = [(397, 192, 504), (789, 192, 1272), (2999, 1600, 760), (397, 2048, 504), (789, 2112, 1272), (2999, 2048, 760),
+         (2999, 192, 760)]
+
+
+@pytest.mark.parametrize("T,K,O,N,M", [(*s, *lv) for s in SPARSE for lv in ((2, 4), (1, 8))] +
+                         [(*s, *lv) for s in DENSE for lv in ((4, 8), (4, 4))])
+def test_products(T, K, O, N, M):
+    rng = np.random.default_rng(13000 + N * 17 + M + T)
+    X, W = wl.draw_activations(rng, T, K), wl.draw_weights(rng, O, K)
+    bias = rng.standard_normal(O).astype(np.float32)
+    Yref, B = orc.nm_linear_from_bits(X, W, N, M, bias=bias)
+    B = B + np.abs(bias)[None, :]
+    v, i = nm.nm_pack(dev_bf16(W), N, M)
+    Xd, bd = dev_bf16(X), torch.from_numpy(bias).cuda()
+    y = nm.nm_linear_forward(v, i, K, N, M, Xd, bias=bd)
+    check_output(host_output(y), Yref, B, K // M * N + 1, True, (T, K, O, N, M))
+    out = torch.full((T + 1, O), 7.0, dtype=torch.bfloat16, device="cuda")
+    ws = nm.nm_spmm_prepare(v, i, K, N, M, T)
+    nm.nm_linear_forward_prepared(v, i, K, N, M, Xd, ws, bias=bd, out=out[:T])
+    check_output(host_output(out[:T]), Yref, B, K // M * N + 1, False, (T, K, O, N, M))
+    assert bool((out[T] == 7).all())
+    both = [torch.empty((T, O), dtype=torch.float32, device="cuda") for _ in range(2)]
+    nm.nm_linear_forward_prepared_batched([(v, i, K, N, M, Xd, ws, bd, b) for b in both])
+    assert torch.equal(both[0], y) and torch.equal(both[1], y)
