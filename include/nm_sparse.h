@@ -219,7 +219,7 @@ int32_t nm_pack_ranked_batched(const nm_pack_ranked_desc* descs, int32_t count, 
  *                    Without a workspace (NULL, or too small), a product of T <= 208 tokens at a level of
  *                    {1:4, 1:8, 2:8, 4:8, 1:16, 2:16, 4:16} with K % 64 == 0 and O % 4 == 0 still runs: a
  *                    kernel reads the packed format itself (Fig. 2: values + positions, decoded on the fly;
- *                    slower than the workspace path, nothing to prepare).  Every other shape reports
+ *                    a prepared call is faster).  Every other shape reports
  *                    NM_ERR_WORKSPACE.
  * The fastest matrix-core kernels need K % 64 == 0, 16-byte aligned X, values and Y and ldx, ldy
  * multiples of 8; any other K above 64 and any other alignment of X and Y runs a matrix-core kernel that

@@ -1,0 +1,292 @@
+// One launch from the packed weight to the product of a few tokens.  A call that brings a packed weight and no prepared
+// copy of it otherwise runs the stream-order pre-pass over the weight and then the tiled kernel; at up to a few dozen
+// tokens the pre-pass is the longer of the two and its output is read once.  Here a block decodes the weight of its 32
+// out-features into LDS as the operand of the matrix instructions and multiplies it with up to 64 tokens.
+//
+// What bounds it: latency.  768 -> 1000 at 4:8 and 8 tokens is 1.3 MB, under 1 us of HBM time; what takes time is one
+// round trip to memory, decoding 16 weights per lane and pass (a 2-byte LDS write per kept value), and a serial chain of
+// K / 64 steps.  So a block is small (768 out-features are 24 of them per 64 tokens), all four waves decode, the loads
+// of two spans of 256 reduction positions are in flight in registers while a third is multiplied, and a span has one
+// barrier.  In a graph, pre-pass and product before: 768 -> 1000 at 4:8 and 16 tokens 9.4 -> 5.9 us, 3072 -> 768 at 1:4
+// 16.4 -> 12.5, 1024 -> 4096 at 4:8 16.3 -> 7.1.
+//
+// Two summation orders, so that a product is the same bytes whichever kernel of its route computes it:
+//   PACKED = false  the tiled kernel's (nm_spmm.hip): the sum starts from the bias; the dense instruction takes the
+//                   positions of a 64-wide step as 0 .. 31 and 32 .. 63
+//   PACKED = true   the few-token kernel's (nm_fewtok.hip): the bias is added last; the dense instruction takes the even
+//                   and the odd runs of 8 positions
+#include "nm_launch.h"
+#include "nm_mma.h"
+
+namespace nm {
+namespace {
+
+constexpr int kRows = 32, kToks = 64, kSteps = 4;  // of a block: out-features, tokens, 64-wide steps per span
+constexpr int kXStep = kToks * 128;                // bytes of a step's activations
+constexpr int kXSpan = kSteps * kXStep;
+
+struct DirectArgs {
+  const bf16_t* values;
+  const uint32_t* indices;
+  const bf16_t* X;
+  const float* bias;  // nullable
+  void* Y;
+  int64_t ldx, ldy;
+  int32_t O, K, T;
+  int32_t out_bf16, pieces;  // pieces: rows of Y are made of aligned runs of four outputs
+};
+
+template <int N, int M>
+struct DirectCfg {
+  static constexpr bool SPARSE = N <= 2 && N < M;
+  static constexpr int B = log2_of(M);
+  static constexpr int VPC = 16 / M * N;               // kept values of 16 weights
+  static constexpr int BITS = VPC * B;                 // their index fields
+  static constexpr int WORDS = 32 % BITS == 0 ? 1 : 2;  // 32-bit words those may lie in
+  static constexpr int A_ROWB = SPARSE ? 64 : 128;     // bytes of a weight row per step
+  static constexpr int A_STEP = kRows * A_ROWB;
+  static constexpr int S_STEP = SPARSE ? 256 : 0;      // a selector word per pair of rows and lane group
+  static constexpr int SPAN = kXSpan + kSteps * (A_STEP + S_STEP);
+  static constexpr int LDS_BYTES = 2 * SPAN;
+  static constexpr int VW = (VPC + 1) / 2;             // registers of a chunk's values
+  static_assert(BITS <= 32 && LDS_BYTES <= 160 * 1024, "chunk fields and LDS budget");
+};
+
+// What a lane brings of a span: the packed form of two 16-weight chunks and eight 16-byte pieces of X.
+template <int N, int M>
+struct DirectLoads {
+  using C = DirectCfg<N, M>;
+  uint32_t v[2][C::VW], f[2][C::WORDS];
+  u32x4_t x[8];
+};
+
+template <int N, int M, bool PACKED>
+__global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
+  using C = DirectCfg<N, M>;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r16 = lane & 15, kb = lane >> 4;
+  const int o0 = (int)blockIdx.x * kRows, t0 = (int)blockIdx.y * kToks;
+  const int nk = a.K >> 6, spans = (nk + kSteps - 1) / kSteps;
+  const int64_t nf = (int64_t)a.K / M * N;
+  const int64_t nw = (nf * C::B + 31) / 32;
+
+  // a lane's chunks are tid and tid + 256 of the span's 32 rows x 16, its pieces of X tid + 256 i of 64 rows x 32
+  auto fetch = [&](DirectLoads<N, M>& d, int span) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int o = o0 + (tid >> 4) + 16 * u, c = span * 16 + (tid & 15);
+#pragma unroll
+      for (int i = 0; i < C::VW; ++i) d.v[u][i] = 0;
+#pragma unroll
+      for (int i = 0; i < C::WORDS; ++i) d.f[u][i] = 0;
+      if (o < a.O && c < nk * 4) {  // rows past O and steps past K are zero
+        const bf16_t* src = a.values + o * nf + (int64_t)c * C::VPC;
+        if constexpr (C::VPC % 8 == 0) {
+          const uint4 q = *reinterpret_cast<const uint4*>(src);
+          d.v[u][0] = q.x; d.v[u][1] = q.y; d.v[u][2] = q.z; d.v[u][3] = q.w;
+        } else if constexpr (C::VPC % 4 == 0) {
+#pragma unroll
+          for (int i = 0; i < C::VW; i += 2) {
+            const uint2 q = *reinterpret_cast<const uint2*>(src + 2 * i);
+            d.v[u][i] = q.x; d.v[u][i + 1] = q.y;
+          }
+        } else if constexpr (C::VPC % 2 == 0) {
+#pragma unroll
+          for (int i = 0; i < C::VW; ++i) d.v[u][i] = *reinterpret_cast<const uint32_t*>(src + 2 * i);
+        } else {
+          d.v[u][0] = src[0];
+        }
+        const int64_t w = ((int64_t)c * C::BITS) >> 5;
+        d.f[u][0] = a.indices[o * nw + w];
+        if constexpr (C::WORDS == 2) {
+          if (w + 1 < nw) d.f[u][1] = a.indices[o * nw + w + 1];
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int t = t0 + (tid >> 5) + 8 * i, k = span * 256 + (tid & 31) * 8;
+      d.x[i] = u32x4_t{0, 0, 0, 0};
+      if (t < a.T && k < a.K) d.x[i] = *reinterpret_cast<const u32x4_t*>(a.X + t * a.ldx + k);
+    }
+  };
+  // the same into the span's LDS buffer, the weight decoded.  16-byte pieces of a row are XOR-swizzled with the row.
+  auto put = [&](const DirectLoads<N, M>& d, int span, unsigned char* buf) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int row = (tid >> 4) + 16 * u, step = (tid & 15) >> 2, c = tid & 3;
+      uint64_t fields = d.f[u][0];
+      if constexpr (C::WORDS == 2)
+        fields = (fields | (uint64_t)d.f[u][1] << 32) >> (((uint32_t)(span * 16 + (tid & 15)) * C::BITS) & 31);
+      else
+        fields >>= ((uint32_t)(tid & 15) * C::BITS) & 31;  // a span starts on a word
+      unsigned char* at = buf + kXSpan + step * C::A_STEP + row * C::A_ROWB;
+      if constexpr (C::SPARSE) {
+        // the 2:4 form: the first kept value of a run of four in slot 2 run, a second one in slot 2 run + 1
+        at += (c ^ ((row >> 1) & 3)) * 16;
+        *reinterpret_cast<u32x4_t*>(at) = u32x4_t{0, 0, 0, 0};
+        uint32_t sel = 0, prev = 0xFFFFFFFFu;
+#pragma unroll
+        for (int j = 0; j < C::VPC; ++j) {
+          const uint32_t pos = (uint32_t)(j / N * M) + ((uint32_t)(fields >> (C::B * j)) & (uint32_t)(M - 1));
+          const uint32_t run = pos >> 2, second = run == prev ? 1u : 0u;
+          prev = run;
+          *reinterpret_cast<uint16_t*>(at + 4 * run + 2 * second) = (uint16_t)(d.v[u][j / 2] >> (16 * (j & 1)));
+          sel |= (pos & 3u) << (4 * run + 2 * second);
+        }
+        *reinterpret_cast<uint16_t*>(buf + kXSpan + kSteps * C::A_STEP + step * C::S_STEP + (row & 15) * 16 + c * 4 +
+                                     (row >> 4) * 2) = (uint16_t)sel;
+      } else {
+        const int key = row & 7;
+        *reinterpret_cast<u32x4_t*>(at + ((2 * c) ^ key) * 16) = u32x4_t{0, 0, 0, 0};
+        *reinterpret_cast<u32x4_t*>(at + ((2 * c + 1) ^ key) * 16) = u32x4_t{0, 0, 0, 0};
+#pragma unroll
+        for (int j = 0; j < C::VPC; ++j) {
+          const uint32_t pos = (uint32_t)(j / N * M) + ((uint32_t)(fields >> (C::B * j)) & (uint32_t)(M - 1));
+          *reinterpret_cast<uint16_t*>(at + (((2 * c + (pos >> 3)) ^ key) * 16) + (pos & 7) * 2) =
+              (uint16_t)(d.v[u][j / 2] >> (16 * (j & 1)));
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int row = (tid >> 5) + 8 * i, p = tid & 31;
+      *reinterpret_cast<u32x4_t*>(buf + (p >> 3) * kXStep + row * 128 + (((p & 7) ^ (row & 7)) * 16)) = d.x[i];
+    }
+  };
+
+  f32x4_t acc[2];
+  const int o_lane = o0 + kb * 4;  // a lane holds out-features o_lane + 16 i .. + 3 of token r16 of its wave's 16
+  auto bias_of = [&](int i) {
+    f32x4_t b = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    if (a.bias != nullptr)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (o_lane + 16 * i + e < a.O) b[e] = a.bias[o_lane + 16 * i + e];
+    return b;
+  };
+#pragma unroll
+  for (int i = 0; i < 2; ++i) acc[i] = PACKED ? f32x4_t{0.f, 0.f, 0.f, 0.f} : bias_of(i);
+
+  auto multiply = [&](const unsigned char* buf, int span) {
+    const int steps = nk - span * kSteps < kSteps ? nk - span * kSteps : kSteps;
+    if (t0 + wave * 16 >= a.T) return;  // (wave-uniform: no token of this wave is stored)
+#pragma unroll
+    for (int st = 0; st < kSteps; ++st) {
+      if (st >= steps) break;
+      const unsigned char* x = buf + st * kXStep + (wave * 16 + r16) * 128;
+      const unsigned char* w = buf + kXSpan + st * C::A_STEP + r16 * C::A_ROWB;
+      const int xk = r16 & 7;
+      if constexpr (C::SPARSE) {
+        const int at = (kb ^ ((r16 >> 1) & 3)) * 16;
+        const u32x4_t a0 = *reinterpret_cast<const u32x4_t*>(w + at);
+        const u32x4_t a1 = *reinterpret_cast<const u32x4_t*>(w + 16 * C::A_ROWB + at);
+        const int sel = (int)*reinterpret_cast<const uint32_t*>(buf + kXSpan + kSteps * C::A_STEP + st * C::S_STEP + r16 * 16 + kb * 4);
+        const u32x4_t lo = *reinterpret_cast<const u32x4_t*>(x + ((kb ^ xk) * 16));
+        const u32x4_t hi = *reinterpret_cast<const u32x4_t*>(x + (((4 + kb) ^ xk) * 16));
+        const u32x8_t b = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        acc[0] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(__builtin_bit_cast(bf16x8_t, a0), __builtin_bit_cast(bf16x16_t, b), acc[0], sel, 0, 0);
+        acc[1] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(__builtin_bit_cast(bf16x8_t, a1), __builtin_bit_cast(bf16x16_t, b), acc[1], sel, 0, 1);
+      } else {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int at = ((PACKED ? 2 * kb + h : 4 * h + kb) ^ xk) * 16;
+          const u32x4_t a0 = *reinterpret_cast<const u32x4_t*>(w + at);
+          const u32x4_t a1 = *reinterpret_cast<const u32x4_t*>(w + 16 * C::A_ROWB + at);
+          const u32x4_t b = *reinterpret_cast<const u32x4_t*>(x + at);
+          acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a0), __builtin_bit_cast(bf16x8_t, b), acc[0], 0, 0, 0);
+          acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a1), __builtin_bit_cast(bf16x8_t, b), acc[1], 0, 0, 0);
+        }
+      }
+    }
+  };
+
+  // Two register sets and two LDS buffers.  A buffer is written again two spans later: between the two lies a barrier
+  // that every wave reaches only after it has multiplied the first.
+  DirectLoads<N, M> even, odd;
+  fetch(even, 0);
+  if (spans > 1) fetch(odd, 1);
+  for (int span = 0; span < spans; span += 2) {
+    put(even, span, smem);
+    if (span + 2 < spans) fetch(even, span + 2);
+    __syncthreads();
+    multiply(smem, span);
+    if (span + 1 < spans) {
+      put(odd, span + 1, smem + C::SPAN);
+      if (span + 3 < spans) fetch(odd, span + 3);
+      __syncthreads();
+      multiply(smem + C::SPAN, span + 1);
+    }
+  }
+
+  const int t = t0 + wave * 16 + r16;
+  if (t >= a.T) return;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int o = o_lane + 16 * i;
+    if (o >= a.O) continue;
+    const f32x4_t y = PACKED ? acc[i] + bias_of(i) : acc[i];
+    const uint32_t p[2] = {pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
+    if (a.out_bf16) {
+      bf16_t* dst = reinterpret_cast<bf16_t*>(a.Y) + t * a.ldy + o;
+      if (a.pieces) *reinterpret_cast<uint2*>(dst) = make_uint2(p[0], p[1]);
+      else
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (o + e < a.O) dst[e] = (bf16_t)(p[e >> 1] >> (16 * (e & 1)));
+    } else {
+      float* dst = reinterpret_cast<float*>(a.Y) + t * a.ldy + o;
+      if (a.pieces) *reinterpret_cast<f32x4_t*>(dst) = y;
+      else
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (o + e < a.O) dst[e] = y[e];
+    }
+  }
+}
+
+template <int N, int M, bool PACKED>
+hipError_t launch_level(const DirectArgs& g, hipStream_t s) {
+  using C = DirectCfg<N, M>;
+  auto kern = nm_direct_kernel<N, M, PACKED>;
+  static PerDeviceOnce lds_limit;
+  if (hipError_t e = raise_dynamic_lds_limit(kern, C::LDS_BYTES, lds_limit); e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)((g.O + kRows - 1) / kRows), (unsigned)((g.T + kToks - 1) / kToks)), dim3(256),
+                     C::LDS_BYTES, s, g);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+// The levels whose packed form the matrix instructions cannot read as it lies and whose 16 weights have at most 32 bits
+// of fields.
+bool direct_level(int N, int M) {
+  switch (N * 32 + M) {
+    case 1 * 32 + 4: case 3 * 32 + 4: case 1 * 32 + 8: case 2 * 32 + 8: case 3 * 32 + 8: case 4 * 32 + 8:
+    case 1 * 32 + 16: case 2 * 32 + 16: case 4 * 32 + 16: return true;
+    default: return false;
+  }
+}
+
+// The caller has checked the operands (K % 64 == 0, 16-byte aligned X rows and values, sizes as the tiled kernel's).
+hipError_t launch_direct(const SpmmArgs& a, bool packed_order, hipStream_t s) {
+  DirectArgs g;
+  g.values = a.values; g.indices = a.indices; g.X = a.X; g.bias = a.bias; g.Y = a.Y;
+  g.ldx = a.ldx; g.ldy = a.ldy;
+  g.O = (int32_t)a.O; g.K = (int32_t)a.K; g.T = (int32_t)a.T;
+  g.out_bf16 = a.out_bf16;
+  g.pieces = (a.O % 4 == 0) && (a.ldy % 4 == 0) && ((uintptr_t)a.Y & (a.out_bf16 ? 7u : 15u)) == 0;
+  switch (a.N * 32 + a.M) {
+#define X(n, m)                                                                              \
+  case n * 32 + m:                                                                           \
+    return packed_order ? launch_level<n, m, true>(g, s) : launch_level<n, m, false>(g, s);
+    X(1, 4) X(1, 8) X(2, 8) X(4, 8) X(1, 16) X(2, 16) X(4, 16)
+#undef X
+    case 3 * 32 + 4: return launch_level<3, 4, false>(g, s);
+    case 3 * 32 + 8: return launch_level<3, 8, false>(g, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace nm

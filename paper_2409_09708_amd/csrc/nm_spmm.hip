@@ -1930,6 +1930,17 @@ static bool packed_path(const SpmmArgs& a) {
   return fewtok_takes(a);
 }
 
+// A call that prepares and multiplies in one: the kernel that decodes the weight itself (nm_direct.hip) as long as its
+// blocks of 32 out-features x 64 tokens have a compute unit each, and up to 208 tokens in any case (a weight tile is then
+// decoded at most four times).  Pre-pass and product against it, in a graph: 768 -> 1000 at 4:8 and 8 tokens 9.4 and
+// 5.7 us, 768 -> 768 at 394 tokens 9.2 and 6.3, 1024 -> 4096 at 197 23.4 and 13.9, 3072 -> 768 at 600 18.1 and 17.7; past
+// that line 9.8 and 11.2 for 768 -> 1000 at 600 tokens, 18.3 and 33.6 for 3072 -> 768 at 788.  Its sums are those of the
+// tiled kernel; a layer that the persistent kernel or a cut reduction would sum in another order stays there.
+static bool direct_takes(const SpmmArgs& a, int pick) {
+  const int64_t blocks = ((a.O + 31) / 32) * ((a.T + 63) / 64);
+  return (a.T <= 208 || blocks <= 256) && pick != 0 && direct_level(a.N, a.M) && split_count(a.O, a.K, a.T, a.N <= 2) == 1;
+}
+
 hipError_t launch_spmm(const SpmmArgs& a, hipStream_t s, bool* workspace_short, int phases) {
   *workspace_short = false;
   const bool prepare = phases & SPMM_PREPARE, product = phases & SPMM_PRODUCT;
@@ -1959,13 +1970,11 @@ hipError_t launch_spmm(const SpmmArgs& a, hipStream_t s, bool* workspace_short, 
   if (need && (a.workspace == nullptr || a.workspace_bytes < need || !aligned_to(a.workspace, 256))) {
     // no workspace: few tokens can still be multiplied straight from the packed format
     if (!packed_path(a)) *workspace_short = true;
-    else if (product) {
-      const SpmmArgs* one = &a;
-      return launch_fewtok(&one, 1, s);
-    }
+    else if (product) return launch_direct(a, true, s);
     return hipSuccess;
   }
   const int pick = pick_tile(a.O, a.K, a.T, sparse_form);
+  if (prepare && product && direct_takes(a, pick)) return launch_direct(a, false, s);
   GemmArgs g;
   fill_gemm_args(a, form, sparse_form, &g);
   if (prepare && form == FORM_STREAM) {

@@ -1,0 +1,36 @@
+"""The kernel that takes a few tokens from the packed weight to the product in one launch: every level it decodes, at
+the edges of its spans (4 steps of 64 reduction positions), its 32 out-features and its 64 tokens, aligned and unaligned
+outputs; the same bytes as a prepared call."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2409_09708_amd as nm
+from oracle import nm_oracle as orc
+from paper_2409_09708_amd import workloads as wl
+from gpu_util import check_output, dev_bf16, host_output
+
+pytestmark = pytest.mark.gpu
+
+LEVELS = [(1, 4), (3, 4), (1, 8), (2, 8), (3, 8), (4, 8), (1, 16), (2, 16), (4, 16)]
+SHAPES = [(1, 64, 1), (16, 256, 31), (17, 320, 32), (64, 576, 33), (65, 512, 72), (208, 1088, 100), (395, 192, 264)]
+
+
+@pytest.mark.parametrize("N,M", LEVELS)
+@pytest.mark.parametrize("T,K,O", SHAPES)
+def test_products(T, K, O, N, M):
+    rng = np.random.default_rng(14000 + N * 17 + M + T + K)
+    X = wl.draw_activations(rng, T, K)
+    W = wl.tie_heavy_weights(rng, O, K) if (T + O) % 2 else wl.draw_weights(rng, O, K)
+    bias = rng.standard_normal(O).astype(np.float32)
+    Yref, B = orc.nm_linear_from_bits(X, W, N, M, bias=bias)
+    B = B + np.abs(bias)[None, :]
+    v, i = nm.nm_pack(dev_bf16(W), N, M)
+    Xd, bd = dev_bf16(X), torch.from_numpy(bias).cuda()
+    ws = nm.nm_spmm_prepare(v, i, K, N, M, T)
+    for dt, pad in ((torch.float32, 4), (torch.bfloat16, 8), (torch.float32, 1), (torch.bfloat16, 3)):
+        out = torch.full((T + 1, O + 2 * pad), 7.0, dtype=dt, device="cuda")
+        y = nm.nm_linear_forward(v, i, K, N, M, Xd, bias=bd, out=out[:T, pad:pad + O])
+        check_output(host_output(y.contiguous()), Yref, B, K // M * N + 1, dt == torch.float32, (T, K, O, N, M, dt))
+        assert bool((out[T] == 7).all() and (out[:, :pad] == 7).all() and (out[:, pad + O:] == 7).all())
+        assert torch.equal(y, nm.nm_linear_forward_prepared(v, i, K, N, M, Xd, ws, bias=bd, out_dtype=dt))
