@@ -235,7 +235,10 @@ __device__ __forceinline__ f32x4_t bias_init(const float* bias, int64_t o, int64
 // or a dense level's values, read as they lie).
 // X_REGS: X travels through registers instead of by asynchronous copies, so that its rows may start anywhere and K
 // may end anywhere (see the loop); two stages.
-template <bool SPARSE, int WO, int WT, int OT, int TT, int STAGES, bool STREAM, bool X_REGS = false>
+// TAIL: K, a multiple of 8, may end inside the last step (rows of X still start on 16 bytes).  The pieces of that step past K are fetched
+// from its first piece instead (what lies behind a row's end may be no memory at all) and cleared in LDS by the lanes
+// that brought them, so they never enter a sum.
+template <bool SPARSE, int WO, int WT, int OT, int TT, int STAGES, bool STREAM, bool X_REGS = false, bool TAIL = false>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned block, unsigned char* smem) {
   using C = GemmCfg<SPARSE, WO, WT, OT, TT, STAGES>;
   static_assert(!STREAM || (OT % 2 == 0 && C::BO % 32 == 0 && 256 % C::BO == 0), "stream order: whole 32-row pairs inside one 256-row tile");
@@ -534,9 +537,35 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned block, uns
       stage_done();
     }
   } else {
+    static_assert(!TAIL || C::X_LOADS % C::NW == 0, "every piece is brought by one lane");
+    const int k_tail = (int)(a.K - (int64_t)(nk_all - 1) * 64);  // elements of the last step, 8 .. 64
+    int x_piece[C::X_PW];
+    if constexpr (TAIL) {
+#pragma unroll
+      for (int i = 0; i < C::X_PW; ++i) {
+        const int row = 8 * (wave + i * C::NW) + (lane >> 3);
+        x_piece[i] = (lane & 7) ^ (row & 7);
+      }
+    }
+    auto last_sources = [&]() {  // the next stage to be issued is the last one
+#pragma unroll
+      for (int i = 0; i < C::X_PW; ++i)
+        if (x_piece[i] * 8 >= k_tail) x_voff[i] -= (uint32_t)x_piece[i] * 16;
+    };
+    auto clear_tail = [&](int buf) {
+#pragma unroll
+      for (int i = 0; i < C::X_PW; ++i) {
+        if (x_piece[i] * 8 >= k_tail)
+          *reinterpret_cast<u32x4_t*>(smem + buf * C::STAGE + x_dst[i] + lane * 16) = u32x4_t{0, 0, 0, 0};
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    };
 #pragma unroll
     for (int s = 0; s < STAGES; ++s)
-      if (s < STAGES - 1 && s < nk) issue_stage(s);
+      if (s < STAGES - 1 && s < nk) {
+        if (TAIL && s == nk - 1) last_sources();
+        issue_stage(s);
+      }
 
     // One barrier per stage; the buffer multiplied in the previous step is refilled right after the barrier,
     // STAGES-1 stages ahead.  A wave issues one instruction at a time, so whatever the step spends on addresses and
@@ -544,7 +573,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned block, uns
     // steps at a time, which makes every LDS buffer a constant and leaves the step without branches; the last steps
     // run the general form.
     int ks = 0;
-    for (; ks + 2 * STAGES - 2 < nk; ks += STAGES) {
+    for (; ks + 2 * STAGES - 2 < nk - (TAIL ? 1 : 0); ks += STAGES) {
       [&]<int... B>(std::integer_sequence<int, B...>) {
         ([&] {
           constexpr int buf = B, nbuf = (B + STAGES - 1) % STAGES;
@@ -562,7 +591,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned block, uns
       int buf = 0;  // ks is a multiple of STAGES here
       for (; ks < nk; ++ks) {
         wait_stage(nk - 1 - ks < STAGES - 2 ? nk - 1 - ks : STAGES - 2);
+        if (TAIL && ks + 1 == nk && k_tail < 64) clear_tail(buf);
         __builtin_amdgcn_s_barrier();
+        if (TAIL && ks + STAGES == nk) last_sources();
         int nbuf = buf + STAGES - 1;
         if (nbuf >= STAGES) nbuf -= STAGES;
 #pragma unroll
@@ -605,12 +636,13 @@ nm_gemm_kernel(const GemmArgs a) {
   else gemm_tile<SPARSE, WO, WT, OT, TT, STAGES, false>(a, blockIdx.x, smem);
 }
 
-// Any K, any alignment of X and Y: the weight in stream order (K padded with zeros to whole steps), X through registers.
-template <bool SPARSE, int WO, int WT, int OT, int TT>
+// Any K, any alignment of X and Y: the weight in stream order (K padded with zeros to whole steps), X by asynchronous
+// copies where its rows are whole 16-byte pieces, else through registers.
+template <bool SPARSE, int WO, int WT, int OT, int TT, int STAGES, bool X_REGS>
 __global__ void __launch_bounds__(WO * WT * 64)
 nm_gemm_ragged_kernel(const GemmArgs a) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  gemm_tile<SPARSE, WO, WT, OT, TT, 2, true, true>(a, blockIdx.x, smem);
+  gemm_tile<SPARSE, WO, WT, OT, TT, STAGES, true, X_REGS, !X_REGS>(a, blockIdx.x, smem);
 }
 
 // The tiles of many small layers in one launch, whatever their operand form and weight order: products of a few
@@ -1788,27 +1820,35 @@ static hipError_t dispatch_gemm(const GemmArgs& g, int pick, hipStream_t s) {
   }
 }
 
-// The ragged form of the tiled kernel: 128 x 128 tiles once there is one for every compute unit, else 64 x 64.  A call
-// on 1579 tokens x 1000 -> 1001 out-features at 2:8 (pre-pass and product) takes 20.8 us; the gather kernel, which
-// took such shapes before and still takes them when there is no workspace, 1096 us.
+// The ragged form of the tiled kernel.  K and the rows of X in whole 16-byte pieces: the
+// tile of the aligned form.  A product of 1579 x 1000 -> 1001 at 2:8 takes 9.1 us that way and 15.5 through registers.
+// Other rows: 128 x 128 tiles once there is one for every compute unit, else 64 x 64.  (The gather kernel, which still
+// takes such shapes when there is no workspace: 1096 us.)
 template <bool SPARSE>
 static hipError_t launch_ragged(GemmArgs g, hipStream_t s) {
-  auto go = [&](auto kern, int bo, int bt, int threads, int lds, PerDeviceOnce& once) {
-    if (hipError_t e = raise_dynamic_lds_limit(kern, lds, once); e != hipSuccess) return e;
-    g.n_o_tiles = (int)((g.O + bo - 1) / bo);
-    g.n_t_tiles = (int)((g.T + bt - 1) / bt);
+  auto go = [&](auto kern, auto cfg, PerDeviceOnce& once) {
+    using C = decltype(cfg);
+    if (hipError_t e = raise_dynamic_lds_limit(kern, C::LDS_BYTES, once); e != hipSuccess) return e;
+    g.n_o_tiles = (int)((g.O + C::BO - 1) / C::BO);
+    g.n_t_tiles = (int)((g.T + C::BT - 1) / C::BT);
     const int64_t grid = (((int64_t)g.n_o_tiles * g.n_t_tiles + 7) / 8) * 8;
     if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), lds, s, g);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(C::NT), C::LDS_BYTES, s, g);
     return hipGetLastError();
   };
-  static PerDeviceOnce once_mid, once_small;
-  if (((g.O + 127) / 128) * ((g.T + 127) / 128) >= 256) {
-    using C = GemmCfg<SPARSE, 2, 2, 4, 4, 2>;
-    return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 4, 4>, C::BO, C::BT, C::NT, C::LDS_BYTES, once_mid);
+  const int64_t tiles_mid = ((g.O + 127) / 128) * ((g.T + 127) / 128);
+  static PerDeviceOnce once[6];
+  if (g.x_align == 16 && g.K % 8 == 0 && g.ldx <= (1 << 22)) {  // (per-lane byte offsets inside a tile stay below 2^32)
+    switch (tile_kind(g.O, padded_k(g.K), g.T, SPARSE, tiles_mid < 64 ? 3 : 2)) {
+      case TILE_64: return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 2, 2, 3, false>, GemmCfg<SPARSE, 2, 2, 2, 2, 3>{}, once[0]);
+      case TILE_128_64: return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 4, 2, 3, false>, GemmCfg<SPARSE, 2, 2, 4, 2, 3>{}, once[1]);
+      case TILE_128_TWO: return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 4, 4, 2, false>, GemmCfg<SPARSE, 2, 2, 4, 4, 2>{}, once[2]);
+      default: return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 4, 4, 3, false>, GemmCfg<SPARSE, 2, 2, 4, 4, 3>{}, once[3]);
+    }
   }
-  using C = GemmCfg<SPARSE, 2, 2, 2, 2, 2>;
-  return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 2, 2>, C::BO, C::BT, C::NT, C::LDS_BYTES, once_small);
+  if (tiles_mid >= 256)
+    return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 4, 4, 2, true>, GemmCfg<SPARSE, 2, 2, 4, 4, 2>{}, once[4]);
+  return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 2, 2, 2, true>, GemmCfg<SPARSE, 2, 2, 2, 2, 2>{}, once[5]);
 }
 
 static hipError_t launch_general(const SpmmArgs& a, hipStream_t s) {

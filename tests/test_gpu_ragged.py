@@ -80,3 +80,18 @@ def test_ragged_layers_packed_and_prepared_in_one_call():
     for W, (v, i), ws, (T, K, O, N, M) in zip(Ws, packed, wss, specs):
         alone = nm.nm_spmm_prepare(v, i, K, N, M, T)
         assert torch.equal(ws, alone), (T, K, O, N, M)
+
+
+# X in whole 16-byte pieces with a reduction that ends inside a step, on each tile of that form: 1 to 7 pieces in the last
+# step, steps fewer and more than the stages; the rows' neighbours and what follows the last row are NaN
+@pytest.mark.parametrize("N,M", [(2, 8), (4, 8)])
+@pytest.mark.parametrize("T,K,O", [(67, 72, 65), (130, 248, 131), (789, 1000, 1272), (2999, 200, 761), (2999, 968, 761)])
+def test_whole_pieces_and_a_short_last_step(T, K, O, N, M):
+    X, v, i, bias, Yref, B = layer(11980 + N + T + K, T, K, O, N, M)
+    flat = torch.full((T * (K + 16) + 64,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    for pitch in (K, K + 16):
+        view = torch.as_strided(flat, (T, K), (pitch, 1), 8)
+        view.copy_(dev_bf16(X))
+        y = nm.nm_linear_forward(v, i, K, N, M, view, bias=bias)
+        check_output(host_output(y), Yref, B, K // M * N + 1, True, (T, K, O, N, M, pitch))
+        flat.fill_(float("nan"))
