@@ -662,7 +662,7 @@ struct TileLayer {
   int64_t ldy;
   uint32_t O, T;           // O <= 2^24, T < 2^31
   uint32_t K : 23, rot : 3;  // K <= 2^22
-  uint32_t ldx : 23, out_bf16 : 1, vec_store : 1, stream_form : 1, sparse_form : 1, splits : 4;
+  uint32_t ldx : 23, out_bf16 : 1, vec_store : 1, stream_form : 1, sparse_form : 1, splits : 4, narrow : 1;
   uint32_t block_end;      // exclusive prefix end, in blocks
 };
 struct TileGroup {
@@ -671,8 +671,9 @@ struct TileGroup {
 };
 static_assert(sizeof(TileLayer) == 80 && sizeof(TileGroup) <= 4096, "the table must fit the kernel argument segment");
 
-// SS, SD: LDS stages of the 2:4-form and of the dense-form tiles (the launch's LDS is the larger of the two).
-template <int WO, int WT, int OT, int TT, int SS, int SD>
+// SS, SD: LDS stages of the 2:4-form and of the dense-form tiles (the launch's LDS is the larger of the two).  NARROW: a
+// layer may take tiles of half the out-features, three stages in either form (tile_group_narrow).
+template <int WO, int WT, int OT, int TT, int SS, int SD, bool NARROW>
 __global__ void __launch_bounds__(WO * WT * 64)
 nm_gemm_group_kernel(const TileGroup g) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -687,10 +688,23 @@ nm_gemm_group_kernel(const TileGroup g) {
   GemmArgs a;
   a.A = L.A; a.sel = L.sel; a.X = L.X; a.bias = L.bias; a.Y = L.Y; a.partial = L.partial;
   a.O = L.O; a.K = L.K; a.T = L.T; a.ldx = L.ldx; a.ldy = L.ldy;
-  a.n_o_tiles = (int)((L.O + WO * OT * 16 - 1) / (WO * OT * 16));
+  const uint32_t rows = WO * OT * 16 >> (NARROW ? L.narrow : 0);
+  a.n_o_tiles = (int)((L.O + rows - 1) / rows);
   a.n_t_tiles = (int)((L.T + WT * TT * 16 - 1) / (WT * TT * 16));
   a.out_bf16 = L.out_bf16; a.vec_store = L.vec_store; a.stream_form = L.stream_form; a.splits = L.splits;
   a.rot = L.rot;
+  if constexpr (NARROW) {
+    if (L.narrow) {
+      if (L.sparse_form) {
+        if (L.stream_form) gemm_tile<true, WO, WT, OT / 2, TT, 3, true>(a, block, smem);
+        else gemm_tile<true, WO, WT, OT / 2, TT, 3, false>(a, block, smem);
+      } else {
+        if (L.stream_form) gemm_tile<false, WO, WT, OT / 2, TT, 3, true>(a, block, smem);
+        else gemm_tile<false, WO, WT, OT / 2, TT, 3, false>(a, block, smem);
+      }
+      return;
+    }
+  }
   if (L.sparse_form) {
     if (L.stream_form) gemm_tile<true, WO, WT, OT, TT, SS, true>(a, block, smem);
     else gemm_tile<true, WO, WT, OT, TT, SS, false>(a, block, smem);
@@ -1573,14 +1587,37 @@ static hipError_t launch_gemm(GemmArgs g, hipStream_t s) {
 // Tiled kernel, many layers in one launch.  tile_group_append fills the table (false: full, launch it and retry;
 // a layer with more blocks than a grid holds never fits and is launched alone).
 template <int BO, int BT>
-static int64_t tile_layer_blocks(const TileLayer& L) {
-  const int64_t tiles = (int64_t)((L.O + BO - 1) / BO) * ((L.T + BT - 1) / BT);
-  return ((tiles * (L.splits > 1 ? L.splits : 1) + 7) / 8) * 8;
+static int64_t tile_layer_units(const TileLayer& L) {
+  const int bo = BO >> L.narrow;
+  const int64_t tiles = (int64_t)((L.O + bo - 1) / bo) * ((L.T + BT - 1) / BT);
+  return tiles * (L.splits > 1 ? L.splits : 1);
 }
+template <int BO, int BT>
+static int64_t tile_layer_blocks(const TileLayer& L) { return (tile_layer_units<BO, BT>(L) + 7) / 8 * 8; }
+constexpr double kTileBlockUs = 2.0;   // a block's start and write-out
+constexpr double kNarrowShare = 1.5;
 // estimated duration of one of the layer's blocks (the model of pick_tile): the order of the launch
 static double tile_layer_cost(const TileLayer& L) {
   const int n = L.splits > 1 ? L.splits : 1;
-  return (double)((L.K / 64 + n - 1) / n) * (L.sparse_form ? 0.34 : 0.5);
+  return (double)((L.K / 64 + n - 1) / n) * (L.sparse_form ? 0.34 : 0.5) * (L.narrow ? 0.6 : 1.0);
+}
+
+// A launch ends with its longest blocks, and a deep layer's may run far longer than the launch's even share of work.
+// Where a block of 128 out-features would run 1.5 times that share, the layer takes tiles of 64 out-features: twice the
+// blocks, each a little over half as long.  One image (in a graph): 4 linears at C = 768 36 -> 23 us, 12 of them 36.5 ->
+// 26.9, 24 43.0 -> 32.7, 32 at C = 512 32.6 -> 25.9; 48 at C = 768 (55 us: bound by reading 170 MB of weights) stay.
+// Below 1.5 the larger calls lose (48 at C = 768 57 us at 0.85).  The 2:4 form of more than 512 tokens, whose X is
+// then read by many more blocks, keeps its tiles (8 linears at 788 tokens 31.0, 33.4 narrow).
+template <int BO, int BT>
+static void tile_group_narrow(TileGroup& grp) {
+  double total = 0;
+  for (int i = 0; i < grp.count; ++i)
+    total += (double)tile_layer_units<BO, BT>(grp.layer[i]) * (tile_layer_cost(grp.layer[i]) + kTileBlockUs);
+  const double even = total / (2.0 * kModelUnits);  // two blocks share a unit
+  for (int i = 0; i < grp.count; ++i) {
+    TileLayer& L = grp.layer[i];
+    L.narrow = L.splits <= 1 && !(L.sparse_form && L.T > 512) && tile_layer_cost(L) + kTileBlockUs > kNarrowShare * even;
+  }
 }
 
 template <int WO, int WT, int OT, int TT>
@@ -1592,7 +1629,7 @@ static bool tile_group_append(TileGroup& grp, const GemmArgs& g, bool sparse_for
   L.O = (uint32_t)g.O; L.K = (uint32_t)g.K; L.T = (uint32_t)g.T;   // tiles_ok has bounded them
   L.ldx = (uint32_t)g.ldx; L.out_bf16 = g.out_bf16; L.vec_store = g.vec_store; L.stream_form = g.stream_form;
   L.sparse_form = sparse_form; L.splits = g.splits > 1 ? g.splits : 1;
-  L.block_end = 0; L.rot = 0;
+  L.block_end = 0; L.rot = 0; L.narrow = 0;
   int64_t total = tile_layer_blocks<WO * OT * 16, WT * TT * 16>(L);
   for (int i = 0; i < grp.count; ++i) total += tile_layer_blocks<WO * OT * 16, WT * TT * 16>(grp.layer[i]);
   if (total > 0x7FFFFFF0) return false;
@@ -1600,15 +1637,17 @@ static bool tile_group_append(TileGroup& grp, const GemmArgs& g, bool sparse_for
   return true;
 }
 
-template <int WO, int WT, int OT, int TT, int SS, int SD>
+template <int WO, int WT, int OT, int TT, int SS, int SD, bool NARROW>
 static hipError_t launch_gemm_group(TileGroup& grp, hipStream_t s) {
   using CS = GemmCfg<true, WO, WT, OT, TT, SS>;
   using CD = GemmCfg<false, WO, WT, OT, TT, SD>;
   constexpr int LDS = CS::LDS_BYTES > CD::LDS_BYTES ? CS::LDS_BYTES : CD::LDS_BYTES;
+  static_assert(!NARROW || GemmCfg<false, WO, WT, OT / 2, TT, 3>::LDS_BYTES <= LDS, "LDS of the narrow tiles");
   if (grp.count == 0) return hipSuccess;
-  auto kern = nm_gemm_group_kernel<WO, WT, OT, TT, SS, SD>;
+  auto kern = nm_gemm_group_kernel<WO, WT, OT, TT, SS, SD, NARROW>;
   static PerDeviceOnce lds_limit;
   if (hipError_t e = raise_dynamic_lds_limit(kern, LDS, lds_limit); e != hipSuccess) return e;
+  if constexpr (NARROW) tile_group_narrow<CS::BO, CS::BT>(grp);
   // longest blocks first (insertion sort, stable), so that the launch ends with the shortest ones
   for (int i = 1; i < grp.count; ++i) {
     const TileLayer L = grp.layer[i];
@@ -1625,8 +1664,8 @@ static hipError_t launch_gemm_group(TileGroup& grp, hipStream_t s) {
     TileLayer& L = grp.layer[i];
     const int64_t blocks = tile_layer_blocks<CS::BO, CS::BT>(L);
     const int64_t per_xcd = blocks / 8;
-    const int64_t units = (int64_t)((L.O + CS::BO - 1) / CS::BO) * ((L.T + CS::BT - 1) / CS::BT) * L.splits;
-    const double cost = tile_layer_cost(L) + 2.0;  // plus a block's start and write-out
+    const int64_t units = tile_layer_units<CS::BO, CS::BT>(L);
+    const double cost = tile_layer_cost(L) + kTileBlockUs;
     double share[8];
     for (int sl = 0; sl < 8; ++sl) {
       int64_t u = units - sl * per_xcd;
@@ -2094,8 +2133,8 @@ hipError_t launch_spmm_batched(const SpmmArgs* layers, int count, hipStream_t s)
                       : tile_group_append<2, 2, 2, 2>(tile_grp[1], g, sparse_form);
   };
   auto tile_flush = [&](int which) {
-    return which == 0 ? launch_gemm_group<2, 2, 4, 4, 3, kGroupDenseStages>(tile_grp[0], s)
-                      : launch_gemm_group<2, 2, 2, 2, 3, 3>(tile_grp[1], s);
+    return which == 0 ? launch_gemm_group<2, 2, 4, 4, 3, kGroupDenseStages, true>(tile_grp[0], s)
+                      : launch_gemm_group<2, 2, 2, 2, 3, 3, false>(tile_grp[1], s);
   };
   // A layer alone takes 64 x 64 tiles when 128 x 128 ones would leave most compute units idle; the layers of a
   // call fill the chip together, so they take the larger tiles (half the operand traffic into the compute

@@ -39,3 +39,24 @@ def test_products(T, K, O, N, M):
     both = [torch.empty((T, O), dtype=torch.float32, device="cuda") for _ in range(2)]
     nm.nm_linear_forward_prepared_batched([(v, i, K, N, M, Xd, ws, bd, b) for b in both])
     assert torch.equal(both[0], y) and torch.equal(both[1], y)
+
+
+@pytest.mark.parametrize("blocks,T", [(1, 197), (2, 197), (3, 130)])
+def test_batched_calls_with_narrow_tiles(blocks, T):
+    # few layers of unequal depth: the deep ones take tiles of 64 out-features, ragged in both directions; the same bytes
+    # as the single calls
+    rng = np.random.default_rng(13500 + blocks + T)
+    levels = [(2, 4), (4, 8), (1, 8), (4, 4), (2, 8), (4, 16), (1, 16)]
+    descs, singles = [], []
+    for n in range(4 * blocks):
+        K, O = ((768, 2304), (768, 776), (768, 3072), (3072, 776))[n % 4]
+        N, M = levels[(n + n // 4) % 7]
+        X = dev_bf16(wl.draw_activations(rng, T, K))
+        v, i = nm.nm_pack(dev_bf16(wl.draw_weights(rng, O, K)), N, M)
+        ws = nm.nm_spmm_prepare(v, i, K, N, M, T)
+        out = torch.full((T + 1, O), 7.0, dtype=torch.bfloat16 if n % 2 else torch.float32, device="cuda")
+        singles.append(nm.nm_linear_forward_prepared(v, i, K, N, M, X, ws, out_dtype=out.dtype))
+        descs.append((v, i, K, N, M, X, ws, None, out))
+    nm.nm_linear_forward_prepared_batched([d[:8] + (d[8][:T],) for d in descs])
+    for d, y in zip(descs, singles):
+        assert torch.equal(d[8][:T], y) and bool((d[8][T] == 7).all()), d[2:5]
