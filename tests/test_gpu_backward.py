@@ -146,3 +146,18 @@ def test_gradients_at_batch256_sampled():
     orows = np.unique(np.concatenate([np.arange(4), np.arange(O - 4, O), rng.integers(4, O - 4, size=8)]))
     _, dWref, _, BW = orc.nm_linear_backward(dY[:, orows], X, W[orows], mask[orows])
     check_output(host_output(dW[torch.from_numpy(orows).cuda()]), dWref, BW, T, True, "dW")
+
+
+def test_input_gradient_of_a_misaligned_weight():
+    # the transposing pre-pass reads the weight element by element where its rows are no whole 16-byte pieces; columns
+    # that end inside a 64-wide tile, more than one tile of reduction rows
+    T, K, O, N, M = 27 * 256 + 37, 8 * 256 + 8, 192, 2, 8
+    assert nm.nm_backward_input_workspace_bytes(O, K, T) > 0
+    X, W, dY, mask = draw(6160, T, K, O, N, M)
+    Ws = dev_bf16(orc.apply_mask(W, mask))
+    dX = nm.nm_linear_backward_input(Ws, dev_bf16(dY))
+    dXref, _, BX, _ = orc.nm_linear_backward(dY, X, W, mask)
+    check_output(host_output(dX), dXref, BX, O, True, "aligned")
+    big = torch.full((O, K + 5), float("nan"), dtype=torch.bfloat16, device="cuda")
+    big[:, 1:K + 1] = Ws
+    assert torch.equal(nm.nm_linear_backward_input(big[:, 1:K + 1], dev_bf16(dY)), dX)
