@@ -1126,30 +1126,42 @@ nm_stream_kernel(const StreamGroup g) {
 
   // ---- prologue: three stages in flight, the first one landed, its first fragments in registers
   // A stage's loads leave LPG at a time (one, when there are as many groups as loads), SPREAD groups apart, from
-  // the barrier that frees the buffer (after group TT-3) round to the groups before the next step's barrier:
-  // loads d LPG .. d LPG + LPG - 1 after group (TT - 3 + d SPREAD) mod TT.
+  // the barrier that frees the buffer (before group BAR) round to the groups before the next step's barrier:
+  // loads d LPG .. d LPG + LPG - 1 after group (BAR + d SPREAD) mod TT.
   // HEAD of them fall into the step that freed the buffer, the others into the next one.  The requests of the
   // eight waves then reach the CU's one load path spread over the step instead of in one burst, behind which
   // every wave's matrix instructions would queue (a wave issues in order).
+  // 2:4 form (bfloat16): the W loads of a stage leave in the next step, after the write-out of a tile that ended with the buffer's
+  // step: the write-out uses the part of the buffer that they refill.  Where the even spacing brings them earlier, the X
+  // loads and selectors go into the groups of the step that freed the buffer and the W loads into the first ones of the next.
   constexpr int LPG = (C::LPW + C::TT - 1) / C::TT;                     // loads that leave together
   constexpr int SLOTS = (C::LPW + LPG - 1) / LPG;
   constexpr int SPREAD = 2 * SLOTS <= C::TT ? 2 : 1;
-  constexpr int HEAD = ((C::PRE + SPREAD - 1) / SPREAD) * LPG < C::LPW ? ((C::PRE + SPREAD - 1) / SPREAD) * LPG : C::LPW;
-  static_assert((SLOTS - 1) * SPREAD < C::TT, "the last load must be out before the next step's wait");
+  constexpr bool TURN_IN_LDS = SPARSE && !I8;                           // which write-out, see there
+  constexpr bool EVEN = !TURN_IN_LDS || C::X_PW / LPG * SPREAD >= C::PRE;
+  constexpr int EARLY = C::X_PW + C::S_PW;                              // loads that are not of W
+  constexpr int EARLY_PER = (EARLY + C::PRE - 1) / C::PRE;
+  constexpr int LAST = EVEN ? C::LPW - 1 : C::X_PW + C::A_PW - 1;       // the load that completes a stage
+  auto since_of = [](int d) constexpr {                                 // groups between the barrier and the d-th load
+    if (EVEN) return d / LPG * SPREAD;
+    const int q = d - C::X_PW;
+    if (q >= 0 && q < C::A_PW) return C::PRE + (q < C::BAR ? q : C::BAR - 1);
+    return (q < 0 ? d : d - C::A_PW) / EARLY_PER;
+  };
+  constexpr int HEAD_EVEN = (C::PRE + SPREAD - 1) / SPREAD * LPG;
+  constexpr int HEAD = !EVEN ? EARLY : HEAD_EVEN < C::LPW ? HEAD_EVEN : C::LPW;  // loads that leave in the step that freed the buffer
+  static_assert(since_of(C::LPW - 1) < C::TT && since_of(LAST) < C::TT && HEAD <= C::LPW, "the last load must be out before the next step's wait");
+  static_assert(!TURN_IN_LDS || since_of(C::X_PW) >= C::PRE && since_of(C::X_PW + C::A_PW - 1) >= C::PRE, "W loads follow the write-out");
   cursor_tile(0);
 #pragma unroll
   for (int s = 0; s < STAGES; ++s) {
-    if (s + 1 < STAGES) {
-      [&]<int... D>(std::integer_sequence<int, D...>) {
-        (issue_one(std::integral_constant<int, D>{}, (uint32_t)(s * C::STAGE)), ...);
-      }(std::make_integer_sequence<int, C::LPW>{});
-      cursor_advance();
-    } else {  // the last one's tail leaves in the first step
-      [&]<int... D>(std::integer_sequence<int, D...>) {
-        (issue_one(std::integral_constant<int, D>{}, (uint32_t)(s * C::STAGE)), ...);
-      }(std::make_integer_sequence<int, HEAD>{});
-      if constexpr (HEAD == C::LPW) cursor_advance();
-    }
+    [&]<int... D>(std::integer_sequence<int, D...>) {  // the last one's tail leaves in the first step
+      ([&] {
+        constexpr int d = D;
+        if (s + 1 < STAGES || since_of(d) < C::PRE) issue_one(std::integral_constant<int, d>{}, (uint32_t)(s * C::STAGE));
+      }(), ...);
+    }(std::make_integer_sequence<int, C::LPW>{});
+    if (s + 1 < STAGES || HEAD == C::LPW) cursor_advance();
   }
   wait_younger(std::integral_constant<int, HEAD>{});
   __builtin_amdgcn_s_barrier();
@@ -1225,17 +1237,15 @@ nm_stream_kernel(const StreamGroup g) {
           // the load that leaves after this group, if any: into the buffer this step has consumed (free since the
           // barrier), or the rest of the stage begun in the previous step into the buffer consumed there
           constexpr int since = (j - C::BAR + TT) % TT;  // groups since the barrier
-          if constexpr (since % SPREAD == 0 && since / SPREAD < SLOTS) {
-            [&]<int... Q>(std::integer_sequence<int, Q...>) {
-              ([&] {
-                constexpr int d = since / SPREAD * LPG + Q;
-                if constexpr (d < C::LPW) {
-                  issue_one(std::integral_constant<int, d>{}, j >= C::BAR ? cur_off : prev_off);
-                  if constexpr (d == C::LPW - 1) cursor_advance();
-                }
-              }(), ...);
-            }(std::make_integer_sequence<int, LPG>{});
-          }
+          [&]<int... D>(std::integer_sequence<int, D...>) {
+            ([&] {
+              constexpr int d = D;
+              if constexpr (since_of(d) == since) {
+                issue_one(std::integral_constant<int, d>{}, j >= C::BAR ? cur_off : prev_off);
+                if constexpr (d == LAST) cursor_advance();
+              }
+            }(), ...);
+          }(std::make_integer_sequence<int, C::LPW>{});
         }
         __builtin_amdgcn_sched_barrier(0);
       }(), ...);
@@ -1292,14 +1302,12 @@ nm_stream_kernel(const StreamGroup g) {
     }
     if (n + 1 == my_tiles) wait_loads_outstanding<0>();  // the surplus stages: nothing in flight when the block ends
 
-    // ---- write the tile out (no LDS memory: the stage ring already holds the next tile).  A lane holds
-    // out-features o .. o+3 of token r16 per 16 x 16 block; for bfloat16 two blocks are exchanged between
-    // the lane rows kb and kb^1, so that every lane owns 8 consecutive out-features (16 bytes), and a lane
-    // permutation then puts the eight pieces of a token row's 128 bytes (the wave's 64 out-features) into eight
-    // consecutive lanes: a store instruction is merged only across consecutive lanes, and whole lines leave as
-    // single requests.  The stores carry the non-temporal hint: the output is never read back by this kernel, and
-    // lines that linger in L2 until write-back push out the X rows the neighbouring tiles still need (with the
-    // hint the launch fetches a quarter less; on half lines the same hint costs 40 % more written bytes).
+    // ---- write the tile out.  A lane holds out-features o .. o+3 of token r16 per 16 x 16 block; for bfloat16 the eight
+    // pieces of a token row's 128 bytes (the wave's 64 out-features) are brought into eight consecutive lanes: a store
+    // instruction is merged only across consecutive lanes, and whole lines leave as single requests.  The stores
+    // carry the non-temporal hint: the output is never read back by this kernel, and lines that linger in L2 until
+    // write-back push out the X rows the neighbouring tiles still need (with the hint the launch fetches a quarter
+    // less; on half lines the same hint costs 40 % more written bytes).
     // int8: the sums are rescaled first, y = fma(float(acc), x_scale * w_scale[o], bias[o]); the tile's scales
     // and bias came with its first stage (pair n mod 2, so the next tile's do not overwrite them)
     f32x4_t sc[I8 ? OT : 1], bi[I8 ? OT : 1];
@@ -1329,12 +1337,26 @@ nm_stream_kernel(const StreamGroup g) {
     using gpiece_t = __attribute__((address_space(1))) u32x4_t;
     const int first_row = (int)(t_lo - t0);  // rows of a shifted last tile below this one belong to its neighbour
     if (kind_s == 1) {
-      // Whole 128-byte lines per store: a wave's 64 out-features are one line of a token row.  The two 16-byte
-      // pieces a lane holds for a token block (out-feature pairs 0 and 1, after the exchange between lane rows)
-      // are pushed to the lanes that store them: lane 8m + p stores piece p (0..7) of token row m (first store) and
-      // of token row m + 8 (second store).
-      static_assert(OT % 4 == 0, "a line is two out-feature pairs");
-      constexpr int LINES = OT / 4;  // 128-byte lines per token row of the wave
+      // Whole 128-byte lines per store: a wave's 64 out-features are one line of a token row.  lines_of(j) gives a lane
+      // its pieces of token rows lane / 8 and lane / 8 + 8 of 16-row block j.
+      static_assert(OT == 4 && C::A_PW == 2, "a line is four blocks; two kilobytes per wave");
+      struct Lines { u32x4_t first, second; };
+      // 2:4 form: the wave turns 16 token rows at a time through two kilobytes of LDS, the places of its own W loads in the
+      // buffer that the last step has freed (they leave in the next step): 8 bytes per lane and block in, 16-byte pieces
+      // of whole rows out, the pieces of a row XOR-swizzled with the row.  The LDS operations of a wave run in order, so
+      // nothing waits between a write and a read.  Against the exchange below: 12608 tokens x 768 -> 768 15.1 -> 14.5 us,
+      // 3072 -> 768 36.3 -> 35.0, 50432 x 768 -> 3072 145 -> 140.  The dense form, whose loads would have to move for it,
+      // loses up to 6 % (3072 -> 768 54.0 -> 57.4); int8 gains nothing.
+      const uint32_t freed = cur_off == 0 ? (uint32_t)((STAGES - 1) * C::STAGE) : cur_off - (uint32_t)C::STAGE;
+      unsigned char* slice = smem + freed + C::X_BYTES + wave * 1024;     // rows 0..7; rows 8..15 lie C::NW kilobytes further
+      unsigned char* put = slice + (r16 >> 3) * (C::NW * 1024) + (r16 & 7) * 128 + (kb & 1) * 8;
+      uint32_t put_at[OT];
+#pragma unroll
+      for (int i = 0; i < OT; ++i) put_at[i] = (uint32_t)(((2 * i + (kb >> 1)) ^ (r16 & 7)) * 16);
+      const unsigned char* get = slice + (lane >> 3) * 128 + ((lane & 7) ^ (lane >> 3)) * 16;
+      // Dense form and int8: the two 16-byte pieces a lane holds for a token block (out-feature pairs 0 and 1, after the exchange
+      // between lane rows) are pushed to the lanes that store them: lane 8m + p stores piece p (0..7) of token row m
+      // (first store) and of token row m + 8 (second store).
       const int qk = ((kb & 1) << 1) | (kb >> 1);            // place of this lane's piece inside its pair's 64 bytes
       const int hi_rows = r16 >> 3;                          // this lane's token row belongs to the second store
       const int dest_a = (8 * (r16 & 7) + 4 * hi_rows + qk) * 4;
@@ -1348,44 +1370,49 @@ nm_stream_kernel(const StreamGroup g) {
         const auto s1 = __builtin_amdgcn_permlane16_swap(a1, b1, false, false);
         return u32x4_t{(uint32_t)s0[0], (uint32_t)s1[0], (uint32_t)s0[1], (uint32_t)s1[1]};
       };
-      struct Lines { u32x4_t first, second; };
-      auto lines_of = [&](int q) {  // q = j * LINES + line
-        const int j = q / LINES, h = q % LINES;
-        const u32x4_t p0 = swapped(j, 2 * h), p1 = swapped(j, 2 * h + 1);
-        u32x4_t ra, rb;
+      auto lines_of = [&](int j) {
+        if constexpr (TURN_IN_LDS) {
+          asm volatile("" ::: "memory");  // (nor does the compiler move them past one another)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          // rows 0..7 send pair 0 the first way and pair 1 the second way, rows 8..15 the other way round
-          const int send_a = hi_rows ? (int)p1[e] : (int)p0[e];
-          const int send_b = hi_rows ? (int)p0[e] : (int)p1[e];
-          ra[e] = (uint32_t)__builtin_amdgcn_ds_permute(dest_a, send_a);
-          rb[e] = (uint32_t)__builtin_amdgcn_ds_permute(dest_b, send_b);
-        }
-        Lines l;
+          for (int i = 0; i < OT; ++i) {
+            const f32x4_t v = value(i, j);
+            *reinterpret_cast<uint2*>(put + put_at[i]) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+          }
+          asm volatile("" ::: "memory");
+          return Lines{*reinterpret_cast<const u32x4_t*>(get), *reinterpret_cast<const u32x4_t*>(get + C::NW * 1024)};
+        } else {
+          const u32x4_t p0 = swapped(j, 0), p1 = swapped(j, 1);
+          u32x4_t ra, rb;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          l.first[e] = upper ? rb[e] : ra[e];
-          l.second[e] = upper ? ra[e] : rb[e];
+          for (int e = 0; e < 4; ++e) {
+            // rows 0..7 send pair 0 the first way and pair 1 the second way, rows 8..15 the other way round
+            const int send_a = hi_rows ? (int)p1[e] : (int)p0[e];
+            const int send_b = hi_rows ? (int)p0[e] : (int)p1[e];
+            ra[e] = (uint32_t)__builtin_amdgcn_ds_permute(dest_a, send_a);
+            rb[e] = (uint32_t)__builtin_amdgcn_ds_permute(dest_b, send_b);
+          }
+          Lines l;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            l.first[e] = upper ? rb[e] : ra[e];
+            l.second[e] = upper ? ra[e] : rb[e];
+          }
+          return l;
         }
-        return l;
       };
       const int row = wt * C::TW + (lane >> 3);                            // this lane's row of the tile in block j = 0, first store
       const int64_t col = o0 + wo * C::OW + (lane & 7) * 8;              // its out-features in line 0
       gbyte_t* dst = (gbyte_t*)y_s + ((t0 + row) * (int64_t)ldy_s + col) * 2;
       const int64_t half_bytes = (int64_t)ldy_s * 16;                    // 8 token rows further
-      bool col_ok[LINES];
-#pragma unroll
-      for (int h = 0; h < LINES; ++h) col_ok[h] = col + h * 64 < o_s;
+      const bool col_ok = col < o_s;
       Lines cur = lines_of(0);
 #pragma unroll
-      for (int q = 0; q < TT * LINES; ++q) {
-        const int j = q / LINES, h = q % LINES;
+      for (int j = 0; j < TT; ++j) {
         Lines nxt = cur;
-        if (q + 1 < TT * LINES) nxt = lines_of(q + 1);
-        if (row + j * 16 >= first_row && col_ok[h]) __builtin_nontemporal_store(cur.first, (gpiece_t*)(dst + h * 128));
-        if (row + j * 16 + 8 >= first_row && col_ok[h])
-          __builtin_nontemporal_store(cur.second, (gpiece_t*)(dst + half_bytes + h * 128));
-        if (h == LINES - 1) dst += 2 * half_bytes;
+        if (j + 1 < TT) nxt = lines_of(j + 1);
+        if (row + j * 16 >= first_row && col_ok) __builtin_nontemporal_store(cur.first, (gpiece_t*)dst);
+        if (row + j * 16 + 8 >= first_row && col_ok) __builtin_nontemporal_store(cur.second, (gpiece_t*)(dst + half_bytes));
+        dst += 2 * half_bytes;
         cur = nxt;
       }
     } else {
