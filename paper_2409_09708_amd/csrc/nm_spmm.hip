@@ -209,7 +209,31 @@ struct GemmArgs {
   uint8_t splits;       // ranges the reduction is cut into (tiled kernel only; 1 = the whole K in one block)
   uint8_t rot;          // tiled kernel: XCD x takes the layer's share number (x + rot) mod 8
   uint8_t x_align;      // bytes every X row start is a multiple of: 16, 8, 4 or 2 (read by the register-staged form only)
+  // ragged form only: the packed weight itself, for the sums that are computed a second time
+  uint8_t N, M;
+  const bf16_t* values;
+  const uint32_t* indices;
 };
+
+// One output by the definition: the kept weights of out-feature o in stored order times the activations at their
+// positions, then the bias.  An activation at a pruned position is not read.
+__device__ __forceinline__ float gather_output(const bf16_t* __restrict__ values, const uint32_t* __restrict__ indices,
+                                               int64_t K, int N, int M, const bf16_t* __restrict__ x,
+                                               const float* __restrict__ bias, int64_t o) {
+  const int b = log2_of(M);
+  const int64_t nf = K / M * N;
+  const int64_t nw = (nf * b + 31) / 32;
+  const uint32_t* row = indices + o * nw;
+  float acc = 0.f;
+  for (int64_t g = 0; g < K / M; ++g) {
+    for (int j = 0; j < N; ++j) {
+      const int64_t f = g * N + j;
+      const uint32_t p = stream_bits(row, nw, f * b, b);
+      acc = fmaf(bf16_to_f32(x[g * M + p]), bf16_to_f32(values[o * nf + f]), acc);
+    }
+  }
+  return bias ? acc + bias[o] : acc;
+}
 
 template <bool SPARSE, int WO, int WT, int OT, int TT, int STAGES_>
 struct GemmCfg {
@@ -652,6 +676,38 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned block, uns
     write_wave_tile_rows<OT, TT, 2>(smem + wave * wave_tile_slice_bytes<OT, 4>(), lane, get, out_ptr, out_ld, row0, col0, a.T, a.O);
   } else {
     write_wave_tile_rows<OT, TT, 4>(smem + wave * wave_tile_slice_bytes<OT, 4>(), lane, get, out_ptr, out_ld, row0, col0, a.T, a.O);
+  }
+
+  if constexpr (X_REGS || TAIL) {
+    // The shapes of the ragged form are the gather kernel's when there is no workspace, and an infinity or NaN among the
+    // activations must not change a product by the way it was computed: a zero of the padded weight makes NaN of it
+    // where the gather skips it.  Sums that ended as NaN are computed again by the definition.  The test is one
+    // comparison per two sums (1579 x 1000 -> 1001 at 2:8: no measurable time).
+    bool any = false;
+#pragma unroll
+    for (int i = 0; i < OT; ++i)
+#pragma unroll
+      for (int j = 0; j < TT; ++j)
+        any |= __builtin_isunordered(acc[i][j][0], acc[i][j][1]) || __builtin_isunordered(acc[i][j][2], acc[i][j][3]);
+    if (any) {
+      uint64_t which = 0;  // bit 4 (i TT + j) + e
+#pragma unroll
+      for (int i = 0; i < OT; ++i)
+#pragma unroll
+        for (int j = 0; j < TT; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            which |= (uint64_t)(__builtin_isnan(acc[i][j][e]) ? 1 : 0) << (4 * (i * TT + j) + e);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // another lane of this wave has stored the element: it is out
+      for (; which != 0; which &= which - 1) {
+        const int bit = __ffsll((unsigned long long)which) - 1;
+        const int64_t o = col0 + (bit >> 2) / TT * 16 + kb * 4 + (bit & 3), t = row0 + (bit >> 2) % TT * 16 + r16;
+        if (o >= a.O || t >= a.T) continue;
+        const float y = gather_output(a.values, a.indices, a.K, a.N, a.M, a.X + t * a.ldx, a.bias, o);
+        if (out_bf16) reinterpret_cast<bf16_t*>(out_ptr)[t * out_ld + o] = (bf16_t)f32_to_bf16_rne(y);
+        else reinterpret_cast<float*>(out_ptr)[t * out_ld + o] = y;
+      }
+    }
   }
 }
 
@@ -1445,22 +1501,10 @@ __global__ void __launch_bounds__(256)
 spmm_general_kernel(const bf16_t* __restrict__ values, const uint32_t* __restrict__ indices, int64_t O, int64_t K, int N,
                     int M, const bf16_t* __restrict__ X, int64_t T, int64_t ldx, const float* __restrict__ bias,
                     void* __restrict__ Y, int64_t ldy, int out_bf16, int64_t n_o_tiles) {
-  const int b = log2_of(M);
   const int64_t o = (blockIdx.x % n_o_tiles) * 16 + (threadIdx.x & 15);
   const int64_t t = (blockIdx.x / n_o_tiles) * 16 + (threadIdx.x >> 4);
   if (o >= O || t >= T) return;
-  const int64_t nf = K / M * N;
-  const int64_t nw = (nf * b + 31) / 32;
-  const uint32_t* row = indices + o * nw;
-  float acc = 0.f;
-  for (int64_t g = 0; g < K / M; ++g) {
-    for (int j = 0; j < N; ++j) {
-      const int64_t f = g * N + j;
-      const uint32_t p = stream_bits(row, nw, f * b, b);
-      acc = fmaf(bf16_to_f32(X[t * ldx + g * M + p]), bf16_to_f32(values[o * nf + f]), acc);
-    }
-  }
-  if (bias) acc += bias[o];
+  const float acc = gather_output(values, indices, K, N, M, X + t * ldx, bias, o);
   if (out_bf16) reinterpret_cast<bf16_t*>(Y)[t * ldy + o] = (bf16_t)f32_to_bf16_rne(acc);
   else reinterpret_cast<float*>(Y)[t * ldy + o] = acc;
 }
@@ -2026,6 +2070,7 @@ static hipError_t launch_stream_prepass(const SpmmArgs& a, bool sparse_form, hip
 static void fill_gemm_args(const SpmmArgs& a, int form, bool sparse_form, GemmArgs* g) {
   g->X = a.X; g->bias = a.bias; g->Y = a.Y;
   g->O = a.O; g->K = a.K; g->T = a.T; g->ldx = a.ldx; g->ldy = a.ldy;
+  g->N = (uint8_t)a.N; g->M = (uint8_t)a.M; g->values = a.values; g->indices = a.indices;
   g->out_bf16 = a.out_bf16;
   g->n_o_tiles = g->n_t_tiles = 0;
   g->rot = 0;

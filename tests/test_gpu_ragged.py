@@ -95,3 +95,39 @@ def test_whole_pieces_and_a_short_last_step(T, K, O, N, M):
         y = nm.nm_linear_forward(v, i, K, N, M, view, bias=bias)
         check_output(host_output(y), Yref, B, K // M * N + 1, True, (T, K, O, N, M, pitch))
         flat.fill_(float("nan"))
+
+
+# An infinity or NaN among the activations: products that reach the zero-padded operand give what the gather gives, which
+# never reads an activation at a pruned position (without a workspace these views run it).  The forms are the
+# asynchronous copies and the registers, on both tiles, and an output whose rows the persistent kernel cannot write.
+@pytest.mark.parametrize("N,M", [(1, 4), (2, 8), (4, 8), (1, 16), (6, 16)])
+@pytest.mark.parametrize("T,K,O,offset", [(67, 80, 65, 0), (70, 80, 64, 0), (67, 176, 65, 1), (2049, 176, 2047, 0), (2049, 176, 2047, 1),
+                                          (130, 192, 131, 2), (12001, 192, 771, 0)])
+def test_activations_that_are_not_finite(T, K, O, offset, N, M):
+    rng = np.random.default_rng(11990 + T + K + N + M)
+    X = dev_bf16(wl.draw_activations(rng, T, K))
+    X[:, 5] = float("inf")
+    X[T // 2, 17] = float("nan")
+    X[T - 1, :] = float("-inf")
+    v, i = nm.nm_pack(dev_bf16(wl.draw_weights(rng, O, K)), N, M)
+    bias = torch.from_numpy(rng.standard_normal(O).astype(np.float32)).cuda()
+    wide = torch.zeros((T, K + 9), dtype=torch.bfloat16, device="cuda")
+    one = wide[:, 1:K + 1]  # a view that is multiplied by the gather kernel when there is no workspace
+    one.copy_(X)
+    view = X
+    if offset:
+        wide2 = torch.zeros((T, K + 10), dtype=torch.bfloat16, device="cuda")
+        view = wide2[:, offset:offset + K]
+        view.copy_(X)
+    ref = nm.nm_linear_forward(v, i, K, N, M, one, bias=bias, from_packed=True)
+    y = nm.nm_linear_forward(v, i, K, N, M, view, bias=bias)
+    assert torch.equal(torch.isnan(y), torch.isnan(ref))
+    assert torch.equal(torch.isinf(y), torch.isinf(ref)) and torch.equal(y[torch.isinf(y)], ref[torch.isinf(ref)])
+    assert bool(torch.isfinite(y).any())
+    # finite sums: two orders of an fp32 sum of terms + 1 products, each within (terms + 2) 2^-24 sum |x w| of the exact one
+    finite = torch.where(torch.isfinite(X), X, torch.zeros_like(X))
+    B = finite.double().abs() @ nm.nm_unpack(v, i, K, N, M).double().abs().t() + bias.double().abs()
+    ok = torch.isfinite(ref)
+    assert bool(((y.double() - ref.double()).abs()[ok] <= 2 * (K // M * N + 3) * 2.0 ** -24 * B[ok]).all())
+    y16 = nm.nm_linear_forward(v, i, K, N, M, view, bias=bias, out_dtype=torch.bfloat16)
+    assert torch.equal(torch.isnan(y16), torch.isnan(ref)) and torch.equal(torch.isinf(y16), torch.isinf(ref.bfloat16()))
