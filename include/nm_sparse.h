@@ -252,6 +252,9 @@ int32_t nm_linear_forward(const nm_bf16* values, const uint32_t* indices, int64_
  *                     (A layer whose cut reduction, see nm_spmm, does not fit beside that copy, i.e.
  *                     nm_spmm_workspace_bytes(O, K, N, M, T) > nm_static_scratch_bytes(), is multiplied uncut: the
  *                     result of nm_linear_forward up to rounding order.)
+ *   A layer with K % 64 != 0 is never refused: a copy larger than the array is made and used a run of out-features at
+ *   a time, with the same bytes written.  Above K = 16384 (N > 2) or 29120 (N <= 2) not even 256 out-features
+ *   fit; the general kernel then reads the packed layout (the result of nm_linear_forward up to rounding order).
  * All calls on one device share that device's array: two such calls whose kernels may overlap (different streams,
  * or threads) race on it; calls on one stream are ordered and safe.  The array keeps the last call's contents;
  * every call rewrites the part it reads, so nothing needs clearing.

@@ -326,7 +326,7 @@ int32_t nm_linear_forward_static(const nm_bf16* values, const uint32_t* indices,
   a.workspace = ws;
   a.workspace_bytes = kStaticScratchBytes;
   bool workspace_short = false;
-  hipError_t e = nm::launch_spmm(a, (hipStream_t)stream, &workspace_short, nm::SPMM_PREPARE | nm::SPMM_PRODUCT);
+  hipError_t e = nm::launch_spmm_on_scratch(a, (hipStream_t)stream, &workspace_short);
   if (workspace_short) return NM_ERR_WORKSPACE;
   return device_status(e);
 }

@@ -124,6 +124,7 @@ bool spmm_stream_order(int64_t O, int64_t K, int64_t T, int N, int M, bool* spar
 // missing, misaligned or too small (nothing is launched then)
 enum { SPMM_PREPARE = 1, SPMM_PRODUCT = 2 };
 hipError_t launch_spmm(const SpmmArgs& a, hipStream_t s, bool* workspace_short, int phases);
+hipError_t launch_spmm_on_scratch(const SpmmArgs& a, hipStream_t s, bool* workspace_short);
 // the products (SPMM_PRODUCT) of many prepared layers, sharing launches where the shapes allow
 // (the caller has checked the workspaces with spmm_workspace_short)
 bool spmm_workspace_short(const SpmmArgs& a);

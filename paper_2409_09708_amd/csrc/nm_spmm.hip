@@ -2173,6 +2173,27 @@ hipError_t launch_spmm(const SpmmArgs& a, hipStream_t s, bool* workspace_short, 
   return sparse_form ? dispatch_gemm<true>(g, pick, s) : dispatch_gemm<false>(g, pick, s);
 }
 
+// nm_linear_forward on a scratch of a given size.  The operand copy of a ragged reduction may be larger than that: the
+// layer is then prepared and multiplied a run of out-features at a time, as many 256-row tiles as fit.  An output's
+// sum does not depend on the tiles around it, so the bytes are those of the whole layer in one workspace.
+hipError_t launch_spmm_on_scratch(const SpmmArgs& a, hipStream_t s, bool* workspace_short) {
+  bool sparse_form = false;
+  const size_t tile_bytes = ragged_shape(a.O, a.K, a.T) ? operand_bytes(256, a.K, a.N, a.M, a.T, &sparse_form) : 0;
+  const int64_t rows = tile_bytes ? (int64_t)(a.workspace_bytes / tile_bytes) * 256 : 0;
+  if (rows == 0) return launch_spmm(a, s, workspace_short, SPMM_PREPARE | SPMM_PRODUCT);
+  const int64_t nf = values_per_row(a.K, a.N, a.M), nw = index_words_per_row(a.K, a.N, a.M);
+  for (int64_t o = 0; o < a.O; o += rows) {
+    SpmmArgs part = a;
+    part.values += o * nf;
+    part.indices += o * nw;
+    if (part.bias) part.bias += o;
+    part.Y = static_cast<unsigned char*>(a.Y) + o * (a.out_bf16 ? 2 : 4);
+    part.O = a.O - o < rows ? a.O - o : rows;
+    if (hipError_t e = launch_spmm(part, s, workspace_short, SPMM_PREPARE | SPMM_PRODUCT); e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // The product of a prepared layer on the tiled kernel, as a table entry (the operands launch_spmm would hand the
 // kernel): false when the layer takes another path.
 static bool tiled_entry(const SpmmArgs& a, GemmArgs* g, bool* sparse_form, int* pick) {

@@ -131,3 +131,18 @@ def test_activations_that_are_not_finite(T, K, O, offset, N, M):
     assert bool(((y.double() - ref.double()).abs()[ok] <= 2 * (K // M * N + 3) * 2.0 ** -24 * B[ok]).all())
     y16 = nm.nm_linear_forward(v, i, K, N, M, view, bias=bias, out_dtype=torch.bfloat16)
     assert torch.equal(torch.isnan(y16), torch.isnan(ref)) and torch.equal(torch.isinf(y16), torch.isinf(ref.bfloat16()))
+
+
+# The call on the fixed scratch, at operand copies that fit it and that are larger: 16 blocks of 256 out-features fit at
+# K = 1000 in the dense form, 29 in the 2:4 form
+@pytest.mark.parametrize("T,K,O,N,M", [(70, 1000, 4096, 4, 8), (70, 1000, 4097, 4, 8), (300, 1000, 8448, 4, 8),
+                                       (70, 1000, 7425, 2, 8), (70, 4004, 3001, 3, 4)])
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
+def test_fixed_scratch_writes_the_same_bytes(T, K, O, N, M, out_dtype):
+    X, v, i, bias, _, _ = layer(12100 + O + N, T, K, O, N, M)
+    Xd = dev_bf16(X)
+    y = nm.nm_linear_forward(v, i, K, N, M, Xd, bias=bias, out_dtype=out_dtype)
+    out = torch.full((T, O + 3), 7.0, dtype=out_dtype, device="cuda")
+    nm.nm_linear_forward_static(v, i, K, N, M, Xd, bias=bias, out=out[:, 1:O + 1])
+    assert torch.equal(out[:, 1:O + 1], y)
+    assert bool((out[:, 0] == 7).all() and (out[:, O + 1:] == 7).all())
