@@ -1797,17 +1797,32 @@ static hipError_t launch_gemm_group(TileGroup& grp, hipStream_t s) {
   return hipGetLastError();
 }
 
-// The tile height of a launch: the smallest estimate.  The tiles of several layers form one list, which ends in one
-// partial round.
+template <bool SPARSE, bool I8>
+static constexpr int stream_stages(int tt) {
+  return tt == 4   ? StreamCfg<SPARSE, 4, I8>::STAGES
+         : tt == 5 ? StreamCfg<SPARSE, 5, I8>::STAGES
+         : tt == 6 ? StreamCfg<SPARSE, 6, I8>::STAGES
+         : tt == 7 ? StreamCfg<SPARSE, 7, I8>::STAGES
+                   : StreamCfg<SPARSE, 8, I8>::STAGES;
+}
+// int8: the per-tile constants alternate between two LDS slices, so a tile has to have as many steps as stages.
+template <bool SPARSE>
+static constexpr int stream_i8_min_steps() {
+  int least = stream_stages<SPARSE, true>(kStreamHeights[0]);
+  for (int tt : kStreamHeights)
+    if (stream_stages<SPARSE, true>(tt) < least) least = stream_stages<SPARSE, true>(tt);
+  return least;
+}
+
+// The tile height of a launch: the smallest estimate; 0 when no height can take it.  The tiles of several layers form
+// one list, which ends in one partial round.
 template <bool SPARSE, bool I8>
 static int stream_height(const StreamGroup& grp) {
   const StreamModel& m = kStreamModel[I8][SPARSE];
-  int best_tt = kStreamHeights[0];
+  int best_tt = 0;
   double best = 0;
   for (int tt : kStreamHeights) {
-    if (I8 && grp.layer[0].nk < (tt > 6 ? StreamCfg<SPARSE, 8, I8>::STAGES : tt > 5 ? StreamCfg<SPARSE, 6, I8>::STAGES
-                                                                                   : StreamCfg<SPARSE, 4, I8>::STAGES))
-      continue;  // the per-tile constants alternate between two LDS slices: a tile has to have as many steps as stages
+    if (I8 && grp.layer[0].nk < stream_stages<SPARSE, I8>(tt)) continue;
     double e = 0;
     if (grp.count == 1) {
       e = stream_estimate(m, grp.layer[0].O, grp.layer[0].T, grp.layer[0].nk, tt);
@@ -1821,7 +1836,7 @@ static int stream_height(const StreamGroup& grp) {
       }
       e = (e < longest ? longest : e) + longest / 2;
     }
-    if (tt == kStreamHeights[0] || e < best) { best = e; best_tt = tt; }
+    if (best_tt == 0 || e < best) { best = e; best_tt = tt; }
   }
   return best_tt;
 }
@@ -1857,7 +1872,8 @@ static hipError_t launch_stream_group(StreamGroup& grp, hipStream_t s) {
     case 5: return launch_stream_kernel<SPARSE, 5, I8>(grp, s);
     case 6: return launch_stream_kernel<SPARSE, 6, I8>(grp, s);
     case 7: return launch_stream_kernel<SPARSE, 7, I8>(grp, s);
-    default: return launch_stream_kernel<SPARSE, 8, I8>(grp, s);
+    case 8: return launch_stream_kernel<SPARSE, 8, I8>(grp, s);
+    default: return hipErrorInvalidValue;
   }
 }
 
@@ -1891,9 +1907,25 @@ static hipError_t launch_stream(const GemmArgs& g, hipStream_t s) {
 bool stream_i8_takes(int64_t O, int64_t K, int64_t T, int N, int M) {
   const bool sparse_form = N <= 2 && N < M;
   const int64_t kstep = sparse_form ? 128 : 64;
-  // the per-tile constants alternate between two LDS slices, which needs tiles of at least three steps (the highest
-  // tiles have three stages)
-  return pick_tile(O, T, K / kstep, kStreamModel[1][sparse_form], K / 128, sparse_form ? 0.5 : 1.0) == 0 && K % kstep == 0 && K / kstep >= 3 && O <= (1 << 24) && T < (1ll << 31) && K <= (1 << 22);
+  const int64_t min_steps = sparse_form ? stream_i8_min_steps<true>() : stream_i8_min_steps<false>();
+  return pick_tile(O, T, K / kstep, kStreamModel[1][sparse_form], K / 128, sparse_form ? 0.5 : 1.0) == 0 && K % kstep == 0 && K / kstep >= min_steps && O <= (1 << 24) && T < (1ll << 31) && K <= (1 << 22);
+}
+
+// Not in the public header, for tests: tokens per tile and LDS stages of a launch of the persistent kernel for one layer
+// of nk steps (0: no height takes it).
+extern "C" int32_t nm_internal_stream_tile(int32_t int8, int32_t sparse_form, int64_t O, int64_t T, int64_t nk, int32_t* stages) {
+  StreamGroup grp;
+  grp.count = 1; grp.n_tiles = 0;
+  StreamLayer& L = grp.layer[0];
+  L.O = (int32_t)O; L.T = (int32_t)T; L.nk = (int32_t)nk; L.n_o_tiles = (int32_t)((O + 255) / 256);
+  int tt = 0;
+  auto ask = [&](auto sparse, auto i8) {
+    tt = stream_height<decltype(sparse)::value, decltype(i8)::value>(grp);
+    *stages = tt ? stream_stages<decltype(sparse)::value, decltype(i8)::value>(tt) : 0;
+  };
+  if (sparse_form) int8 ? ask(std::true_type{}, std::true_type{}) : ask(std::true_type{}, std::false_type{});
+  else int8 ? ask(std::false_type{}, std::true_type{}) : ask(std::false_type{}, std::false_type{});
+  return 32 * tt;
 }
 
 hipError_t launch_stream_i8(const StreamI8Args& a, hipStream_t s) {

@@ -425,3 +425,16 @@ def test_weights_beyond_the_grid_limit_are_refused(lib):
     assert lib.nm_prune(FAKE, big, big, big, 2, 4, FAKE, None, None) == 2
     assert lib.nm_unpack(FAKE, FAKE, big, big, 2, 4, FAKE, big, None) == 2
     assert lib.nm_values_bytes(1 << 20, 1 << 20, 2, 4) == (1 << 40)
+
+
+def test_int8_tiles_have_as_many_steps_as_stages(lib):
+    # the scales and biases of a tile alternate between two slices: a tile shorter than the load pipeline would have its
+    # own overwritten before it is written out
+    for sparse_form in (0, 1):
+        for nk in range(1, 9):
+            for O, T in ((128, 256), (768, 1576), (768, 12608), (3072, 50432), (200, 200704)):
+                stages = ctypes.c_int32(0)
+                tokens = lib.nm_internal_stream_tile(1, sparse_form, ctypes.c_int64(O), ctypes.c_int64(T),
+                                                     ctypes.c_int64(nk), ctypes.byref(stages))
+                assert tokens in (0, 128, 160, 192, 224, 256)
+                assert stages.value <= nk and (tokens != 0) == (nk >= (3 if sparse_form else 4)), (sparse_form, nk, tokens)
