@@ -158,7 +158,7 @@ score_mask_kernel(const float* __restrict__ score, int64_t O, int64_t K, int64_t
                   uint32_t* __restrict__ mask) {
   constexpr int PER_WORD = 32 / M;  // a power of two: the lanes of a word are neighbours in one wave
   const int64_t nw = mask_words_per_row(K), per_row = nw * PER_WORD;
-  const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t id = flat_lane_256();
   int64_t o, g;  // row and group of the row (past K / M in a row's last word: nothing kept)
   if (O * per_row < (int64_t)1 << 31) {
     o = (uint32_t)id / (uint32_t)per_row;
@@ -263,8 +263,7 @@ hipError_t launch_rank_mask(const uint8_t* rank, int64_t O, int64_t K, int N, ui
 hipError_t launch_score_mask(const float* score, int64_t O, int64_t K, int64_t lds, int N, int M, uint32_t* mask,
                              hipStream_t s) {
   const int64_t n = O * mask_words_per_row(K) * (32 / M);
-  if ((n + 255) / 256 > 0x7FFFFFFF) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)((n + 255) / 256));
+  const dim3 grid = flat_grid_256(n);
   const bool wide = lds % 4 == 0 && ((uintptr_t)score & 15u) == 0;
   auto go = [&](auto m, auto w) {
     hipLaunchKernelGGL((score_mask_kernel<decltype(m)::value, decltype(w)::value>), grid, dim3(256), 0, s, score, O, K,

@@ -57,7 +57,7 @@ operand_stream_kernel(const bf16_t* __restrict__ values, const uint32_t* __restr
   constexpr int BYTES = SPARSE ? 16 : 32, STRIDE = BYTES + 16;
   __shared__ __attribute__((aligned(16))) unsigned char places[256 * STRIDE];
   const int64_t per_row = K_pad / 16;
-  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t id = flat_lane_256();
   if (id >= O_pad * per_row) return;
   int64_t o, kc;
   if (O_pad * per_row < (int64_t)1 << 31) {  // the 32-bit division is a fifth of the 64-bit one
@@ -2081,9 +2081,7 @@ static hipError_t launch_stream_prepass(const SpmmArgs& a, bool sparse_form, hip
   unsigned char* ws = reinterpret_cast<unsigned char*>(a.workspace);
   const int64_t o_pad = ((a.O + 255) / 256) * 256, k_pad = padded_k(a.K);
   unsigned char* sel_s = sparse_form ? ws + (size_t)o_pad * (size_t)k_pad : nullptr;
-  const int64_t n = o_pad * (k_pad / 16);
-  if ((n + 255) / 256 > 0x7FFFFFFF) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)((n + 255) / 256));
+  const dim3 grid = flat_grid_256(o_pad * (k_pad / 16));
   const int wide = (a.K % 16 == 0) && aligned_to(a.values, 16);  // every 16-weight chunk is whole and its values aligned
   switch (a.N * 32 + a.M) {
 #define X(n_, m_)                                                                                                  \
