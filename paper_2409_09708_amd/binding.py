@@ -272,8 +272,8 @@ def _contiguous_weight(W, caller: str) -> Tuple[int, int]:
     _need(W, _torch().bfloat16, "W")
     if not W.is_contiguous():
         raise ValueError(f"{caller} needs contiguous weights")
-    O, K = W.shape
-    return O, K
+    shape = W.shape  # (a weight with trailing dimensions of one is a matrix to these calls)
+    return shape[0], shape[1]
 
 
 def _packed(values, indices, dtype) -> int:

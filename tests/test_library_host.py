@@ -438,3 +438,20 @@ def test_int8_tiles_have_as_many_steps_as_stages(lib):
                                                      ctypes.c_int64(nk), ctypes.byref(stages))
                 assert tokens in (0, 128, 160, 192, 224, 256)
                 assert stages.value <= nk and (tokens != 0) == (nk >= (3 if sparse_form else 4)), (sparse_form, nk, tokens)
+
+
+def test_batched_calls_read_the_first_two_sizes_of_a_weight():
+    import torch
+
+    class DeviceWeight:  # what the check reads of a device tensor
+        is_cuda, dtype = True, torch.bfloat16
+
+        def __init__(self, *shape):
+            self.shape = torch.Size(shape)
+
+        def is_contiguous(self):
+            return True
+
+    assert binding._contiguous_weight(DeviceWeight(8, 64), "call") == (8, 64)
+    assert binding._contiguous_weight(DeviceWeight(8, 64, 1), "call") == (8, 64)
+    assert binding._contiguous_weight(DeviceWeight(8, 64, 1, 1), "call") == (8, 64)
