@@ -7,7 +7,7 @@
 // round trip to memory, decoding 16 weights per lane and pass (a 2-byte LDS write per kept value), and a serial chain of
 // K / 64 steps.  So a block is small (768 out-features are 24 of them per 64 tokens), all four waves decode, the loads
 // of two spans of 256 reduction positions are in flight in registers while a third is multiplied, and a span has one
-// barrier.  In a graph, pre-pass and product before: 768 -> 1000 at 4:8 and 16 tokens 9.4 -> 5.9 us, 3072 -> 768 at 1:4
+// barrier.  Which products it takes is decided in nm_spmm.hip (direct_takes).  In a graph, pre-pass and product before: 768 -> 1000 at 4:8 and 16 tokens 9.4 -> 5.9 us, 3072 -> 768 at 1:4
 // 16.4 -> 12.5, 1024 -> 4096 at 4:8 16.3 -> 7.1.
 //
 // Two summation orders, so that a product is the same bytes whichever kernel of its route computes it:

@@ -3,7 +3,7 @@
 // positions.  The weight is read once, in its packed form, and decoded in registers into matrix-core operands
 // (Fig. 2, lower part: the positions select the activations); there is no operand-order copy and no workspace.
 // It is the path of the layers of a batched call that come WITHOUT a workspace (one launch for all of them; a layer
-// alone takes the kernel of nm_direct.hip, whose small blocks fill the chip better and whose sums are the same: 768 ->
+// alone takes the kernel of nm_direct.hip as long as its small blocks are few rounds on the chip, with the same sums: 768 ->
 // 1000 at 4:8 and 16 tokens 23.0 us here, 6.1 there): with one, the tiled kernel of nm_spmm.hip reads
 // the operand-order copy and is the faster of the two (measured on the 48 linears of the model at 197 tokens:
 // 73 us against 89 us here; this kernel reads 112 MB where the other reads 170 MB, but its windows are bound by

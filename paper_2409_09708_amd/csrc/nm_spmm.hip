@@ -1962,18 +1962,18 @@ constexpr TileModel kTileModel[2][TILE_KINDS] = {  // [2:4 form]
      {128, 128, 1.88, 0.338, 2.19, 0.26}},
     {{64, 64, 2.75, 0.099, 0.31, 0.30}, {128, 64, 2.81, 0.127, 0.40, 0.65}, {128, 128, 2.46, 0.359, 0.85, 0.06},
      {128, 128, 2.68, 0.215, 0.97, 0.45}}};
+static double tile_estimate(const TileModel& m, int64_t O, int64_t K, int64_t T) {
+  const double tiles = (double)((O + m.bo - 1) / m.bo) * (double)((T + m.bt - 1) / m.bt);
+  const double full = (double)(int64_t)(tiles / kModelUnits), rest = tiles - full * kModelUnits;
+  return m.start + ((double)(K / 64) * m.step + m.epi) *
+                       (full * (1.0 + m.busy) + (rest > 0 ? 1.0 + m.busy * rest / kModelUnits : 0.0));
+}
 // The 128 x 128 or 64 x 64 tile of pick_tile's choice keeps the layer unless another is 2 % faster.
 static TileKind tile_kind(int64_t O, int64_t K, int64_t T, bool sparse_form, int pick) {
-  auto estimate = [&](const TileModel& m) {
-    const double tiles = (double)((O + m.bo - 1) / m.bo) * (double)((T + m.bt - 1) / m.bt);
-    const double full = (double)(int64_t)(tiles / kModelUnits), rest = tiles - full * kModelUnits;
-    return m.start + ((double)(K / 64) * m.step + m.epi) *
-                         (full * (1.0 + m.busy) + (rest > 0 ? 1.0 + m.busy * rest / kModelUnits : 0.0));
-  };
   int best = pick == 3 ? TILE_64 : TILE_128;
-  double least = 0.98 * estimate(kTileModel[sparse_form][best]);
+  double least = 0.98 * tile_estimate(kTileModel[sparse_form][best], O, K, T);
   for (int k = 0; k < TILE_KINDS; ++k) {
-    if (const double e = estimate(kTileModel[sparse_form][k]); e < least) { best = k; least = e; }
+    if (const double e = tile_estimate(kTileModel[sparse_form][k], O, K, T); e < least) { best = k; least = e; }
   }
   return (TileKind)best;
 }
@@ -2146,16 +2146,32 @@ static bool packed_path(const SpmmArgs& a) {
   return fewtok_takes(a);
 }
 
-// A call that prepares and multiplies in one: the kernel that decodes the weight itself (nm_direct.hip) as long as its
-// blocks of 32 out-features x 64 tokens have a compute unit each, and up to 208 tokens in any case (a weight tile is then
-// decoded at most four times).  Pre-pass and product against it, in a graph: 768 -> 1000 at 4:8 and 8 tokens 9.4 and
-// 5.7 us, 768 -> 768 at 394 tokens 9.2 and 6.3, 1024 -> 4096 at 197 23.4 and 13.9, 3072 -> 768 at 600 18.1 and 17.7; past
-// that line 9.8 and 11.2 for 768 -> 1000 at 600 tokens, 18.3 and 33.6 for 3072 -> 768 at 788.  Its sums are those of the
-// tiled kernel; a layer that the persistent kernel or a cut reduction would sum in another order stays there.
-static bool direct_takes(const SpmmArgs& a, int pick) {
-  const int64_t blocks = ((a.O + 31) / 32) * ((a.T + 63) / 64);
-  return (a.T <= 208 || blocks <= 256) && pick != 0 && direct_level(a.N, a.M) && split_count(a.O, a.K, a.T, a.N <= 2) == 1;
+// A call that prepares and multiplies in one takes the kernel that decodes the weight itself (nm_direct.hip) where its
+// estimate is below the pre-pass and the tiled kernel together.  It decodes the weight once per 64 tokens, so it wins as
+// long as its blocks of 32 out-features x 64 tokens are few rounds on the chip, later for a shallow weight.  Both fitted on
+// 3000 shapes per form (64 .. 16384 deep, 64 .. 49152 wide, 1 .. 1000 tokens, in a graph); the route it picks costs 1 % on
+// average over the better of the two.  Pre-pass and product against it: 768 -> 1000 at 4:8 and 8 tokens 9.4 and 5.7 us,
+// 768 -> 768 at 394 tokens 9.2 and 6.3; 2048 -> 16384 at 1:8 and 208 tokens 33.4 and 68.9, which stays with the two.
+// Its sums are those of the tiled kernel; a layer that the persistent kernel or a cut reduction would sum in another
+// order stays there.
+constexpr TileModel kDirectModel[2] = {{32, 64, 3.81, 0.130, 0.57, 1.09}, {32, 64, 3.22, 0.117, 0.85, 0.68}};  // [2:4 form]
+static bool direct_takes(int64_t O, int64_t K, int N, int M, int64_t T, int pick) {
+  const bool sparse_form = N <= 2;
+  if (pick == 0 || !direct_level(N, M) || split_count(O, K, T, sparse_form) != 1) return false;
+  const int64_t blocks = ((O + 31) / 32) * ((T + 63) / 64);
+  if ((T + 63) / 64 > 65535 || blocks > (1 << 20)) return false;  // (a grid's second dimension)
+  double two = 1e30;
+  for (const TileModel& m : kTileModel[sparse_form])
+    if (const double e = tile_estimate(m, O, K, T); e < two) two = e;
+  two += 3.85 + (sparse_form ? 0.49 : 0.85) * 1e-6 * (double)((O + 255) / 256 * 256) * (double)K;
+  return tile_estimate(kDirectModel[sparse_form], O, K, T) < two;
 }
+
+// A call without a workspace takes it up to four rounds of blocks, and at one block of tokens in any case; beyond, it would
+// decode a wide weight two to four times, and the kernel of nm_fewtok.hip, with the same sums, is the faster one (12288 ->
+// 49152 at 1:8 and 208 tokens 370 us, 1080 that way; 2048 -> 16384 at 130 tokens 38.7 and 53.3; 768 -> 1000 at 4:8 and 16
+// tokens 23.0 and 6.1).
+static bool direct_takes_packed(int64_t O, int64_t T) { return T <= 64 || ((O + 31) / 32) * ((T + 63) / 64) <= 1024; }
 
 hipError_t launch_spmm(const SpmmArgs& a, hipStream_t s, bool* workspace_short, int phases) {
   *workspace_short = false;
@@ -2185,12 +2201,17 @@ hipError_t launch_spmm(const SpmmArgs& a, hipStream_t s, bool* workspace_short, 
   const size_t need = spmm_operand_workspace_bytes(a.O, a.K, a.N, a.M, a.T);
   if (need && (a.workspace == nullptr || a.workspace_bytes < need || !aligned_to(a.workspace, 256))) {
     // no workspace: few tokens can still be multiplied straight from the packed format
-    if (!packed_path(a)) *workspace_short = true;
-    else if (product) return launch_direct(a, true, s);
+    if (!packed_path(a)) {
+      *workspace_short = true;
+    } else if (product) {
+      if (direct_takes_packed(a.O, a.T)) return launch_direct(a, true, s);
+      const SpmmArgs* one = &a;
+      return launch_fewtok(&one, 1, s);
+    }
     return hipSuccess;
   }
   const int pick = pick_tile(a.O, a.K, a.T, sparse_form);
-  if (prepare && product && direct_takes(a, pick)) return launch_direct(a, false, s);
+  if (prepare && product && direct_takes(a.O, a.K, a.N, a.M, a.T, pick)) return launch_direct(a, false, s);
   GemmArgs g;
   fill_gemm_args(a, form, sparse_form, &g);
   if (prepare && form == FORM_STREAM) {
@@ -2201,6 +2222,19 @@ hipError_t launch_spmm(const SpmmArgs& a, hipStream_t s, bool* workspace_short, 
   // the persistent kernel writes Y in 16-byte pieces only; other outputs take the ragged form of the tiled kernel
   if (pick == 0 && (!g.vec_store || a.ldy > 0x7FFFFFFF)) return ragged_product();
   return sparse_form ? dispatch_gemm<true>(g, pick, s) : dispatch_gemm<false>(g, pick, s);
+}
+
+// Not in the public header, for tests: the kernel that a product of aligned operands takes at one layer's shape.
+// call: 0 the weight is prepared in the same call, 1 it has been, 2 there is no workspace.
+extern "C" int32_t nm_internal_product_route(int32_t call, int64_t O, int64_t K, int32_t N, int32_t M, int64_t T) {
+  enum { ROUTE_GENERAL, ROUTE_TILED, ROUTE_PERSISTENT, ROUTE_RAGGED, ROUTE_DIRECT, ROUTE_FEWTOK };
+  const bool sparse_form = N <= 2 && N < M;
+  if (K % 64) return call != 2 && ragged_shape(O, K, T) ? ROUTE_RAGGED : ROUTE_GENERAL;
+  const int pick = pick_tile(O, K, T, sparse_form);
+  if (call == 2 && spmm_operand_workspace_bytes(O, K, N, M, T) != 0)
+    return !fewtok_shape(O, K, N, M, T) ? -1 : direct_takes_packed(O, T) ? ROUTE_DIRECT : ROUTE_FEWTOK;
+  if (call == 0 && direct_takes(O, K, N, M, T, pick)) return ROUTE_DIRECT;
+  return pick == 0 ? ROUTE_PERSISTENT : ROUTE_TILED;
 }
 
 // nm_linear_forward on a scratch of a given size.  The operand copy of a ragged reduction may be larger than that: the

@@ -427,6 +427,29 @@ def test_weights_beyond_the_grid_limit_are_refused(lib):
     assert lib.nm_values_bytes(1 << 20, 1 << 20, 2, 4) == (1 << 40)
 
 
+ROUTES = ("general", "tiled", "persistent", "ragged", "direct", "fewtok")
+
+
+def route(lib, call, T, K, O, N, M):
+    """The kernel a product of aligned operands takes; call: "plain", "prepared" or "packed" (no workspace)."""
+    i64 = ctypes.c_int64
+    r = lib.nm_internal_product_route(("plain", "prepared", "packed").index(call), i64(O), i64(K), N, M, i64(T))
+    return ROUTES[r] if r >= 0 else "refused"
+
+
+@pytest.mark.parametrize("N,M", [(1, 8), (2, 8), (4, 8), (1, 16)])
+def test_wide_weights_are_not_decoded_over_and_over(lib, N, M):
+    # the one-launch kernel decodes the weight once per 64 tokens: few tokens or a narrow weight are its own, a wide
+    # weight at several times 64 tokens is not
+    for call in ("plain", "packed"):
+        assert route(lib, call, 8, 768, 1000, N, M) == "direct"
+        assert route(lib, call, 64, 2048, 1024, N, M) == "direct"
+        assert route(lib, call, 197, 768, 768, N, M) == "direct"
+        for T, K, O in ((208, 8192, 16384), (192, 12288, 49152), (208, 4096, 16384)):
+            assert route(lib, call, T, K, O, N, M) == ("tiled" if call == "plain" else "fewtok")
+    assert route(lib, "packed", 209, 768, 768, N, M) == "refused"
+
+
 def test_int8_tiles_have_as_many_steps_as_stages(lib):
     # the scales and biases of a tile alternate between two slices: a tile shorter than the load pipeline would have its
     # own overwritten before it is written out
