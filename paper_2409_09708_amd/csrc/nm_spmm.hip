@@ -1570,11 +1570,17 @@ static int pick_tile(int64_t O, int64_t T, int64_t stream_steps, const StreamMod
   return stream_estimate(m, O, T, stream_steps) <= margin * est_tiled ? 0 : 2;
 }
 static int pick_tile(int64_t O, int64_t K, int64_t T, bool sparse_form) {
-  // The 2:4 form takes the persistent kernel where it is 10 % faster by the estimates: within that the tiled one, whose
-  // tile is chosen afterwards (tile_kind), wins (9201 tokens x 64 -> 2456 21.0 and 15.6 us, 45581 x 512 -> 384 in fp32
-  // 31.9 and 27.7).
-  return pick_tile(O, T, sparse_form ? K / 64 : K / 32, kStreamModel[0][sparse_form], K / 64, sparse_form ? 0.34 : 0.5,
-                   sparse_form ? 0.9 : 1.0);
+  // A layer takes the persistent kernel where it is 10 % (2:4 form) or 12 % (dense) faster by the estimates: within that
+  // the tiled one, whose tile is chosen afterwards (tile_kind), wins (45581 x 512 -> 384 at 2:16 in fp32
+  // 31.9 and 27.7 us).  A tile of one 64-wide step has no step to load the next one under: a quarter more (6666 x 64 ->
+  // 1176 at 2:8 14.7 and 11.4).  An output beyond 200 MB leaves the memory-side
+  // cache, and the persistent kernel's stores, which do not linger there, make up for it (dense form, 35857 x 64 -> 4096
+  // 54 and 91 us).  Measured on 43000 shapes in every kernel and tile, buffers in the cache and not: of 10300 dense-form
+  // ones 890 lost over 5 % to a fixed tile by shape alone without the two last rules, a margin and tile_kind's, 510 with them.
+  double margin = sparse_form ? 0.9 : 0.88;
+  if (K == 64) margin *= 0.75;
+  if (T * O > 100000000) margin = sparse_form ? 0.9 : 1.0;
+  return pick_tile(O, T, sparse_form ? K / 64 : K / 32, kStreamModel[0][sparse_form], K / 64, sparse_form ? 0.34 : 0.5, margin);
 }
 
 // A reduction that is no whole number of 64-wide steps: the ragged form of the tiled kernel multiplies it from stream
@@ -1970,25 +1976,44 @@ static double tile_estimate(const TileModel& m, int64_t O, int64_t K, int64_t T)
 }
 // The 128 x 128 or 64 x 64 tile of pick_tile's choice keeps the layer unless another is 2 % faster.
 static TileKind tile_kind(int64_t O, int64_t K, int64_t T, bool sparse_form, int pick) {
+  const int64_t tiles = ((O + 127) / 128) * ((T + 127) / 128);  // of 128 x 128
+  // Tiles of 64 tokens read the weight up to twice as often as those of 128.  Of a weight past the L2s (16 MB) that is memory
+  // traffic, which the model does not see: with the chip at least half full of 128 x 128 tiles, 65 tokens x 4096 -> 16384 in
+  // the dense form take 28.5 us on those and 42.8 on 128 x 64, 65 x 1024 -> 16384 at 2:8 8.4 and 10.2.
+  const double weight = (double)((O + 255) / 256 * 256) * (double)K * (sparse_form ? 1.125 : 2.0);
+  const bool reread = pick != 3 && weight > 16e6 && tiles >= 128 && T > 64;
   int best = pick == 3 ? TILE_64 : TILE_128;
   double least = 0.98 * tile_estimate(kTileModel[sparse_form][best], O, K, T);
   for (int k = 0; k < TILE_KINDS; ++k) {
+    if (reread && (k == TILE_64 || k == TILE_128_64)) continue;
+    if (k == TILE_128_TWO && !sparse_form && tiles <= 256) continue;  // a block per unit: two stages leave it waiting
     if (const double e = tile_estimate(kTileModel[sparse_form][k], O, K, T); e < least) { best = k; least = e; }
   }
   return (TileKind)best;
 }
 
-// pick: pick_tile's choice.  A cut reduction keeps the tile its range count was computed for.
+// Tile and LDS stages.  pick: pick_tile's choice.  A cut reduction keeps the tile its range count was computed for.
+// A fourth stage pays where a unit has one block and that block 32 steps or more: 64 x 64 8.6 -> 8.3 us (dense form
+// 13.8 -> 11.6) at 394 x 3072 -> 768, 128 x 64 14.5 -> 11.9 at 1576 x 3072 -> 768, 128 x 128 23.7 -> 21.0 at 3136 x
+// 4096 -> 1024; at K = 768 it costs 2 - 5 %, with two blocks on a unit it gains nothing, and neither does a fifth.
+struct TileChoice {
+  TileKind kind;
+  int stages;
+};
+static TileChoice tile_choice(int64_t O, int64_t K, int64_t T, bool sparse_form, int pick, int splits) {
+  const TileKind kind = splits > 1 ? (pick == 2 ? TILE_128 : TILE_64) : tile_kind(O, K, T, sparse_form, pick);
+  if (kind == TILE_128_TWO) return {kind, 2};
+  const TileModel& m = kTileModel[sparse_form][kind];
+  const bool deep = splits <= 1 && K >= 2048 && ((O + m.bo - 1) / m.bo) * ((T + m.bt - 1) / m.bt) <= 256;
+  return {kind, deep ? 4 : 3};
+}
+
 template <bool SPARSE>
 static hipError_t dispatch_gemm(const GemmArgs& g, int pick, hipStream_t s) {
   if (pick == 0) return launch_stream<SPARSE>(g, s);
-  const TileKind kind = g.splits > 1 ? (pick == 2 ? TILE_128 : TILE_64) : tile_kind(g.O, g.K, g.T, SPARSE, pick);
-  // A fourth stage pays where a unit has one block and that block 32 steps or more: 64 x 64 8.6 -> 8.3 us (dense form
-  // 13.8 -> 11.6) at 394 x 3072 -> 768, 128 x 64 14.5 -> 11.9 at 1576 x 3072 -> 768, 128 x 128 23.7 -> 21.0 at 3136 x
-  // 4096 -> 1024; at K = 768 it costs 2 - 5 %, with two blocks on a unit it gains nothing, and neither does a fifth.
-  const TileModel& m = kTileModel[SPARSE][kind];
-  const bool deep = g.splits <= 1 && g.K >= 2048 && ((g.O + m.bo - 1) / m.bo) * ((g.T + m.bt - 1) / m.bt) <= 256;
-  switch (kind) {
+  const TileChoice c = tile_choice(g.O, g.K, g.T, SPARSE, pick, g.splits);
+  const bool deep = c.stages == 4;
+  switch (c.kind) {
     case TILE_64: return deep ? launch_gemm<SPARSE, 2, 2, 2, 2, 4>(g, s) : launch_gemm<SPARSE, 2, 2, 2, 2, 3>(g, s);
     case TILE_128_64: return deep ? launch_gemm<SPARSE, 2, 2, 4, 2, 4>(g, s) : launch_gemm<SPARSE, 2, 2, 4, 2, 3>(g, s);
     case TILE_128_TWO: return launch_gemm<SPARSE, 2, 2, 4, 4, 2>(g, s);
@@ -2038,8 +2063,11 @@ static hipError_t launch_general(const SpmmArgs& a, hipStream_t s) {
 // Out[t, i] = sum_r Q[t, r] * Ws[r, i] on the persistent dense kernel: the weight is written transposed into
 // stream order first (a pass over the weight only), then it is an ordinary product with I out-features and a
 // reduction of R.  Shapes: enough tiles, R % 64 == 0, Out rows in whole aligned 16-byte pieces.
+static bool dense_transposed_takes(int64_t R, int64_t I, int64_t T) {
+  return R % 64 == 0 && pick_tile(I, T, R / 32, kStreamModel[0][0], R / 64, 0.5) == 0;
+}
 size_t dense_transposed_workspace_bytes(int64_t R, int64_t I, int64_t T) {
-  if ((R % 64) || pick_tile(I, R, T, false) != 0) return 0;
+  if (!dense_transposed_takes(R, I, T)) return 0;
   return (size_t)(((I + 255) / 256) * 256) * (size_t)R * 2;
 }
 
@@ -2137,6 +2165,14 @@ static void fill_gemm_args(const SpmmArgs& a, int form, bool sparse_form, GemmAr
   }
 }
 
+// The persistent kernel writes Y in 16-byte pieces only; other outputs of layers of its size take the ragged form of the
+// tiled kernel, whichever of the two the estimates name (the ragged form does not multiply an activation at a pruned
+// position that is not finite, and that must not hang on an estimate).
+static bool unaligned_output(const SpmmArgs& a, const GemmArgs& g, int pick) {
+  if (pick == 0) return !g.vec_store || a.ldy > 0x7FFFFFFF;
+  return g.stream_form && !g.vec_store && ((a.O + 127) / 128) * ((a.T + 127) / 128) > 256;
+}
+
 // A layer whose operand-order workspace is missing (or too small) and which the few-token kernel can multiply
 // from the packed format instead.
 static bool packed_path(const SpmmArgs& a) {
@@ -2219,14 +2255,14 @@ hipError_t launch_spmm(const SpmmArgs& a, hipStream_t s, bool* workspace_short, 
     if (e != hipSuccess) return e;
   }
   if (!product) return hipSuccess;
-  // the persistent kernel writes Y in 16-byte pieces only; other outputs take the ragged form of the tiled kernel
-  if (pick == 0 && (!g.vec_store || a.ldy > 0x7FFFFFFF)) return ragged_product();
+  if (unaligned_output(a, g, pick)) return ragged_product();
   return sparse_form ? dispatch_gemm<true>(g, pick, s) : dispatch_gemm<false>(g, pick, s);
 }
 
-// Not in the public header, for tests: the kernel that a product of aligned operands takes at one layer's shape.
+// Not in the public header, for tests: the kernel that a product of aligned operands takes at one layer's shape and, for
+// the tiled and the persistent one, its tile (out-features, tokens, LDS stages).
 // call: 0 the weight is prepared in the same call, 1 it has been, 2 there is no workspace.
-extern "C" int32_t nm_internal_product_route(int32_t call, int64_t O, int64_t K, int32_t N, int32_t M, int64_t T) {
+extern "C" int32_t nm_internal_product_route(int32_t call, int64_t O, int64_t K, int32_t N, int32_t M, int64_t T, int32_t* tile) {
   enum { ROUTE_GENERAL, ROUTE_TILED, ROUTE_PERSISTENT, ROUTE_RAGGED, ROUTE_DIRECT, ROUTE_FEWTOK };
   const bool sparse_form = N <= 2 && N < M;
   if (K % 64) return call != 2 && ragged_shape(O, K, T) ? ROUTE_RAGGED : ROUTE_GENERAL;
@@ -2234,7 +2270,16 @@ extern "C" int32_t nm_internal_product_route(int32_t call, int64_t O, int64_t K,
   if (call == 2 && spmm_operand_workspace_bytes(O, K, N, M, T) != 0)
     return !fewtok_shape(O, K, N, M, T) ? -1 : direct_takes_packed(O, T) ? ROUTE_DIRECT : ROUTE_FEWTOK;
   if (call == 0 && direct_takes(O, K, N, M, T, pick)) return ROUTE_DIRECT;
-  return pick == 0 ? ROUTE_PERSISTENT : ROUTE_TILED;
+  if (pick == 0) {
+    tile[0] = 256;
+    tile[1] = nm_internal_stream_tile(0, sparse_form, O, T, sparse_form ? K / 64 : K / 32, &tile[2]);
+    return ROUTE_PERSISTENT;
+  }
+  const TileChoice c = tile_choice(O, K, T, sparse_form, pick, split_count(O, K, T, sparse_form));
+  tile[0] = kTileModel[sparse_form][c.kind].bo;
+  tile[1] = kTileModel[sparse_form][c.kind].bt;
+  tile[2] = c.stages;
+  return ROUTE_TILED;
 }
 
 // nm_linear_forward on a scratch of a given size.  The operand copy of a ragged reduction may be larger than that: the
@@ -2267,7 +2312,7 @@ static bool tiled_entry(const SpmmArgs& a, GemmArgs* g, bool* sparse_form, int* 
   *pick = pick_tile(a.O, a.K, a.T, *sparse_form);
   if (*pick == 0) return false;
   fill_gemm_args(a, form, *sparse_form, g);
-  return true;
+  return !unaligned_output(a, *g, *pick);
 }
 
 // The product of a prepared layer on the persistent kernel, as a table entry: false when this layer takes

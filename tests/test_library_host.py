@@ -432,9 +432,14 @@ ROUTES = ("general", "tiled", "persistent", "ragged", "direct", "fewtok")
 
 def route(lib, call, T, K, O, N, M):
     """The kernel a product of aligned operands takes; call: "plain", "prepared" or "packed" (no workspace)."""
-    i64 = ctypes.c_int64
-    r = lib.nm_internal_product_route(("plain", "prepared", "packed").index(call), i64(O), i64(K), N, M, i64(T))
-    return ROUTES[r] if r >= 0 else "refused"
+    return route_and_tile(lib, call, T, K, O, N, M)[0]
+
+
+def route_and_tile(lib, call, T, K, O, N, M):
+    """... and the tile of the tiled and the persistent kernel: (out-features, tokens, stages)."""
+    i64, tile = ctypes.c_int64, (ctypes.c_int32 * 3)()
+    r = lib.nm_internal_product_route(("plain", "prepared", "packed").index(call), i64(O), i64(K), N, M, i64(T), tile)
+    return (ROUTES[r] if r >= 0 else "refused"), tuple(tile)
 
 
 @pytest.mark.parametrize("N,M", [(1, 8), (2, 8), (4, 8), (1, 16)])
@@ -448,6 +453,20 @@ def test_wide_weights_are_not_decoded_over_and_over(lib, N, M):
         for T, K, O in ((208, 8192, 16384), (192, 12288, 49152), (208, 4096, 16384)):
             assert route(lib, call, T, K, O, N, M) == ("tiled" if call == "plain" else "fewtok")
     assert route(lib, "packed", 209, 768, 768, N, M) == "refused"
+
+
+def test_a_wide_weight_is_not_read_twice_for_few_tokens(lib):
+    # past the L2s, 64-token tiles would bring it from memory once more per 128 tokens
+    for T, K, O, N, M in ((65, 4096, 16384, 4, 8), (65, 4096, 16384, 8, 8), (100, 1024, 16384, 4, 8), (65, 1024, 16384, 2, 8)):
+        kernel, (_, tokens, _) = route_and_tile(lib, "prepared", T, K, O, N, M)
+        assert kernel == "tiled" and tokens == 128, (T, K, O, tokens)
+    assert route_and_tile(lib, "prepared", 64, 1024, 16384, 4, 8)[1][1] == 64  # one row of tiles either way
+
+
+def test_shallow_layers_stay_on_the_tiled_kernel(lib):
+    for T, K, O, N, M in ((6666, 64, 1176, 2, 8), (35502, 64, 168, 1, 8), (14788, 64, 400, 6, 16), (15279, 64, 1400, 15, 16)):
+        assert route(lib, "prepared", T, K, O, N, M) == "tiled", (T, K, O)
+    assert route(lib, "prepared", 35857, 64, 4096, 4, 8) == "persistent"  # an output past the memory-side cache
 
 
 def test_int8_tiles_have_as_many_steps_as_stages(lib):
