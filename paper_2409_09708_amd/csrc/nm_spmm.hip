@@ -1558,6 +1558,12 @@ static double stream_estimate(const StreamModel& m, int64_t O, int64_t T, int64_
   return best;
 }
 
+// `steps` K steps of 64 or 128, step_us each
+static double tiled_estimate(int64_t O, int64_t T, int64_t steps, double step_us) {
+  const int64_t tiles = ((O + 127) / 128) * ((T + 127) / 128);
+  return (double)((tiles + 255) / 256) * ((double)steps * step_us + 1.5) + 3.0;
+}
+
 // Which product kernel a layer of O out-features runs at T tokens: 0 = the persistent kernel, 2 = the tiled kernel with
 // 128 x 128 tiles, 3 = with 64 x 64 tiles: the smaller estimate.  A layer with fewer than 64 tiles of 128 x 128 takes
 // 64 x 64 tiles: the few tiles there are finish sooner.
@@ -1566,8 +1572,7 @@ static int pick_tile(int64_t O, int64_t T, int64_t stream_steps, const StreamMod
   const int64_t tiles_mid = ((O + 127) / 128) * ((T + 127) / 128);
   if (tiles_mid < 64) return 3;
   if (T < 256) return 2;
-  const double est_tiled = (double)((tiles_mid + 255) / 256) * ((double)tiled_steps * tiled_step_us + 1.5) + 3.0;
-  return stream_estimate(m, O, T, stream_steps) <= margin * est_tiled ? 0 : 2;
+  return stream_estimate(m, O, T, stream_steps) <= margin * tiled_estimate(O, T, tiled_steps, tiled_step_us) ? 0 : 2;
 }
 static int pick_tile(int64_t O, int64_t K, int64_t T, bool sparse_form) {
   // A layer takes the persistent kernel where it is 10 % (2:4 form) or 12 % (dense) faster by the estimates: within that
@@ -2063,8 +2068,15 @@ static hipError_t launch_general(const SpmmArgs& a, hipStream_t s) {
 // Out[t, i] = sum_r Q[t, r] * Ws[r, i] on the persistent dense kernel: the weight is written transposed into
 // stream order first (a pass over the weight only), then it is an ordinary product with I out-features and a
 // reduction of R.  Shapes: enough tiles, R % 64 == 0, Out rows in whole aligned 16-byte pieces.
+// The alternative, nm_grad.hip's kernel, reads the weight as it lies, so the pass over the weight counts: 2.5 us and a
+// quarter of one per MB, about half of that beside a short reduction, whose tiles the estimates make 30 % too cheap at
+// R = 64.  Over 8200 shapes (256 to 200704 tokens, buffers from memory) the choice is 1.8 % from the better of the two on
+// average, 4.2 % without the pass in it: 5388 tokens x 64 -> 904 7.1 and 11.8 us, 12608 x 64 -> 768 9.2 and 12.2.
 static bool dense_transposed_takes(int64_t R, int64_t I, int64_t T) {
-  return R % 64 == 0 && pick_tile(I, T, R / 32, kStreamModel[0][0], R / 64, 0.5) == 0;
+  if (R % 64 || ((I + 127) / 128) * ((T + 127) / 128) < 64 || T < 256) return false;
+  const double weight_mb = (double)((I + 255) / 256 * 256) * (double)R * 2e-6;
+  const double pass = R > 192 ? 2.5 + 0.25 * weight_mb : 1.3;
+  return stream_estimate(kStreamModel[0][0], I, T, R / 32) + pass <= tiled_estimate(I, T, R / 64, 0.5) * (R == 64 ? 0.7 : 1.0);
 }
 size_t dense_transposed_workspace_bytes(int64_t R, int64_t I, int64_t T) {
   if (!dense_transposed_takes(R, I, T)) return 0;

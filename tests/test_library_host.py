@@ -469,6 +469,14 @@ def test_shallow_layers_stay_on_the_tiled_kernel(lib):
     assert route(lib, "prepared", 35857, 64, 4096, 4, 8) == "persistent"  # an output past the memory-side cache
 
 
+def test_input_gradients_of_short_reductions_need_no_transposed_copy(lib):
+    # (O, K, T): the reduction runs over O; a pass over the weight does not pay for a step or two of it
+    for O, K, T in ((64, 904, 5388), (64, 736, 29629), (64, 768, 12608), (192, 944, 5187), (64, 2392, 200704)):
+        assert lib.nm_backward_input_workspace_bytes(O, K, T) == 0, (O, K, T)
+    for O, K, T in ((768, 768, 12608), (2304, 768, 12608), (768, 3072, 12608), (3072, 768, 12608)):
+        assert lib.nm_backward_input_workspace_bytes(O, K, T) == O * K * 2, (O, K, T)
+
+
 def test_int8_tiles_have_as_many_steps_as_stages(lib):
     # the scales and biases of a tile alternate between two slices: a tile shorter than the load pipeline would have its
     # own overwritten before it is written out
