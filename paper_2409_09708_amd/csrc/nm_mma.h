@@ -105,7 +105,9 @@ __device__ __forceinline__ void write_wave_tile_pieces(unsigned char* slice, int
 
 // Any alignment, any row length: 16 rows at a time through the wave's LDS slice (wave_tile_slice_bytes<OT, 4>) as
 // 32-bit patterns, then one element per lane, consecutive lanes on consecutive columns of a row, so that a store
-// instruction covers one contiguous row segment (or two) instead of 64 scattered elements.
+// instruction covers one contiguous row segment (or two) instead of 64 scattered elements.  Up to 16 columns, where rows are
+// no longer than what a lane group holds, the elements leave from their registers (a product of one to a few
+// out-features 4.0 us, 4.9 with an address product per store and through LDS).
 template <int OT, int TT, int ES, typename Get>
 __device__ __forceinline__ void write_wave_tile_rows(unsigned char* slice, int lane, Get get, void* Y, int64_t ldy,
                                                      int64_t row0, int64_t col0, int64_t n_rows, int64_t n_cols) {
@@ -113,22 +115,42 @@ __device__ __forceinline__ void write_wave_tile_rows(unsigned char* slice, int l
   static_assert(OW <= 64 && 64 % OW == 0, "whole rows per store");
   constexpr int RS = OW * 4 + 16;       // padded LDS row
   constexpr int ROWS = 64 / OW;         // rows per store instruction
+  if (col0 >= n_cols) return;           // (wave-uniform)
   const int r16 = lane & 15, kb = lane >> 4;
-  const int col = lane % OW;
-  const bool col_ok = col0 + col < n_cols;
+  const int rows_left = (int)(n_rows - row0 < TT * 16 ? n_rows - row0 : TT * 16);
+  auto store = [](unsigned char* at, uint32_t v) {
+    if constexpr (ES == 2) *reinterpret_cast<bf16_t*>(at) = (bf16_t)f32_to_bf16_rne(__uint_as_float(v));
+    else *reinterpret_cast<uint32_t*>(at) = v;
+  };
+  if (n_cols - col0 <= 16) {
+    const int cols = (int)(n_cols - col0) - kb * 4;  // of this lane's four
+    unsigned char* dst = reinterpret_cast<unsigned char*>(Y) + ((row0 + r16) * ldy + col0 + kb * 4) * ES;
+#pragma unroll
+    for (int j = 0; j < TT; ++j) {
+      const u32x4_t v = get(0, j);
+      if (j * 16 + r16 < rows_left) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (e < cols) store(dst + e * ES, v[e]);
+      }
+      dst += 16 * ldy * ES;
+    }
+    return;
+  }
+  const int first = lane / OW, col = lane % OW;
+  const int rows = col0 + col < n_cols ? rows_left : 0;
+  unsigned char* dst = reinterpret_cast<unsigned char*>(Y) + ((row0 + first) * ldy + col0 + col) * ES;
 #pragma unroll
   for (int j = 0; j < TT; ++j) {
 #pragma unroll
     for (int i = 0; i < OT; ++i) *reinterpret_cast<u32x4_t*>(slice + r16 * RS + (i * 16 + kb * 4) * 4) = get(i, j);
+    uint32_t v[16 / ROWS];
+#pragma unroll
+    for (int q = 0; q < 16 / ROWS; ++q) v[q] = *reinterpret_cast<const uint32_t*>(slice + (q * ROWS + first) * RS + col * 4);
 #pragma unroll
     for (int q = 0; q < 16 / ROWS; ++q) {
-      const int row = q * ROWS + lane / OW;
-      const uint32_t v = *reinterpret_cast<const uint32_t*>(slice + row * RS + col * 4);
-      const int64_t r = row0 + j * 16 + row;
-      if (r < n_rows && col_ok) {
-        if constexpr (ES == 2) reinterpret_cast<bf16_t*>(Y)[r * ldy + col0 + col] = (bf16_t)f32_to_bf16_rne(__uint_as_float(v));
-        else reinterpret_cast<uint32_t*>(Y)[r * ldy + col0 + col] = v;
-      }
+      if (j * 16 + q * ROWS + first < rows) store(dst, v[q]);
+      dst += ROWS * ldy * ES;
     }
   }
 }

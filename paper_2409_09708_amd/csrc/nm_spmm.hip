@@ -2182,7 +2182,7 @@ static void fill_gemm_args(const SpmmArgs& a, int form, bool sparse_form, GemmAr
 // position that is not finite, and that must not hang on an estimate).
 static bool unaligned_output(const SpmmArgs& a, const GemmArgs& g, int pick) {
   if (pick == 0) return !g.vec_store || a.ldy > 0x7FFFFFFF;
-  return g.stream_form && !g.vec_store && ((a.O + 127) / 128) * ((a.T + 127) / 128) > 256;
+  return g.stream_form && !g.vec_store && a.O > 128 && ((a.O + 127) / 128) * ((a.T + 127) / 128) > 256;
 }
 
 // A layer whose operand-order workspace is missing (or too small) and which the few-token kernel can multiply

@@ -146,3 +146,44 @@ def test_fixed_scratch_writes_the_same_bytes(T, K, O, N, M, out_dtype):
     nm.nm_linear_forward_static(v, i, K, N, M, Xd, bias=bias, out=out[:, 1:O + 1])
     assert torch.equal(out[:, 1:O + 1], y)
     assert bool((out[:, 0] == 7).all() and (out[:, O + 1:] == 7).all())
+
+
+# Outputs of a few columns, on either side of the widths where the write-out changes (16 columns; a wave's 32 or 64), by
+# every kernel that writes rows of any alignment; what lies beside the view stays
+@pytest.mark.parametrize("cols", [1, 3, 4, 13, 15, 16, 17, 31, 33, 65])
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
+def test_narrow_outputs(cols, out_dtype):
+    T, K = 133, 128
+    rng = np.random.default_rng(12300 + cols)
+    Xd = dev_bf16(wl.draw_activations(rng, T, K))
+    W = dev_bf16(wl.draw_weights(rng, cols, K))
+    out = torch.full((T + 1, cols + 3), 7.0, dtype=out_dtype, device="cuda")
+
+    def same(view, ref, B, terms):
+        bound = (terms + 2) * 2.0 ** -24 * B + (2.0 ** -8 * ref.abs() if out_dtype == torch.bfloat16 else 0)
+        assert bool(((view.double() - ref).abs() <= bound).all())
+        assert bool((out[:, 0] == 7).all() and (out[:, 1 + view.shape[1]:] == 7).all() and (out[view.shape[0]:] == 7).all())
+        out.fill_(7.0)
+
+    for N, M in ((2, 4), (1, 8), (4, 8)):
+        v, i = nm.nm_pack(W, N, M)
+        Ws = nm.nm_unpack(v, i, K, N, M).double()
+        ws = nm.nm_spmm_prepare(v, i, K, N, M, T)
+        y = nm.nm_linear_forward_prepared(v, i, K, N, M, Xd, ws, out=out[:T, 1:cols + 1])
+        same(y, Xd.double() @ Ws.t(), Xd.double().abs() @ Ws.abs().t(), K // M * N)
+    # weight gradient: rows of `cols` columns; input gradient likewise
+    dY = dev_bf16(wl.draw_activations(rng, T, 96))
+    Xn = dev_bf16(wl.draw_activations(rng, T, cols))
+    if cols % 8 == 0:
+        dW = nm.nm_linear_backward_weight(dY, Xn, out=out[:96, 1:cols + 1])
+        same(dW, dY.double().t() @ Xn.double(), dY.double().abs().t() @ Xn.double().abs(), T)
+        Wd = dev_bf16(wl.draw_weights(rng, 96, cols))
+        dX = nm.nm_linear_backward_input(Wd, dY, out=out[:T, 1:cols + 1])
+        same(dX, dY.double() @ Wd.double(), dY.double().abs() @ Wd.double().abs(), 96)
+    # int8: the rescaled sums, one rounding of a fused multiply-add
+    Xq, Wq = torch.from_numpy(wl.draw_int8(rng, T, K)).cuda(), torch.from_numpy(wl.draw_int8(rng, cols, K)).cuda()
+    mask = nm.nm_prune(Wq.to(torch.bfloat16), 2, 4)
+    y = nm.nm_linear_forward_i8(Wq, mask, 2, 4, Xq, x_scale=0.25, out=out[:T, 1:cols + 1])
+    kept = ((mask[:, :, None] >> torch.arange(32, device="cuda")) & 1).reshape(cols, -1)[:, :K]
+    ref = 0.25 * (Xq.double() @ (Wq * kept).double().t())
+    same(y, ref, ref.abs(), 1)
