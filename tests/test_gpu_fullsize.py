@@ -11,7 +11,7 @@ import torch
 import paper_2409_09708_amd as nm
 from oracle import nm_oracle as orc
 from paper_2409_09708_amd import workloads as wl
-from gpu_util import check_output, dev_bf16, host_bits, host_output, host_words
+from gpu_util import check_output, dev_bf16, host_bits, host_output, host_words, product_route
 
 pytestmark = pytest.mark.gpu
 
@@ -180,9 +180,11 @@ def test_pack_prepare_batched_writes_what_the_two_calls_write():
                                                (192, (4, 8), torch.float32), (320, (2, 16), torch.bfloat16)])
 def test_persistent_kernel_short_and_odd_reductions(K, level, out_dtype):
     # one, three and five K steps per tile (the step loop runs in pairs), a ragged last token tile and a
-    # ragged out-feature tile, with bias: 2 x 129 tiles put the layer on the persistent kernel
+    # ragged out-feature tile, with bias: 2 x 129 tiles put the layer on the persistent kernel, at one step per tile an
+    # output past the memory-side cache does
     rng = np.random.default_rng(zlib.crc32(f"short-{K}-{level}".encode()))
-    T, O = 128 * 256 + 37, 504
+    T, O = 128 * 256 + 37, 504 if K > 64 else 3064
+    assert product_route("prepared", T, K, O, *level)[0] == "persistent"
     X, W = wl.draw_activations(rng, T, K), wl.draw_weights(rng, O, K)
     bias = rng.standard_normal(O).astype(np.float32)
     v, i = nm.nm_pack(dev_bf16(W), *level)

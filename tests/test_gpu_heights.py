@@ -8,17 +8,30 @@ import torch
 import paper_2409_09708_amd as nm
 from oracle import nm_oracle as orc
 from paper_2409_09708_amd import workloads as wl
-from gpu_util import check_output, dev_bf16, dev_words, host_output
+from gpu_util import check_output, dev_bf16, dev_words, host_output, int8_route, product_route
 
 pytestmark = pytest.mark.gpu
 
-# (T, K, O): chosen so that 256-row tiles number just above a multiple of the compute units and lower ones do not
-SHAPES = [(12001, 192, 768), (15873, 128, 768), (6301, 64, 2560), (5500, 320, 3072), (8200, 192, 2048), (16384, 128, 1024)]
+# (T, K, O) by operand form and tokens per tile: odd and even step counts, T and O off the tile edge
+SPARSE = {128: (16565, 320, 136), 160: (16413, 128, 392), 192: (13733, 320, 520), 224: (16409, 192, 648), 256: (19586, 128, 520)}
+DENSE = {128: (16525, 192, 136), 160: (16654, 128, 392), 192: (13625, 192, 520), 224: (16414, 128, 648), 256: (19713, 192, 520)}
+CASES = ([(s, lv, tokens) for tokens, s in SPARSE.items() for lv in ((2, 4), (1, 8))] +
+         [(s, lv, tokens) for tokens, s in DENSE.items() for lv in ((4, 8), (8, 8))])
+OTHERS = [(s, lv, None) for lv in ((2, 4), (1, 8), (4, 8), (8, 8))  # whichever kernel
+          for s in ((12001, 192, 768), (15873, 128, 768), (6301, 64, 2560), (5500, 320, 3072), (8200, 192, 2048), (16384, 128, 1024))]
+SPARSE_I8 = {128: (16451, 512, 136), 160: (16444, 384, 136), 192: (13658, 384, 528), 224: (16368, 384, 520), 256: (19889, 384, 520)}
+DENSE_I8 = {128: (4164, 512, 136), 160: (16826, 256, 264), 192: (13702, 256, 520), 224: (16392, 256, 520), 256: (19280, 256, 520)}
+INT8_CASES = [(s, (2, 4), t) for t, s in SPARSE_I8.items()] + [(s, (4, 8), t) for t, s in DENSE_I8.items()]
+INT8_OTHERS = [(s, lv, None) for lv in ((2, 4), (4, 8))
+               for s in ((12001, 384, 768), (15873, 512, 768), (6301, 640, 2560), (8200, 1024, 2048))]
 
 
-@pytest.mark.parametrize("N,M", [(2, 4), (1, 8), (4, 8), (8, 8)])
-@pytest.mark.parametrize("T,K,O", SHAPES)
-def test_products(T, K, O, N, M):
+@pytest.mark.parametrize("shape,level,tokens", CASES + OTHERS)
+def test_products(shape, level, tokens):
+    (T, K, O), (N, M) = shape, level
+    if tokens is not None:
+        kernel, tile = product_route("prepared", T, K, O, N, M)
+        assert kernel == "persistent" and tile[1] == tokens
     rng = np.random.default_rng(12000 + N * 17 + M + T)
     X, W = wl.draw_activations(rng, T, K), wl.draw_weights(rng, O, K)
     bias = rng.standard_normal(O).astype(np.float32)
@@ -43,9 +56,10 @@ def test_products(T, K, O, N, M):
     assert torch.equal(both, y)
 
 
-@pytest.mark.parametrize("N,M", [(2, 4), (4, 8)])
-@pytest.mark.parametrize("T,K,O", [(12001, 384, 768), (15873, 512, 768), (6301, 640, 2560), (8200, 1024, 2048)])
-def test_int8_products(T, K, O, N, M):
+@pytest.mark.parametrize("shape,level,tokens", INT8_CASES + INT8_OTHERS)
+def test_int8_products(shape, level, tokens):
+    (T, K, O), (N, M) = shape, level
+    assert tokens is None or int8_route(T, K, O, N, M) == ("persistent", tokens)
     rng = np.random.default_rng(12500 + N + T)
     xq, wq = wl.draw_int8(rng, T, K), wl.draw_int8(rng, O, K)
     mask = orc.nm_mask(wl.f32_to_bf16_bits(wq.astype(np.float32)), N, M)

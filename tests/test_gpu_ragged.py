@@ -48,7 +48,7 @@ def test_reductions_that_end_inside_a_piece(K):
 # X and Y as views: rows that start on 16-, 8-, 4- and 2-byte boundaries; what lies beside the view (NaN around X, a
 # guard value around Y) is neither read into a sum nor written
 @pytest.mark.parametrize("offset,pad", [(0, 8), (4, 12), (2, 6), (1, 7), (3, 1)])
-@pytest.mark.parametrize("K,N,M", [(104, 2, 8), (192, 4, 8), (192, 1, 4)])
+@pytest.mark.parametrize("K,N,M", [(104, 2, 8), (192, 4, 8), (192, 1, 4), (192, 2, 4), (192, 4, 4)])
 @pytest.mark.parametrize("T", [75, 4200])
 def test_views_of_any_alignment(offset, pad, K, N, M, T):
     O = 263 if T < 4000 else 2051

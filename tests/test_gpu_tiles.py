@@ -1,4 +1,4 @@
-"""The tiles of the tiled product kernel a single layer may take (64 x 64 to 256 x 128, two to four LDS stages): one
+"""The tiles of the tiled product kernel a single layer may take (64 x 64 to 128 x 128, two to four LDS stages): one
 shape per tile and operand form, tokens and out-features off the tile edge, both weight orders, both output types; the
 same bytes as inside a batched call, which may use another tile."""
 import numpy as np
@@ -8,20 +8,26 @@ import torch
 import paper_2409_09708_amd as nm
 from oracle import nm_oracle as orc
 from paper_2409_09708_amd import workloads as wl
-from gpu_util import check_output, dev_bf16, host_output
+from gpu_util import check_output, dev_bf16, host_output, product_route
 
 pytestmark = pytest.mark.gpu
 
-# (T, K, O): 64 x 64, 128 x 64, 128 x 128 tiles with three stages, then with four (K from 2048 on), two stages last
-SPARSE = [(397, 192, 504), (789, 192, 1272), (2999, 512, 760), (397, 3072, 504), (789, 2048, 1272), (2999, 2048, 760),
-          (2999, 192, 760)]
-DENSE = [(397, 192, 504), (789, 192, 1272), (2999, 1600, 760), (397, 2048, 504), (789, 2112, 1272), (2999, 2048, 760),
-         (2999, 192, 760)]
+# (T, K, O) by operand form and tile (out-features, tokens, stages)
+SPARSE = {(64, 64, 3): (397, 192, 504), (128, 64, 3): (789, 192, 1272), (128, 128, 3): (2999, 512, 760),
+          (64, 64, 4): (397, 3072, 504), (128, 64, 4): (789, 2048, 1272), (128, 128, 4): (2999, 2048, 760),
+          (128, 128, 2): (2999, 192, 760)}
+DENSE = {(64, 64, 3): (397, 192, 504), (128, 64, 3): (789, 192, 1272), (128, 128, 3): (2999, 1600, 760),
+         (64, 64, 4): (397, 2048, 504), (128, 64, 4): (789, 2112, 1272), (128, 128, 4): (2999, 2048, 760),
+         (128, 128, 2): (8133, 192, 584)}
+CASES = ([(s, lv, tile) for tile, s in SPARSE.items() for lv in ((2, 4), (1, 8))] +
+         [(s, lv, tile) for tile, s in DENSE.items() for lv in ((4, 8), (4, 4))])
+OTHERS = [((2999, 192, 760), lv, None) for lv in ((4, 8), (4, 4))]  # whichever tile
 
 
-@pytest.mark.parametrize("T,K,O,N,M", [(*s, *lv) for s in SPARSE for lv in ((2, 4), (1, 8))] +
-                         [(*s, *lv) for s in DENSE for lv in ((4, 8), (4, 4))])
-def test_products(T, K, O, N, M):
+@pytest.mark.parametrize("shape,level,tile", CASES + OTHERS)
+def test_products(shape, level, tile):
+    (T, K, O), (N, M) = shape, level
+    assert tile is None or product_route("prepared", T, K, O, N, M) == ("tiled", tile)
     rng = np.random.default_rng(13000 + N * 17 + M + T)
     X, W = wl.draw_activations(rng, T, K), wl.draw_weights(rng, O, K)
     bias = rng.standard_normal(O).astype(np.float32)

@@ -8,6 +8,7 @@ import pytest
 
 from oracle import nm_oracle as orc
 from paper_2409_09708_amd import binding
+from gpu_util import int8_route, product_route
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 FAKE = 0x1000  # a non-NULL, well aligned address that is never dereferenced on the error paths
@@ -427,19 +428,8 @@ def test_weights_beyond_the_grid_limit_are_refused(lib):
     assert lib.nm_values_bytes(1 << 20, 1 << 20, 2, 4) == (1 << 40)
 
 
-ROUTES = ("general", "tiled", "persistent", "ragged", "direct", "fewtok")
-
-
-def route(lib, call, T, K, O, N, M):
-    """The kernel a product of aligned operands takes; call: "plain", "prepared" or "packed" (no workspace)."""
-    return route_and_tile(lib, call, T, K, O, N, M)[0]
-
-
-def route_and_tile(lib, call, T, K, O, N, M):
-    """... and the tile of the tiled and the persistent kernel: (out-features, tokens, stages)."""
-    i64, tile = ctypes.c_int64, (ctypes.c_int32 * 3)()
-    r = lib.nm_internal_product_route(("plain", "prepared", "packed").index(call), i64(O), i64(K), N, M, i64(T), tile)
-    return (ROUTES[r] if r >= 0 else "refused"), tuple(tile)
+def product_kernel(*call):
+    return product_route(*call)[0]
 
 
 @pytest.mark.parametrize("N,M", [(1, 8), (2, 8), (4, 8), (1, 16)])
@@ -447,26 +437,26 @@ def test_wide_weights_are_not_decoded_over_and_over(lib, N, M):
     # the one-launch kernel decodes the weight once per 64 tokens: few tokens or a narrow weight are its own, a wide
     # weight at several times 64 tokens is not
     for call in ("plain", "packed"):
-        assert route(lib, call, 8, 768, 1000, N, M) == "direct"
-        assert route(lib, call, 64, 2048, 1024, N, M) == "direct"
-        assert route(lib, call, 197, 768, 768, N, M) == "direct"
+        assert product_kernel(call, 8, 768, 1000, N, M) == "direct"
+        assert product_kernel(call, 64, 2048, 1024, N, M) == "direct"
+        assert product_kernel(call, 197, 768, 768, N, M) == "direct"
         for T, K, O in ((208, 8192, 16384), (192, 12288, 49152), (208, 4096, 16384)):
-            assert route(lib, call, T, K, O, N, M) == ("tiled" if call == "plain" else "fewtok")
-    assert route(lib, "packed", 209, 768, 768, N, M) == "refused"
+            assert product_kernel(call, T, K, O, N, M) == ("tiled" if call == "plain" else "fewtok")
+    assert product_kernel("packed", 209, 768, 768, N, M) == "refused"
 
 
 def test_a_wide_weight_is_not_read_twice_for_few_tokens(lib):
     # past the L2s, 64-token tiles would bring it from memory once more per 128 tokens
     for T, K, O, N, M in ((65, 4096, 16384, 4, 8), (65, 4096, 16384, 8, 8), (100, 1024, 16384, 4, 8), (65, 1024, 16384, 2, 8)):
-        kernel, (_, tokens, _) = route_and_tile(lib, "prepared", T, K, O, N, M)
+        kernel, (_, tokens, _) = product_route("prepared", T, K, O, N, M)
         assert kernel == "tiled" and tokens == 128, (T, K, O, tokens)
-    assert route_and_tile(lib, "prepared", 64, 1024, 16384, 4, 8)[1][1] == 64  # one row of tiles either way
+    assert product_route("prepared", 64, 1024, 16384, 4, 8)[1][1] == 64  # one row of tiles either way
 
 
 def test_shallow_layers_stay_on_the_tiled_kernel(lib):
     for T, K, O, N, M in ((6666, 64, 1176, 2, 8), (35502, 64, 168, 1, 8), (14788, 64, 400, 6, 16), (15279, 64, 1400, 15, 16)):
-        assert route(lib, "prepared", T, K, O, N, M) == "tiled", (T, K, O)
-    assert route(lib, "prepared", 35857, 64, 4096, 4, 8) == "persistent"  # an output past the memory-side cache
+        assert product_kernel("prepared", T, K, O, N, M) == "tiled", (T, K, O)
+    assert product_kernel("prepared", 35857, 64, 4096, 4, 8) == "persistent"  # an output past the memory-side cache
 
 
 def test_input_gradients_of_short_reductions_need_no_transposed_copy(lib):
@@ -505,3 +495,21 @@ def test_batched_calls_read_the_first_two_sizes_of_a_weight():
     assert binding._contiguous_weight(DeviceWeight(8, 64), "call") == (8, 64)
     assert binding._contiguous_weight(DeviceWeight(8, 64, 1), "call") == (8, 64)
     assert binding._contiguous_weight(DeviceWeight(8, 64, 1, 1), "call") == (8, 64)
+
+
+def test_shapes_of_the_tile_and_height_tests_reach_them():
+    # the GPU tests name the tile or height each of their shapes is there for; a change of the rules that moves a shape
+    # shows here
+    import test_gpu_heights as heights
+    import test_gpu_tiles as tiles
+
+    for shape, level, tile in tiles.CASES:
+        assert product_route("prepared", *shape, *level) == ("tiled", tile), (shape, level)
+    for shape, level, tokens in heights.CASES:
+        kernel, tile = product_route("prepared", *shape, *level)
+        assert kernel == "persistent" and tile[1] == tokens, (shape, level, kernel, tile)
+    for shape, level, tokens in heights.INT8_CASES:
+        assert int8_route(*shape, *level) == ("persistent", tokens), (shape, level)
+    for cases in (heights.CASES, heights.INT8_CASES):
+        for sparse in (True, False):
+            assert {t for _, (N, M), t in cases if (N <= 2 and N < M) == sparse} == {128, 160, 192, 224, 256}
