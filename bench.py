@@ -5,9 +5,10 @@ One step = one pass of the whole path over the DeiT-B batch-256 linear stack (50
 x {qkv, proj, fc1, fc2}, layer-wise level drawn with seed 0 from {1:4,2:4,1:8,2:8,4:8,1:16,4:16}):
 magnitude N:M selection + packing of all 48 weights (one batched launch), then the 48 sparse-weight x
 dense-activation products from the packed form (bf16 in, fp32 accumulate, bf16 out).  All inputs are
-resident in HBM before the timed region.  Prints ONE JSON line; besides the headline it carries the
-other workloads (single 2:4 layer, DeiT-B block at batch 64, Swin-B-shaped stages, batch 1), the rates
-measured on the device in the same process, and the parity of the timed buffers with the CPU checker.
+resident in HBM before the timed region.  Prints ONE JSON line, short enough for the tail of a log; besides the
+headline it carries the other workloads (single 2:4 layer, DeiT-B block at batch 64, Swin-B-shaped stages, batch 1), the rates
+measured on the device in the same process, and the parity of the timed buffers with the CPU checker.  The full
+record, layer by layer, goes to stderr.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W]
 """
@@ -250,6 +251,27 @@ def measured_peaks(nm, torch, stream):
     out["copy_1GiB"] = {"read_plus_write_gbs": 2 * src.numel() / ms / 1e6, "best": 2 * src.numel() / ms_min / 1e6, "ms": ms}
     del src, dst
     return out
+
+
+def short_record(out):
+    """The record in one line that a log's tail holds: numbers to five digits, descriptions left to the full record (stderr),
+    a workload's layers as their times."""
+    def short(v, top=False):
+        if isinstance(v, float):
+            return float(f"{v:.5g}")
+        if isinstance(v, list):
+            return [short(x) for x in v]
+        if not isinstance(v, dict):
+            return v
+        kept = {k: short(x) for k, x in v.items() if top or k not in ("workload", "note", "layers", "best")}
+        if not top and isinstance(v.get("layers"), list):
+            kept["layer_ms"] = [float(f"{r['ms']:.4g}") for r in v["layers"]]
+        return kept
+
+    line = {k: v for k, v in out.items() if k != "layers"}
+    line = short(line, top=True)
+    line["config"] = out["config"]
+    return line
 
 
 def main():
@@ -713,7 +735,8 @@ def main():
                                                         "batch1_fc_layers") for r in out.get(key, {}).get("layers", [])]
         out["parity"]["other_workloads_pass"] = bool(all(extra))
         out["parity"]["other_workloads_checked_layers"] = len(extra)
-    print(json.dumps(out), flush=True)
+    log("full record:", json.dumps(out))
+    print(json.dumps(short_record(out)), flush=True)
 
 
 if __name__ == "__main__":
