@@ -222,10 +222,14 @@ int32_t nm_pack_ranked_batched(const nm_pack_ranked_desc* descs, int32_t count, 
  *                    a prepared call is faster).  Every other shape reports
  *                    NM_ERR_WORKSPACE.
  * The fastest matrix-core kernels need K % 64 == 0, 16-byte aligned X, values and Y and ldx, ldy
- * multiples of 8; any other K above 64 and any other alignment of X and Y runs a matrix-core kernel that
- * stages X through registers (it needs the workspace); what is left (K < 64, no workspace) runs a slower
- * general kernel with the same results.  Rows of X and Y that start on 128-byte boundaries (ldx, ldy multiples
- * of 64) are fastest.
+ * multiples of 8; any other K above 64 and any other alignment of Y runs them with shorter last steps and
+ * narrower stores, and any other alignment of X a form that stages X through registers.  These need the
+ * workspace, and at K % 64 == 0 a level whose weight lies in it: an unaligned X at 2:4 and at N = M (small layers, which
+ * ask for no workspace) runs a slower general kernel that reads the packed layout, as do K < 64 and a ragged K
+ * without a workspace: the same sums, in the order of the packed values.  Rows of X and Y that start on 128-byte
+ * boundaries (ldx, ldy multiples of 64) are fastest.
+ * Activations are taken to be finite.  An infinity or NaN at a position that is pruned does not enter the general kernel's
+ * sums, nor those of any K % 64 != 0; elsewhere the matrix instructions may multiply it by a zero, which is NaN.
  */
 int32_t nm_spmm(const nm_bf16* values, const uint32_t* indices, int64_t O, int64_t K,
                 int32_t N, int32_t M, const nm_bf16* X, int64_t T, int64_t ldx,

@@ -16,7 +16,9 @@
 // words, or dense rows) and the X tile are copied global -> LDS asynchronously, two to four stages
 // deep with one barrier per step; each wave reads its operand fragments with 16-byte LDS reads
 // (XOR-swizzled rows, conflict free) and keeps an (OT*16) x (TT*16) accumulator tile.
-// Shapes the tiles cannot take (K % 64 != 0, unaligned pointers) run a plain gather kernel.
+// A reduction that is no whole number of steps, or X and Y at any alignment, run the ragged form of the same tiles from a
+// workspace; what is left (K < 64, no workspace, an unaligned X at 2:4 and N = M, whose weight is read as packed) runs a
+// plain gather kernel.
 #include "nm_device.h"
 #include "nm_launch.h"
 #include "nm_mma.h"
