@@ -48,12 +48,13 @@ inline hipError_t compute_units(int* n) {
 
 // A grid of 256-lane blocks for n lanes, and a lane's number in it: a launch holds fewer than 2^32 lanes per dimension, so
 // beyond 2^23 blocks they are laid out in two.  (The last row of blocks may reach past n.)
+constexpr int kFlatRow = 23;  // log2 of the blocks in a row: a constant, so that the kernels need no grid size
 inline dim3 flat_grid_256(int64_t n) {
-  const int64_t blocks = (n + 255) / 256, row = (int64_t)1 << 23;
+  const int64_t blocks = (n + 255) / 256, row = (int64_t)1 << kFlatRow;
   return blocks <= row ? dim3((unsigned)blocks) : dim3((unsigned)row, (unsigned)((blocks + row - 1) / row));
 }
 __device__ __forceinline__ int64_t flat_lane_256() {
-  return ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
+  return (((int64_t)blockIdx.y << kFlatRow) + blockIdx.x) * 256 + threadIdx.x;
 }
 
 struct PackDesc {
