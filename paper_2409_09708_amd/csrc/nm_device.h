@@ -111,4 +111,24 @@ __host__ __device__ __forceinline__ int64_t stream_selector8_offset(int64_t row,
   return (((row >> 8) * nk + step) << 12) + (r >> 4) * 256 + (r & 15) * 16 + kb * 4;
 }
 
+// One output by the definition: the kept weights of out-feature o in stored order times the activations at their
+// positions, then the bias.  An activation at a pruned position is not read.
+__device__ __forceinline__ float gather_output(const bf16_t* __restrict__ values, const uint32_t* __restrict__ indices,
+                                               int64_t K, int N, int M, const bf16_t* __restrict__ x,
+                                               const float* __restrict__ bias, int64_t o) {
+  const int b = log2_of(M);
+  const int64_t nf = K / M * N;
+  const int64_t nw = (nf * b + 31) / 32;
+  const uint32_t* row = indices + o * nw;
+  float acc = 0.f;
+  for (int64_t g = 0; g < K / M; ++g) {
+    for (int j = 0; j < N; ++j) {
+      const int64_t f = g * N + j;
+      const uint32_t p = stream_bits(row, nw, f * b, b);
+      acc = fmaf(bf16_to_f32(x[g * M + p]), bf16_to_f32(values[o * nf + f]), acc);
+    }
+  }
+  return bias ? acc + bias[o] : acc;
+}
+
 }  // namespace nm

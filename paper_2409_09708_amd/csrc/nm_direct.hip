@@ -67,7 +67,7 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r16 = lane & 15, kb = lane >> 4;
   const int o0 = (int)blockIdx.x * kRows, t0 = (int)blockIdx.y * kToks;
-  const int nk = a.K >> 6, spans = (nk + kSteps - 1) / kSteps;
+  const int nk = (a.K + 63) >> 6, spans = (nk + kSteps - 1) / kSteps;  // a last step may be short (K % 16 == 0)
   const int64_t nf = (int64_t)a.K / M * N;
   const int64_t nw = (nf * C::B + 31) / 32;
 
@@ -80,7 +80,7 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
       for (int i = 0; i < C::VW; ++i) d.v[u][i] = 0;
 #pragma unroll
       for (int i = 0; i < C::WORDS; ++i) d.f[u][i] = 0;
-      if (o < a.O && c < nk * 4) {  // rows past O and steps past K are zero
+      if (o < a.O && c * 16 < a.K) {  // rows past O and chunks past K are zero
         const bf16_t* src = a.values + o * nf + (int64_t)c * C::VPC;
         if constexpr (C::VPC % 8 == 0) {
           const uint4 q = *reinterpret_cast<const uint4*>(src);
@@ -226,7 +226,13 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
   for (int i = 0; i < 2; ++i) {
     const int o = o_lane + 16 * i;
     if (o >= a.O) continue;
-    const f32x4_t y = PACKED ? acc[i] + bias_of(i) : acc[i];
+    f32x4_t y = PACKED ? acc[i] + bias_of(i) : acc[i];
+    if (a.K & 63) {  // a sum that ended as NaN again by the definition, as the ragged form of the tiled kernel has it
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (__builtin_isnan(y[e]) && o + e < a.O)
+          y[e] = gather_output(a.values, a.indices, a.K, N, M, a.X + t * a.ldx, a.bias, o + e);
+    }
     const uint32_t p[2] = {pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
     if (a.out_bf16) {
       bf16_t* dst = reinterpret_cast<bf16_t*>(a.Y) + t * a.ldy + o;
@@ -269,7 +275,8 @@ bool direct_level(int N, int M) {
   }
 }
 
-// The caller has checked the operands (K % 64 == 0, 16-byte aligned X rows and values, sizes as the tiled kernel's).
+// The caller has checked the operands (K % 64 == 0, or K % 16 == 0 in the tiled kernel's order; 16-byte aligned X rows and
+// values, sizes as the tiled kernel's).
 hipError_t launch_direct(const SpmmArgs& a, bool packed_order, hipStream_t s) {
   DirectArgs g;
   g.values = a.values; g.indices = a.indices; g.X = a.X; g.bias = a.bias; g.Y = a.Y;

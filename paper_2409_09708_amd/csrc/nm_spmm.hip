@@ -217,26 +217,6 @@ struct GemmArgs {
   const uint32_t* indices;
 };
 
-// One output by the definition: the kept weights of out-feature o in stored order times the activations at their
-// positions, then the bias.  An activation at a pruned position is not read.
-__device__ __forceinline__ float gather_output(const bf16_t* __restrict__ values, const uint32_t* __restrict__ indices,
-                                               int64_t K, int N, int M, const bf16_t* __restrict__ x,
-                                               const float* __restrict__ bias, int64_t o) {
-  const int b = log2_of(M);
-  const int64_t nf = K / M * N;
-  const int64_t nw = (nf * b + 31) / 32;
-  const uint32_t* row = indices + o * nw;
-  float acc = 0.f;
-  for (int64_t g = 0; g < K / M; ++g) {
-    for (int j = 0; j < N; ++j) {
-      const int64_t f = g * N + j;
-      const uint32_t p = stream_bits(row, nw, f * b, b);
-      acc = fmaf(bf16_to_f32(x[g * M + p]), bf16_to_f32(values[o * nf + f]), acc);
-    }
-  }
-  return bias ? acc + bias[o] : acc;
-}
-
 template <bool SPARSE, int WO, int WT, int OT, int TT, int STAGES_>
 struct GemmCfg {
   static constexpr int STAGES = STAGES_;
@@ -2217,6 +2197,11 @@ static bool direct_takes(int64_t O, int64_t K, int N, int M, int64_t T, int pick
   return tile_estimate(kDirectModel[sparse_form], O, K, T) < two;
 }
 
+// A ragged reduction of whole 16-weight chunks is decoded likewise (210 x 144 -> 332 at 1:16 8.5 us in two launches, 4.4 here).
+static bool direct_takes_ragged(int64_t O, int64_t K, int N, int M, int64_t T) {
+  return K % 16 == 0 && direct_takes(O, padded_k(K), N, M, T, 2);
+}
+
 // A call without a workspace takes it up to four rounds of blocks, and at one block of tokens in any case; beyond, it would
 // decode a wide weight two to four times, and the kernel of nm_fewtok.hip, with the same sums, is the faster one (12288 ->
 // 49152 at 1:8 and 208 tokens 370 us, 1080 that way; 2048 -> 16384 at 130 tokens 38.7 and 53.3; 768 -> 1000 at 4:8 and 16
@@ -2241,6 +2226,9 @@ hipError_t launch_spmm(const SpmmArgs& a, hipStream_t s, bool* workspace_short, 
   if (!tiles_ok(a.K, a.X, a.ldx, a.values, a.indices, a.O, a.T)) {
     // without the workspace the gather kernel reads the packed layout itself
     const bool ragged = copy_fits && (a.K % 64 != 0 || tiles_ok(a.K, nullptr, a.K, a.values, a.indices, a.O, a.T));
+    if (ragged && prepare && product && a.K % 64 != 0 && aligned_to(a.X, 16) && a.ldx % 8 == 0 && aligned_to(a.values, 16) &&
+        direct_takes_ragged(a.O, a.K, a.N, a.M, a.T))
+      return launch_direct(a, false, s);
     if (ragged && prepare) {
       hipError_t e = launch_stream_prepass(a, sparse_form, s);
       if (e != hipSuccess) return e;
@@ -2279,7 +2267,10 @@ hipError_t launch_spmm(const SpmmArgs& a, hipStream_t s, bool* workspace_short, 
 extern "C" int32_t nm_internal_product_route(int32_t call, int64_t O, int64_t K, int32_t N, int32_t M, int64_t T, int32_t* tile) {
   enum { ROUTE_GENERAL, ROUTE_TILED, ROUTE_PERSISTENT, ROUTE_RAGGED, ROUTE_DIRECT, ROUTE_FEWTOK };
   const bool sparse_form = N <= 2 && N < M;
-  if (K % 64) return call != 2 && ragged_shape(O, K, T) ? ROUTE_RAGGED : ROUTE_GENERAL;
+  if (K % 64) {
+    if (call == 2 || !ragged_shape(O, K, T)) return ROUTE_GENERAL;
+    return call == 0 && direct_takes_ragged(O, K, N, M, T) ? ROUTE_DIRECT : ROUTE_RAGGED;
+  }
   const int pick = pick_tile(O, K, T, sparse_form);
   if (call == 2 && spmm_operand_workspace_bytes(O, K, N, M, T) != 0)
     return !fewtok_shape(O, K, N, M, T) ? -1 : direct_takes_packed(O, T) ? ROUTE_DIRECT : ROUTE_FEWTOK;

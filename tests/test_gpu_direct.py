@@ -8,7 +8,7 @@ import torch
 import paper_2409_09708_amd as nm
 from oracle import nm_oracle as orc
 from paper_2409_09708_amd import workloads as wl
-from gpu_util import check_output, dev_bf16, host_output
+from gpu_util import check_output, dev_bf16, host_output, product_route
 
 pytestmark = pytest.mark.gpu
 
@@ -33,4 +33,26 @@ def test_products(T, K, O, N, M):
         y = nm.nm_linear_forward(v, i, K, N, M, Xd, bias=bd, out=out[:T, pad:pad + O])
         check_output(host_output(y.contiguous()), Yref, B, K // M * N + 1, dt == torch.float32, (T, K, O, N, M, dt))
         assert bool((out[T] == 7).all() and (out[:, :pad] == 7).all() and (out[:, pad + O:] == 7).all())
+        assert torch.equal(y, nm.nm_linear_forward_prepared(v, i, K, N, M, Xd, ws, bias=bd, out_dtype=dt))
+
+
+# Reductions that end inside a step or a span (whole 16-weight chunks): the bytes of a prepared call, whose ragged form sums
+# in the same order; rows of X start on 16 bytes and what lies behind them is NaN
+@pytest.mark.parametrize("N,M", LEVELS)
+@pytest.mark.parametrize("T,K,O", [(1, 80, 1), (20, 80, 1028), (65, 272, 33), (64, 336, 72), (130, 496, 100), (70, 1040, 31)])
+def test_ragged_reductions(T, K, O, N, M):
+    rng = np.random.default_rng(14500 + N * 17 + M + T + K)
+    X, W = wl.draw_activations(rng, T, K), wl.draw_weights(rng, O, K)
+    bias = rng.standard_normal(O).astype(np.float32)
+    Yref, B = orc.nm_linear_from_bits(X, W, N, M, bias=bias)
+    v, i = nm.nm_pack(dev_bf16(W), N, M)
+    bd = torch.from_numpy(bias).cuda()
+    wide = torch.full((T, K + 16), float("nan"), dtype=torch.bfloat16, device="cuda")
+    Xd = wide[:, 8:K + 8]
+    Xd.copy_(dev_bf16(X))
+    assert product_route("plain", T, K, O, N, M)[0] == "direct"
+    ws = nm.nm_spmm_prepare(v, i, K, N, M, T)
+    for dt in (torch.float32, torch.bfloat16):
+        y = nm.nm_linear_forward(v, i, K, N, M, Xd, bias=bd, out_dtype=dt)
+        check_output(host_output(y), Yref, B + np.abs(bias)[None, :], K // M * N + 1, dt == torch.float32, (T, K, O, N, M))
         assert torch.equal(y, nm.nm_linear_forward_prepared(v, i, K, N, M, Xd, ws, bias=bd, out_dtype=dt))

@@ -445,6 +445,13 @@ def test_wide_weights_are_not_decoded_over_and_over(lib, N, M):
     assert product_kernel("packed", 209, 768, 768, N, M) == "refused"
 
 
+def test_small_ragged_layers_take_one_launch(lib):
+    # ... as they did when the gather kernel ran them; whole 16-weight chunks only
+    for T, K, O, N, M in ((20, 80, 1028, 2, 16), (210, 144, 332, 1, 16), (197, 80, 100, 1, 4), (18, 80, 784, 4, 16)):
+        assert product_kernel("plain", T, K, O, N, M) == "direct" and product_kernel("prepared", T, K, O, N, M) == "ragged"
+    assert product_kernel("plain", 20, 72, 1028, 1, 4) == "ragged" and product_kernel("packed", 20, 80, 1028, 2, 16) == "general"
+
+
 def test_a_wide_weight_is_not_read_twice_for_few_tokens(lib):
     # past the L2s, 64-token tiles would bring it from memory once more per 128 tokens
     for T, K, O, N, M in ((65, 4096, 16384, 4, 8), (65, 4096, 16384, 8, 8), (100, 1024, 16384, 4, 8), (65, 1024, 16384, 2, 8)):
