@@ -16,8 +16,10 @@ namespace nm {
 
 constexpr int kPackThreads = 256;
 constexpr int kChunk = 16;          // weights per chunk in the fast kernels (two 16-byte loads)
-constexpr int kChunksPerLane = 2;   // chunks a lane handles, all their loads in flight before the first is coded
-constexpr int kBlockChunks = kPackThreads * kChunksPerLane;
+// Chunks a lane handles, all their loads in flight before the first is coded: two where the matrices of a whole model share
+// a launch, one for a matrix alone, whose few blocks are bound by one block's load, coding and store.
+constexpr int kBatchChunks = 2;
+constexpr int kBatchBlock = kPackThreads * kBatchChunks;
 
 // One 16-weight chunk: selection, compaction in ascending position, index fields.
 template <int N, int M, bool EXTERNAL_MASK>
@@ -100,17 +102,21 @@ constexpr bool kFastLevel = (N == 1 || N == 2 || N == 4) && N < M;
 // Work of one block on kBlockChunks consecutive chunks of one contiguous matrix.
 //   values/indices may be NULL (prune only); mask_out / w_masked may be NULL (pack only).
 // SRC: where the selection comes from: 0 = magnitude (Eq. (1)), 1 = the caller's mask words, 2 = stored ranks
-// (4 bits per weight; kept = rank < N)
+// (4 bits per weight; kept = rank < N).  A given selection at the fast levels is compacted by the same networks as the
+// magnitude selection: comparing every weight with every place it could have bound these kernels by vector instructions
+// (48 weights from ranks, 85 M weights: 59 -> 43 us, 6.2 TB/s; 3072 x 768 at 2:4 under a mask 5.7 -> 3.9).  Chunks with a
+// group that has another number of kept weights take the general coder.
 // stream_ws (magnitude selection at the fast levels only): the product kernel's operand order, written beside the
 // packed form.
-template <int N, int M, int SRC>
+template <int N, int M, int SRC, int CHUNKS>
 __device__ __forceinline__ void code_block(const bf16_t* W, int64_t n_chunks, int64_t chunk0,
                                            const uint32_t* __restrict__ mask_in, bf16_t* __restrict__ values,
                                            uint32_t* __restrict__ indices, uint32_t* __restrict__ mask_out,
                                            bf16_t* w_masked, uint32_t* sbits, unsigned char* stream_ws = nullptr,
                                            int64_t K = 0) {
-  constexpr bool FAST = SRC == 0 && kFastLevel<N, M>;
+  constexpr bool FAST = kFastLevel<N, M>;
   using Coder = std::conditional_t<FAST, FastChunkCoder<N, M>, ChunkCoder<N, M, SRC != 0>>;
+  constexpr int kChunksPerLane = CHUNKS, kBlockChunks = kPackThreads * CHUNKS;
   constexpr int NB = Coder::NB;
   constexpr bool DIRECT_INDEX = (NB == 8 || NB == 16 || NB == 32 || NB == 64);
   constexpr int BLOCK_WORDS = kBlockChunks * NB / 32;
@@ -122,6 +128,8 @@ __device__ __forceinline__ void code_block(const bf16_t* W, int64_t n_chunks, in
   }
   // this lane's chunks: tid, tid + 256, ... of the block's run; every load leaves before anything is coded
   uint32_t d[kChunksPerLane][8];
+  constexpr int BITS = SRC == 2 ? 4 : 1, WORDS = SRC == 2 ? 2 : 1;  // a given selection: a bit per weight, or its rank
+  uint32_t given[kChunksPerLane][WORDS];
 #pragma unroll
   for (int u = 0; u < kChunksPerLane; ++u) {
     const int64_t c = chunk0 + u * kPackThreads + tid;
@@ -130,6 +138,11 @@ __device__ __forceinline__ void code_block(const bf16_t* W, int64_t n_chunks, in
       const uint4 a = src[0], b = src[1];
       d[u][0] = a.x; d[u][1] = a.y; d[u][2] = a.z; d[u][3] = a.w;
       d[u][4] = b.x; d[u][5] = b.y; d[u][6] = b.z; d[u][7] = b.w;
+      if constexpr (SRC == 1) given[u][0] = reinterpret_cast<const uint16_t*>(mask_in)[c];
+      if constexpr (SRC == 2) {
+        const uint2 r = reinterpret_cast<const uint2*>(mask_in)[c];
+        given[u][0] = r.x; given[u][WORDS - 1] = r.y;
+      }
     }
   }
 #pragma unroll
@@ -138,22 +151,59 @@ __device__ __forceinline__ void code_block(const bf16_t* W, int64_t n_chunks, in
     if (c >= n_chunks) continue;
     Coder coder;
     uint32_t keep16 = 0;
-    if constexpr (FAST) {
+    if constexpr (FAST && SRC == 0) {
       coder.run(d[u]);
       if (mask_out || w_masked || (stream_ws && N > 2)) keep16 = coder.keep16();
     } else {
-      uint32_t e[kChunk];
+      // weight i kept: bit BITS i of kept; N of them in every group unless the caller says otherwise
+      uint32_t kept[WORDS] = {};
+      if constexpr (SRC != 0) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) { e[2 * i] = d[u][i] & 0xFFFFu; e[2 * i + 1] = d[u][i] >> 16; }
-      uint32_t mask16 = 0;
-      if (SRC == 1) mask16 = reinterpret_cast<const uint16_t*>(mask_in)[c];
-      if (SRC == 2) {
-        const uint64_t r = reinterpret_cast<const uint64_t*>(mask_in)[c];
-#pragma unroll
-        for (int i = 0; i < kChunk; ++i) mask16 |= (((uint32_t)(r >> (4 * i)) & 15u) < (uint32_t)N ? 1u : 0u) << i;
+        for (int w = 0; w < WORDS; ++w) kept[w] = given[u][w];
       }
-      coder.run(e, mask16);
-      keep16 = coder.keep16;
+      if constexpr (SRC == 2) {
+        if constexpr ((N & (N - 1)) == 0) {  // rank < N: no bit from N on
+#pragma unroll
+          for (int w = 0; w < 2; ++w) {
+            uint32_t t = kept[w] & (0x11111111u * (15u & ~(uint32_t)(N - 1)));
+            t |= t >> 2;
+            t |= t >> 1;
+            kept[w] = ~t & 0x11111111u;
+          }
+        } else {
+#pragma unroll
+          for (int w = 0; w < 2; ++w) {
+            uint32_t t = 0;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) t |= (((kept[w] >> (4 * i)) & 15u) < (uint32_t)N ? 1u : 0u) << (4 * i);
+            kept[w] = t;
+          }
+        }
+      }
+      bool regular = FAST;
+      if constexpr (FAST) {
+#pragma unroll
+        for (int g = 0; g < 16 / M; ++g) {
+          uint32_t n = 0;
+          if constexpr (M * BITS == 64) n = (uint32_t)(__popc(kept[0]) + __popc(kept[WORDS - 1]));
+          else n = (uint32_t)__popc((kept[g * M * BITS / 32] >> (g * M * BITS % 32)) & (M * BITS == 32 ? ~0u : (1u << (M * BITS % 32)) - 1u));
+          regular &= n == (uint32_t)N;
+        }
+        if (regular) coder.template run_kept<BITS, WORDS>(d[u], kept);
+      }
+      if (!regular) {
+        uint32_t e[kChunk], mask16 = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) { e[2 * i] = d[u][i] & 0xFFFFu; e[2 * i + 1] = d[u][i] >> 16; }
+#pragma unroll
+        for (int i = 0; i < kChunk; ++i) mask16 |= ((kept[i * BITS / 32] >> (i * BITS % 32)) & 1u) << i;
+        ChunkCoder<N, M, SRC != 0> any;
+        any.run(e, mask16);
+        if constexpr (!FAST) keep16 = any.keep16;
+#pragma unroll
+        for (int i = 0; i < Coder::NV; ++i) coder.vals[i] = any.vals[i];
+        coder.ibits = any.ibits;
+      }
     }
 
     if (values) store_values<Coder::NV>(values + c * Coder::NV, coder.vals);
@@ -173,7 +223,7 @@ __device__ __forceinline__ void code_block(const bf16_t* W, int64_t n_chunks, in
       }
     }
     if (mask_out) reinterpret_cast<uint16_t*>(mask_out)[c] = (uint16_t)keep16;
-    if constexpr (FAST) {
+    if constexpr (FAST && SRC == 0) {
       if (stream_ws) {
         // this lane's 16 weights are one 16-byte chunk of a row's K step (2:4 form), or two of them (dense form)
         const int64_t per_row = K / kChunk;
@@ -208,24 +258,23 @@ __device__ __forceinline__ void code_block(const bf16_t* W, int64_t n_chunks, in
   }
   if (!DIRECT_INDEX && indices) {
     __syncthreads();
-    const int64_t left = n_chunks - chunk0;
-    const int nact = left < kBlockChunks ? (int)left : kBlockChunks;
+    const int64_t left = n_chunks - chunk0;  // (none in the last blocks of a two-dimensional grid)
+    const int nact = left < 0 ? 0 : left < kBlockChunks ? (int)left : kBlockChunks;
     const int nwords = (nact * NB) >> 5;  // exact: whole rows hold whole words
     uint32_t* dst = indices + (chunk0 * NB >> 5);
     for (int i = tid; i < nwords; i += kPackThreads) dst[i] = sbits[i];
   }
 }
 
-constexpr int kSbitsWords = kBlockChunks * 64 / 32 + 2;  // room for the widest per-chunk index field run (<= 64 bits)
+constexpr int kSbitsWords = kBatchBlock * 64 / 32 + 2;  // room for the widest per-chunk index field run (<= 64 bits)
 
 template <int N, int M, int SRC>
 __global__ void __launch_bounds__(kPackThreads)
 code_flat_kernel(const bf16_t* W, int64_t n_chunks, const uint32_t* __restrict__ mask_in,
                  bf16_t* __restrict__ values, uint32_t* __restrict__ indices, uint32_t* __restrict__ mask_out,
                  bf16_t* w_masked) {  // w_masked may be W itself (in-place pruning)
-  __shared__ uint32_t sbits[kSbitsWords];
-  code_block<N, M, SRC>(W, n_chunks, (int64_t)blockIdx.x * kBlockChunks, mask_in, values, indices,
-                                  mask_out, w_masked, sbits);
+  __shared__ uint32_t sbits[kPackThreads * 64 / 32 + 2];
+  code_block<N, M, SRC, 1>(W, n_chunks, flat_lane_256() - threadIdx.x, mask_in, values, indices, mask_out, w_masked, sbits);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -270,12 +319,12 @@ __global__ void __launch_bounds__(kPackThreads) pack_batched_kernel(const BatchA
   }
   const BatchEntry& d = args.e[m];
   const uint32_t first = m ? args.e[m - 1].block_end : 0u;
-  const int64_t chunk0 = (int64_t)(blockIdx.x - first) * kBlockChunks;
+  const int64_t chunk0 = (int64_t)(blockIdx.x - first) * kBatchBlock;
   const int level = d.N * 32 + d.M;
   switch (level) {
 #define X(n, mm)                                                                                      \
   case n * 32 + mm:                                                                                   \
-    code_block<n, mm, SRC>(d.W, d.n_chunks, chunk0, SRC ? d.rank : nullptr, d.values, d.indices, nullptr, \
+    code_block<n, mm, SRC, kBatchChunks>(d.W, d.n_chunks, chunk0, SRC ? d.rank : nullptr, d.values, d.indices, nullptr, \
                            nullptr, sbits, d.stream_ws, d.K);                                         \
     break;
     NM_FOR_EACH_BATCH_LEVEL(X)
@@ -501,7 +550,7 @@ static bool flat_ok(int64_t O, int64_t K, int64_t ldw, int N, int M, const void*
                     const void* d, const void* e) {
   if (ldw != K || (K % 32) != 0) return false;
   if ((values_per_row(K, N, M) * log2_of(M)) % 32 != 0) return false;
-  if ((O * K / kChunk + kBlockChunks - 1) / kBlockChunks > 0x7FFFFFFF) return false;
+  if ((O * K / kChunk + kBatchBlock - 1) / kBatchBlock > 0x7FFFFFFF) return false;
   const uintptr_t all = (uintptr_t)a | (uintptr_t)b | (uintptr_t)c | (uintptr_t)d | (uintptr_t)e;
   return (all & 15u) == 0;
 }
@@ -525,7 +574,7 @@ hipError_t launch_prune(const bf16_t* W, int64_t O, int64_t K, int64_t ldw, int 
                         bf16_t* w_masked, hipStream_t s) {
   if (flat_ok(O, K, ldw, N, M, W, mask, w_masked, nullptr, nullptr)) {
     const int64_t n_chunks = O * K / kChunk;
-    launch_flat<0>(N, M, dim3(blocks_for(n_chunks, kBlockChunks)), s, W, n_chunks, nullptr, nullptr, nullptr, mask,
+    launch_flat<0>(N, M, flat_grid_256(n_chunks), s, W, n_chunks, nullptr, nullptr, nullptr, mask,
                        w_masked);
   } else {
     const int64_t n = O * mask_words_per_row(K);
@@ -539,7 +588,7 @@ hipError_t launch_pack(const bf16_t* W, int64_t O, int64_t K, int64_t ldw, int N
                        bf16_t* values, uint32_t* indices, hipStream_t s) {
   if (flat_ok(O, K, ldw, N, M, W, mask, values, indices, nullptr)) {
     const int64_t n_chunks = O * K / kChunk;
-    const dim3 grid(blocks_for(n_chunks, kBlockChunks));
+    const dim3 grid = flat_grid_256(n_chunks);
     if (mask) launch_flat<1>(N, M, grid, s, W, n_chunks, mask, values, indices, nullptr, nullptr);
     else launch_flat<0>(N, M, grid, s, W, n_chunks, nullptr, values, indices, nullptr, nullptr);
   } else {
@@ -558,7 +607,7 @@ hipError_t launch_pack_ranked(const bf16_t* W, const uint8_t* rank, int64_t O, i
                               bf16_t* values, uint32_t* indices, hipStream_t s) {
   if (flat_ok(O, K, ldw, N, M, W, rank, values, indices, nullptr)) {
     const int64_t n_chunks = O * K / kChunk;
-    launch_flat<2>(N, M, dim3(blocks_for(n_chunks, kBlockChunks)), s, W, n_chunks,
+    launch_flat<2>(N, M, flat_grid_256(n_chunks), s, W, n_chunks,
                    reinterpret_cast<const uint32_t*>(rank), values, indices, nullptr, nullptr);
   } else {
     const int64_t ng = O * (K / M);
@@ -600,7 +649,7 @@ hipError_t launch_pack_batched(const PackDesc* descs, int count, hipStream_t s) 
       continue;
     }
     const int64_t n_chunks = d.O * d.K / kChunk;
-    const uint64_t nb = blocks_for(n_chunks, kBlockChunks);
+    const uint64_t nb = blocks_for(n_chunks, kBatchBlock);
     if (args.count == kBatchMax || blocks + nb > 0x7FFFFFFFull) flush();
     BatchEntry& e = args.e[args.count++];
     e.W = d.W; e.values = d.values; e.indices = d.indices; e.n_chunks = n_chunks;
@@ -633,7 +682,7 @@ hipError_t launch_pack_ranked_batched(const PackRankedDesc* descs, int count, hi
       continue;
     }
     const int64_t n_chunks = d.O * d.K / kChunk;
-    const uint64_t nb = blocks_for(n_chunks, kBlockChunks);
+    const uint64_t nb = blocks_for(n_chunks, kBatchBlock);
     if (args.count == kBatchMax || blocks + nb > 0x7FFFFFFFull) flush();
     BatchEntry& e = args.e[args.count++];
     e.W = d.W; e.values = d.values; e.indices = d.indices; e.n_chunks = n_chunks;
@@ -676,7 +725,7 @@ hipError_t launch_pack_prepare_batched(const LayerDesc* descs, int count, hipStr
     const bool fused = flat && spmm_stream_order(d.O, d.K, d.T, d.N, d.M, &sparse_form) && (d.O % 256) == 0;
     if (flat) {
       const int64_t n_chunks = d.O * d.K / kChunk;
-      const uint64_t nb = blocks_for(n_chunks, kBlockChunks);
+      const uint64_t nb = blocks_for(n_chunks, kBatchBlock);
       if (args.count == kBatchMax || blocks + nb > 0x7FFFFFFFull) flush();
       BatchEntry& e = args.e[args.count++];
       e.W = d.W; e.values = d.values; e.indices = d.indices; e.n_chunks = n_chunks;

@@ -104,6 +104,53 @@ __host__ __device__ __forceinline__ void select_group(const uint32_t (&key)[M], 
   }
 }
 
+// The kept weights of one group whose selection is given, N of them: key[i] is the place key of position i, or 0 for a pruned
+// weight, so the N largest keys in descending order are the kept ones in ascending position.  (A zero in the last position
+// has the key 0 as well, and it decodes to just that.)
+template <int N, int M>
+__host__ __device__ __forceinline__ void compact_group(const uint32_t (&key)[M], uint32_t (&win)[N]) {
+  static_assert((N == 1 || N == 2 || N == 4) && N < M && (M == 4 || M == 8 || M == 16), "levels of the fast selection");
+  if constexpr (N == 1) {
+    uint32_t best = key[0];
+#pragma unroll
+    for (int i = 1; i < M; ++i) best |= key[i];  // one of them at most is not 0
+    win[0] = best;
+  } else if constexpr (N == 2) {
+    uint32_t hi[M / 2], lo[M / 2];
+#pragma unroll
+    for (int i = 0; i < M / 2; ++i) { hi[i] = umax(key[2 * i], key[2 * i + 1]); lo[i] = umin(key[2 * i], key[2 * i + 1]); }
+#pragma unroll
+    for (int n = M / 2; n > 1; n /= 2) {
+#pragma unroll
+      for (int i = 0; i < n / 2; ++i) {
+        const uint32_t h = umax(hi[2 * i], hi[2 * i + 1]);
+        const uint32_t l = umax(umin(hi[2 * i], hi[2 * i + 1]), umax(lo[2 * i], lo[2 * i + 1]));
+        hi[i] = h; lo[i] = l;
+      }
+    }
+    win[0] = hi[0]; win[1] = lo[0];
+  } else {
+    uint32_t run[M / 4][4];
+#pragma unroll
+    for (int r = 0; r < M / 4; ++r) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) run[r][i] = key[4 * r + i];
+      sort4_desc(run[r]);
+    }
+    if constexpr (M == 8) {
+      top4_of_sorted(run[0], run[1], win);
+    } else {
+      uint32_t t[4], u[4];
+      top4_of_sorted(run[0], run[1], t);
+      top4_of_sorted(run[2], run[3], u);
+      sort4_bitonic_desc(t);
+      sort4_bitonic_desc(u);
+      top4_of_sorted(t, u, win);
+    }
+    sort4_bitonic_desc(win);
+  }
+}
+
 // One 16-weight chunk (8 dwords of a row, weight 2i in the low half of d[i]): per group the kept values in
 // ascending position, the index fields, and on request the keep mask.
 template <int N, int M>
@@ -118,7 +165,6 @@ struct FastChunkCoder {
   uint64_t ibits;
 
   __host__ __device__ __forceinline__ void run(const uint32_t (&d)[8]) {
-    uint64_t inv = 0;  // the fields with M - 1 - position; complemented at the end
 #pragma unroll
     for (int g = 0; g < G; ++g) {
       uint32_t key[M];
@@ -128,12 +174,38 @@ struct FastChunkCoder {
         key[i + 1] = order_key<1>(d[(g * M + i) / 2], i + 1, M);
       }
       select_group<N, M>(key, win[g]);
+    }
+    fields();
+  }
+
+  // The same with the selection given: weight i of the chunk is kept where bit BITS (i mod 32/BITS) of kept[BITS i / 32] is
+  // set.  Every group has N kept weights.
+  template <int BITS, int WORDS>
+  __host__ __device__ __forceinline__ void run_kept(const uint32_t (&d)[8], const uint32_t (&kept)[WORDS]) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      uint32_t key[M];
+#pragma unroll
+      for (int i = 0; i < M; ++i) {
+        const int w = g * M + i;
+        const uint32_t v = (w & 1) ? d[w / 2] >> 4 : d[w / 2] << 12;
+        const uint32_t on = (uint32_t)((int32_t)(kept[w * BITS / 32] << (31 - w * BITS % 32)) >> 31);
+        key[i] = ((v & 0x0FFFF000u) | ((uint32_t)(M - 1 - i) << 28)) & on;
+      }
+      compact_group<N, M>(key, win[g]);
+    }
+    fields();
+  }
+
+  __host__ __device__ __forceinline__ void fields() {
+    uint64_t inv = 0;  // the fields with M - 1 - position; complemented at the end
+#pragma unroll
+    for (int g = 0; g < G; ++g)
 #pragma unroll
       for (int j = 0; j < N; ++j) {
         vals[g * N + j] = place_value(win[g][j]);
         inv |= (uint64_t)place_invpos(win[g][j]) << (B * (g * N + j));
       }
-    }
     ibits = ~inv & (NB == 64 ? ~0ull : ((1ull << NB) - 1ull));
   }
 
