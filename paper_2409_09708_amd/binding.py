@@ -1,5 +1,6 @@
 """ctypes binding of libnm_sparse.so.  Argument marshalling only: every step of the path runs in the
-HIP kernels behind the C ABI (include/nm_sparse.h).  torch provides device memory and the stream.
+HIP kernels behind the C ABI (include/nm_sparse.h).  torch provides device memory and the stream.  The calls made per
+layer go through the native marshalling of csrc/nm_calls.cpp first, which declines what is not in the ordinary form.
 
 Tensor conventions: weights / activations / packed values are torch.bfloat16 CUDA tensors; index and
 mask words are torch.int32 tensors holding the uint32 bit patterns.
@@ -7,12 +8,15 @@ mask words are torch.int32 tensors holding the uint32 bit patterns.
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 import struct
 from ctypes import c_char_p, c_int32, c_int64, c_size_t, c_void_p
 from typing import List, Optional, Sequence, Tuple
 
 _LIB = None
+_CALLS = None
 _PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 
 NM_OK = 0
@@ -200,6 +204,22 @@ def load_library() -> ctypes.CDLL:
     return lib
 
 
+def _native():
+    """The native marshalling, bound to the loaded library.  As with the library there is no fallback for a missing build."""
+    global _CALLS
+    lib = load_library()
+    path = os.path.join(_PKG_DIR, "_nm_calls.so")
+    if not os.path.exists(path):
+        raise RuntimeError(f"{path} is missing: build it with `python -m paper_2409_09708_amd.build`")
+    _torch()
+    loader = importlib.machinery.ExtensionFileLoader("_nm_calls", path)
+    calls = importlib.util.module_from_spec(importlib.util.spec_from_loader("_nm_calls", loader))
+    loader.exec_module(calls)
+    calls.bind({name: ctypes.cast(getattr(lib, name), c_void_p).value for name in EXPORTS}, _check, _workspace)
+    _CALLS = calls
+    return calls
+
+
 def nm_status_string(status: int) -> str:
     return load_library().nm_status_string(status).decode()
 
@@ -323,6 +343,9 @@ def _empty_packed(O: int, K: int, N: int, M: int, W):
 
 def nm_prune(W, N: int, M: int, W_masked=None, stream=None):
     """Mask words [O, ceil(K/32)] (int32) of Eq. (1); optionally writes the pruned weight to W_masked."""
+    done = (_CALLS or _native()).prune(W, N, M, W_masked, stream)
+    if done is not NotImplemented:
+        return done
     torch = _torch()
     _need(W, torch.bfloat16, "W")
     O, K, ldw = _rows(W, "W")
@@ -339,6 +362,9 @@ def nm_prune(W, N: int, M: int, W_masked=None, stream=None):
 
 def nm_prune_scored(score, N: int, M: int, stream=None):
     """Mask words [O, ceil(K/32)] (int32) keeping the N largest of every M scores (float32 [O, K])."""
+    done = (_CALLS or _native()).prune_scored(score, N, M, stream)
+    if done is not NotImplemented:
+        return done
     torch = _torch()
     _need(score, torch.float32, "score")
     O, K, lds = _rows(score, "score")
@@ -452,6 +478,9 @@ def nm_pack_ranked_batched(layers: Sequence[Tuple[object, object, int, int]], st
 
 def nm_pack(W, N: int, M: int, mask=None, stream=None):
     """(values bf16 [O, K*N/M], indices int32 [O, words]) of W at level N:M."""
+    done = (_CALLS or _native()).pack(W, N, M, mask, stream)
+    if done is not NotImplemented:
+        return done
     torch = _torch()
     _need(W, torch.bfloat16, "W")
     O, K, ldw = _rows(W, "W")
@@ -499,6 +528,9 @@ def nm_pack_prepare_batched(layers: Sequence[Tuple[object, int, int, int]], stre
 
 
 def nm_unpack(values, indices, K: int, N: int, M: int, stream=None):
+    done = (_CALLS or _native()).unpack(values, indices, K, N, M, stream)
+    if done is not NotImplemented:
+        return done
     torch = _torch()
     _need(values, torch.bfloat16, "values")
     _need(indices, torch.int32, "indices")
@@ -572,6 +604,9 @@ def nm_spmm_prepare(values, indices, K: int, N: int, M: int, T: int, workspace=N
 def nm_linear_forward_prepared(values, indices, K: int, N: int, M: int, X, workspace, bias=None, out_dtype=None,
                                out=None, stream=None):
     """The product alone, from a workspace filled by nm_spmm_prepare."""
+    done = (_CALLS or _native()).forward(values, indices, K, N, M, X, bias, out_dtype, out, workspace, stream, 1)
+    if done is not NotImplemented:
+        return done
     return nm_linear_forward(values, indices, K, N, M, X, bias, out_dtype, out, workspace, stream, _prepared=True)
 
 
@@ -580,6 +615,10 @@ def nm_linear_forward(values, indices, K: int, N: int, M: int, X, bias=None, out
     """Y = X * W_s^T (+ bias) from the packed weight; Y is float32 (default) or bfloat16 [T, O].
     from_packed: hand the library no workspace, so that a product of up to 208 tokens runs straight from the packed
     format (the library reports a missing workspace for shapes that path does not take)."""
+    done = (_CALLS or _native()).forward(values, indices, K, N, M, X, bias, out_dtype, out, workspace, stream,
+                                         1 if _prepared else 2 if from_packed else 0)
+    if done is not NotImplemented:
+        return done
     torch = _torch()
     lib = load_library()
     O = _packed(values, indices, torch.bfloat16)
@@ -608,6 +647,9 @@ def nm_static_scratch_bytes() -> int:
 def nm_linear_forward_static(values, indices, K: int, N: int, M: int, X, bias=None, out_dtype=None, out=None,
                              stream=None):
     """nm_linear_forward on the library's own fixed scratch: the call itself allocates nothing (pass `out`)."""
+    done = (_CALLS or _native()).forward(values, indices, K, N, M, X, bias, out_dtype, out, None, stream, 3)
+    if done is not NotImplemented:
+        return done
     torch = _torch()
     O = _packed(values, indices, torch.bfloat16)
     _need(X, torch.bfloat16, "X")

@@ -1,16 +1,18 @@
-"""Builds libnm_sparse.so (HIP, gfx950 only) in-tree with hipcc."""
+"""Builds libnm_sparse.so (HIP, gfx950 only) in-tree with hipcc, and the native marshalling of the calls of a layer."""
 from __future__ import annotations
 
 import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libnm_sparse.so")
+CALLS_PATH = os.path.join(PKG_DIR, "_nm_calls.so")
 SOURCES = ("nm_api.hip", "nm_direct.hip", "nm_fewtok.hip", "nm_grad.hip", "nm_int8.hip", "nm_pack.hip", "nm_probe.hip", "nm_rank.hip", "nm_search.hip", "nm_spmm.hip")
 
 HIPCC_FLAGS = [
@@ -29,8 +31,22 @@ def hipcc() -> str:
     return exe
 
 
+def build_calls() -> None:
+    """Compile the host-only extension that reads torch tensors (against the installed torch)."""
+    from torch.utils import cpp_extension
+    includes = [os.path.join(ROOT, "include"), *cpp_extension.include_paths(), "/opt/rocm/include", sysconfig.get_paths()["include"]]
+    tmp = CALLS_PATH + ".tmp"
+    cmd = ["g++", "-O2", "-std=c++20", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           *[f"-I{p}" for p in includes], os.path.join(CSRC, "nm_calls.cpp"), "-o", tmp,
+           *[f"-L{p}" for p in cpp_extension.library_paths()], "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10", "-lc10_hip"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"compiling nm_calls.cpp failed:\n{res.stderr}")
+    os.replace(tmp, CALLS_PATH)
+
+
 def build_library(verbose: bool = False) -> str:
-    """Compile every translation unit and link the shared library; returns its path."""
+    """Compile every translation unit and link the shared library, and the extension beside it; returns the library's path."""
     obj_dir = os.path.join(PKG_DIR, "_build")
     os.makedirs(obj_dir, exist_ok=True)
     cc = hipcc()
@@ -48,8 +64,10 @@ def build_library(verbose: bool = False) -> str:
             print(err, file=sys.stderr)
         return obj
 
-    with ThreadPoolExecutor(max_workers=len(SOURCES)) as pool:
+    with ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as pool:
+        calls = pool.submit(build_calls)
         objs = list(pool.map(compile_one, SOURCES))
+        calls.result()
     tmp = LIB_PATH + ".tmp"
     cmd = [cc, "--offload-arch=gfx950", "-shared", "-fPIC", "-fno-gpu-rdc", *objs, "-o", tmp]
     res = subprocess.run(cmd, capture_output=True, text=True)
