@@ -7,8 +7,9 @@
 // round trip to memory, decoding 16 weights per lane and pass (a 2-byte LDS write per kept value), and a serial chain of
 // K / 64 steps.  So a block is small (768 out-features are 24 of them per 64 tokens), all four waves decode, the loads
 // of two spans of 256 reduction positions are in flight in registers while a third is multiplied, and a span has one
-// barrier.  Which products it takes is decided in nm_spmm.hip (direct_takes).  In a graph, pre-pass and product before: 768 -> 1000 at 4:8 and 16 tokens 9.4 -> 5.9 us, 3072 -> 768 at 1:4
-// 16.4 -> 12.5, 1024 -> 4096 at 4:8 16.3 -> 7.1.
+// barrier; up to 16 tokens, four spans share one (launch_level).  Which products it takes is decided in nm_spmm.hip
+// (direct_takes).  In a graph, pre-pass and product before: 768 -> 1000 at 4:8 and 16 tokens 9.4 -> 4.6 us, 3072 -> 768 at
+// 1:4 16.4 -> 9.4, 1024 -> 4096 at 4:8 16.3 -> 6.0.
 //
 // Two summation orders, so that a product is the same bytes whichever kernel of its route computes it:
 //   PACKED = false  the tiled kernel's (nm_spmm.hip): the sum starts from the bias; the dense instruction takes the
@@ -21,9 +22,7 @@
 namespace nm {
 namespace {
 
-constexpr int kRows = 32, kToks = 64, kSteps = 4;  // of a block: out-features, tokens, 64-wide steps per span
-constexpr int kXStep = kToks * 128;                // bytes of a step's activations
-constexpr int kXSpan = kSteps * kXStep;
+constexpr int kRows = 32, kSteps = 4;  // of a block: out-features, 64-wide steps per span; TOKS: its tokens, 64 or 16
 
 struct DirectArgs {
   const bf16_t* values;
@@ -36,8 +35,10 @@ struct DirectArgs {
   int32_t out_bf16, pieces;  // pieces: rows of Y are made of aligned runs of four outputs
 };
 
-template <int N, int M>
+template <int N, int M, int TOKS>
 struct DirectCfg {
+  static constexpr int X_STEP = TOKS * 128, X_SPAN = kSteps * X_STEP;  // bytes of the activations of a step, of a span
+  static constexpr int SETS = TOKS == 16 ? 4 : 2;      // spans in flight
   static constexpr bool SPARSE = N <= 2 && N < M;
   static constexpr int B = log2_of(M);
   static constexpr int VPC = 16 / M * N;               // kept values of 16 weights
@@ -46,33 +47,35 @@ struct DirectCfg {
   static constexpr int A_ROWB = SPARSE ? 64 : 128;     // bytes of a weight row per step
   static constexpr int A_STEP = kRows * A_ROWB;
   static constexpr int S_STEP = SPARSE ? 256 : 0;      // a selector word per pair of rows and lane group
-  static constexpr int SPAN = kXSpan + kSteps * (A_STEP + S_STEP);
-  static constexpr int LDS_BYTES = 2 * SPAN;
+  static constexpr int SPAN = X_SPAN + kSteps * (A_STEP + S_STEP);
+  static constexpr int LDS_BYTES = SETS * SPAN;
   static constexpr int VW = (VPC + 1) / 2;             // registers of a chunk's values
   static_assert(BITS <= 32 && LDS_BYTES <= 160 * 1024, "chunk fields and LDS budget");
 };
 
-// What a lane brings of a span: the packed form of two 16-weight chunks and eight 16-byte pieces of X.
-template <int N, int M>
+// What a lane brings of a span: the packed form of two 16-weight chunks and TOKS / 8 16-byte pieces of X.
+template <int N, int M, int TOKS>
 struct DirectLoads {
-  using C = DirectCfg<N, M>;
+  using C = DirectCfg<N, M, TOKS>;
   uint32_t v[2][C::VW], f[2][C::WORDS];
-  u32x4_t x[8];
+  u32x4_t x[TOKS / 8];
 };
 
-template <int N, int M, bool PACKED>
+template <int N, int M, int TOKS, bool PACKED>
 __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
-  using C = DirectCfg<N, M>;
+  using C = DirectCfg<N, M, TOKS>;
+  using Loads = DirectLoads<N, M, TOKS>;
+  constexpr int kXStep = C::X_STEP, kXSpan = C::X_SPAN;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r16 = lane & 15, kb = lane >> 4;
-  const int o0 = (int)blockIdx.x * kRows, t0 = (int)blockIdx.y * kToks;
+  const int o0 = (int)blockIdx.x * kRows, t0 = (int)blockIdx.y * TOKS;
   const int nk = (a.K + 63) >> 6, spans = (nk + kSteps - 1) / kSteps;  // a last step may be short (K % 16 == 0)
   const int64_t nf = (int64_t)a.K / M * N;
   const int64_t nw = (nf * C::B + 31) / 32;
 
-  // a lane's chunks are tid and tid + 256 of the span's 32 rows x 16, its pieces of X tid + 256 i of 64 rows x 32
-  auto fetch = [&](DirectLoads<N, M>& d, int span) {
+  // a lane's chunks are tid and tid + 256 of the span's 32 rows x 16, its pieces of X tid + 256 i of TOKS rows x 32
+  auto fetch = [&](Loads& d, int span) {
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int o = o0 + (tid >> 4) + 16 * u, c = span * 16 + (tid & 15);
@@ -105,14 +108,14 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
       }
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < TOKS / 8; ++i) {
       const int t = t0 + (tid >> 5) + 8 * i, k = span * 256 + (tid & 31) * 8;
       d.x[i] = u32x4_t{0, 0, 0, 0};
       if (t < a.T && k < a.K) d.x[i] = *reinterpret_cast<const u32x4_t*>(a.X + t * a.ldx + k);
     }
   };
   // the same into the span's LDS buffer, the weight decoded.  16-byte pieces of a row are XOR-swizzled with the row.
-  auto put = [&](const DirectLoads<N, M>& d, int span, unsigned char* buf) {
+  auto put = [&](const Loads& d, int span, unsigned char* buf) {
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int row = (tid >> 4) + 16 * u, step = (tid & 15) >> 2, c = tid & 3;
@@ -150,14 +153,16 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
       }
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < TOKS / 8; ++i) {
       const int row = (tid >> 5) + 8 * i, p = tid & 31;
       *reinterpret_cast<u32x4_t*>(buf + (p >> 3) * kXStep + row * 128 + (((p & 7) ^ (row & 7)) * 16)) = d.x[i];
     }
   };
 
   f32x4_t acc[2];
-  const int o_lane = o0 + kb * 4;  // a lane holds out-features o_lane + 16 i .. + 3 of token r16 of its wave's 16
+  // a lane holds out-features o_lane + 16 i .. + 3 of token r16 of its wave's 16; of 16 tokens, waves 0 and 1 hold one block of
+  // 16 out-features each (acc[0])
+  const int o_lane = o0 + kb * 4;
   auto bias_of = [&](int i) {
     f32x4_t b = f32x4_t{0.f, 0.f, 0.f, 0.f};
     if (a.bias != nullptr)
@@ -167,7 +172,7 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
     return b;
   };
 #pragma unroll
-  for (int i = 0; i < 2; ++i) acc[i] = PACKED ? f32x4_t{0.f, 0.f, 0.f, 0.f} : bias_of(i);
+  for (int i = 0; i < 2; ++i) acc[i] = PACKED ? f32x4_t{0.f, 0.f, 0.f, 0.f} : bias_of(TOKS == 16 ? wave : i);
 
   auto multiply = [&](const unsigned char* buf, int span) {
     const int steps = nk - span * kSteps < kSteps ? nk - span * kSteps : kSteps;
@@ -202,31 +207,89 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
     }
   };
 
-  // Two register sets and two LDS buffers.  A buffer is written again two spans later: between the two lies a barrier
-  // that every wave reaches only after it has multiplied the first.
-  DirectLoads<N, M> even, odd;
-  fetch(even, 0);
-  if (spans > 1) fetch(odd, 1);
-  for (int span = 0; span < spans; span += 2) {
-    put(even, span, smem);
-    if (span + 2 < spans) fetch(even, span + 2);
-    __syncthreads();
-    multiply(smem, span);
-    if (span + 1 < spans) {
-      put(odd, span + 1, smem + C::SPAN);
-      if (span + 3 < spans) fetch(odd, span + 3);
-      __syncthreads();
-      multiply(smem + C::SPAN, span + 1);
+  // The same for out-features 16 wave .. + 15 alone, in the same order.
+  auto multiply_block = [&](const unsigned char* buf, int span) {
+    const unsigned char* x = buf + r16 * 128;
+    const unsigned char* w = buf + kXSpan + (wave * 16 + r16) * C::A_ROWB;
+    const int xk = r16 & 7;
+    auto one = [&](int st) {
+      if constexpr (C::SPARSE) {
+        const u32x4_t a0 = *reinterpret_cast<const u32x4_t*>(w + st * C::A_STEP + (kb ^ ((r16 >> 1) & 3)) * 16);
+        const uint32_t sel = *reinterpret_cast<const uint32_t*>(buf + kXSpan + kSteps * C::A_STEP + st * C::S_STEP + r16 * 16 + kb * 4);
+        const u32x4_t lo = *reinterpret_cast<const u32x4_t*>(x + st * kXStep + ((kb ^ xk) * 16));
+        const u32x4_t hi = *reinterpret_cast<const u32x4_t*>(x + st * kXStep + (((4 + kb) ^ xk) * 16));
+        const u32x8_t b = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        acc[0] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(__builtin_bit_cast(bf16x8_t, a0), __builtin_bit_cast(bf16x16_t, b), acc[0],
+                                                           (int)(sel >> (16 * wave)), 0, 0);
+      } else {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int at = ((PACKED ? 2 * kb + h : 4 * h + kb) ^ xk) * 16;
+          const u32x4_t a0 = *reinterpret_cast<const u32x4_t*>(w + st * C::A_STEP + at);
+          const u32x4_t b = *reinterpret_cast<const u32x4_t*>(x + st * kXStep + at);
+          acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a0), __builtin_bit_cast(bf16x8_t, b), acc[0], 0, 0, 0);
+        }
+      }
+    };
+    const int steps = nk - span * kSteps;
+    if (steps >= kSteps) {
+#pragma unroll
+      for (int st = 0; st < kSteps; ++st) one(st);
+    } else {
+      for (int st = 0; st < steps; ++st) one(st);
     }
+  };
+
+  if constexpr (TOKS == 64) {
+    // Two register sets and two LDS buffers.  A buffer is written again two spans later: between the two lies a barrier
+    // that every wave reaches only after it has multiplied the first.
+    Loads even, odd;
+    fetch(even, 0);
+    if (spans > 1) fetch(odd, 1);
+    for (int span = 0; span < spans; span += 2) {
+      put(even, span, smem);
+      if (span + 2 < spans) fetch(even, span + 2);
+      __syncthreads();
+      multiply(smem, span);
+      if (span + 1 < spans) {
+        put(odd, span + 1, smem + C::SPAN);
+        if (span + 3 < spans) fetch(odd, span + 3);
+        __syncthreads();
+        multiply(smem + C::SPAN, span + 1);
+      }
+    }
+  } else {
+    // Four spans at a time, all their loads in flight together and one barrier for them.
+    Loads d[4];
+    auto fetch_four = [&](int first) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (first + u < spans) fetch(d[u], first + u);
+    };
+    fetch_four(0);
+    for (int first = 0; first < spans; first += 4) {
+      if (first) __syncthreads();  // the four before have been multiplied
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (first + u < spans) put(d[u], first + u, smem + u * C::SPAN);
+      fetch_four(first + 4);
+      __syncthreads();
+      if (wave < 2) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (first + u < spans) multiply_block(smem + u * C::SPAN, first + u);
+      }
+    }
+    if (wave >= 2) return;
   }
 
-  const int t = t0 + wave * 16 + r16;
+  const int t = t0 + (TOKS == 64 ? wave * 16 : 0) + r16;
   if (t >= a.T) return;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int o = o_lane + 16 * i;
+  for (int i = 0; i < TOKS / 32 + (TOKS == 16); ++i) {
+    const int o = o_lane + 16 * (TOKS == 16 ? wave : i);
     if (o >= a.O) continue;
-    f32x4_t y = PACKED ? acc[i] + bias_of(i) : acc[i];
+    f32x4_t y = PACKED ? acc[i] + bias_of(TOKS == 16 ? wave : i) : acc[i];
     if (a.K & 63) {  // a sum that ended as NaN again by the definition, as the ragged form of the tiled kernel has it
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -252,15 +315,23 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
   }
 }
 
-template <int N, int M, bool PACKED>
-hipError_t launch_level(const DirectArgs& g, hipStream_t s) {
-  using C = DirectCfg<N, M>;
-  auto kern = nm_direct_kernel<N, M, PACKED>;
+template <int N, int M, int TOKS, bool PACKED>
+hipError_t launch_tokens(const DirectArgs& g, hipStream_t s) {
+  using C = DirectCfg<N, M, TOKS>;
+  auto kern = nm_direct_kernel<N, M, TOKS, PACKED>;
   static PerDeviceOnce lds_limit;
   if (hipError_t e = raise_dynamic_lds_limit(kern, C::LDS_BYTES, lds_limit); e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)((g.O + kRows - 1) / kRows), (unsigned)((g.T + kToks - 1) / kToks)), dim3(256),
+  hipLaunchKernelGGL(kern, dim3((unsigned)((g.O + kRows - 1) / kRows), (unsigned)((g.T + TOKS - 1) / TOKS)), dim3(256),
                      C::LDS_BYTES, s, g);
   return hipGetLastError();
+}
+
+// Up to 16 tokens a block of 64 would bring, store and skip rows of zeros, and its two spans in flight make two round trips of
+// K = 768: 768 -> 1000 at 4:8 and 8 tokens 5.8 -> 4.6 us, 3072 -> 768 at 1:4 12.6 -> 9.4, 16 tokens x
+// 1024 -> 4096 at 4:8 7.0 -> 6.0, one token x 256 -> 128 at 2:8 3.1 -> 2.8 (in a graph).
+template <int N, int M, bool PACKED>
+hipError_t launch_level(const DirectArgs& g, hipStream_t s) {
+  return g.T <= 16 ? launch_tokens<N, M, 16, PACKED>(g, s) : launch_tokens<N, M, 64, PACKED>(g, s);
 }
 
 }  // namespace
