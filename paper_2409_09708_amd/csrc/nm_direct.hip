@@ -8,7 +8,7 @@
 // K / 64 steps.  So a block is small (768 out-features are 24 of them per 64 tokens), all four waves decode, the loads
 // of two spans of 256 reduction positions are in flight in registers while a third is multiplied, and a span has one
 // barrier; up to 16 tokens, four spans share one (launch_level).  Which products it takes is decided in nm_spmm.hip
-// (direct_takes).  In a graph, pre-pass and product before: 768 -> 1000 at 4:8 and 16 tokens 9.4 -> 4.6 us, 3072 -> 768 at
+// (direct_takes).  In a graph, pre-pass and product before: 768 -> 1000 at 4:8 and 8 tokens 9.4 -> 4.6 us, 3072 -> 768 at
 // 1:4 16.4 -> 9.4, 1024 -> 4096 at 4:8 16.3 -> 6.0.
 //
 // Two summation orders, so that a product is the same bytes whichever kernel of its route computes it:

@@ -362,7 +362,9 @@ nm_tgemm_kernel(const TGemmArgs a) {
 }
 
 // Sum of the partial tiles in split order, the mask of the step (bit k % 32 of word k / 32 of row o; NULL =
-// every weight receives its gradient) and the rounding.  One lane per accumulator of the tile kernel.
+// every weight receives its gradient) and the rounding.  One lane per accumulator of the tile kernel.  Bound by reading the
+// partial tiles (66 MB at 5.3 TB/s); six of a lane's loads are in flight at a time: 768 -> 3072 at 12608 tokens, 7 ranges,
+// 14.0 -> 12.4 us.
 __global__ void __launch_bounds__(256)
 grad_reduce_kernel(const float* __restrict__ partial, int splits, int n_tiles, int n_i_tiles, int64_t I, int64_t J,
                    const uint32_t* __restrict__ mask, void* __restrict__ out, int64_t ldo, int out_bf16) {
@@ -375,7 +377,15 @@ grad_reduce_kernel(const float* __restrict__ partial, int splits, int n_tiles, i
   const f32x4_t* src = reinterpret_cast<const f32x4_t*>(partial) + id;
   const size_t stride = (size_t)n_tiles * (C::MMA * C::NT);
   f32x4_t sum = src[0];
-  for (int s = 1; s < splits; ++s) sum += src[(size_t)s * stride];
+  int s = 1;
+  for (; s + 6 <= splits; s += 6) {
+    f32x4_t p[6];
+#pragma unroll
+    for (int u = 0; u < 6; ++u) p[u] = src[(size_t)(s + u) * stride];
+#pragma unroll
+    for (int u = 0; u < 6; ++u) sum += p[u];
+  }
+  for (; s < splits; ++s) sum += src[(size_t)s * stride];
   const int lane = tid & 63, wave = tid >> 6;
   const int wi = wave % C::WI, wj = wave / C::WI;
   const int i = q / C::JT, j = q % C::JT;
