@@ -7,7 +7,7 @@
 // round trip to memory, decoding 16 weights per lane and pass (a 2-byte LDS write per kept value), and a serial chain of
 // K / 64 steps.  So a block is small (768 out-features are 24 of them per 64 tokens), all four waves decode, the loads
 // of two spans of 256 reduction positions are in flight in registers while a third is multiplied, and a span has one
-// barrier; up to 16 tokens, four spans share one (launch_level).  Which products it takes is decided in nm_spmm.hip
+// barrier; up to 16 or 32 tokens, four spans share one (launch_level).  Which products it takes is decided in nm_spmm.hip
 // (direct_takes).  In a graph, pre-pass and product before: 768 -> 1000 at 4:8 and 8 tokens 9.4 -> 4.6 us, 3072 -> 768 at
 // 1:4 16.4 -> 9.4, 1024 -> 4096 at 4:8 16.3 -> 6.0.
 //
@@ -22,7 +22,7 @@
 namespace nm {
 namespace {
 
-constexpr int kRows = 32, kSteps = 4;  // of a block: out-features, 64-wide steps per span; TOKS: its tokens, 64 or 16
+constexpr int kRows = 32, kSteps = 4;  // of a block: out-features, 64-wide steps per span; TOKS: its tokens, 64, 32 or 16
 
 struct DirectArgs {
   const bf16_t* values;
@@ -38,7 +38,7 @@ struct DirectArgs {
 template <int N, int M, int TOKS>
 struct DirectCfg {
   static constexpr int X_STEP = TOKS * 128, X_SPAN = kSteps * X_STEP;  // bytes of the activations of a step, of a span
-  static constexpr int SETS = TOKS == 16 ? 4 : 2;      // spans in flight
+  static constexpr int SETS = TOKS == 64 ? 2 : 4;      // spans in flight
   static constexpr bool SPARSE = N <= 2 && N < M;
   static constexpr int B = log2_of(M);
   static constexpr int VPC = 16 / M * N;               // kept values of 16 weights
@@ -160,8 +160,8 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
   };
 
   f32x4_t acc[2];
-  // a lane holds out-features o_lane + 16 i .. + 3 of token r16 of its wave's 16; of 16 tokens, waves 0 and 1 hold one block of
-  // 16 out-features each (acc[0])
+  // a lane holds out-features o_lane + 16 i .. + 3 of token r16 of its wave's 16; up to 32 tokens a wave holds one
+  // block of 16 out-features (acc[0]), the lower one in the even waves
   const int o_lane = o0 + kb * 4;
   auto bias_of = [&](int i) {
     f32x4_t b = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -172,7 +172,7 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
     return b;
   };
 #pragma unroll
-  for (int i = 0; i < 2; ++i) acc[i] = PACKED ? f32x4_t{0.f, 0.f, 0.f, 0.f} : bias_of(TOKS == 16 ? wave : i);
+  for (int i = 0; i < 2; ++i) acc[i] = PACKED ? f32x4_t{0.f, 0.f, 0.f, 0.f} : bias_of(TOKS == 64 ? i : wave & 1);
 
   auto multiply = [&](const unsigned char* buf, int span) {
     const int steps = nk - span * kSteps < kSteps ? nk - span * kSteps : kSteps;
@@ -207,10 +207,10 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
     }
   };
 
-  // The same for out-features 16 wave .. + 15 alone, in the same order.
+  // The same for one block of out-features, in the same order.
   auto multiply_block = [&](const unsigned char* buf, int span) {
-    const unsigned char* x = buf + r16 * 128;
-    const unsigned char* w = buf + kXSpan + (wave * 16 + r16) * C::A_ROWB;
+    const unsigned char* x = buf + ((wave >> 1) * 16 + r16) * 128;
+    const unsigned char* w = buf + kXSpan + ((wave & 1) * 16 + r16) * C::A_ROWB;
     const int xk = r16 & 7;
     auto one = [&](int st) {
       if constexpr (C::SPARSE) {
@@ -220,7 +220,7 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
         const u32x4_t hi = *reinterpret_cast<const u32x4_t*>(x + st * kXStep + (((4 + kb) ^ xk) * 16));
         const u32x8_t b = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
         acc[0] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(__builtin_bit_cast(bf16x8_t, a0), __builtin_bit_cast(bf16x16_t, b), acc[0],
-                                                           (int)(sel >> (16 * wave)), 0, 0);
+                                                           (int)(sel >> (16 * (wave & 1))), 0, 0);
       } else {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -261,6 +261,7 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
   } else {
     // Four spans at a time, all their loads in flight together and one barrier for them.
     Loads d[4];
+    const bool stored = (wave >> 1) * 16 < TOKS && t0 + (wave >> 1) * 16 < a.T;  // some token of this wave's 16 is
     auto fetch_four = [&](int first) {
 #pragma unroll
       for (int u = 0; u < 4; ++u)
@@ -274,22 +275,22 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
         if (first + u < spans) put(d[u], first + u, smem + u * C::SPAN);
       fetch_four(first + 4);
       __syncthreads();
-      if (wave < 2) {
+      if (stored) {
 #pragma unroll
         for (int u = 0; u < 4; ++u)
           if (first + u < spans) multiply_block(smem + u * C::SPAN, first + u);
       }
     }
-    if (wave >= 2) return;
+    if (!stored) return;
   }
 
-  const int t = t0 + (TOKS == 64 ? wave * 16 : 0) + r16;
+  const int t = t0 + (TOKS == 64 ? wave : wave >> 1) * 16 + r16;
   if (t >= a.T) return;
 #pragma unroll
-  for (int i = 0; i < TOKS / 32 + (TOKS == 16); ++i) {
-    const int o = o_lane + 16 * (TOKS == 16 ? wave : i);
+  for (int i = 0; i < (TOKS == 64 ? 2 : 1); ++i) {
+    const int o = o_lane + 16 * (TOKS == 64 ? i : wave & 1);
     if (o >= a.O) continue;
-    f32x4_t y = PACKED ? acc[i] + bias_of(TOKS == 16 ? wave : i) : acc[i];
+    f32x4_t y = PACKED ? acc[i] + bias_of(TOKS == 64 ? i : wave & 1) : acc[i];
     if (a.K & 63) {  // a sum that ended as NaN again by the definition, as the ragged form of the tiled kernel has it
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -328,10 +329,16 @@ hipError_t launch_tokens(const DirectArgs& g, hipStream_t s) {
 
 // Up to 16 tokens a block of 64 would bring, store and skip rows of zeros, and its two spans in flight make two round trips of
 // K = 768: 768 -> 1000 at 4:8 and 8 tokens 5.8 -> 4.6 us, 3072 -> 768 at 1:4 12.6 -> 9.4, 16 tokens x
-// 1024 -> 4096 at 4:8 7.0 -> 6.0, one token x 256 -> 128 at 2:8 3.1 -> 2.8 (in a graph).
+// 1024 -> 4096 at 4:8 7.0 -> 6.0, one token x 256 -> 128 at 2:8 3.1 -> 2.8 (in a graph).  Up to 32 the same holds for the dense
+// form (24 tokens x 768 -> 1000 at 4:8 5.8 -> 5.2, 20 x 2048 -> 2048 at 4:16 10.3 -> 8.8); the 2:4 form, with half the matrix
+// instructions and LDS reads per step, gains nothing on average (32 x 768 -> 768 at 1:4 5.0 and 4.9, x 768 -> 3072 at 1:16 4.7
+// and 4.8).
 template <int N, int M, bool PACKED>
 hipError_t launch_level(const DirectArgs& g, hipStream_t s) {
-  return g.T <= 16 ? launch_tokens<N, M, 16, PACKED>(g, s) : launch_tokens<N, M, 64, PACKED>(g, s);
+  if (g.T <= 16) return launch_tokens<N, M, 16, PACKED>(g, s);
+  if constexpr (N > 2)
+    if (g.T <= 32) return launch_tokens<N, M, 32, PACKED>(g, s);
+  return launch_tokens<N, M, 64, PACKED>(g, s);
 }
 
 }  // namespace

@@ -1,4 +1,4 @@
-"""Up to 16 tokens the one-launch kernel takes four spans of 256 reduction positions at a time: reductions that end at, before
+"""Up to 16 or 32 tokens the one-launch kernel takes four spans of 256 reduction positions at a time: reductions that end at, before
 and behind four spans, tokens at the edges of the tile, both summation orders; the bytes of a prepared and of a batched call."""
 import numpy as np
 import pytest
@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("N,M", [(1, 4), (3, 4), (2, 8), (4, 8), (1, 16), (4, 16)])
 @pytest.mark.parametrize("T,K,O", [(1, 64, 36), (8, 768, 1000), (15, 1024, 33), (16, 1088, 64), (16, 2304, 20), (9, 1040, 31),
-                                   (17, 1024, 32)])
+                                   (17, 1024, 32), (31, 1088, 100), (32, 2304, 33), (33, 320, 72)])
 def test_few_tokens(T, K, O, N, M):
     rng = np.random.default_rng(1000 * T + K + N * M)
     X, W = wl.draw_activations(rng, T, K), wl.draw_weights(rng, O, K)
