@@ -4,8 +4,8 @@
 // handed to the C ABI here.  Anything else is declined (NotImplemented), and the Python function goes on with it: it
 // knows the other forms that are accepted and names what is wrong with the ones that are not.  Nothing is kept
 // between calls.
-// Measured per call: the projection above 7.0 -> 3.8 us; 768 -> 1000 at 4:8 on 8 tokens, plain, 8.2 -> 6.2; the twelve
-// calls and sixteen allocations that compress a block by scores and expand it 96 -> 64.
+// Measured per call: the projection above 7.2 -> 4.0 us; 768 -> 1000 at 4:8 on 8 tokens, plain, 8.2 -> 6.2 (5.0 with a kernel
+// that has become faster since); the twelve calls and sixteen allocations that compress a block by scores and expand it 96 -> 64.
 #include <Python.h>
 
 #include <ATen/PythonTorchFunctionTLS.h>
@@ -100,8 +100,12 @@ bool stream_of(PyObject* obj, void** out) {
 // Tracing modes and the like see every tensor operation: they get the Python functions.
 bool observed() { return at::impl::torch_function_mode_enabled() || c10::impl::TorchDispatchModeTLS::any_modes_set(); }
 
+template <class T>
+T* pointer(const at::Tensor* t) { return t ? static_cast<T*>(t->data_ptr()) : nullptr; }
+
+// Other threads run meanwhile: `call` gets pointers that were taken before (a tensor may refuse its own, by an exception).
 template <class F>
-int32_t released(F&& call) {  // other threads run meanwhile
+int32_t released(F&& call) noexcept {
   int32_t st;
   Py_BEGIN_ALLOW_THREADS;
   st = call();
@@ -133,10 +137,10 @@ PyObject* prune(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return declined();
   if (!stream_of(a[4], &s)) return declined();
   at::Tensor mask = fresh(*W, w.rows, (w.cols + 31) / 32, at::kInt);
-  const int32_t st = released([&] {
-    return lib.prune(static_cast<const uint16_t*>(W->data_ptr()), w.rows, w.cols, w.ld, N, M, static_cast<uint32_t*>(mask.data_ptr()),
-                     Wm ? static_cast<uint16_t*>(Wm->data_ptr()) : nullptr, s);
-  });
+  const uint16_t* wp = pointer<uint16_t>(W);
+  uint32_t* mp = pointer<uint32_t>(&mask);
+  uint16_t* wmp = pointer<uint16_t>(Wm);
+  const int32_t st = released([&] { return lib.prune(wp, w.rows, w.cols, w.ld, N, M, mp, wmp, s); });
   return result(st, THPVariable_Wrap(std::move(mask)));
   END_HANDLE_TH_ERRORS
 }
@@ -152,10 +156,9 @@ PyObject* prune_scored(PyObject*, PyObject* const* a, Py_ssize_t n) {
       !stream_of(a[3], &s))
     return declined();
   at::Tensor mask = fresh(*score, m.rows, (m.cols + 31) / 32, at::kInt);
-  const int32_t st = released([&] {
-    return lib.prune_scored(static_cast<const float*>(score->data_ptr()), m.rows, m.cols, m.ld, N, M,
-                            static_cast<uint32_t*>(mask.data_ptr()), s);
-  });
+  const float* sp = pointer<float>(score);
+  uint32_t* mp = pointer<uint32_t>(&mask);
+  const int32_t st = released([&] { return lib.prune_scored(sp, m.rows, m.cols, m.ld, N, M, mp, s); });
   return result(st, THPVariable_Wrap(std::move(mask)));
   END_HANDLE_TH_ERRORS
 }
@@ -175,11 +178,11 @@ PyObject* pack(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (vb == 0 || !stream_of(a[4], &s)) return declined();
   at::Tensor values = fresh(*W, w.rows, (int64_t)vb / (2 * w.rows), at::kBFloat16);
   at::Tensor indices = fresh(*W, w.rows, (int64_t)lib.index_bytes(w.rows, w.cols, N, M) / (4 * w.rows), at::kInt);
-  const int32_t st = released([&] {
-    return lib.pack(static_cast<const uint16_t*>(W->data_ptr()), w.rows, w.cols, w.ld, N, M,
-                    mask ? static_cast<const uint32_t*>(mask->data_ptr()) : nullptr, static_cast<uint16_t*>(values.data_ptr()),
-                    static_cast<uint32_t*>(indices.data_ptr()), s);
-  });
+  const uint16_t* wp = pointer<uint16_t>(W);
+  const uint32_t* mp = pointer<uint32_t>(mask);
+  uint16_t* vp = pointer<uint16_t>(&values);
+  uint32_t* ip = pointer<uint32_t>(&indices);
+  const int32_t st = released([&] { return lib.pack(wp, w.rows, w.cols, w.ld, N, M, mp, vp, ip, s); });
   return result(st, Py_BuildValue("(NN)", THPVariable_Wrap(std::move(values)), THPVariable_Wrap(std::move(indices))));
   END_HANDLE_TH_ERRORS
 }
@@ -196,10 +199,10 @@ PyObject* unpack(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return declined();
   const int64_t O = values->size(0);
   at::Tensor Wd = fresh(*values, O, K, at::kBFloat16);
-  const int32_t st = released([&] {
-    return lib.unpack(static_cast<const uint16_t*>(values->data_ptr()), static_cast<const uint32_t*>(indices->data_ptr()), O, K, N, M,
-                      static_cast<uint16_t*>(Wd.data_ptr()), K, s);
-  });
+  const uint16_t* vp = pointer<uint16_t>(values);
+  const uint32_t* ip = pointer<uint32_t>(indices);
+  uint16_t* wp = pointer<uint16_t>(&Wd);
+  const int32_t st = released([&] { return lib.unpack(vp, ip, O, K, N, M, wp, K, s); });
   return result(st, THPVariable_Wrap(std::move(Wd)));
   END_HANDLE_TH_ERRORS
 }
@@ -270,9 +273,9 @@ PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     Py_INCREF(a[8]);
     value = a[8];
   }
-  const uint16_t *v = static_cast<const uint16_t*>(values->data_ptr()), *xp = static_cast<const uint16_t*>(X->data_ptr());
-  const uint32_t* ix = static_cast<const uint32_t*>(indices->data_ptr());
-  const float* b = bias ? static_cast<const float*>(bias->data_ptr()) : nullptr;
+  const uint16_t *v = pointer<uint16_t>(values), *xp = pointer<uint16_t>(X);
+  const uint32_t* ix = pointer<uint32_t>(indices);
+  const float* b = pointer<float>(bias);
   void* yp = out->data_ptr();
   const int32_t st = released([&] {
     if (how == 3) return lib.forward_static(v, ix, O, K, N, M, xp, T, x.ld, b, yp, y.ld, code, s);
