@@ -31,18 +31,18 @@ def hipcc() -> str:
     return exe
 
 
-def build_calls() -> None:
+def compile_calls(source: str, path: str) -> None:
     """Compile the host-only extension that reads torch tensors (against the installed torch)."""
     from torch.utils import cpp_extension
     includes = [os.path.join(ROOT, "include"), *cpp_extension.include_paths(), "/opt/rocm/include", sysconfig.get_paths()["include"]]
-    tmp = CALLS_PATH + ".tmp"
+    tmp = path + ".tmp"
     cmd = ["g++", "-O2", "-std=c++20", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           *[f"-I{p}" for p in includes], os.path.join(CSRC, "nm_calls.cpp"), "-o", tmp,
+           *[f"-I{p}" for p in includes], source, "-o", tmp,
            *[f"-L{p}" for p in cpp_extension.library_paths()], "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10", "-lc10_hip"]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
-        raise RuntimeError(f"compiling nm_calls.cpp failed:\n{res.stderr}")
-    os.replace(tmp, CALLS_PATH)
+        raise RuntimeError(f"compiling {source} failed:\n{res.stderr}")
+    os.replace(tmp, path)
 
 
 def build_library(verbose: bool = False) -> str:
@@ -65,7 +65,7 @@ def build_library(verbose: bool = False) -> str:
         return obj
 
     with ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as pool:
-        calls = pool.submit(build_calls)
+        calls = pool.submit(compile_calls, os.path.join(CSRC, "nm_calls.cpp"), CALLS_PATH)
         objs = list(pool.map(compile_one, SOURCES))
         calls.result()
     tmp = LIB_PATH + ".tmp"

@@ -104,8 +104,9 @@ template <class T>
 T* pointer(const at::Tensor* t) { return t ? static_cast<T*>(t->data_ptr()) : nullptr; }
 
 // Other threads run meanwhile: `call` gets pointers that were taken before (a tensor may refuse its own, by an exception).
+// Not noexcept: where the interpreter has ended meanwhile, taking its lock again ends this thread by unwinding its stack.
 template <class F>
-int32_t released(F&& call) noexcept {
+int32_t released(F&& call) {
   int32_t st;
   Py_BEGIN_ALLOW_THREADS;
   st = call();
