@@ -19,6 +19,9 @@
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/utils/object_ptr.h>
 
+#include <exception>
+#include <optional>
+
 #include "nm_sparse.h"
 
 namespace {
@@ -103,15 +106,23 @@ bool observed() { return at::impl::torch_function_mode_enabled() || c10::impl::T
 template <class T>
 T* pointer(const at::Tensor* t) { return t ? static_cast<T*>(t->data_ptr()) : nullptr; }
 
-// Other threads run meanwhile: `call` gets pointers that were taken before (a tensor may refuse its own, by an exception).
-// Not noexcept: where the interpreter has ended meanwhile, taking its lock again ends this thread by unwinding its stack.
+// f without the interpreter lock: other threads run meanwhile, and a stream's host function that needs it can end.  For the
+// library's calls, whose pointers are taken before, and for allocations, which may free cached memory and wait for the device.
+// An exception of f goes on when the lock is held again.  Not noexcept: where the interpreter has ended meanwhile, taking its
+// lock again ends this thread by unwinding its stack.
 template <class F>
-int32_t released(F&& call) {
-  int32_t st;
-  Py_BEGIN_ALLOW_THREADS;
-  st = call();
-  Py_END_ALLOW_THREADS;
-  return st;
+auto unlocked(F&& f) {
+  std::optional<decltype(f())> r;
+  std::exception_ptr failed;
+  PyThreadState* self = PyEval_SaveThread();
+  try {
+    r.emplace(f());
+  } catch (...) {
+    failed = std::current_exception();
+  }
+  PyEval_RestoreThread(self);
+  if (failed) std::rethrow_exception(failed);
+  return *std::move(r);
 }
 PyObject* result(int32_t st, PyObject* value) {  // steals value
   if (st == NM_OK) return value;
@@ -122,7 +133,7 @@ PyObject* result(int32_t st, PyObject* value) {  // steals value
 }
 
 at::Tensor fresh(const at::Tensor& like, int64_t rows, int64_t cols, at::ScalarType type) {
-  return at::empty({rows, cols}, at::TensorOptions().dtype(type).device(like.device()));
+  return unlocked([&] { return at::empty({rows, cols}, at::TensorOptions().dtype(type).device(like.device())); });
 }
 
 // prune(W, N, M, W_masked, stream)
@@ -141,7 +152,7 @@ PyObject* prune(PyObject*, PyObject* const* a, Py_ssize_t n) {
   const uint16_t* wp = pointer<uint16_t>(W);
   uint32_t* mp = pointer<uint32_t>(&mask);
   uint16_t* wmp = pointer<uint16_t>(Wm);
-  const int32_t st = released([&] { return lib.prune(wp, w.rows, w.cols, w.ld, N, M, mp, wmp, s); });
+  const int32_t st = unlocked([&] { return lib.prune(wp, w.rows, w.cols, w.ld, N, M, mp, wmp, s); });
   return result(st, THPVariable_Wrap(std::move(mask)));
   END_HANDLE_TH_ERRORS
 }
@@ -159,7 +170,7 @@ PyObject* prune_scored(PyObject*, PyObject* const* a, Py_ssize_t n) {
   at::Tensor mask = fresh(*score, m.rows, (m.cols + 31) / 32, at::kInt);
   const float* sp = pointer<float>(score);
   uint32_t* mp = pointer<uint32_t>(&mask);
-  const int32_t st = released([&] { return lib.prune_scored(sp, m.rows, m.cols, m.ld, N, M, mp, s); });
+  const int32_t st = unlocked([&] { return lib.prune_scored(sp, m.rows, m.cols, m.ld, N, M, mp, s); });
   return result(st, THPVariable_Wrap(std::move(mask)));
   END_HANDLE_TH_ERRORS
 }
@@ -183,7 +194,7 @@ PyObject* pack(PyObject*, PyObject* const* a, Py_ssize_t n) {
   const uint32_t* mp = pointer<uint32_t>(mask);
   uint16_t* vp = pointer<uint16_t>(&values);
   uint32_t* ip = pointer<uint32_t>(&indices);
-  const int32_t st = released([&] { return lib.pack(wp, w.rows, w.cols, w.ld, N, M, mp, vp, ip, s); });
+  const int32_t st = unlocked([&] { return lib.pack(wp, w.rows, w.cols, w.ld, N, M, mp, vp, ip, s); });
   return result(st, Py_BuildValue("(NN)", THPVariable_Wrap(std::move(values)), THPVariable_Wrap(std::move(indices))));
   END_HANDLE_TH_ERRORS
 }
@@ -203,7 +214,7 @@ PyObject* unpack(PyObject*, PyObject* const* a, Py_ssize_t n) {
   const uint16_t* vp = pointer<uint16_t>(values);
   const uint32_t* ip = pointer<uint32_t>(indices);
   uint16_t* wp = pointer<uint16_t>(&Wd);
-  const int32_t st = released([&] { return lib.unpack(vp, ip, O, K, N, M, wp, K, s); });
+  const int32_t st = unlocked([&] { return lib.unpack(vp, ip, O, K, N, M, wp, K, s); });
   return result(st, THPVariable_Wrap(std::move(Wd)));
   END_HANDLE_TH_ERRORS
 }
@@ -264,26 +275,25 @@ PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
       ws_bytes = ws->nbytes();
     }
   }
-  THPObjectPtr value;
   if (out == nullptr) {
     made = fresh(*X, T, O, code == NM_OUT_F32 ? at::kFloat : at::kBFloat16);
     out = &made;
     y.ld = O;
-    value = THPVariable_Wrap(made);
-  } else {
-    Py_INCREF(a[8]);
-    value = a[8];
   }
   const uint16_t *v = pointer<uint16_t>(values), *xp = pointer<uint16_t>(X);
   const uint32_t* ix = pointer<uint32_t>(indices);
   const float* b = pointer<float>(bias);
   void* yp = out->data_ptr();
-  const int32_t st = released([&] {
+  const int32_t st = unlocked([&] {
     if (how == 3) return lib.forward_static(v, ix, O, K, N, M, xp, T, x.ld, b, yp, y.ld, code, s);
     if (how == 1) return lib.forward_prepared(v, ix, O, K, N, M, xp, T, x.ld, b, yp, y.ld, code, ws_ptr, ws_bytes, s);
     return lib.forward(v, ix, O, K, N, M, xp, T, x.ld, b, yp, y.ld, code, ws_ptr, ws_bytes, s);
   });
-  return result(st, value.release());
+  if (!made.defined()) {
+    Py_INCREF(a[8]);
+    return result(st, a[8]);
+  }
+  return result(st, THPVariable_Wrap(std::move(made)));
   END_HANDLE_TH_ERRORS
 }
 

@@ -1,5 +1,5 @@
-"""The interpreter lock in the native marshalling: it is not held while the library runs, and a thread that cannot have it back
-because the interpreter ends goes quietly.  csrc/nm_calls.cpp is compiled for CPU tensors (the device's name exchanged in
+"""The interpreter lock in the native marshalling: it is not held while the library runs or memory is allocated, and a thread that
+cannot have it back because the interpreter ends goes quietly.  csrc/nm_calls.cpp is compiled for CPU tensors (the device's name exchanged in
 its text) beside a library whose entries only look at the lock; each test is a process of its own."""
 import os
 import subprocess
@@ -13,6 +13,8 @@ from paper_2409_09708_amd import build as nm_build
 LIBRARY = r"""
 #include <unistd.h>
 #include <atomic>
+#include <stdexcept>
+#include <c10/core/CPUAllocator.h>
 static std::atomic<int> entered{0}, held{0};
 extern "C" int look_pause = 0;  // microseconds
 extern "C" int looks() { return entered; }
@@ -23,6 +25,16 @@ extern "C" int look() {
   if (look_pause) usleep(look_pause);
   return 0;
 }
+struct Allocator final : c10::Allocator {  // of every tensor, those that Python makes among them
+  c10::Allocator* plain = c10::GetCPUAllocator();
+  c10::DataPtr allocate(size_t n) override {
+    look();
+    if (n > 1000000) throw std::runtime_error("no memory of that size");
+    return plain->allocate(n);
+  }
+  void copy_data(void* to, const void* from, size_t n) const override { plain->copy_data(to, from, n); }
+};
+extern "C" void look_at_allocations() { c10::SetCPUAllocator(new Allocator, 255); }
 extern "C" size_t kilobyte() { return 1024; }
 """
 
@@ -45,6 +57,7 @@ class Stream:
     cuda_stream = 0
 s = Stream()
 W, words = torch.zeros(8, 64, dtype=torch.bfloat16), torch.zeros(8, 4, dtype=torch.int32)
+score = W.float()
 def prune():
     return calls.prune(W, 2, 4, None, s)
 def forward():
@@ -83,3 +96,21 @@ while not own.looks():
     time.sleep(0.01)
 """)
     assert done.returncode == 0 and "ended" in done.stdout, (done.returncode, done.stderr[-500:])
+
+
+def test_allocations_and_library_calls_release_the_lock(cpu_edition):
+    done = run(cpu_edition, r"""
+own.look_at_allocations()
+for call, looks in ((prune, 2), (lambda: calls.prune_scored(score, 2, 4, s), 2), (lambda: calls.pack(W, 2, 4, None, s), 3),
+                    (lambda: calls.unpack(W, words, 128, 2, 4, s), 2), (forward, 3)):
+    before = own.looks()
+    assert call() is not NotImplemented
+    assert (own.looks() - before, own.looks_held()) == (looks, 0), (own.looks() - before, own.looks_held())
+try:  # a refused allocation arrives as an exception, and the thread has the lock again
+    calls.unpack(W, words, 1 << 30, 2, 4, s)
+except RuntimeError as e:
+    assert "no memory of that size" in str(e)
+    print("raised")
+prune()
+""")
+    assert done.returncode == 0 and "raised" in done.stdout, (done.returncode, done.stderr[-500:])
