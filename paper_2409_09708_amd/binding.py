@@ -12,6 +12,7 @@ import importlib.machinery
 import importlib.util
 import os
 import struct
+import sysconfig
 from ctypes import c_char_p, c_int32, c_int64, c_size_t, c_void_p
 from typing import List, Optional, Sequence, Tuple
 
@@ -83,6 +84,12 @@ class ForwardDesc(ctypes.Structure):
 
 def library_path() -> str:
     return os.path.join(_PKG_DIR, "libnm_sparse.so")
+
+
+def calls_path() -> str:
+    """The native marshalling reads torch's C++ objects as they lie, so it serves the Python and the torch that it was built
+    against, and its file name says which."""
+    return os.path.join(_PKG_DIR, f"_nm_calls.{sysconfig.get_config_var('SOABI')}.torch-{_torch().__version__}.so")
 
 
 def load_library() -> ctypes.CDLL:
@@ -208,10 +215,9 @@ def _native():
     """The native marshalling, bound to the loaded library.  As with the library there is no fallback for a missing build."""
     global _CALLS
     lib = load_library()
-    path = os.path.join(_PKG_DIR, "_nm_calls.so")
+    path = calls_path()
     if not os.path.exists(path):
         raise RuntimeError(f"{path} is missing: build it with `python -m paper_2409_09708_amd.build`")
-    _torch()
     loader = importlib.machinery.ExtensionFileLoader("_nm_calls", path)
     calls = importlib.util.module_from_spec(importlib.util.spec_from_loader("_nm_calls", loader))
     loader.exec_module(calls)

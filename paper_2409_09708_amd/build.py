@@ -8,11 +8,12 @@ import sys
 import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
+from .binding import calls_path
+
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libnm_sparse.so")
-CALLS_PATH = os.path.join(PKG_DIR, "_nm_calls.so")
 SOURCES = ("nm_api.hip", "nm_direct.hip", "nm_fewtok.hip", "nm_grad.hip", "nm_int8.hip", "nm_pack.hip", "nm_probe.hip", "nm_rank.hip", "nm_search.hip", "nm_spmm.hip")
 
 HIPCC_FLAGS = [
@@ -65,7 +66,7 @@ def build_library(verbose: bool = False) -> str:
         return obj
 
     with ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as pool:
-        calls = pool.submit(compile_calls, os.path.join(CSRC, "nm_calls.cpp"), CALLS_PATH)
+        calls = pool.submit(compile_calls, os.path.join(CSRC, "nm_calls.cpp"), calls_path())
         objs = list(pool.map(compile_one, SOURCES))
         calls.result()
     tmp = LIB_PATH + ".tmp"
