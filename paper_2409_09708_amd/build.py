@@ -47,7 +47,8 @@ def compile_calls(source: str, path: str) -> None:
 
 
 def build_library(verbose: bool = False) -> str:
-    """Compile every translation unit and link the shared library, and the extension beside it; returns the library's path."""
+    """Compile every translation unit and link the shared library, and the extension beside it; returns the library's path.
+    The library knows nothing of torch: it is in place also where the extension, reported last, could not be built."""
     obj_dir = os.path.join(PKG_DIR, "_build")
     os.makedirs(obj_dir, exist_ok=True)
     cc = hipcc()
@@ -66,15 +67,15 @@ def build_library(verbose: bool = False) -> str:
         return obj
 
     with ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as pool:
-        calls = pool.submit(compile_calls, os.path.join(CSRC, "nm_calls.cpp"), calls_path())
+        calls = pool.submit(lambda: compile_calls(os.path.join(CSRC, "nm_calls.cpp"), calls_path()))
         objs = list(pool.map(compile_one, SOURCES))
-        calls.result()
     tmp = LIB_PATH + ".tmp"
     cmd = [cc, "--offload-arch=gfx950", "-shared", "-fPIC", "-fno-gpu-rdc", *objs, "-o", tmp]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError(f"link failed:\n{res.stderr}")
     os.replace(tmp, LIB_PATH)
+    calls.result()
     return LIB_PATH
 
 
