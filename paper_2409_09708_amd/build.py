@@ -35,7 +35,8 @@ def hipcc() -> str:
 def compile_calls(source: str, path: str) -> None:
     """Compile the host-only extension that reads torch tensors (against the installed torch)."""
     from torch.utils import cpp_extension
-    includes = [os.path.join(ROOT, "include"), *cpp_extension.include_paths(), "/opt/rocm/include", sysconfig.get_paths()["include"]]
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc())))
+    includes = [os.path.join(ROOT, "include"), *cpp_extension.include_paths(), os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]
     tmp = path + ".tmp"
     cmd = ["g++", "-O2", "-std=c++20", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            *[f"-I{p}" for p in includes], source, "-o", tmp,

@@ -33,3 +33,12 @@ def test_library_is_linked_where_the_marshalling_cannot_be_built(monkeypatch, tm
     with pytest.raises(RuntimeError, match="no torch headers"):
         nm_build.build_library()
     assert (tmp_path / "lib.so").exists()
+
+
+def test_rocm_headers_are_those_of_the_compiler_found(monkeypatch, tmp_path):
+    seen = []
+    monkeypatch.setattr(nm_build, "hipcc", lambda: str(tmp_path / "rocm" / "bin" / "hipcc"))
+    monkeypatch.setattr(nm_build.subprocess, "run", lambda cmd, **kw: seen.extend(cmd) or subprocess.CompletedProcess(cmd, 1, "", ""))
+    with pytest.raises(RuntimeError):
+        nm_build.compile_calls("nm_calls.cpp", str(tmp_path / "calls.so"))
+    assert f"-I{tmp_path}/rocm/include" in seen and "-I/opt/rocm/include" not in seen
