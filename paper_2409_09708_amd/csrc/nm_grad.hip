@@ -363,8 +363,11 @@ nm_tgemm_kernel(const TGemmArgs a) {
 
 // Sum of the partial tiles in split order, the mask of the step (bit k % 32 of word k / 32 of row o; NULL =
 // every weight receives its gradient) and the rounding.  One lane per accumulator of the tile kernel.  Bound by reading the
-// partial tiles (66 MB at 5.3 TB/s); six of a lane's loads are in flight at a time: 768 -> 3072 at 12608 tokens, 7 ranges,
-// 14.0 -> 12.4 us.
+// partial tiles (66 MB at 5.3 TB/s).  64 tiles are one round of the chip's wavefront slots.  Where the last round has at most 16 of
+// them, its few wavefronts do not hide a load and a lane reads six ranges at a time (16 tiles in 29 ranges 16.8 -> 10.5 us, 2 in
+// 64 16.8 -> 6.6, 72 in 7, which is 768 -> 3072 at 12608 tokens, 12.8 -> 12.0).  A fuller round is bound by memory, and ranges
+// read at once disturb each other there (32 in 15 10.8 one by one, 12.0; 35 in 14 10.8 and 12.0, 91 in 11 20.7 and 21.3).
+// Fewer than seven ranges are read one by one in any case.
 __global__ void __launch_bounds__(256)
 grad_reduce_kernel(const float* __restrict__ partial, int splits, int n_tiles, int n_i_tiles, int64_t I, int64_t J,
                    const uint32_t* __restrict__ mask, void* __restrict__ out, int64_t ldo, int out_bf16) {
@@ -378,12 +381,14 @@ grad_reduce_kernel(const float* __restrict__ partial, int splits, int n_tiles, i
   const size_t stride = (size_t)n_tiles * (C::MMA * C::NT);
   f32x4_t sum = src[0];
   int s = 1;
-  for (; s + 6 <= splits; s += 6) {
-    f32x4_t p[6];
+  if (((n_tiles - 1) & 63) < 16) {
+    for (; s + 6 <= splits; s += 6) {
+      f32x4_t p[6];
 #pragma unroll
-    for (int u = 0; u < 6; ++u) p[u] = src[(size_t)(s + u) * stride];
+      for (int u = 0; u < 6; ++u) p[u] = src[(size_t)(s + u) * stride];
 #pragma unroll
-    for (int u = 0; u < 6; ++u) sum += p[u];
+      for (int u = 0; u < 6; ++u) sum += p[u];
+    }
   }
   for (; s < splits; ++s) sum += src[(size_t)s * stride];
   const int lane = tid & 63, wave = tid >> 6;
