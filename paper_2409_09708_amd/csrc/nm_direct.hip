@@ -332,12 +332,23 @@ hipError_t launch_tokens(const DirectArgs& g, hipStream_t s) {
 // 1024 -> 4096 at 4:8 7.0 -> 6.0, one token x 256 -> 128 at 2:8 3.1 -> 2.8 (in a graph).  Up to 32 the same holds for the dense
 // form (24 tokens x 768 -> 1000 at 4:8 5.8 -> 5.2, 20 x 2048 -> 2048 at 4:16 10.3 -> 8.8); the 2:4 form, with half the matrix
 // instructions and LDS reads per step, gains nothing on average (32 x 768 -> 768 at 1:4 5.0 and 4.9, x 768 -> 3072 at 1:16 4.7
-// and 4.8).
+// and 4.8).  In the dense form this holds while round trips bound the launch.  A large weight is bound by what its blocks pull in and
+// decode, and there the longer run of a block of 64 is the faster one, the earlier the more tokens there are.  The limits are in
+// kept values, where the two cross at 4:8, 4:16, 3:8 and 3:4: 32 tokens x 2048 -> 4096 at 4:8 (4 M) 12.1 us in blocks of 64 and 11.2,
+// x 3072 -> 16384 (25 M) 31.6 and 35.2; 28 tokens x 3072 -> 6144 (9 M) 16.7 and 16.0, x 3072 -> 16384 31.4 and 32.4; up to 24 tokens a
+// weight beyond the memory-side cache (24 tokens x 8192 -> 32768, 134 M, 150 and 177).  At 3:4 the two waves that multiply in a block
+// of 16 hold up a large weight (16 tokens x 3072 -> 8192, 19 M: 19.0 in blocks of 64, 20.8 in blocks of 16, 18.5 in blocks of 32).
 template <int N, int M, bool PACKED>
 hipError_t launch_level(const DirectArgs& g, hipStream_t s) {
-  if (g.T <= 16) return launch_tokens<N, M, 16, PACKED>(g, s);
-  if constexpr (N > 2)
-    if (g.T <= 32) return launch_tokens<N, M, 32, PACKED>(g, s);
+  if constexpr (N <= 2) {
+    if (g.T <= 16) return launch_tokens<N, M, 16, PACKED>(g, s);
+  } else {
+    const int64_t kept = (int64_t)g.O * (g.K / M * N), full = 1 << 24;
+    if (kept < (g.T <= 24 ? 6 * full : g.T <= 28 ? full : g.T <= 32 ? full / 2 : 0)) {
+      if (g.T <= 16 && (M > 4 || kept < full)) return launch_tokens<N, M, 16, PACKED>(g, s);
+      return launch_tokens<N, M, 32, PACKED>(g, s);
+    }
+  }
   return launch_tokens<N, M, 64, PACKED>(g, s);
 }
 

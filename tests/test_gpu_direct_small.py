@@ -34,3 +34,20 @@ def test_few_tokens(T, K, O, N, M):
             q = torch.zeros_like(p)
             nm.nm_linear_forward_prepared_batched([(v, i, K, N, M, Xd, None, bd, q)])
             assert torch.equal(p, q)
+
+
+@pytest.mark.parametrize("T,K,O,N,M", [(32, 512, 32752, 4, 8), (32, 512, 32768, 4, 8), (28, 1024, 32752, 4, 8), (28, 1024, 32768, 4, 8),
+                                       (29, 1024, 32768, 4, 16), (25, 2048, 32768, 4, 16), (16, 1024, 21856, 3, 4), (9, 1024, 21824, 3, 4),
+                                       (16, 2048, 98304, 4, 8), (24, 2048, 98304, 4, 8), (24, 2048, 98272, 4, 8)])
+def test_large_weights(T, K, O, N, M):
+    """The tokens of a block by the size of the weight: the bytes are those of its first and last rows alone, which are few."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T + O)
+    W, X = (torch.empty(n, K, dtype=torch.bfloat16, device="cuda").normal_(generator=g) for n in (O, T))
+    v, i = nm.nm_pack(W, N, M)
+    for packed in (False, True) if N == 4 else (False,):
+        assert product_route("packed" if packed else "plain", T, K, O, N, M)[0] == "direct"
+        y = nm.nm_linear_forward(v, i, K, N, M, X, from_packed=packed)
+        for rows in (slice(0, 72), slice(O - 72, O)):
+            part = nm.nm_linear_forward(v[rows], i[rows], K, N, M, X, from_packed=packed)
+            assert torch.equal(y[:, rows], part)
