@@ -12,10 +12,11 @@ from gpu_util import check_output, dev_bf16, host_output, product_route
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("N,M", [(1, 4), (3, 4), (2, 8), (4, 8), (1, 16), (4, 16)])
+@pytest.mark.parametrize("N,M", [(1, 4), (3, 4), (1, 8), (2, 8), (3, 8), (4, 8), (1, 16), (2, 16), (4, 16)])
 @pytest.mark.parametrize("T,K,O", [(1, 64, 36), (8, 768, 1000), (15, 1024, 33), (16, 1088, 64), (16, 2304, 20), (9, 1040, 31),
                                    (17, 1024, 32), (31, 1088, 100), (32, 2304, 33), (33, 320, 72)])
 def test_few_tokens(T, K, O, N, M):
+    assert product_route("plain", T, K, O, N, M)[0] == "direct"
     rng = np.random.default_rng(1000 * T + K + N * M)
     X, W = wl.draw_activations(rng, T, K), wl.draw_weights(rng, O, K)
     bias = rng.standard_normal(O).astype(np.float32)
@@ -28,7 +29,7 @@ def test_few_tokens(T, K, O, N, M):
         check_output(host_output(y), Yref, B + np.abs(bias)[None, :], K // M * N + 1, dt == torch.float32, (T, K, O, N, M))
         if product_route("prepared", T, K, O, N, M)[0] in ("tiled", "ragged"):
             assert torch.equal(y, nm.nm_linear_forward_prepared(v, i, K, N, M, Xd, ws, bias=bd, out_dtype=dt))
-        if K % 64 == 0 and O % 4 == 0 and (N, M) != (3, 4):
+        if K % 64 == 0 and O % 4 == 0 and N != 3:
             p = nm.nm_linear_forward(v, i, K, N, M, Xd, bias=bd, out_dtype=dt, from_packed=True)
             check_output(host_output(p), Yref, B + np.abs(bias)[None, :], K // M * N + 1, dt == torch.float32, (T, K, O, N, M))
             q = torch.zeros_like(p)
