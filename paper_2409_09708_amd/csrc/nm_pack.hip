@@ -17,7 +17,10 @@ namespace nm {
 constexpr int kPackThreads = 256;
 constexpr int kChunk = 16;          // weights per chunk in the fast kernels (two 16-byte loads)
 // Chunks a lane handles, all their loads in flight before the first is coded: two where the matrices of a whole model share
-// a launch, one for a matrix alone, whose few blocks are bound by one block's load, coding and store.
+// a launch, one for a matrix alone, whose few blocks are bound by one block's load, coding and store (768 x 768 at 2:4, mask and
+// pruned weight 2.8 -> 2.2 us, packing 2.4 -> 2.0).  A larger one is bound by memory and gains 0 - 5 % (16384 x 16384 packed at 2:4
+// 149 -> 145; a matrix of 32 MB packed over and over from L2 loses instead, at 1:8 5.6 -> 6.6), but for pruning that writes the weight
+// as well, see prune_pairs.
 constexpr int kBatchChunks = 2;
 constexpr int kBatchBlock = kPackThreads * kBatchChunks;
 
@@ -268,13 +271,13 @@ __device__ __forceinline__ void code_block(const bf16_t* W, int64_t n_chunks, in
 
 constexpr int kSbitsWords = kBatchBlock * 64 / 32 + 2;  // room for the widest per-chunk index field run (<= 64 bits)
 
-template <int N, int M, int SRC>
+template <int N, int M, int SRC, int CHUNKS>
 __global__ void __launch_bounds__(kPackThreads)
 code_flat_kernel(const bf16_t* W, int64_t n_chunks, const uint32_t* __restrict__ mask_in,
                  bf16_t* __restrict__ values, uint32_t* __restrict__ indices, uint32_t* __restrict__ mask_out,
                  bf16_t* w_masked) {  // w_masked may be W itself (in-place pruning)
-  __shared__ uint32_t sbits[kPackThreads * 64 / 32 + 2];
-  code_block<N, M, SRC, 1>(W, n_chunks, flat_lane_256() - threadIdx.x, mask_in, values, indices, mask_out, w_masked, sbits);
+  __shared__ uint32_t sbits[kPackThreads * CHUNKS * 64 / 32 + 2];
+  code_block<N, M, SRC, CHUNKS>(W, n_chunks, (flat_lane_256() - threadIdx.x) * CHUNKS, mask_in, values, indices, mask_out, w_masked, sbits);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -555,13 +558,14 @@ static bool flat_ok(int64_t O, int64_t K, int64_t ldw, int N, int M, const void*
   return (all & 15u) == 0;
 }
 
-template <int SRC>
-static bool launch_flat(int N, int M, dim3 grid, hipStream_t s, const bf16_t* W, int64_t n_chunks, const uint32_t* mask_in,
+template <int SRC, int CHUNKS = 1>
+static bool launch_flat(int N, int M, hipStream_t s, const bf16_t* W, int64_t n_chunks, const uint32_t* mask_in,
                         bf16_t* values, uint32_t* indices, uint32_t* mask_out, bf16_t* w_masked) {
+  const dim3 grid = flat_grid_256((n_chunks + CHUNKS - 1) / CHUNKS);
   switch (N * 32 + M) {
 #define X(n, mm)                                                                                                  \
   case n * 32 + mm:                                                                                               \
-    hipLaunchKernelGGL((code_flat_kernel<n, mm, SRC>), grid, dim3(kPackThreads), 0, s, W, n_chunks, mask_in, values, \
+    hipLaunchKernelGGL((code_flat_kernel<n, mm, SRC, CHUNKS>), grid, dim3(kPackThreads), 0, s, W, n_chunks, mask_in, values, \
                        indices, mask_out, w_masked);                                                              \
     return true;
     NM_FOR_EACH_LEVEL(X)
@@ -570,12 +574,22 @@ static bool launch_flat(int N, int M, dim3 grid, hipStream_t s, const bf16_t* W,
   }
 }
 
+// Pruning that writes the weight takes two chunks per lane from 1536 blocks on, while matrix and result may still be in a cache: one
+// by one 2560 x 3072 at 2:4 takes 8.2 us for 7.6, 4608 x 4096 in place 14.5 for 12.3; outside, 2048 x 3072 6.6 for 6.5, 8192 x 8192 45.8
+// for 47.4.
+// The levels of the general selection are bound by its instructions (3:8 there 11.8 for 13.5 at 3456 x 3072).
+static bool prune_pairs(int64_t n_chunks, int N, int M) {
+  return (N == 1 || N == 2 || N == 4) && N < M && n_chunks > 1536 * kPackThreads && n_chunks <= 12288 * kPackThreads;
+}
+
 hipError_t launch_prune(const bf16_t* W, int64_t O, int64_t K, int64_t ldw, int N, int M, uint32_t* mask,
                         bf16_t* w_masked, hipStream_t s) {
   if (flat_ok(O, K, ldw, N, M, W, mask, w_masked, nullptr, nullptr)) {
     const int64_t n_chunks = O * K / kChunk;
-    launch_flat<0>(N, M, flat_grid_256(n_chunks), s, W, n_chunks, nullptr, nullptr, nullptr, mask,
-                       w_masked);
+    if (w_masked != nullptr && prune_pairs(n_chunks, N, M))
+      launch_flat<0, kBatchChunks>(N, M, s, W, n_chunks, nullptr, nullptr, nullptr, mask, w_masked);
+    else
+      launch_flat<0>(N, M, s, W, n_chunks, nullptr, nullptr, nullptr, mask, w_masked);
   } else {
     const int64_t n = O * mask_words_per_row(K);
     hipLaunchKernelGGL(prune_general_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, W, O, K, ldw, N, M, mask,
@@ -588,9 +602,8 @@ hipError_t launch_pack(const bf16_t* W, int64_t O, int64_t K, int64_t ldw, int N
                        bf16_t* values, uint32_t* indices, hipStream_t s) {
   if (flat_ok(O, K, ldw, N, M, W, mask, values, indices, nullptr)) {
     const int64_t n_chunks = O * K / kChunk;
-    const dim3 grid = flat_grid_256(n_chunks);
-    if (mask) launch_flat<1>(N, M, grid, s, W, n_chunks, mask, values, indices, nullptr, nullptr);
-    else launch_flat<0>(N, M, grid, s, W, n_chunks, nullptr, values, indices, nullptr, nullptr);
+    if (mask) launch_flat<1>(N, M, s, W, n_chunks, mask, values, indices, nullptr, nullptr);
+    else launch_flat<0>(N, M, s, W, n_chunks, nullptr, values, indices, nullptr, nullptr);
   } else {
     const int64_t ng = O * (K / M);
     hipLaunchKernelGGL(pack_values_general_kernel, dim3(blocks_for(ng, 256)), dim3(256), 0, s, W, O, K, ldw, N, M,
@@ -607,7 +620,7 @@ hipError_t launch_pack_ranked(const bf16_t* W, const uint8_t* rank, int64_t O, i
                               bf16_t* values, uint32_t* indices, hipStream_t s) {
   if (flat_ok(O, K, ldw, N, M, W, rank, values, indices, nullptr)) {
     const int64_t n_chunks = O * K / kChunk;
-    launch_flat<2>(N, M, flat_grid_256(n_chunks), s, W, n_chunks,
+    launch_flat<2>(N, M, s, W, n_chunks,
                    reinterpret_cast<const uint32_t*>(rank), values, indices, nullptr, nullptr);
   } else {
     const int64_t ng = O * (K / M);
