@@ -2179,9 +2179,11 @@ static bool packed_path(const SpmmArgs& a) {
 // A call that prepares and multiplies in one takes the kernel that decodes the weight itself (nm_direct.hip) where its
 // estimate is below the pre-pass and the tiled kernel together.  It decodes the weight once per 64 tokens, so it wins as
 // long as its blocks of 32 out-features x 64 tokens are few rounds on the chip, later for a shallow weight.  Both fitted on
-// 3000 shapes per form (64 .. 16384 deep, 64 .. 49152 wide, 1 .. 1000 tokens, in a graph); the route it picks costs 1 % on
-// average over the better of the two.  Pre-pass and product against it: 768 -> 1000 at 4:8 and 8 tokens 9.4 and 5.7 us,
-// 768 -> 768 at 394 tokens 9.2 and 6.3; 2048 -> 16384 at 1:8 and 208 tokens 33.4 and 68.9, which stays with the two.
+// 3000 shapes per form (64 .. 16384 deep, 64 .. 49152 wide, 1 .. 1000 tokens, in a graph); with blocks of 64 tokens the route
+// it picks cost 1 % on average over the better of the two.  Up to 32 tokens the kernel may take smaller blocks, 0.44 - 1.0 of
+// the time (launch_level there), which the estimate does not know: near the border such a call still goes to the two launches.
+// Pre-pass and product against it: 768 -> 1000 at 4:8 and 8 tokens 9.4 and 4.9 us, 768 -> 768 at 394 tokens 9.2 and 6.3;
+// 2048 -> 16384 at 1:8 and 208 tokens 33.4 and 68.9, which stays with the two.
 // Its sums are those of the tiled kernel; a layer that the persistent kernel or a cut reduction would sum in another
 // order stays there.
 constexpr TileModel kDirectModel[2] = {{32, 64, 3.81, 0.130, 0.57, 1.09}, {32, 64, 3.22, 0.117, 0.85, 0.68}};  // [2:4 form]
@@ -2205,7 +2207,7 @@ static bool direct_takes_ragged(int64_t O, int64_t K, int N, int M, int64_t T) {
 // A call without a workspace takes it up to four rounds of blocks, and at one block of tokens in any case; beyond, it would
 // decode a wide weight two to four times, and the kernel of nm_fewtok.hip, with the same sums, is the faster one (12288 ->
 // 49152 at 1:8 and 208 tokens 370 us, 1080 that way; 2048 -> 16384 at 130 tokens 38.7 and 53.3; 768 -> 1000 at 4:8 and 16
-// tokens 23.0 and 6.1).
+// tokens 23.0 and 5.4).
 static bool direct_takes_packed(int64_t O, int64_t T) { return T <= 64 || ((O + 31) / 32) * ((T + 63) / 64) <= 1024; }
 
 hipError_t launch_spmm(const SpmmArgs& a, hipStream_t s, bool* workspace_short, int phases) {
