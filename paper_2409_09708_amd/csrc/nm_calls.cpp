@@ -1,11 +1,11 @@
 // Native marshalling of the calls that a program makes per layer.  A small layer's call costs the host more than the device
-// (one image through a 384 x 384 projection: 3.8 us of kernel, 7.0 us per call in Python), so a call whose arguments are all
+// (one image through a 384 x 384 projection: 3.8 us of kernel, 7.3 us per call in Python), so a call whose arguments are all
 // in the ordinary form -- plain device tensors of the right types and shapes, Python integers -- is read, checked and
 // handed to the C ABI here.  Anything else is declined (NotImplemented), and the Python function goes on with it: it
 // knows the other forms that are accepted and names what is wrong with the ones that are not.  Nothing is kept
 // between calls.
-// Measured per call: the projection above 7.2 -> 4.0 us; 768 -> 1000 at 4:8 on 8 tokens, plain, 8.2 -> 6.2 (5.0 with a kernel
-// that has become faster since); the twelve calls and sixteen allocations that compress a block by scores and expand it 96 -> 64.
+// Measured per call: the projection above 7.3 -> 4.1 us; 768 -> 1000 at 4:8 on 8 tokens, plain, 8.2 -> 6.2 (5.0 with a kernel
+// that has become faster since); the twelve calls and sixteen allocations that compress a block by scores and expand it 94 -> 63.
 #include <Python.h>
 
 #include <ATen/PythonTorchFunctionTLS.h>
