@@ -7,7 +7,7 @@
 // round trip to memory, decoding 16 weights per lane and pass (a 2-byte LDS write per kept value), and a serial chain of
 // K / 64 steps.  So a block is small (768 out-features are 24 of them per 64 tokens), all four waves decode, the loads
 // of two spans of 256 reduction positions are in flight in registers while a third is multiplied, and a span has one
-// barrier; up to 16 or 32 tokens, four spans share one (launch_level).  Which products it takes is decided in nm_spmm.hip
+// barrier; in blocks of 16 or 32 tokens four spans share one (launch_level).  Which products it takes is decided in nm_spmm.hip
 // (direct_takes).  In a graph, pre-pass and product before: 768 -> 1000 at 4:8 and 8 tokens 9.4 -> 4.6 us, 3072 -> 768 at
 // 1:4 16.4 -> 9.4, 1024 -> 4096 at 4:8 16.3 -> 6.0.
 //
@@ -160,7 +160,7 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
   };
 
   f32x4_t acc[2];
-  // a lane holds out-features o_lane + 16 i .. + 3 of token r16 of its wave's 16; up to 32 tokens a wave holds one
+  // a lane holds out-features o_lane + 16 i .. + 3 of token r16 of its wave's 16; in blocks of 16 or 32 tokens a wave holds one
   // block of 16 out-features (acc[0]), the lower one in the even waves
   const int o_lane = o0 + kb * 4;
   auto bias_of = [&](int i) {
