@@ -94,12 +94,26 @@ __device__ __forceinline__ void strided_load_place(int n, int lane, int* row, in
   *piece = (lane % PER_ROW) ^ (2 * (*row & 3)) ^ (8 * ((*row >> 3) & 1));
 }
 
-template <bool Q_STRIDED>
-__global__ void __launch_bounds__(TCfg::NT, 2)
+// PAIR (split reductions only): a block of eight waves, two halves of four, each half a tile of its own range as above with its
+// own LDS stages.  The halves of a block take two neighbouring ranges of one tile and add their sums through LDS before they
+// leave, so half as many partial tiles are written and read back: those bytes (64 MB written and 64 MB read by the sum, whatever
+// the layer) and the wait for them at the end, when every block writes at once, were what the kernels of a layer at 12608 tokens
+// spent most of their time on beside the instructions.  The ranges stay as they were, so no sum gets longer.  The second half runs one
+// barrier behind the first: on every SIMD one wave reads its fragments while the other multiplies.  12608 tokens, both
+// kernels: 768 -> 2304 59.4 -> 51.7 us, 768 -> 768 33.5 -> 29.0, 768 -> 3072 67.6 -> 61.8; 25216 x 768 -> 3072 115 -> 104.
+// Blocks of the paired form: one per tile and pair of ranges, and one per two tiles for the last of an odd number of ranges.
+__host__ __device__ constexpr int64_t pair_blocks(int64_t n_tiles, int splits) {
+  return n_tiles * (splits / 2) + (splits % 2 ? (n_tiles + 1) / 2 : 0);
+}
+
+template <bool Q_STRIDED, bool PAIR>
+__global__ void __launch_bounds__(PAIR ? 2 * TCfg::NT : TCfg::NT, 2)
 nm_tgemm_kernel(const TGemmArgs a) {
   using C = TCfg;
   constexpr int IT = C::IT, JT = C::JT, STAGES = C::STAGES;
-  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_all[];
+  const int half = PAIR ? (int)__builtin_amdgcn_readfirstlane(threadIdx.x / C::NT) : 0;
+  unsigned char* const smem = smem_all + half * C::LDS_BYTES;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
   // Block -> (tile, split).  Consecutive block ids land on different XCDs (8, each with its own L2); every
@@ -107,12 +121,16 @@ nm_tgemm_kernel(const TGemmArgs a) {
   // blocks that share an L2 share rows of Q, and each range of rows of a split reduction is fetched into one
   // L2 (two where a split straddles a boundary).
   const int n_tiles = a.n_i_tiles * a.n_j_tiles;
-  const int64_t n_blocks = (int64_t)n_tiles * a.splits;
+  const int64_t n_paired = PAIR ? (int64_t)n_tiles * (a.splits / 2) : 0;
+  const int64_t n_blocks = PAIR ? pair_blocks(n_tiles, a.splits) : (int64_t)n_tiles * a.splits;
   const int64_t per_xcd = (n_blocks + 7) >> 3;
   const int64_t virt = (int64_t)(blockIdx.x & 7) * per_xcd + (int64_t)(blockIdx.x >> 3);
   if (virt >= n_blocks) return;
-  const int split = (int)(virt / n_tiles);
-  const int tile = (int)(virt % n_tiles);
+  // PAIR: the halves take ranges 2p and 2p + 1 of one tile, or the last range of two neighbouring tiles
+  const bool paired = PAIR && virt < n_paired;
+  const int plane = (int)(PAIR && !paired ? a.splits / 2 : virt / n_tiles);  // partial tile it is stored as
+  const int split = !PAIR ? plane : paired ? 2 * plane + half : a.splits - 1;
+  const int tile = (int)(PAIR && !paired ? 2 * (virt - n_paired) + half : virt % n_tiles);
   const int64_t i0 = (int64_t)(tile % a.n_i_tiles) * C::BI;
   const int64_t j0 = (int64_t)(tile / a.n_i_tiles) * C::BJ;
 
@@ -124,9 +142,13 @@ nm_tgemm_kernel(const TGemmArgs a) {
     step_first = split * share + (split < extra ? split : extra);
     nk = share + (split < extra ? 1 : 0);
   }
+  // PAIR: both halves pass the same barriers: the second range of a pair is never the longer one, and a half without a tile
+  // only keeps step
+  const int64_t nk_block = PAIR && half && paired ? nk + (split - 1 < steps_all % a.splits && split >= steps_all % a.splits ? 1 : 0) : nk;
+  if (PAIR && tile >= n_tiles) nk = 0;
   const int64_t r_first = step_first * C::RS;
 
-  const int tid = threadIdx.x;
+  const int tid = PAIR ? threadIdx.x % C::NT : threadIdx.x;  // in the half
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wi = wave % C::WI;
@@ -239,7 +261,7 @@ nm_tgemm_kernel(const TGemmArgs a) {
     const StageSrc src = stage_src(load ? lr : r_first);
     [&]<int... Q>(std::integer_sequence<int, Q...>) {
       ([&] {
-        constexpr int j = Q / IT, i = Q % IT;
+        constexpr int j = Q / IT, i = j & 1 ? IT - 1 - Q % IT : Q % IT;
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pf[i]),
                                                             __builtin_bit_cast(bf16x8_t, qf[j]), acc[i][j], 0, 0, 0);
         if constexpr (Q % 4 == 3 && Q / 4 < C::LPW) {
@@ -259,6 +281,16 @@ nm_tgemm_kernel(const TGemmArgs a) {
   for (int s = 0; s < STAGES - 1; ++s)
     if (s < nk) issue_stage(r_first + (int64_t)s * C::RS, s);
 
+  // PAIR: the second half runs one barrier behind the first
+  auto turn = [&] {
+    if constexpr (PAIR) {
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  if (half) turn();
   // One barrier per stage; the buffer multiplied in the previous step is refilled right after the barrier,
   // STAGES - 1 stages ahead.
   {
@@ -281,11 +313,12 @@ nm_tgemm_kernel(const TGemmArgs a) {
         wait_loads_outstanding<(STAGES - 2) * C::LPW>();
         __builtin_amdgcn_s_barrier();
         read_frags(buf);
+        turn();
         const uniform_ptr_t up = make_uniform(fp), uq = make_uniform(fq);
         const uint32_t lds = __builtin_amdgcn_readfirstlane(lds_load);
         [&]<int... Q>(std::integer_sequence<int, Q...>) {
           ([&] {
-            constexpr int j = Q / IT, i = Q % IT;
+            constexpr int j = Q / IT, i = j & 1 ? IT - 1 - Q % IT : Q % IT;
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pf[i]),
                                                                 __builtin_bit_cast(bf16x8_t, qf[j]), acc[i][j], 0, 0, 0);
             if constexpr (Q % 4 == 3 && Q / 4 < C::LPW) {
@@ -326,14 +359,45 @@ nm_tgemm_kernel(const TGemmArgs a) {
       int nbuf = buf + STAGES - 1;
       if (nbuf >= STAGES) nbuf -= STAGES;
       read_frags(buf);
+      turn();
       multiply(ks + STAGES - 1 < nk, r + (int64_t)(STAGES - 1) * C::RS, nbuf);
       if (++buf == STAGES) buf = 0;
     }
+    if constexpr (PAIR)
+      for (; ks < nk_block; ++ks) {
+        turn();
+        turn();
+      }
   }
+  if (PAIR && !half) turn();
 
   // ---- split reduction: the partial tile, 16 bytes per lane and accumulator, fully coalesced
   if (a.partial) {
-    f32x4_t* mine = reinterpret_cast<f32x4_t*>(a.partial) + ((size_t)split * n_tiles + tile) * (C::MMA * C::NT) + tid;
+    f32x4_t* mine = reinterpret_cast<f32x4_t*>(a.partial) + ((size_t)plane * n_tiles + tile) * (C::MMA * C::NT) + tid;
+    if (PAIR && paired) {
+      // the two ranges are added here: each half hands the other 16 of its 32 accumulators through its own stages
+      static_assert(C::MMA / 2 * C::NT * 16 <= C::LDS_BYTES && JT % 2 == 0, "half the accumulators fit the half's stages");
+      turn();  // nobody reads operands any more
+      auto swap_and_store = [&](auto keep_tag) {
+        constexpr int KEEP = decltype(keep_tag)::value * (JT / 2), GIVE = JT / 2 - KEEP;
+        f32x4_t* out = reinterpret_cast<f32x4_t*>(smem) + tid;
+        const f32x4_t* in = reinterpret_cast<const f32x4_t*>(smem_all + (1 - half) * C::LDS_BYTES) + tid;
+#pragma unroll
+        for (int j = 0; j < JT / 2; ++j)
+#pragma unroll
+          for (int i = 0; i < IT; ++i) out[(j * IT + i) * C::NT] = acc[i][GIVE + j];
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        turn();
+#pragma unroll
+        for (int j = 0; j < JT / 2; ++j)
+#pragma unroll
+          for (int i = 0; i < IT; ++i) mine[(i * JT + KEEP + j) * C::NT] = acc[i][KEEP + j] + in[(j * IT + i) * C::NT];
+      };
+      if (half) swap_and_store(std::integral_constant<int, 1>{});
+      else swap_and_store(std::integral_constant<int, 0>{});
+      return;
+    }
+    if (PAIR && tile >= n_tiles) return;
 #pragma unroll
     for (int i = 0; i < IT; ++i)
 #pragma unroll
@@ -361,13 +425,13 @@ nm_tgemm_kernel(const TGemmArgs a) {
   }
 }
 
-// Sum of the partial tiles in split order, the mask of the step (bit k % 32 of word k / 32 of row o; NULL =
-// every weight receives its gradient) and the rounding.  One lane per accumulator of the tile kernel.  Bound by reading the
-// partial tiles (66 MB at 5.3 TB/s).  64 tiles are one round of the chip's wavefront slots.  Where the last round has at most 16 of
-// them, its few wavefronts do not hide a load and a lane reads six ranges at a time (16 tiles in 29 ranges 16.8 -> 10.5 us, 2 in
-// 64 16.8 -> 6.6, 72 in 7, which is 768 -> 3072 at 12608 tokens, 12.8 -> 12.0).  A fuller round is bound by memory, and ranges
-// read at once disturb each other there (32 in 15 10.8 one by one, 12.0; 35 in 14 10.8 and 12.0, 91 in 11 20.7 and 21.3).
-// Fewer than seven ranges are read one by one in any case.
+// Sum of the partial tiles (of a range, or of a pair of ranges) in order, the mask of the step (bit k % 32 of word k / 32 of row
+// o; NULL = every weight receives its gradient) and the rounding.  One lane per accumulator of the tile kernel.  Bound by reading
+// the partial tiles, and by its launch (72 tiles of 4 pairs, 47 MB in all, 8.3 us; 12.2 with the 7 single ranges; 32 of 8 pairs 7.4, 10.8 with 15).
+// 64 tiles are one round of the chip's wavefront slots.  Where the last round has at most 16 of them, its few wavefronts do not
+// hide a load and a lane reads six at a time (16 tiles in 29 ranges 16.8 -> 10.5 us, 2 in 64 16.8 -> 6.6).  A fuller round is
+// bound by memory, and six read at once disturb each other there (32 in 15 10.8 one by one, 12.0); it reads two (72 of 4 9.1
+// one by one, 8.3; three or four as two).
 __global__ void __launch_bounds__(256)
 grad_reduce_kernel(const float* __restrict__ partial, int splits, int n_tiles, int n_i_tiles, int64_t I, int64_t J,
                    const uint32_t* __restrict__ mask, void* __restrict__ out, int64_t ldo, int out_bf16) {
@@ -390,7 +454,12 @@ grad_reduce_kernel(const float* __restrict__ partial, int splits, int n_tiles, i
       for (int u = 0; u < 6; ++u) sum += p[u];
     }
   }
-  for (; s < splits; ++s) sum += src[(size_t)s * stride];
+  for (; s + 2 <= splits; s += 2) {
+    const f32x4_t p0 = src[(size_t)s * stride], p1 = src[(size_t)(s + 1) * stride];
+    sum += p0;
+    sum += p1;
+  }
+  if (s < splits) sum += src[(size_t)s * stride];
   const int lane = tid & 63, wave = tid >> 6;
   const int wi = wave % C::WI, wj = wave / C::WI;
   const int i = q / C::JT, j = q % C::JT;
@@ -450,16 +519,17 @@ backward_weight_general_kernel(const bf16_t* __restrict__ dY, int64_t T, int64_t
 
 inline bool aligned_to(const void* p, uintptr_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
 
-template <bool Q_STRIDED>
+template <bool Q_STRIDED, bool PAIR = false>
 hipError_t launch_tgemm(TGemmArgs g, hipStream_t s) {
   using C = TCfg;
-  auto kern = nm_tgemm_kernel<Q_STRIDED>;
+  constexpr int HALVES = PAIR ? 2 : 1;
+  auto kern = nm_tgemm_kernel<Q_STRIDED, PAIR>;
   static PerDeviceOnce lds_limit;
-  if (hipError_t e = raise_dynamic_lds_limit(kern, C::LDS_BYTES, lds_limit); e != hipSuccess) return e;
+  if (hipError_t e = raise_dynamic_lds_limit(kern, HALVES * C::LDS_BYTES, lds_limit); e != hipSuccess) return e;
   const int64_t n_tiles = (int64_t)g.n_i_tiles * g.n_j_tiles;
-  const int64_t grid = ((n_tiles * g.splits + 7) / 8) * 8;
+  const int64_t grid = ((PAIR ? pair_blocks(n_tiles, g.splits) : n_tiles * g.splits) + 7) / 8 * 8;
   if (grid > 0x7FFFFFFF) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(C::NT), C::LDS_BYTES, s, g);
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(HALVES * C::NT), HALVES * C::LDS_BYTES, s, g);
   return hipGetLastError();
 }
 
@@ -490,6 +560,16 @@ WeightGradPlan weight_grad_plan(int64_t O, int64_t K, int64_t T) {
   }
   p.splits = best;
   return p;
+}
+
+// Whether the ranges are taken in pairs (see nm_tgemm_kernel).  Up to 256 ranges of tiles have a compute unit each to themselves
+// as single blocks.  Below 16 steps the ranges are so short that an odd last one, which stays alone, is a third of the work
+// (400 tokens x 1024 -> 4096 in 3 ranges 28.7 us, 30.5 in pairs; 600 in 4 32.4 and 30.2).  Past 200 steps a range the bytes of
+// the partial tiles no longer count and eight waves in step lose to two free blocks (50432 x 768 -> 3072, 225 steps, 215 us,
+// 220 in pairs; 25216 x 1024 -> 4096, 197 steps, 182 and 175).
+bool weight_grad_paired(const WeightGradPlan& p, int64_t T) {
+  const int64_t steps = (T + TCfg::RS - 1) / TCfg::RS;
+  return p.splits > 1 && (int64_t)p.n_i_tiles * p.n_j_tiles * p.splits > 256 && steps >= 16 && steps <= 200 * p.splits;
 }
 
 }  // namespace
@@ -564,10 +644,11 @@ hipError_t launch_backward_weight(const bf16_t* dY, int64_t T, int64_t O, int64_
   g.out = nullptr; g.ldo = 0; g.out_bf16 = 0; g.vec_store = 0;
   g.n_i_tiles = p.n_i_tiles; g.n_j_tiles = p.n_j_tiles;
   g.splits = p.splits; g.partial = reinterpret_cast<float*>(workspace);
-  hipError_t e = launch_tgemm<true>(g, s);
+  const bool pair = weight_grad_paired(p, T);
+  hipError_t e = pair ? launch_tgemm<true, true>(g, s) : launch_tgemm<true>(g, s);
   if (e != hipSuccess) return e;
   const int64_t n = (int64_t)p.n_i_tiles * p.n_j_tiles * TCfg::MMA * TCfg::NT;
-  hipLaunchKernelGGL(grad_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, g.partial, p.splits,
+  hipLaunchKernelGGL(grad_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, g.partial, pair ? (p.splits + 1) / 2 : p.splits,
                      p.n_i_tiles * p.n_j_tiles, p.n_i_tiles, K, O, mask, dW, lddw, out_bf16);
   return hipGetLastError();
 }
