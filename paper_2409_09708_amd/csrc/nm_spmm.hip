@@ -1169,13 +1169,13 @@ nm_stream_kernel(const StreamGroup g) {
   // HEAD of them fall into the step that freed the buffer, the others into the next one.  The requests of the
   // eight waves then reach the CU's one load path spread over the step instead of in one burst, behind which
   // every wave's matrix instructions would queue (a wave issues in order).
-  // 2:4 form (bfloat16): the W loads of a stage leave in the next step, after the write-out of a tile that ended with the buffer's
+  // 2:4 form: the W loads of a stage leave in the next step, after the write-out of a tile that ended with the buffer's
   // step: the write-out uses the part of the buffer that they refill.  Where the even spacing brings them earlier, the X
   // loads and selectors go into the groups of the step that freed the buffer and the W loads into the first ones of the next.
   constexpr int LPG = (C::LPW + C::TT - 1) / C::TT;                     // loads that leave together
   constexpr int SLOTS = (C::LPW + LPG - 1) / LPG;
   constexpr int SPREAD = 2 * SLOTS <= C::TT ? 2 : 1;
-  constexpr bool TURN_IN_LDS = SPARSE && !I8;                           // which write-out, see there
+  constexpr bool TURN_IN_LDS = SPARSE;                                  // which write-out, see there
   constexpr bool EVEN = !TURN_IN_LDS || C::X_PW / LPG * SPREAD >= C::PRE;
   constexpr int EARLY = C::X_PW + C::S_PW;                              // loads that are not of W
   constexpr int EARLY_PER = (EARLY + C::PRE - 1) / C::PRE;
@@ -1220,7 +1220,9 @@ nm_stream_kernel(const StreamGroup g) {
 
   // One K step, free of conditions: a wave issues one instruction at a time, in order, so every other
   // instruction of the step is time its matrix instructions do not get.  PP names the fragment and address
-  // set the step multiplies with.  Every step refills the buffer it has consumed and prefetches fragments
+  // set the step multiplies with.  Every other group takes the W fragments backwards: the chip is bound by power here, and operands
+  // that stay between two instructions take less of it (a loop of dense instructions fed from LDS 0.590 -> 0.580 us a step, int8
+  // 0.615 -> 0.583; the sparse ones do not mind).  Every step refills the buffer it has consumed and prefetches fragments
   // of the next stage, also past the block's last stage.
   auto step = [&](auto pp_tag) {
     constexpr int PP = decltype(pp_tag)::value;
@@ -1253,7 +1255,7 @@ nm_stream_kernel(const StreamGroup g) {
         }
         [&]<int... I>(std::integer_sequence<int, I...>) {
           ([&] {
-            constexpr int i = I;
+            constexpr int i = j & 1 ? OT - 1 - I : I;  // back and forth
             if constexpr (SPARSE && I8)
               acc[i][j] = __builtin_amdgcn_smfmac_i32_16x16x128_i8(__builtin_bit_cast(i32x4_t, afr[PP][i]),
                                                                    __builtin_bit_cast(i32x8_t, bq[j]), acc[i][j],
@@ -1381,18 +1383,20 @@ nm_stream_kernel(const StreamGroup g) {
       struct Lines { u32x4_t first, second; };
       // 2:4 form: the wave turns 16 token rows at a time through two kilobytes of LDS, the places of its own W loads in the
       // buffer that the last step has freed (they leave in the next step): 8 bytes per lane and block in, 16-byte pieces
-      // of whole rows out, the pieces of a row XOR-swizzled with the row.  The LDS operations of a wave run in order, so
+      // of whole rows out, the pieces of a row XOR-swizzled with the row (rows 8..15 on the other parity than rows 0..7, which
+      // lie on the same banks: without it every write takes two passes).  The LDS operations of a wave run in order, so
       // nothing waits between a write and a read.  Against the exchange below: 12608 tokens x 768 -> 768 15.1 -> 14.5 us,
-      // 3072 -> 768 36.3 -> 35.0, 50432 x 768 -> 3072 145 -> 140.  The dense form, whose loads would have to move for it,
-      // loses up to 6 % (3072 -> 768 54.0 -> 57.4); int8 gains nothing.
+      // 3072 -> 768 36.3 -> 35.0, 50432 x 768 -> 3072 145 -> 140; the four int8 layers of a block at C = 768 95.8 -> 94.0.
+      // The dense form, whose loads would have to move for it, loses up to 6 % (3072 -> 768 54.0 -> 57.4).
       const uint32_t freed = cur_off == 0 ? (uint32_t)((STAGES - 1) * C::STAGE) : cur_off - (uint32_t)C::STAGE;
       unsigned char* slice = smem + freed + C::X_BYTES + wave * 1024;     // rows 0..7; rows 8..15 lie C::NW kilobytes further
       unsigned char* put = slice + (r16 >> 3) * (C::NW * 1024) + (r16 & 7) * 128 + (kb & 1) * 8;
       uint32_t put_at[OT];
 #pragma unroll
-      for (int i = 0; i < OT; ++i) put_at[i] = (uint32_t)(((2 * i + (kb >> 1)) ^ (r16 & 7)) * 16);
+      for (int i = 0; i < OT; ++i) put_at[i] = (uint32_t)(((2 * i + (kb >> 1)) ^ (r16 & 7) ^ (r16 >> 3)) * 16);
       const unsigned char* get = slice + (lane >> 3) * 128 + ((lane & 7) ^ (lane >> 3)) * 16;
-      // Dense form and int8: the two 16-byte pieces a lane holds for a token block (out-feature pairs 0 and 1, after the exchange
+      const unsigned char* get_second = slice + C::NW * 1024 + (lane >> 3) * 128 + ((lane & 7) ^ (lane >> 3) ^ 1) * 16;
+      // Dense form: the two 16-byte pieces a lane holds for a token block (out-feature pairs 0 and 1, after the exchange
       // between lane rows) are pushed to the lanes that store them: lane 8m + p stores piece p (0..7) of token row m
       // (first store) and of token row m + 8 (second store).
       const int qk = ((kb & 1) << 1) | (kb >> 1);            // place of this lane's piece inside its pair's 64 bytes
@@ -1417,7 +1421,7 @@ nm_stream_kernel(const StreamGroup g) {
             *reinterpret_cast<uint2*>(put + put_at[i]) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
           }
           asm volatile("" ::: "memory");
-          return Lines{*reinterpret_cast<const u32x4_t*>(get), *reinterpret_cast<const u32x4_t*>(get + C::NW * 1024)};
+          return Lines{*reinterpret_cast<const u32x4_t*>(get), *reinterpret_cast<const u32x4_t*>(get_second)};
         } else {
           const u32x4_t p0 = swapped(j, 0), p1 = swapped(j, 1);
           u32x4_t ra, rb;
