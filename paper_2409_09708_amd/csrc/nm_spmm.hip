@@ -1697,7 +1697,7 @@ static int64_t tile_layer_units(const TileLayer& L) {
 template <int BO, int BT>
 static int64_t tile_layer_blocks(const TileLayer& L) { return (tile_layer_units<BO, BT>(L) + 7) / 8 * 8; }
 constexpr double kTileBlockUs = 2.0;   // a block's start and write-out
-constexpr double kNarrowShare = 1.5;
+constexpr double kNarrowShare = 1.25;
 // estimated duration of one of the layer's blocks (the model of pick_tile): the order of the launch
 static double tile_layer_cost(const TileLayer& L) {
   const int n = L.splits > 1 ? L.splits : 1;
@@ -1705,11 +1705,13 @@ static double tile_layer_cost(const TileLayer& L) {
 }
 
 // A launch ends with its longest blocks, and a deep layer's may run far longer than the launch's even share of work.
-// Where a block of 128 out-features would run 1.5 times that share, the layer takes tiles of 64 out-features: twice the
+// Where a block of 128 out-features would run 1.25 times that share, the layer takes tiles of 64 out-features: twice the
 // blocks, each a little over half as long.  One image (in a graph): 4 linears at C = 768 36 -> 23 us, 12 of them 36.5 ->
-// 26.9, 24 43.0 -> 32.7, 32 at C = 512 32.6 -> 25.9; 48 at C = 768 (55 us: bound by reading 170 MB of weights) stay.
-// Below 1.5 the larger calls lose (48 at C = 768 57 us at 0.85).  The 2:4 form of more than 512 tokens, whose X is
-// then read by many more blocks, keeps its tiles (8 linears at 788 tokens 31.0, 33.4 narrow).
+// 26.9, 24 43.0 -> 32.7, 32 at C = 512 32.6 -> 25.9.  The line, with weights from memory: 48 linears at C = 768 whose deep
+// dense layers run 1.28 or 1.29 shares 60.2 -> 57.9 and 60.0 -> 57.4 us, 44 (1.41) 58.5 -> 52.5, 32 (the 2:4 form at 1.33
+// too) 48.6 -> 45.0; below it the activations read by twice the blocks cost more: 48 with more such layers (1.23) 61.6 and
+// 62.1 narrow, 61.7 and 62.7, 40 with the 2:4 form at 1.08 narrow as well 50.9 and 53.9.  The 2:4 form of more than 512
+// tokens, whose X is then read by many more blocks, keeps its tiles (8 linears at 788 tokens 31.0, 33.4 narrow).
 template <int BO, int BT>
 static void tile_group_narrow(TileGroup& grp) {
   double total = 0;
