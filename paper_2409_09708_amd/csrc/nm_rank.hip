@@ -146,9 +146,28 @@ __device__ __forceinline__ uint32_t score_key(float v) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// Bits of the kept members of a group; every pair of the group is compared once.
+template <int M>
+__device__ __forceinline__ uint32_t score_keep(const float* v, int N) {
+  uint32_t key[M], before[M], keep = 0;
+#pragma unroll
+  for (int i = 0; i < M; ++i) { key[i] = score_key(v[i]); before[i] = 0; }
+#pragma unroll
+  for (int i = 0; i < M; ++i)
+#pragma unroll
+    for (int j = i + 1; j < M; ++j) {
+      const bool i_first = key[i] >= key[j];
+      before[j] += i_first ? 1u : 0u;
+      before[i] += i_first ? 0u : 1u;
+    }
+#pragma unroll
+  for (int i = 0; i < M; ++i) keep |= (before[i] < (uint32_t)N ? 1u : 0u) << i;
+  return keep;
+}
+
 // One lane per group of M scores, neighbouring lanes on neighbouring groups, so that a wave's loads are whole
 // consecutive lines (a lane per mask word reads 128 bytes of its own and leaves most of the chip empty: 590 K scores
-// are 18 K words); the groups of a word are joined by lane exchanges.  Every pair of a group is compared once.
+// are 18 K words); the groups of a word are joined by lane exchanges.
 // Bound by launch and load latency at one layer's size: 768 x 768 at 2:4 18.3 -> 3.2 us,
 // 3072 x 768 21.2 -> 4.9 us.
 // WIDE: rows start and step in whole 16-byte pieces.
@@ -181,25 +200,44 @@ score_mask_kernel(const float* __restrict__ score, int64_t O, int64_t K, int64_t
 #pragma unroll
       for (int i = 0; i < M; ++i) v[i] = src[i];
     }
-    uint32_t key[M], before[M];
-#pragma unroll
-    for (int i = 0; i < M; ++i) { key[i] = score_key(v[i]); before[i] = 0; }
-#pragma unroll
-    for (int i = 0; i < M; ++i)
-#pragma unroll
-      for (int j = i + 1; j < M; ++j) {
-        const bool i_first = key[i] >= key[j];
-        before[j] += i_first ? 1u : 0u;
-        before[i] += i_first ? 0u : 1u;
-      }
-#pragma unroll
-    for (int i = 0; i < M; ++i) keep |= (before[i] < (uint32_t)N ? 1u : 0u) << i;
+    keep = score_keep<M>(v, N);
   }
   const int part = (int)threadIdx.x & (PER_WORD - 1);
   uint32_t word = keep << (part * M);
 #pragma unroll
   for (int d = 1; d < PER_WORD; d *= 2) word |= __shfl_xor(word, d);
   if (o < O && part == 0) mask[o * nw + g / PER_WORD] = word;
+}
+
+// Contiguous rows of whole words at whole 16-byte pieces: the groups form one list, and no lane divides by the groups of a row.
+// Neighbouring lanes on neighbouring groups as above, GROUPS of them per lane a block apart, all loaded before the first is
+// compared.  2:4, in a graph: 768 x 768 2.5 -> 2.2 us, 3072 x 768 4.4 -> 3.9; bound by launch and load latency there, by memory
+// where a launch is many rounds of waves: 8192 x 8192 60 -> 51 with one group per lane, 44 with four (6.2 TB/s).  Four per
+// lane from 2 M groups of 4 on: 4096 x 4096 14.0 -> 13.5, but 1024 x 4096 5.1 -> 5.7.  Groups of 8 and 16 fill a lane by
+// themselves (two of 8: 4096 x 4096 14.2 -> 15.3).
+template <int M, int GROUPS>
+__global__ void __launch_bounds__(256)
+score_mask_flat_kernel(const float* __restrict__ score, int64_t n_groups, int N, uint32_t* __restrict__ mask) {
+  constexpr int PER_WORD = 32 / M;
+  const int64_t g0 = (flat_lane_256() - threadIdx.x) * GROUPS + threadIdx.x;
+  float v[GROUPS][M];
+#pragma unroll
+  for (int u = 0; u < GROUPS; ++u) {
+    const int64_t g = g0 + u * 256 < n_groups ? g0 + u * 256 : n_groups - 1;
+#pragma unroll
+    for (int i = 0; i < M; i += 4) {
+      const float4 q = *reinterpret_cast<const float4*>(score + g * M + i);
+      v[u][i] = q.x; v[u][i + 1] = q.y; v[u][i + 2] = q.z; v[u][i + 3] = q.w;
+    }
+  }
+  const int part = (int)threadIdx.x & (PER_WORD - 1);
+#pragma unroll
+  for (int u = 0; u < GROUPS; ++u) {
+    uint32_t word = score_keep<M>(v[u], N) << (part * M);
+#pragma unroll
+    for (int d = 1; d < PER_WORD; d *= 2) word |= __shfl_xor(word, d);
+    if (part == 0 && g0 + u * 256 < n_groups) mask[(g0 + u * 256) / PER_WORD] = word;
+  }
 }
 
 static bool rank_flat_ok(const bf16_t* W, int64_t O, int64_t K, int64_t ldw, const uint8_t* rank) {
@@ -269,8 +307,16 @@ hipError_t launch_score_mask(const float* score, int64_t O, int64_t K, int64_t l
     hipLaunchKernelGGL((score_mask_kernel<decltype(m)::value, decltype(w)::value>), grid, dim3(256), 0, s, score, O, K,
                        lds, N, mask);
   };
+  const int64_t n_groups = O * K / M;
   auto level = [&](auto m) {
-    if (wide) go(m, std::true_type{});
+    constexpr int MM = decltype(m)::value;
+    if (wide && lds == K && K % 32 == 0) {
+      // four groups of 4 per lane where the launch is many rounds of waves (see the kernel)
+      if (MM == 4 && n_groups > 1 << 21)
+        hipLaunchKernelGGL((score_mask_flat_kernel<MM, MM == 4 ? 4 : 1>), flat_grid_256((n_groups + 3) / 4), dim3(256), 0, s, score, n_groups, N, mask);
+      else
+        hipLaunchKernelGGL((score_mask_flat_kernel<MM, 1>), flat_grid_256(n_groups), dim3(256), 0, s, score, n_groups, N, mask);
+    } else if (wide) go(m, std::true_type{});
     else go(m, std::false_type{});
   };
   if (M == 4) level(std::integral_constant<int, 4>{});

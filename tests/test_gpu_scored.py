@@ -29,6 +29,18 @@ def test_mask_from_scores_lane_maps(O, K, pitch, first, N, M):
     assert np.array_equal(host_words(nm.nm_prune_scored(view, N, M)), orc.mask_to_words(ref))
 
 
+# contiguous rows of whole words: one word, a last block that is partly filled, and both sides of four groups of 4 per lane
+@pytest.mark.parametrize("O,K,N,M", [(1, 32, 2, 4), (3, 32, 1, 8), (5, 32, 3, 16), (33, 96, 3, 4), (65, 160, 5, 8), (67, 224, 9, 16),
+                                     (2048, 4096, 2, 4), (2051, 4096, 1, 4), (1025, 8224, 3, 4)])
+def test_mask_from_scores_contiguous(O, K, N, M):
+    rng = np.random.default_rng(O * 1000 + K)
+    s = rng.integers(-6, 7, size=(O, K)).astype(np.float32)
+    for value in (np.nan, -0.0, -np.inf, np.inf):
+        s[rng.random(s.shape) < 0.04] = value
+    got = host_words(nm.nm_prune_scored(torch.from_numpy(s).cuda(), N, M))
+    assert np.array_equal(got, orc.mask_to_words(orc.nm_mask_from_scores(s, N, M)))
+
+
 @pytest.mark.parametrize("O,K,N,M", [(8, 64, 2, 4), (8, 128, 1, 16), (4, 64, 16, 16), (4, 128, 3, 8), (12, 256, 7, 8),
                                      (4, 128, 13, 16), (257, 64, 1, 4), (3, 1024, 1, 8), (5, 192, 8, 16)])
 def test_unpack_contiguous(O, K, N, M):
