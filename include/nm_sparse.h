@@ -212,7 +212,7 @@ int32_t nm_pack_ranked_batched(const nm_pack_ranked_desc* descs, int32_t count, 
  *                    aligned; may be NULL when that size is 0.  Its contents are undefined
  *                    after the call; concurrent calls need distinct workspaces.
  *                    A layer with few output tiles and a long reduction (one image through a wide layer: T = 197,
- *                    K = 3072) is cut into 2 .. 8 ranges along K; their fp32 partial sums live behind the
+ *                    K = 4096 or more) is cut into 2 .. 8 ranges along K; their fp32 partial sums live behind the
  *                    operand-order copy in the workspace (nm_spmm_workspace_bytes counts them) and a second launch
  *                    adds them in range order.  A workspace that holds the operand-order copy only gives the uncut
  *                    product (same result up to rounding order).
@@ -277,8 +277,15 @@ int32_t nm_linear_forward_static(const nm_bf16* values, const uint32_t* indices,
  *                               calls will use (it selects the same kernels).
  *   nm_linear_forward_prepared  the product alone, reading a workspace that nm_spmm_prepare filled
  *                               for the same (values, indices, O, K, N, M, T); the workspace is
- *                               not modified, so it can serve any number of calls.
- * nm_linear_forward(args) == nm_spmm_prepare(args) followed by nm_linear_forward_prepared(args).
+ *                               not modified, so it can serve any number of calls, also on several
+ *                               streams at once.
+ *   nm_linear_forward_prepared_scratch
+ *                               the same with nm_prepared_scratch_bytes() bytes (0 for most layers), 256-byte aligned,
+ *                               for the partial sums of a layer that is cut along K (see nm_spmm).  Scratch belongs to
+ *                               one call: calls that may overlap need scratch of their own.  With none (or too little)
+ *                               the layer is multiplied uncut, as it is by nm_linear_forward_prepared: the same result
+ *                               up to rounding order, later (197 tokens, 4096 -> 1024 15.0 us for 10.9).
+ * nm_linear_forward(args) == nm_spmm_prepare(args) followed by nm_linear_forward_prepared_scratch(args, scratch).
  */
 int32_t nm_spmm_prepare(const nm_bf16* values, const uint32_t* indices, int64_t O, int64_t K,
                         int32_t N, int32_t M, int64_t T,
@@ -289,6 +296,12 @@ int32_t nm_linear_forward_prepared(const nm_bf16* values, const uint32_t* indice
                                    int64_t ldx, const float* bias, void* Y, int64_t ldy,
                                    int32_t out_dtype, const void* workspace,
                                    size_t workspace_bytes, void* stream);
+size_t nm_prepared_scratch_bytes(int64_t O, int64_t K, int32_t N, int32_t M, int64_t T);
+int32_t nm_linear_forward_prepared_scratch(const nm_bf16* values, const uint32_t* indices, int64_t O,
+                                           int64_t K, int32_t N, int32_t M, const nm_bf16* X, int64_t T,
+                                           int64_t ldx, const float* bias, void* Y, int64_t ldy,
+                                           int32_t out_dtype, const void* workspace, size_t workspace_bytes,
+                                           void* scratch, size_t scratch_bytes, void* stream);
 
 /*
  * nm_linear_forward_prepared_batched -- nm_linear_forward_prepared for every descriptor, in as few launches as
@@ -300,7 +313,10 @@ int32_t nm_linear_forward_prepared(const nm_bf16* values, const uint32_t* indice
  * exception: a layer whose reduction a single call cuts into ranges (few tiles, long K; see nm_spmm) is not cut
  * inside a call that fills the chip anyway, and its sums then differ in rounding order.
  *   descs  HOST array of `count` descriptors, read before the call returns.  Fields as the arguments of
- *          nm_linear_forward_prepared; the outputs must not overlap each other or any input.
+ *          nm_linear_forward_prepared; the outputs must not overlap each other or any input.  Descriptors may share a
+ *          workspace (one layer on two inputs).
+ *   nm_linear_forward_prepared_batched_scratch  the same with scratch of the call's own for the layers that are cut, as
+ *          for nm_linear_forward_prepared_scratch: nm_prepared_batched_scratch_bytes() bytes (0 for most calls).
  * Errors as for nm_linear_forward_prepared (the first offending descriptor decides); nothing is launched on an
  * argument error or a short workspace.
  */
@@ -315,10 +331,13 @@ typedef struct nm_forward_desc {
   void* Y;                  /* device, out, [T, O], ld ldy */
   int64_t ldy;
   int32_t out_dtype, reserved;
-  void* workspace;          /* filled by nm_spmm_prepare / nm_pack_prepare_batched for this layer and T */
+  void* workspace;          /* filled by nm_spmm_prepare / nm_pack_prepare_batched for this layer and T; only read */
   size_t workspace_bytes;
 } nm_forward_desc;
 int32_t nm_linear_forward_prepared_batched(const nm_forward_desc* descs, int32_t count, void* stream);
+size_t nm_prepared_batched_scratch_bytes(const nm_forward_desc* descs, int32_t count);
+int32_t nm_linear_forward_prepared_batched_scratch(const nm_forward_desc* descs, int32_t count, void* scratch,
+                                                   size_t scratch_bytes, void* stream);
 
 /*
  * Training products of one sparse layer (Section 3.2: in every step the gradient of the loss is taken with

@@ -34,7 +34,8 @@ EXPORTS = (
     "nm_rank_bytes", "nm_rank", "nm_rank_batched", "nm_rank_mask", "nm_pack_ranked", "nm_pack_ranked_batched", "nm_pack_prepare_batched",
     "nm_config_cost", "nm_sample_config",
     "nm_backward_input_workspace_bytes", "nm_backward_weight_workspace_bytes", "nm_linear_backward_input", "nm_linear_backward_weight",
-    "nm_linear_forward_prepared_batched", "nm_prune_scored", "nm_i8_workspace_bytes", "nm_linear_forward_i8", "nm_i8_prepare", "nm_linear_forward_i8_prepared",
+    "nm_linear_forward_prepared_batched", "nm_prepared_scratch_bytes", "nm_linear_forward_prepared_scratch",
+    "nm_prepared_batched_scratch_bytes", "nm_linear_forward_prepared_batched_scratch", "nm_prune_scored", "nm_i8_workspace_bytes", "nm_linear_forward_i8", "nm_i8_prepare", "nm_linear_forward_i8_prepared",
 )
 
 
@@ -134,6 +135,10 @@ def load_library() -> ctypes.CDLL:
                                     c_void_p]
     lib.nm_linear_forward_prepared.restype = c_int32
     lib.nm_linear_forward_prepared.argtypes = lib.nm_linear_forward.argtypes
+    lib.nm_prepared_scratch_bytes.restype = c_size_t
+    lib.nm_prepared_scratch_bytes.argtypes = [c_int64, c_int64, c_int32, c_int32, c_int64]
+    lib.nm_linear_forward_prepared_scratch.restype = c_int32
+    lib.nm_linear_forward_prepared_scratch.argtypes = lib.nm_linear_forward.argtypes[:-1] + [c_void_p, c_size_t, c_void_p]
     lib.nm_static_scratch_bytes.restype = c_size_t
     lib.nm_static_scratch_bytes.argtypes = []
     lib.nm_linear_forward_static.restype = c_int32
@@ -179,6 +184,10 @@ def load_library() -> ctypes.CDLL:
                                               c_void_p, c_int64, c_int32, c_void_p, c_size_t, c_void_p]
     lib.nm_linear_forward_prepared_batched.restype = c_int32
     lib.nm_linear_forward_prepared_batched.argtypes = [ctypes.POINTER(ForwardDesc), c_int32, c_void_p]
+    lib.nm_prepared_batched_scratch_bytes.restype = c_size_t
+    lib.nm_prepared_batched_scratch_bytes.argtypes = [ctypes.POINTER(ForwardDesc), c_int32]
+    lib.nm_linear_forward_prepared_batched_scratch.restype = c_int32
+    lib.nm_linear_forward_prepared_batched_scratch.argtypes = [ctypes.POINTER(ForwardDesc), c_int32, c_void_p, c_size_t, c_void_p]
     lib.nm_prune_scored.restype = c_int32
     lib.nm_prune_scored.argtypes = [c_void_p, c_int64, c_int64, c_int64, c_int32, c_int32, c_void_p, c_void_p]
     lib.nm_i8_workspace_bytes.restype = c_size_t
@@ -592,6 +601,19 @@ def _workspace(nbytes: int, device, stream=None):
     return ws
 
 
+def _own_scratch(nbytes: int, stream=None):
+    """A scratch tensor of one call, allocated on its stream: once dropped, its memory goes to later work of that stream
+    only (under graph capture, of that graph)."""
+    torch = _torch()
+    if stream is None:
+        return torch.empty((nbytes,), dtype=torch.uint8, device="cuda")
+    if not isinstance(stream, torch.cuda.Stream):
+        handle = _stream_handle(stream)
+        stream = torch.cuda.ExternalStream(handle) if handle else torch.cuda.default_stream()
+    with torch.cuda.stream(stream):
+        return torch.empty((nbytes,), dtype=torch.uint8, device="cuda")
+
+
 def nm_spmm_prepare(values, indices, K: int, N: int, M: int, T: int, workspace=None, stream=None):
     """Fill (and return) the workspace nm_linear_forward_prepared reads; None if the level needs none."""
     torch = _torch()
@@ -640,9 +662,15 @@ def nm_linear_forward(values, indices, K: int, N: int, M: int, X, bias=None, out
         elif need and K % 64 == 0:  # (a ragged reduction can do without one)
             raise ValueError("a prepared call needs the workspace nm_spmm_prepare filled")
     ws_ptr, ws_bytes = _scratch(workspace)
-    fn = lib.nm_linear_forward_prepared if _prepared else lib.nm_linear_forward
-    _check(fn(values.data_ptr(), indices.data_ptr(), O, K, N, M, X.data_ptr(), T, ldx, _per_feature(bias, O, "bias"),
-              out.data_ptr(), ldy, code, ws_ptr, ws_bytes, _stream_handle(stream)))
+    args = (values.data_ptr(), indices.data_ptr(), O, K, N, M, X.data_ptr(), T, ldx, _per_feature(bias, O, "bias"),
+            out.data_ptr(), ldy, code, ws_ptr, ws_bytes)
+    # partial sums of a prepared layer that is cut (a workspace of the operand part alone asks for the uncut product)
+    need = lib.nm_prepared_scratch_bytes(O, K, N, M, T) if _prepared else 0
+    if need and ws_bytes >= lib.nm_spmm_workspace_bytes(O, K, N, M, T):
+        scratch = _own_scratch(need, stream)
+        _check(lib.nm_linear_forward_prepared_scratch(*args, scratch.data_ptr(), need, _stream_handle(stream)))
+    else:
+        _check((lib.nm_linear_forward_prepared if _prepared else lib.nm_linear_forward)(*args, _stream_handle(stream)))
     return out
 
 
@@ -796,7 +824,10 @@ def nm_linear_forward_prepared_batched(layers, stream=None):
     """The products of many prepared layers in as few launches as their shapes allow; `layers` is a list of
     (values, indices, K, N, M, X, workspace, bias or None, out) or an array made by forward_descs."""
     descs = layers if isinstance(layers, ctypes.Array) else forward_descs(layers)
-    _check(load_library().nm_linear_forward_prepared_batched(descs, len(descs), _stream_handle(stream)))
+    lib = load_library()
+    need = lib.nm_prepared_batched_scratch_bytes(descs, len(descs))  # partial sums of the layers that are cut
+    scratch = _own_scratch(need, stream) if need else None
+    _check(lib.nm_linear_forward_prepared_batched_scratch(descs, len(descs), *_scratch(scratch), _stream_handle(stream)))
 
 
 def nm_i8_workspace_bytes(O: int, K: int, N: int, M: int, T: int) -> int:

@@ -236,20 +236,41 @@ int32_t spmm_check(const nm_bf16* values, const uint32_t* indices, int64_t O, in
   a->X = X; a->T = T; a->ldx = product ? ldx : K; a->bias = bias; a->Y = Y; a->ldy = ldy;
   a->out_bf16 = (out_dtype == NM_OUT_BF16);
   a->workspace = workspace; a->workspace_bytes = workspace_bytes;
+  a->scratch = nullptr; a->scratch_bytes = 0;
   return NM_OK;
 }
 
 int32_t spmm_entry(const nm_bf16* values, const uint32_t* indices, int64_t O, int64_t K, int32_t N, int32_t M,
                    const nm_bf16* X, int64_t T, int64_t ldx, const float* bias, void* Y, int64_t ldy, int32_t out_dtype,
-                   void* workspace, size_t workspace_bytes, void* stream, int phases) {
+                   void* workspace, size_t workspace_bytes, void* scratch, size_t scratch_bytes, void* stream, int phases) {
   nm::SpmmArgs a;
   if (int32_t st = spmm_check(values, indices, O, K, N, M, X, T, ldx, bias, Y, ldy, out_dtype, workspace, workspace_bytes,
                               phases & nm::SPMM_PRODUCT, &a))
     return st;
+  a.scratch = scratch; a.scratch_bytes = scratch_bytes;
+  if (phases & nm::SPMM_PREPARE) nm::spmm_scratch_behind_operand(&a);
   bool workspace_short = false;
   hipError_t e = nm::launch_spmm(a, (hipStream_t)stream, &workspace_short, phases);
   if (workspace_short) return NM_ERR_WORKSPACE;
   return device_status(e);
+}
+
+int32_t forward_args(const nm_forward_desc& d, nm::SpmmArgs* a) {
+  return spmm_check(d.values, d.indices, d.O, d.K, d.N, d.M, d.X, d.T, d.ldx, d.bias, d.Y, d.ldy, d.out_dtype, d.workspace,
+                    d.workspace_bytes, true, a);
+}
+// f(layers, how many) for runs of descriptors, converted without an allocation; ends with the first status that is not NM_OK
+template <class F>
+int32_t forward_chunks(const nm_forward_desc* descs, int32_t count, F&& f) {
+  constexpr int kChunk = 64;
+  nm::SpmmArgs layers[kChunk];
+  for (int32_t first = 0; first < count; first += kChunk) {
+    const int n = count - first < kChunk ? count - first : kChunk;
+    for (int i = 0; i < n; ++i)
+      if (int32_t st = forward_args(descs[first + i], &layers[i])) return st;
+    if (int32_t st = f(layers, n)) return st;
+  }
+  return NM_OK;
 }
 
 // the int8 layer from the dense weight + mask (values == NULL) or from the compressed form (Wq == NULL)
@@ -287,29 +308,43 @@ extern "C" {
 int32_t nm_linear_forward(const nm_bf16* values, const uint32_t* indices, int64_t O, int64_t K, int32_t N, int32_t M,
                           const nm_bf16* X, int64_t T, int64_t ldx, const float* bias, void* Y, int64_t ldy,
                           int32_t out_dtype, void* workspace, size_t workspace_bytes, void* stream) {
-  return spmm_entry(values, indices, O, K, N, M, X, T, ldx, bias, Y, ldy, out_dtype, workspace, workspace_bytes, stream,
-                    nm::SPMM_PREPARE | nm::SPMM_PRODUCT);
+  return spmm_entry(values, indices, O, K, N, M, X, T, ldx, bias, Y, ldy, out_dtype, workspace, workspace_bytes, nullptr, 0,
+                    stream, nm::SPMM_PREPARE | nm::SPMM_PRODUCT);
 }
 
 int32_t nm_spmm(const nm_bf16* values, const uint32_t* indices, int64_t O, int64_t K, int32_t N, int32_t M,
                 const nm_bf16* X, int64_t T, int64_t ldx, void* Y, int64_t ldy, int32_t out_dtype, void* workspace,
                 size_t workspace_bytes, void* stream) {
   return spmm_entry(values, indices, O, K, N, M, X, T, ldx, nullptr, Y, ldy, out_dtype, workspace, workspace_bytes,
-                    stream, nm::SPMM_PREPARE | nm::SPMM_PRODUCT);
+                    nullptr, 0, stream, nm::SPMM_PREPARE | nm::SPMM_PRODUCT);
 }
 
 int32_t nm_spmm_prepare(const nm_bf16* values, const uint32_t* indices, int64_t O, int64_t K, int32_t N, int32_t M,
                         int64_t T, void* workspace, size_t workspace_bytes, void* stream) {
   return spmm_entry(values, indices, O, K, N, M, nullptr, T, K, nullptr, nullptr, O, NM_OUT_F32, workspace,
-                    workspace_bytes, stream, nm::SPMM_PREPARE);
+                    workspace_bytes, nullptr, 0, stream, nm::SPMM_PREPARE);
 }
 
 int32_t nm_linear_forward_prepared(const nm_bf16* values, const uint32_t* indices, int64_t O, int64_t K, int32_t N,
                                    int32_t M, const nm_bf16* X, int64_t T, int64_t ldx, const float* bias, void* Y,
                                    int64_t ldy, int32_t out_dtype, const void* workspace, size_t workspace_bytes,
                                    void* stream) {
+  return nm_linear_forward_prepared_scratch(values, indices, O, K, N, M, X, T, ldx, bias, Y, ldy, out_dtype, workspace,
+                                            workspace_bytes, nullptr, 0, stream);
+}
+
+size_t nm_prepared_scratch_bytes(int64_t O, int64_t K, int32_t N, int32_t M, int64_t T) {
+  if (check_weight(O, K, N, M) != NM_OK || T <= 0) return 0;
+  return nm::spmm_partial_bytes(O, K, N, M, T);
+}
+
+int32_t nm_linear_forward_prepared_scratch(const nm_bf16* values, const uint32_t* indices, int64_t O, int64_t K, int32_t N,
+                                           int32_t M, const nm_bf16* X, int64_t T, int64_t ldx, const float* bias, void* Y,
+                                           int64_t ldy, int32_t out_dtype, const void* workspace, size_t workspace_bytes,
+                                           void* scratch, size_t scratch_bytes, void* stream) {
+  // (the product alone writes Y and the scratch, never the workspace)
   return spmm_entry(values, indices, O, K, N, M, X, T, ldx, bias, Y, ldy, out_dtype, const_cast<void*>(workspace),
-                    workspace_bytes, stream, nm::SPMM_PRODUCT);
+                    workspace_bytes, scratch, scratch_bytes, stream, nm::SPMM_PRODUCT);
 }
 
 size_t nm_static_scratch_bytes(void) { return kStaticScratchBytes; }
@@ -325,6 +360,7 @@ int32_t nm_linear_forward_static(const nm_bf16* values, const uint32_t* indices,
   if (int32_t st = device_status(static_scratch(&ws))) return st;
   a.workspace = ws;
   a.workspace_bytes = kStaticScratchBytes;
+  nm::spmm_scratch_behind_operand(&a);
   bool workspace_short = false;
   hipError_t e = nm::launch_spmm_on_scratch(a, (hipStream_t)stream, &workspace_short);
   if (workspace_short) return NM_ERR_WORKSPACE;
@@ -477,25 +513,35 @@ int32_t nm_probe_copy(const void* src, void* dst, size_t bytes, void* stream) {
 }
 
 int32_t nm_linear_forward_prepared_batched(const nm_forward_desc* descs, int32_t count, void* stream) {
+  return nm_linear_forward_prepared_batched_scratch(descs, count, nullptr, 0, stream);
+}
+
+size_t nm_prepared_batched_scratch_bytes(const nm_forward_desc* descs, int32_t count) {
+  if (!descs) return 0;
+  size_t most = 0;
+  const int32_t st = forward_chunks(descs, count, [&](nm::SpmmArgs* layers, int n) {
+    const size_t bytes = nm::spmm_batched_scratch(layers, n, nullptr, 0);
+    most = bytes > most ? bytes : most;
+    return (int32_t)NM_OK;
+  });
+  return st == NM_OK ? most : 0;
+}
+
+int32_t nm_linear_forward_prepared_batched_scratch(const nm_forward_desc* descs, int32_t count, void* scratch,
+                                                   size_t scratch_bytes, void* stream) {
   if (!descs) return NM_ERR_NULL;
   if (count <= 0) return NM_ERR_SHAPE;
-  constexpr int kChunk = 64;  // descriptors converted at a time (no allocation)
-  nm::SpmmArgs layers[kChunk];
-  auto convert = [&](int32_t i, nm::SpmmArgs* a) {
-    const nm_forward_desc& d = descs[i];
-    return spmm_check(d.values, d.indices, d.O, d.K, d.N, d.M, d.X, d.T, d.ldx, d.bias, d.Y, d.ldy, d.out_dtype,
-                      d.workspace, d.workspace_bytes, true, a);
-  };
-  for (int32_t i = 0; i < count; ++i) {  // every argument error is reported before anything is launched
-    if (int32_t st = convert(i, &layers[0])) return st;
-    if (nm::spmm_workspace_short(layers[0])) return NM_ERR_WORKSPACE;
+  // every argument error is reported before anything is launched
+  for (int32_t i = 0; i < count; ++i) {
+    nm::SpmmArgs a;
+    if (int32_t st = forward_args(descs[i], &a)) return st;
+    if (nm::spmm_workspace_short(a)) return NM_ERR_WORKSPACE;
   }
-  for (int32_t first = 0; first < count; first += kChunk) {
-    const int n = count - first < kChunk ? count - first : kChunk;
-    for (int i = 0; i < n; ++i) convert(first + i, &layers[i]);
-    if (int32_t st = device_status(nm::launch_spmm_batched(layers, n, (hipStream_t)stream))) return st;
-  }
-  return NM_OK;
+  // the launches of one run of layers follow those of the one before, so that all runs use the scratch from its start
+  return forward_chunks(descs, count, [&](nm::SpmmArgs* layers, int n) {
+    nm::spmm_batched_scratch(layers, n, scratch, scratch_bytes);
+    return device_status(nm::launch_spmm_batched(layers, n, (hipStream_t)stream));
+  });
 }
 
 }  // extern "C"

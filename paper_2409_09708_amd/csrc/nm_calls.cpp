@@ -244,6 +244,8 @@ PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
       !matrix(*X, &x) || x.cols != K || !integer(a[11], 0, 3, &how))
     return declined();
   const int64_t O = values->size(0), T = x.rows;
+  // a prepared layer that may be cut along K (64 steps or more on fewer than 128 tiles): Python brings the scratch of the call
+  if (how == 1 && K >= 4096 && (O + 127) / 128 * ((T + 127) / 128) < 128) return declined();
   if (a[6] != Py_None && (!plain(a[6], at::kFloat, &bias) || bias->numel() != O || !bias->is_contiguous())) return declined();
   int32_t code;
   at::Tensor made;

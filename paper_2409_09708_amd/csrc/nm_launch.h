@@ -123,11 +123,15 @@ struct SpmmArgs {
   void* Y;
   int64_t ldy;
   int out_bf16;
-  void* workspace;
+  void* workspace;  // SPMM_PRODUCT alone only reads it: calls on any streams share a prepared layer
   size_t workspace_bytes;
+  void* scratch;    // of this call alone: partial sums of a cut reduction (nullable, or too small: the product is not cut)
+  size_t scratch_bytes;
 };
 size_t spmm_workspace_bytes(int64_t O, int64_t K, int N, int M, int64_t T);
 size_t spmm_operand_workspace_bytes(int64_t O, int64_t K, int N, int M, int64_t T);  // the part that is required
+size_t spmm_partial_bytes(int64_t O, int64_t K, int N, int M, int64_t T);  // scratch of a cut reduction, 0 if it is not cut
+void spmm_scratch_behind_operand(SpmmArgs* a);  // the workspace is this call's own: what lies behind the operand copy is scratch
 bool spmm_stream_order(int64_t O, int64_t K, int64_t T, int N, int M, bool* sparse_form);
 // phases: SPMM_PREPARE rewrites the packed weight into matrix-core operand order in the workspace,
 // SPMM_PRODUCT multiplies (expects a prepared workspace); both = the whole call.
@@ -140,6 +144,8 @@ hipError_t launch_spmm_on_scratch(const SpmmArgs& a, hipStream_t s, bool* worksp
 // (the caller has checked the workspaces with spmm_workspace_short)
 bool spmm_workspace_short(const SpmmArgs& a);
 hipError_t launch_spmm_batched(const SpmmArgs* layers, int count, hipStream_t s);
+// gives each layer of a batched call that is cut its piece of `scratch`, as far as it reaches; returns the bytes they all take
+size_t spmm_batched_scratch(SpmmArgs* layers, int count, void* scratch, size_t scratch_bytes);
 
 // nm_fewtok.hip: products at few tokens straight from the packed format (no workspace)
 bool fewtok_shape(int64_t O, int64_t K, int N, int M, int64_t T);

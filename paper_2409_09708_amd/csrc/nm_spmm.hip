@@ -1601,18 +1601,18 @@ bool spmm_stream_order(int64_t O, int64_t K, int64_t T, int N, int M, bool* spar
 }
 
 // Ranges the reduction of a layer on the tiled kernel is cut into: a layer with far fewer tiles than the chip has
-// compute units and a long K (one image through a wide MLP: 197 tokens, K = 3072) leaves most units idle for many
+// compute units and a long K (one image through a wide MLP: 197 tokens, K = 4096) leaves most units idle for many
 // steps; cut into ranges of at least 12 steps, it fills them, at the price of fp32 partial sums through memory and
 // a reduce launch (about 5 us: below 64 steps the cut gains nothing; measured on ViT-S .. ViT-H shaped layers).
 // A function of the shape alone.
 static int split_count(int64_t O, int64_t K, int64_t T, bool sparse_form) {
-  if (K % 64) return 1;
+  const int64_t steps = K / 64;
+  if (K % 64 || steps < 64) return 1;
   const int pick = pick_tile(O, K, T, sparse_form);
   if (pick == 0) return 1;
   const int64_t side = pick == 2 ? 128 : 64;
   const int64_t tiles = ((O + side - 1) / side) * ((T + side - 1) / side);
-  const int64_t steps = K / 64;
-  if (tiles >= 128 || steps < 64) return 1;
+  if (tiles >= 128) return 1;
   int64_t n = 256 / tiles;
   if (n > steps / 12) n = steps / 12;
   if (n > 8) n = 8;
@@ -1634,13 +1634,27 @@ size_t spmm_operand_workspace_bytes(int64_t O, int64_t K, int N, int M, int64_t 
   return operand_bytes(O, K, N, M, T, &sparse_form);
 }
 
+// Partial sums of a cut reduction.  They belong to one call: a prepared layer's workspace serves calls on several streams at
+// once, and two layers of a batched call may share it, so a call that does not own its workspace brings them beside it.
+size_t spmm_partial_bytes(int64_t O, int64_t K, int N, int M, int64_t T) {
+  const int splits = split_count(O, K, T, N <= 2 && N < M);
+  return splits < 2 ? 0 : (size_t)splits * (size_t)T * (size_t)O * 4;
+}
+
 // Workspace of a product: the operand-order copy (if the level needs one), then the partial sums of a cut reduction.
 size_t spmm_workspace_bytes(int64_t O, int64_t K, int N, int M, int64_t T) {
   bool sparse_form = false;
   const size_t operand = operand_bytes(O, K, N, M, T, &sparse_form);
-  const int splits = split_count(O, K, T, sparse_form);
-  if (splits < 2) return operand;
-  return ((operand + 255) / 256) * 256 + (size_t)splits * (size_t)T * (size_t)O * 4;
+  const size_t partial = spmm_partial_bytes(O, K, N, M, T);
+  return partial ? ((operand + 255) / 256) * 256 + partial : operand;
+}
+
+void spmm_scratch_behind_operand(SpmmArgs* a) {
+  bool sparse_form = false;
+  const size_t at = (operand_bytes(a->O, a->K, a->N, a->M, a->T, &sparse_form) + 255) / 256 * 256;
+  if (a->workspace == nullptr || a->workspace_bytes <= at) return;
+  a->scratch = static_cast<unsigned char*>(a->workspace) + at;
+  a->scratch_bytes = a->workspace_bytes - at;
 }
 
 // The reduce launch of layers whose reduction was cut: split_group_append lists a layer (false: table full),
@@ -2142,17 +2156,12 @@ static void fill_gemm_args(const SpmmArgs& a, int form, bool sparse_form, GemmAr
                  (a.bias == nullptr || aligned_to(a.bias, 16));
   g->stream_form = form == FORM_STREAM;
   {
-    bool sf = false;
-    const size_t operand = operand_bytes(a.O, a.K, a.N, a.M, a.T, &sf);
     int splits = split_count(a.O, a.K, a.T, sparse_form);
-    // the partial sums need the full workspace; a caller that brings the operand part only gets the uncut product
-    if (splits > 1 && (a.workspace == nullptr || !aligned_to(a.workspace, 256) ||
-                       a.workspace_bytes < ((operand + 255) / 256) * 256 + (size_t)splits * (size_t)a.T * (size_t)a.O * 4))
+    if (splits > 1 && (a.scratch == nullptr || !aligned_to(a.scratch, 256) ||
+                       a.scratch_bytes < (size_t)splits * (size_t)a.T * (size_t)a.O * 4))
       splits = 1;
     g->splits = (uint8_t)splits;
-    g->partial = splits > 1 ? reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(a.workspace) +
-                                                       ((operand + 255) / 256) * 256)
-                            : nullptr;
+    g->partial = splits > 1 ? static_cast<float*>(a.scratch) : nullptr;
   }
   if (form == FORM_STREAM) {
     const int64_t o_pad = ((a.O + 255) / 256) * 256;
@@ -2347,6 +2356,37 @@ bool spmm_workspace_short(const SpmmArgs& a) {
   return need && (a.workspace == nullptr || a.workspace_bytes < need || !aligned_to(a.workspace, 256));
 }
 
+// A layer alone takes 64 x 64 tiles when 128 x 128 ones would leave most compute units idle; the layers of a
+// call fill the chip together, so they take the larger tiles (half the operand traffic into the compute
+// units per output) as soon as the call holds enough of them.  A sum is accumulated in the same order under
+// either tile size, so the outputs are the same bytes.
+static bool batch_promotes(const SpmmArgs* layers, int count) {
+  int64_t mid_tiles = 0;
+  for (int i = 0; i < count; ++i) {
+    GemmArgs g;
+    bool sparse_form = false;
+    int pick = 0;
+    if (tiled_entry(layers[i], &g, &sparse_form, &pick))
+      mid_tiles += ((layers[i].O + 127) / 128) * ((layers[i].T + 127) / 128);
+  }
+  return mid_tiles >= 256;
+}
+
+size_t spmm_batched_scratch(SpmmArgs* layers, int count, void* scratch, size_t scratch_bytes) {
+  size_t end = 0;
+  for (int i = 0; i < count; ++i) {
+    SpmmArgs& a = layers[i];
+    const size_t bytes = spmm_partial_bytes(a.O, a.K, a.N, a.M, a.T);
+    if (bytes == 0) continue;
+    if (scratch != nullptr && scratch_bytes >= end + bytes) {
+      a.scratch = static_cast<unsigned char*>(scratch) + end;
+      a.scratch_bytes = bytes;
+    }
+    end += (bytes + 255) / 256 * 256;
+  }
+  return end != 0 && batch_promotes(layers, count) ? 0 : end;  // (such a call cuts nothing)
+}
+
 // LDS stages of the dense-form 128 x 128 tiles in a shared launch: two (64 KB) instead of three (96 KB) keep the
 // launch's LDS at the 2:4 form's 75 KB, so that two blocks share a compute unit (48 layers at 197 tokens: 62 us
 // against 70 us with three).
@@ -2386,19 +2426,7 @@ hipError_t launch_spmm_batched(const SpmmArgs* layers, int count, hipStream_t s)
     return which == 0 ? launch_gemm_group<2, 2, 4, 4, 3, kGroupDenseStages, true>(tile_grp[0], s)
                       : launch_gemm_group<2, 2, 2, 2, 3, 3, false>(tile_grp[1], s);
   };
-  // A layer alone takes 64 x 64 tiles when 128 x 128 ones would leave most compute units idle; the layers of a
-  // call fill the chip together, so they take the larger tiles (half the operand traffic into the compute
-  // units per output) as soon as the call holds enough of them.  A sum is accumulated in the same order under
-  // either tile size, so the outputs are the same bytes.
-  int64_t mid_tiles = 0;
-  for (int i = 0; i < count; ++i) {
-    GemmArgs g;
-    bool sparse_form = false;
-    int pick = 0;
-    if (tiled_entry(layers[i], &g, &sparse_form, &pick))
-      mid_tiles += ((layers[i].O + 127) / 128) * ((layers[i].T + 127) / 128);
-  }
-  const bool promote = mid_tiles >= 256;
+  const bool promote = batch_promotes(layers, count);
   // few tokens and no workspace: all such layers of the call in one launch of the kernel that reads the packed format
   {
     constexpr int kChunk = 64;

@@ -520,3 +520,36 @@ def test_shapes_of_the_tile_and_height_tests_reach_them():
     for cases in (heights.CASES, heights.INT8_CASES):
         for sparse in (True, False):
             assert {t for _, (N, M), t in cases if (N <= 2 and N < M) == sparse} == {128, 160, 192, 224, 256}
+
+
+def test_scratch_of_a_cut_prepared_layer(lib):
+    # the partial sums that a plain call keeps behind the operand copy; a prepared call brings them, its workspace is only read
+    T, K, O = 197, 4096, 1024
+    planes = lib.nm_prepared_scratch_bytes(O, K, 2, 4, T)
+    assert planes % (T * O * 4) == 0 and 2 <= planes // (T * O * 4) <= 8
+    for N, M, operand in ((2, 4, 0), (8, 8, 0), (1, 8, O * K + O * K // 8), (4, 8, O * K * 2)):
+        assert lib.nm_spmm_workspace_bytes(O, K, N, M, T) == operand + lib.nm_prepared_scratch_bytes(O, K, N, M, T)
+    for K_, T_ in ((1024, T), (4096, 50432), (4100, T)):  # short, many tiles, ragged: never cut
+        assert lib.nm_prepared_scratch_bytes(O, K_, 2, 4, T_) == 0
+    assert lib.nm_prepared_scratch_bytes(O, K, 5, 4, T) == 0 and lib.nm_prepared_scratch_bytes(O, K, 2, 4, 0) == 0
+
+
+def test_scratch_of_a_batched_call(lib):
+    D = binding.ForwardDesc
+    ok = dict(values=FAKE, indices=FAKE, O=1024, K=4096, N=2, M=4, X=FAKE, T=197, ldx=4096, bias=None, Y=FAKE, ldy=1024,
+              out_dtype=0, reserved=0, workspace=None, workspace_bytes=0)
+
+    def size(*overrides):
+        d = (D * len(overrides))()
+        for n, kw in enumerate(overrides):
+            d[n] = D(**dict(ok, **kw))
+        return lib.nm_prepared_batched_scratch_bytes(d, len(overrides))
+
+    one = lib.nm_prepared_scratch_bytes(1024, 4096, 2, 4, 197)
+    small = dict(O=64, K=4160, ldx=4160, ldy=64, T=33)  # 8448-byte planes: the next layer's begin on a 256-byte boundary
+    planes = lib.nm_prepared_scratch_bytes(64, 4160, 2, 4, 33)
+    assert planes > 0 and size(small, small) == 2 * ((planes + 255) // 256 * 256)
+    assert size({}) == one and size({}, {}) == 2 * one and size({}, dict(K=768, ldx=768)) == one
+    assert size(*[{}] * 16) == 0                       # fills the chip with whole reductions
+    assert size(*[dict(O=64, ldy=64)] * 100) == 64 * lib.nm_prepared_scratch_bytes(64, 4096, 2, 4, 197)  # runs of 64 share it
+    assert size({}, dict(N=5)) == 0 and lib.nm_prepared_batched_scratch_bytes(None, 1) == 0
