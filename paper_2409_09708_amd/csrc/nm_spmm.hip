@@ -1711,7 +1711,7 @@ static int64_t tile_layer_units(const TileLayer& L) {
 template <int BO, int BT>
 static int64_t tile_layer_blocks(const TileLayer& L) { return (tile_layer_units<BO, BT>(L) + 7) / 8 * 8; }
 constexpr double kTileBlockUs = 2.0;   // a block's start and write-out
-constexpr double kNarrowShare = 1.25;
+constexpr double kNarrowShare = 1.5, kNarrowShareDeep = 1.25;
 // estimated duration of one of the layer's blocks (the model of pick_tile): the order of the launch
 static double tile_layer_cost(const TileLayer& L) {
   const int n = L.splits > 1 ? L.splits : 1;
@@ -1724,8 +1724,13 @@ static double tile_layer_cost(const TileLayer& L) {
 // 26.9, 24 43.0 -> 32.7, 32 at C = 512 32.6 -> 25.9.  The line, with weights from memory: 48 linears at C = 768 whose deep
 // dense layers run 1.28 or 1.29 shares 60.2 -> 57.9 and 60.0 -> 57.4 us, 44 (1.41) 58.5 -> 52.5, 32 (the 2:4 form at 1.33
 // too) 48.6 -> 45.0; below it the activations read by twice the blocks cost more: 48 with more such layers (1.23) 61.6 and
-// 62.1 narrow, 61.7 and 62.7, 40 with the 2:4 form at 1.08 narrow as well 50.9 and 53.9.  The 2:4 form of more than 512
-// tokens, whose X is then read by many more blocks, keeps its tiles (8 linears at 788 tokens 31.0, 33.4 narrow).
+// 62.1 narrow, 61.7 and 62.7, 40 with the 2:4 form at 1.08 narrow as well 50.9 and 53.9.
+// Shallow layers, where most of a block is its start and write-out, take narrow tiles from 1.5 shares on.  792 calls of 1 to 12
+// blocks at C = 128 to 768, 1 to 4 images: between 1.25 and 1.5 narrow tiles gain 2 to 8 % on average in the deep layers (K >= 1024;
+// single level draws from 5 % slower to 13 % faster), 1 to 2 % in the 2:4 form from K = 256 on, nothing in the dense form of K = 256
+// to 640 (0.95 to 1.05), and lose at K = 128 (40 linears of 394 tokens 9.8 us, 11.0 narrow; 44 9.9 and 11.1).
+// The 2:4 form of more than 512 tokens, whose X is then read by many more blocks, keeps its tiles (8 linears at 788 tokens
+// 31.0, 33.4 narrow).
 template <int BO, int BT>
 static void tile_group_narrow(TileGroup& grp) {
   double total = 0;
@@ -1734,7 +1739,8 @@ static void tile_group_narrow(TileGroup& grp) {
   const double even = total / (2.0 * kModelUnits);  // two blocks share a unit
   for (int i = 0; i < grp.count; ++i) {
     TileLayer& L = grp.layer[i];
-    L.narrow = L.splits <= 1 && !(L.sparse_form && L.T > 512) && tile_layer_cost(L) + kTileBlockUs > kNarrowShare * even;
+    const double share = L.K >= (L.sparse_form ? 256u : 1024u) ? kNarrowShareDeep : kNarrowShare;
+    L.narrow = L.splits <= 1 && !(L.sparse_form && L.T > 512) && tile_layer_cost(L) + kTileBlockUs > share * even;
   }
 }
 
@@ -1753,6 +1759,21 @@ static bool tile_group_append(TileGroup& grp, const GemmArgs& g, bool sparse_for
   if (total > 0x7FFFFFF0) return false;
   ++grp.count;
   return true;
+}
+
+// Not in the public header, for tests: which layers of one launch of 128 x 128 tiles take tiles of 64 out-features.
+extern "C" int32_t nm_internal_narrow_layers(int32_t count, const int64_t* O, const int64_t* K, const int64_t* T,
+                                             const int32_t* sparse_form, int32_t* narrow) {
+  TileGroup grp;
+  grp.count = 0;
+  for (int i = 0; i < count; ++i) {
+    GemmArgs g = {};
+    g.O = O[i]; g.K = K[i]; g.T = T[i]; g.splits = 1;
+    if (!tile_group_append<2, 2, 4, 4>(grp, g, sparse_form[i])) return -1;
+  }
+  tile_group_narrow<128, 128>(grp);
+  for (int i = 0; i < count; ++i) narrow[i] = (int32_t)grp.layer[i].narrow;
+  return 0;
 }
 
 template <int WO, int WT, int OT, int TT, int SS, int SD, bool NARROW>

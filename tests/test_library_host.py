@@ -553,3 +553,36 @@ def test_scratch_of_a_batched_call(lib):
     assert size(*[{}] * 16) == 0                       # fills the chip with whole reductions
     assert size(*[dict(O=64, ldy=64)] * 100) == 64 * lib.nm_prepared_scratch_bytes(64, 4096, 2, 4, 197)  # runs of 64 share it
     assert size({}, dict(N=5)) == 0 and lib.nm_prepared_batched_scratch_bytes(None, 1) == 0
+
+
+def narrow_layers(lib, layers):
+    """Which of (O, K, T, 2:4 form) take tiles of 64 out-features when they share a launch."""
+    n = len(layers)
+    out = (ctypes.c_int32 * n)()
+    columns = [(ctypes.c_int64 * n)(*[layer[c] for layer in layers]) for c in range(3)]
+    assert lib.nm_internal_narrow_layers(n, *columns, (ctypes.c_int32 * n)(*[int(layer[3]) for layer in layers]), out) == 0
+    return list(out)
+
+
+def block_layers(C, T, dense):
+    return [(3 * C, C, T, not dense[0]), (C, C, T, not dense[1]), (4 * C, C, T, not dense[2]), (C, 4 * C, T, not dense[3])]
+
+
+def test_shallow_layers_of_a_batched_call_keep_their_tiles(lib):
+    # blocks of two steps run 1.25 to 1.5 times the even share of a call of 9 to 11 small blocks, and most of its tiles are such:
+    # only the layers beyond 1.5 (here the deepest, of 8 steps) take narrow ones
+    for blocks in (9, 10, 11):
+        layers = sum((block_layers(128, 394, [b % 3 == n for n in range(4)]) for b in range(blocks)), [])
+        narrow = narrow_layers(lib, layers)
+        assert all(narrow[n] == 0 for n in range(len(layers)) if layers[n][1] == 128 and layers[n][3])
+        assert all(narrow[n] == 1 for n in range(len(layers)) if layers[n][1] == 512)
+    # dense blocks of 10 steps at 1.45 shares keep them as well, 2:4 ones of 4 steps at 1.34 do not
+    layers = sum((block_layers(640, 197, [b == 1, b == 0, b == 2, False]) for b in range(4)), [])
+    assert [n for n, f in enumerate(narrow_layers(lib, layers)) if f] == [3, 7, 11, 15]
+    layers = sum((block_layers(256, 197, [b < 2, False, False, b > 5]) for b in range(9)), [])
+    assert [n for n, f in enumerate(narrow_layers(lib, layers)) if not f] == []
+    # the deep layers of a whole model at one image, and both forms of them in eight blocks of one
+    layers = sum((block_layers(768, 197, [False, False, False, b % 4 == 0]) for b in range(12)), [])
+    assert [n for n, f in enumerate(narrow_layers(lib, layers)) if f] == [3, 19, 35]
+    layers = sum((block_layers(768, 197, [False, False, False, b < 2]) for b in range(8)), [])
+    assert [n for n, f in enumerate(narrow_layers(lib, layers)) if f] == [4 * b + 3 for b in range(8)]
