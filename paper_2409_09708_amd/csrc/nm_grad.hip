@@ -567,12 +567,26 @@ WeightGradPlan weight_grad_plan(int64_t O, int64_t K, int64_t T) {
 // (400 tokens x 1024 -> 4096 in 3 ranges 28.7 us, 30.5 in pairs; 600 in 4 32.4 and 30.2).  Past 200 steps a range the bytes of
 // the partial tiles no longer count and eight waves in step lose to two free blocks (50432 x 768 -> 3072, 225 steps, 215 us,
 // 220 in pairs; 25216 x 1024 -> 4096, 197 steps, 182 and 175).
+// Many ranges of fewer than six steps on 360 (beyond 32 ranges: 328) to 431 blocks stay single: pairs leave a fifth of the units
+// empty there (7880 x 384 -> 384 in 61 ranges 24.0 us, 25.6 in pairs; 10638 x 320 -> 320 in 64 24.8 and 27.0; 700 shapes of short
+// ranges: pairs take 1.0 to 1.08 of the time there, while fewer blocks (1182 x 512 -> 2048, 288, 26.1 and 23.4), more (2364 x 512
+// -> 2048, 480, 28.1 and 26.6), at most 8 ranges (788 x 768 -> 3072 in 6, 31.1 and 28.3) and longer ones gain).
 bool weight_grad_paired(const WeightGradPlan& p, int64_t T) {
-  const int64_t steps = (T + TCfg::RS - 1) / TCfg::RS;
-  return p.splits > 1 && (int64_t)p.n_i_tiles * p.n_j_tiles * p.splits > 256 && steps >= 16 && steps <= 200 * p.splits;
+  const int64_t steps = (T + TCfg::RS - 1) / TCfg::RS, blocks = (int64_t)p.n_i_tiles * p.n_j_tiles * p.splits;
+  if (p.splits < 2 || blocks <= 256 || steps < 16 || steps > 200 * p.splits) return false;
+  return !(p.splits > 8 && steps < 6 * p.splits && blocks >= (p.splits > 32 ? 328 : 360) && blocks < 432);
 }
 
 }  // namespace
+
+// Not in the public header, for tests: tiles of the weight gradient, ranges of its reduction, and partial tiles of a tile that
+// the sum over them reads (fewer than ranges where they are taken in pairs).  0: another kernel takes the shape.
+extern "C" int32_t nm_internal_weight_grad_plan(int64_t O, int64_t K, int64_t T, int32_t* ranges, int32_t* planes) {
+  const WeightGradPlan p = weight_grad_plan(O, K, T);
+  *ranges = p.splits;
+  *planes = weight_grad_paired(p, T) ? (p.splits + 1) / 2 : p.splits;
+  return p.n_i_tiles * p.n_j_tiles;
+}
 
 size_t backward_input_workspace_bytes(int64_t O, int64_t K, int64_t T) {
   return dense_transposed_workspace_bytes(O, K, T);

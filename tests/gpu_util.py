@@ -65,3 +65,11 @@ def int8_route(T: int, K: int, O: int, N: int, M: int):
         return "tiled", 0
     return "persistent", lib.nm_internal_stream_tile(1, int(sparse_form), i64(O), i64(T), i64(K // (128 if sparse_form else 64)),
                                                      ctypes.byref(stages))
+
+
+def weight_grad_plan(T: int, K: int, O: int):
+    """(tiles, ranges of the token reduction, partial tiles that the sum over them reads) of a weight gradient; the ranges are
+    taken in pairs where there are more of them than partial tiles."""
+    i64, ranges, planes = ctypes.c_int64, ctypes.c_int32(), ctypes.c_int32()
+    tiles = load_library().nm_internal_weight_grad_plan(i64(O), i64(K), i64(T), ctypes.byref(ranges), ctypes.byref(planes))
+    return tiles, ranges.value, planes.value

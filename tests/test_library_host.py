@@ -8,7 +8,7 @@ import pytest
 
 from oracle import nm_oracle as orc
 from paper_2409_09708_amd import binding
-from gpu_util import int8_route, product_route
+from gpu_util import int8_route, product_route, weight_grad_plan
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 FAKE = 0x1000  # a non-NULL, well aligned address that is never dereferenced on the error paths
@@ -586,3 +586,19 @@ def test_shallow_layers_of_a_batched_call_keep_their_tiles(lib):
     assert [n for n, f in enumerate(narrow_layers(lib, layers)) if f] == [3, 19, 35]
     layers = sum((block_layers(768, 197, [False, False, False, b < 2]) for b in range(8)), [])
     assert [n for n, f in enumerate(narrow_layers(lib, layers)) if f] == [4 * b + 3 for b in range(8)]
+
+
+def test_pairs_of_token_ranges(lib):
+    pair = lambda T, K, O: (lambda tiles, ranges, planes: (tiles, ranges, tiles * ranges, planes == (ranges + 1) // 2 < ranges))(*weight_grad_plan(T, K, O))
+    # both sides of 256 ranges of tiles, of 16 steps of 32 tokens, and of 200 steps a range
+    assert pair(512, 1024, 2048) == (64, 4, 256, False) and pair(545, 2040, 4088) == (256, 2, 512, True)
+    assert pair(480, 384, 11008) == (129, 3, 387, False) and pair(481, 384, 11008) == (129, 3, 387, True)
+    assert pair(200 * 32 * 4, 1024, 4096) == (128, 4, 512, True) and pair(200 * 32 * 4 + 1, 1024, 4096) == (128, 4, 512, False)
+    assert pair(12608, 768, 3072) == (72, 7, 504, True) and pair(197, 768, 768) == (18, 1, 18, False)
+    # many ranges of four or five steps on 360 to 431 blocks stay single; more or fewer blocks, few ranges or longer ones do not
+    for T, K, O, plan in ((5516, 224, 896, (8, 43, 344)), (7880, 384, 384, (6, 61, 366)), (9456, 384, 384, (6, 64, 384)), (10638, 320, 320, (6, 64, 384)),
+                          (12214, 288, 288, (6, 64, 384)), (4137, 320, 960, (12, 32, 384)), (6107, 448, 448, (8, 47, 376))):
+        assert pair(T, K, O) == (*plan, False)
+    for T, K, O, plan in ((1182, 512, 2048, (32, 9, 288)), (2364, 512, 2048, (32, 15, 480)), (12608, 384, 384, (6, 64, 384)),
+                          (591, 1024, 3072, (96, 4, 384)), (788, 768, 3072, (72, 6, 432))):
+        assert pair(T, K, O) == (*plan, True)
