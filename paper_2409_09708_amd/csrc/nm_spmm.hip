@@ -947,7 +947,8 @@ struct StreamGroup {
 };
 static_assert(sizeof(StreamGroup) <= 4096, "the table must fit the kernel argument segment");
 
-template <bool SPARSE, int TT_, bool I8 = false>
+// TURN_IN_LDS (2:4 form): which write-out, and when the W loads leave; see there.
+template <bool SPARSE, int TT_, bool I8, bool TURN_IN_LDS>
 __global__ void __launch_bounds__(512, 2)
 nm_stream_kernel(const StreamGroup g) {
   using C = StreamCfg<SPARSE, TT_, I8>;
@@ -1169,13 +1170,12 @@ nm_stream_kernel(const StreamGroup g) {
   // HEAD of them fall into the step that freed the buffer, the others into the next one.  The requests of the
   // eight waves then reach the CU's one load path spread over the step instead of in one burst, behind which
   // every wave's matrix instructions would queue (a wave issues in order).
-  // 2:4 form: the W loads of a stage leave in the next step, after the write-out of a tile that ended with the buffer's
+  // TURN_IN_LDS: the W loads of a stage leave in the next step, after the write-out of a tile that ended with the buffer's
   // step: the write-out uses the part of the buffer that they refill.  Where the even spacing brings them earlier, the X
   // loads and selectors go into the groups of the step that freed the buffer and the W loads into the first ones of the next.
   constexpr int LPG = (C::LPW + C::TT - 1) / C::TT;                     // loads that leave together
   constexpr int SLOTS = (C::LPW + LPG - 1) / LPG;
   constexpr int SPREAD = 2 * SLOTS <= C::TT ? 2 : 1;
-  constexpr bool TURN_IN_LDS = SPARSE;                                  // which write-out, see there
   constexpr bool EVEN = !TURN_IN_LDS || C::X_PW / LPG * SPREAD >= C::PRE;
   constexpr int EARLY = C::X_PW + C::S_PW;                              // loads that are not of W
   constexpr int EARLY_PER = (EARLY + C::PRE - 1) / C::PRE;
@@ -1386,7 +1386,7 @@ nm_stream_kernel(const StreamGroup g) {
       // of whole rows out, the pieces of a row XOR-swizzled with the row (rows 8..15 on the other parity than rows 0..7, which
       // lie on the same banks: without it every write takes two passes).  The LDS operations of a wave run in order, so
       // nothing waits between a write and a read.  Against the exchange below: 12608 tokens x 768 -> 768 15.1 -> 14.5 us,
-      // 3072 -> 768 36.3 -> 35.0, 50432 x 768 -> 3072 145 -> 140; the four int8 layers of a block at C = 768 95.8 -> 94.0.
+      // 3072 -> 768 36.3 -> 35.0, 50432 x 768 -> 3072 145 -> 140; int8 by tile height, see stream_i8_turns.
       // The dense form, whose loads would have to move for it, loses up to 6 % (3072 -> 768 54.0 -> 57.4).
       const uint32_t freed = cur_off == 0 ? (uint32_t)((STAGES - 1) * C::STAGE) : cur_off - (uint32_t)C::STAGE;
       unsigned char* slice = smem + freed + C::X_BYTES + wave * 1024;     // rows 0..7; rows 8..15 lie C::NW kilobytes further
@@ -1875,10 +1875,10 @@ static int stream_height(const StreamGroup& grp) {
   return best_tt;
 }
 
-template <bool SPARSE, int TT, bool I8>
+template <bool SPARSE, int TT, bool I8, bool TURN = SPARSE>
 static hipError_t launch_stream_kernel(StreamGroup& grp, hipStream_t s) {
   using C = StreamCfg<SPARSE, TT, I8>;
-  auto kern = nm_stream_kernel<SPARSE, TT, I8>;
+  auto kern = nm_stream_kernel<SPARSE, TT, I8, TURN>;
   static PerDeviceOnce lds_limit;
   if (hipError_t e = raise_dynamic_lds_limit(kern, C::LDS_BYTES, lds_limit); e != hipSuccess) return e;
   int cus = 0;
@@ -1899,13 +1899,26 @@ static hipError_t launch_stream_kernel(StreamGroup& grp, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Whether the 2:4 form of int8 turns its rows in LDS, for which the W loads leave late (but for 256 tokens, where they leave at the
+// same time).  How much that costs in a long launch of full weights differs by card: tiles of 224 tokens took up to a quarter more
+// on two of five (18912 x 768 -> 3072 46.2 us, 58.9; 23640 53.4 and 59.9; 2 to 3 % less on the others); tiles of 160 and 192 keep
+// 3 to 5 % of gain in bfloat16 on all five (18 to 28 shapes each), and lose up to 8 % in 32 bits, which need no turn (7880 x 1024
+// -> 3072 35.8 and 38.8; 18912 x 1024 -> 1024 29.7 and 31.7); those of 128 gain 6 and 3 %, those of 256 1 to 3 and nothing.
+static bool stream_i8_turns(int tt, int out_kind) { return tt == 4 || tt == 8 || (out_kind == 1 && tt != 7); }
+
 template <bool SPARSE, bool I8 = false>
 static hipError_t launch_stream_group(StreamGroup& grp, hipStream_t s) {
-  switch (stream_height<SPARSE, I8>(grp)) {
+  const int tt = stream_height<SPARSE, I8>(grp);
+  if constexpr (SPARSE && I8) {
+    if (tt == 7) return launch_stream_kernel<true, 7, true, false>(grp, s);
+    if (!stream_i8_turns(tt, grp.layer[0].out_kind))
+      return tt == 5 ? launch_stream_kernel<true, 5, true, false>(grp, s) : launch_stream_kernel<true, 6, true, false>(grp, s);
+  }
+  switch (tt) {
     case 4: return launch_stream_kernel<SPARSE, 4, I8>(grp, s);
     case 5: return launch_stream_kernel<SPARSE, 5, I8>(grp, s);
     case 6: return launch_stream_kernel<SPARSE, 6, I8>(grp, s);
-    case 7: return launch_stream_kernel<SPARSE, 7, I8>(grp, s);
+    case 7: return launch_stream_kernel<SPARSE, 7, I8, SPARSE && !I8>(grp, s);
     case 8: return launch_stream_kernel<SPARSE, 8, I8>(grp, s);
     default: return hipErrorInvalidValue;
   }
@@ -1960,6 +1973,12 @@ extern "C" int32_t nm_internal_stream_tile(int32_t int8, int32_t sparse_form, in
   if (sparse_form) int8 ? ask(std::true_type{}, std::true_type{}) : ask(std::true_type{}, std::false_type{});
   else int8 ? ask(std::false_type{}, std::true_type{}) : ask(std::false_type{}, std::false_type{});
   return 32 * tt;
+}
+
+// Not in the public header, for tests: whether the 2:4 form of an int8 layer of nk steps turns its rows in LDS.
+extern "C" int32_t nm_internal_stream_i8_turns(int64_t O, int64_t T, int64_t nk, int32_t out_kind) {
+  int32_t stages;
+  return stream_i8_turns(nm_internal_stream_tile(1, 1, O, T, nk, &stages) / 32, out_kind);
 }
 
 hipError_t launch_stream_i8(const StreamI8Args& a, hipStream_t s) {

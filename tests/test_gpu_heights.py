@@ -73,3 +73,8 @@ def test_int8_products(shape, level, tokens):
                                 w_scale=scale, bias=bias)
     expect = torch.addcmul(bias.double(), acc.double(), (0.02 * scale).double())  # one rounding of the fused multiply-add
     assert (y.double() - expect).abs().max().item() <= 2.0 ** -23 * expect.abs().max().item()
+    # bfloat16 rows leave by a write-out of their own: the rounding of the fp32 output, bit for bit, and nothing past the last row
+    out = torch.full((T + 1, O), 7.0, dtype=torch.bfloat16, device="cuda")
+    nm.nm_linear_forward_i8(torch.from_numpy(wq).cuda(), words, N, M, torch.from_numpy(xq).cuda(), x_scale=0.02, w_scale=scale,
+                            bias=bias, out=out[:T])
+    assert torch.equal(out[:T], y.bfloat16()) and bool((out[T] == 7).all())

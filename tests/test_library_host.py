@@ -602,3 +602,12 @@ def test_pairs_of_token_ranges(lib):
     for T, K, O, plan in ((1182, 512, 2048, (32, 9, 288)), (2364, 512, 2048, (32, 15, 480)), (12608, 384, 384, (6, 64, 384)),
                           (591, 1024, 3072, (96, 4, 384)), (788, 768, 3072, (72, 6, 432))):
         assert pair(T, K, O) == (*plan, True)
+
+
+def test_which_int8_tiles_turn_their_rows(lib):
+    # by tokens per tile: all outputs, bfloat16 only, none
+    turns = lambda T, K, O, kind: bool(lib.nm_internal_stream_i8_turns(ctypes.c_int64(O), ctypes.c_int64(T), ctypes.c_int64(K // 128), kind))
+    for T, K, O, tokens in ((16451, 512, 136, 128), (16444, 384, 136, 160), (13658, 384, 528, 192), (16368, 384, 520, 224), (19889, 384, 520, 256)):
+        assert int8_route(T, K, O, 2, 4) == ("persistent", tokens), (T, K, O)
+        assert turns(T, K, O, 1) == (tokens != 224)
+        assert turns(T, K, O, 0) == turns(T, K, O, 2) == (tokens in (128, 256))
