@@ -359,7 +359,8 @@ int32_t nm_linear_forward_prepared_batched_scratch(const nm_forward_desc* descs,
  *       dW   out  [O, K], ld lddw, float or bfloat16 (out_dtype)
  *       workspace scratch of nm_backward_weight_workspace_bytes(O, K, T) bytes, 256-byte aligned (the token
  *                 reduction is cut into ranges whose partial sums are added in a fixed order, so results
- *                 repeat bit for bit); NULL allowed when that size is 0.  Contents undefined afterwards;
+ *                 repeat bit for bit; the size is that of all ranges, of which a call may leave half
+ *                 unused); NULL allowed when that size is 0.  Contents undefined afterwards;
  *                 concurrent calls need distinct workspaces.
  * The matrix-core kernels need 16-byte aligned operands, leading dimensions that are multiples of 8, K % 8 == 0
  * and O % 32 == 0 (dX) or O % 8 == 0 (dW); other shapes run a slower general kernel with the same results.

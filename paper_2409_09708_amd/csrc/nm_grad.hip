@@ -19,8 +19,8 @@
 //   dX: P = W (.) m [r = o, i = k], Q = dY as [j = t, r = o] (reduction contiguous), Out = dX [t, k]
 //   dW: P = X       [r = t, i = k], Q = dY as [r = t, j = o] (reduction = row),       Out = dW [o, k]
 // The token reduction of dW is long and its output small (a few dozen 128 x 256 tiles), so it is cut
-// into `splits` ranges; every block leaves an fp32 partial tile and a second kernel adds the partial
-// tiles in split order (the result does not depend on scheduling), applies the mask and rounds.
+// into `splits` ranges; every block leaves an fp32 partial tile, of its range or of a pair of neighbouring ones, and a second
+// kernel adds the partial tiles in order (the result does not depend on scheduling), applies the mask and rounds.
 #include "nm_device.h"
 #include "nm_launch.h"
 #include "nm_mma.h"
@@ -45,8 +45,8 @@ struct TGemmArgs {
   int vec_store;    // Out rows split into whole aligned 16-byte pieces
   int n_i_tiles, n_j_tiles;
   int splits;       // ranges the reduction is cut into (>= 1)
-  float* partial;   // not NULL: fp32 partial tiles [split][tile][accumulator][thread] (16 bytes per thread)
-                    // instead of Out
+  float* partial;   // not NULL: fp32 partial tiles [range, or pair of ranges][tile][accumulator][thread] (16 bytes per
+                    // thread) instead of Out
 };
 
 struct TCfg {
@@ -425,15 +425,15 @@ nm_tgemm_kernel(const TGemmArgs a) {
   }
 }
 
-// Sum of the partial tiles (of a range, or of a pair of ranges) in order, the mask of the step (bit k % 32 of word k / 32 of row
-// o; NULL = every weight receives its gradient) and the rounding.  One lane per accumulator of the tile kernel.  Bound by reading
-// the partial tiles, and by its launch (72 tiles of 4 pairs, 47 MB in all, 8.3 us; 12.2 with the 7 single ranges; 32 of 8 pairs 7.4, 10.8 with 15).
-// 64 tiles are one round of the chip's wavefront slots.  Where the last round has at most 16 of them, its few wavefronts do not
-// hide a load and a lane reads six at a time (16 tiles in 29 ranges 16.8 -> 10.5 us, 2 in 64 16.8 -> 6.6).  A fuller round is
-// bound by memory, and six read at once disturb each other there (32 in 15 10.8 one by one, 12.0); it reads two (72 of 4 9.1
-// one by one, 8.3; three or four as two).
+// Sum of the partial tiles (of a range, or of a pair of ranges: `planes` of them for each tile) in order, the mask of the step
+// (bit k % 32 of word k / 32 of row o; NULL = every weight receives its gradient) and the rounding.  One lane per accumulator of
+// the tile kernel.  Bound by reading the partial tiles, and by its launch (72 tiles in 4 planes, 47 MB in all, 8.3 us; 12.2 with
+// the 7 single ranges; 32 in 8 7.4, 10.8 with 15).  Up to 10 tiles the few wavefronts do not hide a load and a lane reads six at
+// a time, else two (both kernels, six and two: 1 tile in 64 planes 16.4 us and 20.6, 2 in 64 21.3 and 25.7, 8 in 25 25.2 and
+// 26.2, 10 in 15 19.1 and 19.4; from 12 tiles on they differ by 1 % either way: 12 in 20 24.8 and 25.0, 16 in 15 27.3 and 27.0,
+// 32 in 8 37.2 and 36.1, 65 in 8 69.8 and 69.6, 75 in 7 74.7 and 74.7).
 __global__ void __launch_bounds__(256)
-grad_reduce_kernel(const float* __restrict__ partial, int splits, int n_tiles, int n_i_tiles, int64_t I, int64_t J,
+grad_reduce_kernel(const float* __restrict__ partial, int planes, int n_tiles, int n_i_tiles, int64_t I, int64_t J,
                    const uint32_t* __restrict__ mask, void* __restrict__ out, int64_t ldo, int out_bf16) {
   using C = TCfg;
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -445,8 +445,8 @@ grad_reduce_kernel(const float* __restrict__ partial, int splits, int n_tiles, i
   const size_t stride = (size_t)n_tiles * (C::MMA * C::NT);
   f32x4_t sum = src[0];
   int s = 1;
-  if (((n_tiles - 1) & 63) < 16) {
-    for (; s + 6 <= splits; s += 6) {
+  if (n_tiles <= 10) {
+    for (; s + 6 <= planes; s += 6) {
       f32x4_t p[6];
 #pragma unroll
       for (int u = 0; u < 6; ++u) p[u] = src[(size_t)(s + u) * stride];
@@ -454,12 +454,12 @@ grad_reduce_kernel(const float* __restrict__ partial, int splits, int n_tiles, i
       for (int u = 0; u < 6; ++u) sum += p[u];
     }
   }
-  for (; s + 2 <= splits; s += 2) {
+  for (; s + 2 <= planes; s += 2) {
     const f32x4_t p0 = src[(size_t)s * stride], p1 = src[(size_t)(s + 1) * stride];
     sum += p0;
     sum += p1;
   }
-  if (s < splits) sum += src[(size_t)s * stride];
+  if (s < planes) sum += src[(size_t)s * stride];
   const int lane = tid & 63, wave = tid >> 6;
   const int wi = wave % C::WI, wj = wave / C::WI;
   const int i = q / C::JT, j = q % C::JT;
@@ -577,6 +577,9 @@ bool weight_grad_paired(const WeightGradPlan& p, int64_t T) {
   return !(p.splits > 8 && steps < 6 * p.splits && blocks >= (p.splits > 32 ? 328 : 360) && blocks < 432);
 }
 
+// Partial tiles of a tile: one per pair, and the last of an odd number of ranges by itself.
+int weight_grad_planes(const WeightGradPlan& p, int64_t T) { return weight_grad_paired(p, T) ? (p.splits + 1) / 2 : p.splits; }
+
 }  // namespace
 
 // Not in the public header, for tests: tiles of the weight gradient, ranges of its reduction, and partial tiles of a tile that
@@ -584,7 +587,7 @@ bool weight_grad_paired(const WeightGradPlan& p, int64_t T) {
 extern "C" int32_t nm_internal_weight_grad_plan(int64_t O, int64_t K, int64_t T, int32_t* ranges, int32_t* planes) {
   const WeightGradPlan p = weight_grad_plan(O, K, T);
   *ranges = p.splits;
-  *planes = weight_grad_paired(p, T) ? (p.splits + 1) / 2 : p.splits;
+  *planes = weight_grad_planes(p, T);
   return p.n_i_tiles * p.n_j_tiles;
 }
 
@@ -629,6 +632,7 @@ hipError_t launch_backward_input(const bf16_t* Ws, int64_t O, int64_t K, int64_t
   return launch_tgemm<false>(g, s);
 }
 
+// (of every range, also where pairs leave half of it unused)
 size_t backward_weight_workspace_bytes(int64_t O, int64_t K, int64_t T) {
   const WeightGradPlan p = weight_grad_plan(O, K, T);
   if (!p.tiles) return 0;
@@ -659,10 +663,11 @@ hipError_t launch_backward_weight(const bf16_t* dY, int64_t T, int64_t O, int64_
   g.n_i_tiles = p.n_i_tiles; g.n_j_tiles = p.n_j_tiles;
   g.splits = p.splits; g.partial = reinterpret_cast<float*>(workspace);
   const bool pair = weight_grad_paired(p, T);
+  const int planes = weight_grad_planes(p, T);
   hipError_t e = pair ? launch_tgemm<true, true>(g, s) : launch_tgemm<true>(g, s);
   if (e != hipSuccess) return e;
   const int64_t n = (int64_t)p.n_i_tiles * p.n_j_tiles * TCfg::MMA * TCfg::NT;
-  hipLaunchKernelGGL(grad_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, g.partial, pair ? (p.splits + 1) / 2 : p.splits,
+  hipLaunchKernelGGL(grad_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, g.partial, planes,
                      p.n_i_tiles * p.n_j_tiles, p.n_i_tiles, K, O, mask, dW, lddw, out_bf16);
   return hipGetLastError();
 }
