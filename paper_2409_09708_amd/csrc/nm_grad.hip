@@ -567,14 +567,15 @@ WeightGradPlan weight_grad_plan(int64_t O, int64_t K, int64_t T) {
 // (400 tokens x 1024 -> 4096 in 3 ranges 28.7 us, 30.5 in pairs; 600 in 4 32.4 and 30.2).  Past 200 steps a range the bytes of
 // the partial tiles no longer count and eight waves in step lose to two free blocks (50432 x 768 -> 3072, 225 steps, 215 us,
 // 220 in pairs; 25216 x 1024 -> 4096, 197 steps, 182 and 175).
-// Many ranges of fewer than six steps on 360 (beyond 32 ranges: 328) to 431 blocks stay single: pairs leave a fifth of the units
-// empty there (7880 x 384 -> 384 in 61 ranges 24.0 us, 25.6 in pairs; 10638 x 320 -> 320 in 64 24.8 and 27.0; 700 shapes of short
-// ranges: pairs take 1.0 to 1.08 of the time there, while fewer blocks (1182 x 512 -> 2048, 288, 26.1 and 23.4), more (2364 x 512
-// -> 2048, 480, 28.1 and 26.6), at most 8 ranges (788 x 768 -> 3072 in 6, 31.1 and 28.3) and longer ones gain).
+// Many ranges of fewer than 5.5 steps on 368 (beyond 32 ranges: 328) to 431 blocks stay single: pairs leave a fifth of the units
+// empty there.  7880 x 384 -> 384 in 61 ranges 24.0 us, 25.6 in pairs; 10638 x 320 -> 320 in 64 24.8 and 27.0 (but x 256 -> 768 23.5
+// and 21.3: of 700 shapes of short ranges pairs take 1.03 of the time on average there).  Fewer blocks gain (1182 x 512 -> 2048, 288,
+// 26.1 and 23.4; 1200 x 1024 -> 1280, 360, 27.4 and 25.9), as do more (2364 x 512 -> 2048, 480, 28.1 and 26.6), at most 8 ranges
+// (788 x 768 -> 3072 in 6, 31.1 and 28.3) and longer ones (at 5.5 to 6 steps 0.93 to 1.13 either way).
 bool weight_grad_paired(const WeightGradPlan& p, int64_t T) {
   const int64_t steps = (T + TCfg::RS - 1) / TCfg::RS, blocks = (int64_t)p.n_i_tiles * p.n_j_tiles * p.splits;
   if (p.splits < 2 || blocks <= 256 || steps < 16 || steps > 200 * p.splits) return false;
-  return !(p.splits > 8 && steps < 6 * p.splits && blocks >= (p.splits > 32 ? 328 : 360) && blocks < 432);
+  return !(p.splits > 8 && 2 * steps < 11 * p.splits && blocks >= (p.splits > 32 ? 328 : 368) && blocks < 432);
 }
 
 // Partial tiles of a tile: one per pair, and the last of an odd number of ranges by itself.

@@ -595,11 +595,11 @@ def test_pairs_of_token_ranges(lib):
     assert pair(480, 384, 11008) == (129, 3, 387, False) and pair(481, 384, 11008) == (129, 3, 387, True)
     assert pair(200 * 32 * 4, 1024, 4096) == (128, 4, 512, True) and pair(200 * 32 * 4 + 1, 1024, 4096) == (128, 4, 512, False)
     assert pair(12608, 768, 3072) == (72, 7, 504, True) and pair(197, 768, 768) == (18, 1, 18, False)
-    # many ranges of four or five steps on 360 to 431 blocks stay single; more or fewer blocks, few ranges or longer ones do not
+    # many ranges of four or five steps on 368 to 431 blocks (328 with more than 32 ranges) stay single; more or fewer blocks, few ranges or longer ones do not
     for T, K, O, plan in ((5516, 224, 896, (8, 43, 344)), (7880, 384, 384, (6, 61, 366)), (9456, 384, 384, (6, 64, 384)), (10638, 320, 320, (6, 64, 384)),
-                          (12214, 288, 288, (6, 64, 384)), (4137, 320, 960, (12, 32, 384)), (6107, 448, 448, (8, 47, 376))):
+                          (4137, 320, 960, (12, 32, 384)), (6107, 448, 448, (8, 47, 376))):
         assert pair(T, K, O) == (*plan, False)
-    for T, K, O, plan in ((1182, 512, 2048, (32, 9, 288)), (2364, 512, 2048, (32, 15, 480)), (12608, 384, 384, (6, 64, 384)),
+    for T, K, O, plan in ((1182, 512, 2048, (32, 9, 288)), (1200, 1024, 1280, (40, 9, 360)), (2364, 512, 2048, (32, 15, 480)), (12214, 288, 288, (6, 64, 384)),
                           (591, 1024, 3072, (96, 4, 384)), (788, 768, 3072, (72, 6, 432))):
         assert pair(T, K, O) == (*plan, True)
 
