@@ -646,9 +646,9 @@ def main():
         small_descs = nm.forward_descs([(v, i, L.K, L.N, L.M, X[:Ts], ws, None, Y) for (v, i), ws, X, Y, L in
                                         zip(small_packed, small_ws, Xs, small_Y, layers)])
         small_warm_ms = timed(lambda: nm.nm_linear_forward_prepared_batched(small_descs, stream=stream), n=20)
-        # The 170 MB a call reads fit the 256 MB memory-side cache, so repeated calls on one set of buffers are
-        # served from it.  The HBM figure comes from three sets of weights (packed + operand order, 510 MB) taken
-        # in turn: a set has left the cache when its turn comes again.
+        # The 170 MB a call moves (112 MB of weights in operand order, 58 MB of activations and outputs) fit the 256 MB
+        # memory-side cache, so repeated calls on one set of buffers are served from it.  The HBM figure comes from three
+        # sets of weights (336 MB in operand order) taken in turn: a set has left the cache when its turn comes again.
         rot_sets = [(small_packed, small_ws)] + [nm.nm_pack_prepare_batched(small_layers, stream=stream) for _ in range(2)]
         rot_descs = [nm.forward_descs([(v, i, L.K, L.N, L.M, X[:Ts], ws, None, Y) for (v, i), ws, X, Y, L in
                                        zip(pk, wss, Xs, small_Y, layers)]) for (pk, wss) in rot_sets]
@@ -669,7 +669,7 @@ def main():
         packed_ms = timed(lambda: nm.nm_linear_forward_prepared_batched(packed_descs, stream=stream), n=20)
         out["small_batch_products"] = {
             "workload": "the 48 linears at batch 1 (T=197), bf16 out, one batched call; algorithmic bytes = packed weights "
-                        "+ X + Y of every layer; three sets of weight buffers (510 MB) taken in turn, so every call "
+                        "+ X + Y of every layer; three sets of weights (336 MB in operand order) taken in turn, so every call "
                         "reads its weights from HBM (ms_same_buffers: one set again and again, served by the 256 MB "
                         "memory-side cache)",
             "ms": small_ms, "ms_same_buffers": small_warm_ms, "algorithmic_bytes": small_bytes, "bytes_read_in_operand_form": operand_small,

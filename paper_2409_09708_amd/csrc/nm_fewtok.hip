@@ -6,7 +6,7 @@
 // alone takes the kernel of nm_direct.hip as long as its small blocks are few rounds on the chip, with the same sums: 768 ->
 // 1000 at 4:8 and 16 tokens 23.0 us here, 6.1 there): with one, the tiled kernel of nm_spmm.hip reads
 // the operand-order copy and is the faster of the two (measured on the 48 linears of the model at 197 tokens:
-// 73 us against 89 us here; this kernel reads 112 MB where the other reads 170 MB, but its windows are bound by
+// 73 us against 89 us here; with activations and outputs this kernel moves 112 MB and the other 170, but its windows are bound by
 // the LDS traffic of the activation fragments, a kilobyte per matrix instruction).
 //
 // Work item = 128 out-features of one layer over the whole reduction, all tokens: one block of 8 waves per compute

@@ -214,7 +214,8 @@ score_mask_kernel(const float* __restrict__ score, int64_t O, int64_t K, int64_t
 // compared.  2:4, in a graph: 768 x 768 2.5 -> 2.2 us, 3072 x 768 4.4 -> 3.9; bound by launch and load latency there, by memory
 // where a launch is many rounds of waves: 8192 x 8192 60 -> 51 with one group per lane, 44 with four (6.2 TB/s).  Four per
 // lane from 2 M groups of 4 on: 4096 x 4096 14.0 -> 13.5, but 1024 x 4096 5.1 -> 5.7.  Groups of 8 and 16 fill a lane by
-// themselves (two of 8: 4096 x 4096 14.2 -> 15.3).
+// themselves (two of 8: 4096 x 4096 14.2 -> 15.3).  They gain little at a layer's size, where a lane's comparisons count: 4:8 768 x
+// 768 3.1 -> 3.0, 3072 x 768 4.5 -> 4.3, 8:16 4.55 -> 4.3 and the same; 8192 x 8192 61 -> 55 and 78 -> 73.
 template <int M, int GROUPS>
 __global__ void __launch_bounds__(256)
 score_mask_flat_kernel(const float* __restrict__ score, int64_t n_groups, int N, uint32_t* __restrict__ mask) {
