@@ -642,7 +642,7 @@ hipError_t launch_linear_i8(const I8LinearArgs& a, hipStream_t s, bool* workspac
     if (!vec) return general();
     StreamI8Args g;
     g.values = reinterpret_cast<const int8_t*>(ws); g.sel = sparse_form ? reinterpret_cast<const uint32_t*>(sel_s) : nullptr;
-    g.sparse_form = sparse_form; g.X = a.X; g.w_scale = a.w_scale; g.bias = a.bias; g.x_scale = a.x_scale;
+    g.sparse_form = sparse_form; g.full = a.N == 2 && a.M == 4; g.X = a.X; g.w_scale = a.w_scale; g.bias = a.bias; g.x_scale = a.x_scale;
     g.Y = a.Y; g.O = a.O; g.K = a.K; g.T = a.T; g.ldx = a.ldx; g.ldy = a.ldy; g.out_kind = a.out_kind;
     return launch_stream_i8(g, s);
   }

@@ -181,6 +181,7 @@ struct StreamI8Args {
   const int8_t* values;  // stream-order compressed values (2:4 form) or masked dense weight
   const uint32_t* sel;   // stream-order selector words (2:4 form)
   bool sparse_form;
+  bool full;             // level 2:4: every value of the 2:4 form is a kept weight
   const int8_t* X;
   const float* w_scale;  // nullable; 16-byte aligned
   const float* bias;     // nullable; 16-byte aligned

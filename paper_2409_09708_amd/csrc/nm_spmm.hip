@@ -1220,9 +1220,9 @@ nm_stream_kernel(const StreamGroup g) {
 
   // One K step, free of conditions: a wave issues one instruction at a time, in order, so every other
   // instruction of the step is time its matrix instructions do not get.  PP names the fragment and address
-  // set the step multiplies with.  Every other group takes the W fragments backwards: the chip is bound by power here, and operands
-  // that stay between two instructions take less of it (a loop of dense instructions fed from LDS 0.590 -> 0.580 us a step, int8
-  // 0.615 -> 0.583; the sparse ones do not mind).  Every step refills the buffer it has consumed and prefetches fragments
+  // set the step multiplies with.  Every other group takes the W fragments backwards, so that an operand stays between two
+  // instructions: a loop of dense instructions fed from LDS 0.590 -> 0.580 us a step, int8 0.615 -> 0.583, the sparse ones the same;
+  // of the products nothing that their spread shows (0.1 to 0.2 % on average over 360 bfloat16 and 240 int8 shapes).  Every step refills the buffer it has consumed and prefetches fragments
   // of the next stage, also past the block's last stage.
   auto step = [&](auto pp_tag) {
     constexpr int PP = decltype(pp_tag)::value;
@@ -1900,25 +1900,28 @@ static hipError_t launch_stream_kernel(StreamGroup& grp, hipStream_t s) {
 }
 
 // Whether the 2:4 form of int8 turns its rows in LDS, for which the W loads leave late (but for 256 tokens, where they leave at the
-// same time).  How much that costs in a long launch of full weights differs by card: tiles of 224 tokens took up to a quarter more
-// on two of five (18912 x 768 -> 3072 46.2 us, 58.9; 23640 53.4 and 59.9; 2 to 3 % less on the others); tiles of 160 and 192 keep
-// 3 to 5 % of gain in bfloat16 on all five (18 to 28 shapes each), and lose up to 8 % in 32 bits, which need no turn (7880 x 1024
-// -> 3072 35.8 and 38.8; 18912 x 1024 -> 1024 29.7 and 31.7); those of 128 gain 6 and 3 %, those of 256 1 to 3 and nothing.
-static bool stream_i8_turns(int tt, int out_kind) { return tt == 4 || tt == 8 || (out_kind == 1 && tt != 7); }
+// same time).  bfloat16 gains 4 to 6 % in tiles of 128 and 3 to 5 % in those of 160, 192 and 256 tokens.  Tiles of 224 gain 2 to 3 %
+// at the levels sparser than 2:4; at 2:4 (full), whose operand holds twice the weights that are not zero, long launches of them take
+// up to a quarter more on two of six cards (18912 x 768 -> 3072 46.2 us, 58.9; 23640 53.4 and 59.9; 2 to 3 % less on the others).
+// 32-bit rows need no turn: at 160 to 224 tokens the late loads alone cost up to 14 % on four of five cards (18912 x 1024 -> 3072 73.1
+// us, 84.6; 7880 35.8 and 38.8), at 128 they gain 2 to 3 %.
+static bool stream_i8_turns(int tt, int out_kind, bool full) { return out_kind == 1 ? !(tt == 7 && full) : tt == 4 || tt == 8; }
 
 template <bool SPARSE, bool I8 = false>
-static hipError_t launch_stream_group(StreamGroup& grp, hipStream_t s) {
+static hipError_t launch_stream_group(StreamGroup& grp, hipStream_t s, bool full = false) {
   const int tt = stream_height<SPARSE, I8>(grp);
-  if constexpr (SPARSE && I8) {
-    if (tt == 7) return launch_stream_kernel<true, 7, true, false>(grp, s);
-    if (!stream_i8_turns(tt, grp.layer[0].out_kind))
-      return tt == 5 ? launch_stream_kernel<true, 5, true, false>(grp, s) : launch_stream_kernel<true, 6, true, false>(grp, s);
-  }
+  if constexpr (SPARSE && I8)
+    if (!stream_i8_turns(tt, grp.layer[0].out_kind, full)) switch (tt) {
+      case 5: return launch_stream_kernel<true, 5, true, false>(grp, s);
+      case 6: return launch_stream_kernel<true, 6, true, false>(grp, s);
+      case 7: return launch_stream_kernel<true, 7, true, false>(grp, s);
+      default: return hipErrorInvalidValue;
+    }
   switch (tt) {
     case 4: return launch_stream_kernel<SPARSE, 4, I8>(grp, s);
     case 5: return launch_stream_kernel<SPARSE, 5, I8>(grp, s);
     case 6: return launch_stream_kernel<SPARSE, 6, I8>(grp, s);
-    case 7: return launch_stream_kernel<SPARSE, 7, I8, SPARSE && !I8>(grp, s);
+    case 7: return launch_stream_kernel<SPARSE, 7, I8>(grp, s);
     case 8: return launch_stream_kernel<SPARSE, 8, I8>(grp, s);
     default: return hipErrorInvalidValue;
   }
@@ -1976,9 +1979,9 @@ extern "C" int32_t nm_internal_stream_tile(int32_t int8, int32_t sparse_form, in
 }
 
 // Not in the public header, for tests: whether the 2:4 form of an int8 layer of nk steps turns its rows in LDS.
-extern "C" int32_t nm_internal_stream_i8_turns(int64_t O, int64_t T, int64_t nk, int32_t out_kind) {
+extern "C" int32_t nm_internal_stream_i8_turns(int64_t O, int64_t T, int64_t nk, int32_t out_kind, int32_t full) {
   int32_t stages;
-  return stream_i8_turns(nm_internal_stream_tile(1, 1, O, T, nk, &stages) / 32, out_kind);
+  return stream_i8_turns(nm_internal_stream_tile(1, 1, O, T, nk, &stages) / 32, out_kind, full);
 }
 
 hipError_t launch_stream_i8(const StreamI8Args& a, hipStream_t s) {
@@ -1995,7 +1998,7 @@ hipError_t launch_stream_i8(const StreamI8Args& a, hipStream_t s) {
   L.n_o_tiles = (int32_t)n_o; L.n_tiles = (int32_t)(n_o * n_t);
   L.x_scale = a.x_scale; L.out_kind = a.out_kind; L.reserved = 0;
   grp.n_tiles = L.n_tiles;
-  return a.sparse_form ? launch_stream_group<true, true>(grp, s) : launch_stream_group<false, true>(grp, s);
+  return a.sparse_form ? launch_stream_group<true, true>(grp, s, a.full) : launch_stream_group<false, true>(grp, s);
 }
 
 // Tiles of the tiled kernel for one layer alone.  Its blocks are bound by the bytes their compute unit pulls into LDS

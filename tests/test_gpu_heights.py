@@ -21,7 +21,7 @@ OTHERS = [(s, lv, None) for lv in ((2, 4), (1, 8), (4, 8), (8, 8))  # whichever 
           for s in ((12001, 192, 768), (15873, 128, 768), (6301, 64, 2560), (5500, 320, 3072), (8200, 192, 2048), (16384, 128, 1024))]
 SPARSE_I8 = {128: (16451, 512, 136), 160: (16444, 384, 136), 192: (13658, 384, 528), 224: (16368, 384, 520), 256: (19889, 384, 520)}
 DENSE_I8 = {128: (4164, 512, 136), 160: (16826, 256, 264), 192: (13702, 256, 520), 224: (16392, 256, 520), 256: (19280, 256, 520)}
-INT8_CASES = [(s, (2, 4), t) for t, s in SPARSE_I8.items()] + [(s, (4, 8), t) for t, s in DENSE_I8.items()]
+INT8_CASES = [(s, lv, t) for t, s in SPARSE_I8.items() for lv in ((2, 4), (1, 8))] + [(s, (4, 8), t) for t, s in DENSE_I8.items()]
 INT8_OTHERS = [(s, lv, None) for lv in ((2, 4), (4, 8))
                for s in ((12001, 384, 768), (15873, 512, 768), (6301, 640, 2560), (8200, 1024, 2048))]
 

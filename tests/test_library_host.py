@@ -605,9 +605,9 @@ def test_pairs_of_token_ranges(lib):
 
 
 def test_which_int8_tiles_turn_their_rows(lib):
-    # by tokens per tile: all outputs, bfloat16 only, none
-    turns = lambda T, K, O, kind: bool(lib.nm_internal_stream_i8_turns(ctypes.c_int64(O), ctypes.c_int64(T), ctypes.c_int64(K // 128), kind))
+    # bfloat16 everywhere but in tiles of 224 tokens at 2:4; 32 bits in tiles of 128 and 256 only
+    turns = lambda T, K, O, *how: bool(lib.nm_internal_stream_i8_turns(ctypes.c_int64(O), ctypes.c_int64(T), ctypes.c_int64(K // 128), *how))
     for T, K, O, tokens in ((16451, 512, 136, 128), (16444, 384, 136, 160), (13658, 384, 528, 192), (16368, 384, 520, 224), (19889, 384, 520, 256)):
         assert int8_route(T, K, O, 2, 4) == ("persistent", tokens), (T, K, O)
-        assert turns(T, K, O, 1) == (tokens != 224)
-        assert turns(T, K, O, 0) == turns(T, K, O, 2) == (tokens in (128, 256))
+        assert turns(T, K, O, 1, 0) and turns(T, K, O, 1, 1) == (tokens != 224)
+        assert all(turns(T, K, O, kind, full) == (tokens in (128, 256)) for kind in (0, 2) for full in (0, 1))
