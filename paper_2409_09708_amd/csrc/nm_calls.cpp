@@ -38,6 +38,9 @@ struct Library {
   decltype(&nm_spmm_workspace_bytes) workspace_bytes;
   decltype(&nm_values_bytes) values_bytes;
   decltype(&nm_index_bytes) index_bytes;
+  // may be missing: a prepared layer is then multiplied uncut
+  decltype(&nm_linear_forward_prepared_scratch) forward_prepared_scratch;
+  decltype(&nm_prepared_scratch_bytes) prepared_scratch_bytes;
 } lib;
 PyObject* raise_status;    // raises NmError for a status that is not NM_OK
 PyObject* find_workspace;  // the scratch tensor of a device and stream
@@ -244,8 +247,6 @@ PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
       !matrix(*X, &x) || x.cols != K || !integer(a[11], 0, 3, &how))
     return declined();
   const int64_t O = values->size(0), T = x.rows;
-  // a prepared layer that may be cut along K (64 steps or more on fewer than 128 tiles): Python brings the scratch of the call
-  if (how == 1 && K >= 4096 && (O + 127) / 128 * ((T + 127) / 128) < 128) return declined();
   if (a[6] != Py_None && (!plain(a[6], at::kFloat, &bias) || bias->numel() != O || !bias->is_contiguous())) return declined();
   int32_t code;
   at::Tensor made;
@@ -288,6 +289,15 @@ PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
       ws_bytes = ws->nbytes();
     }
   }
+  // partial sums of a prepared layer that is cut along K: scratch of the call, allocated on its stream, so that the memory goes to
+  // later work of that stream only.  (Not for a workspace of the operand part alone, which asks for the uncut product.)
+  size_t scratch_bytes = how == 1 && lib.prepared_scratch_bytes ? lib.prepared_scratch_bytes(O, K, N, M, T) : 0;
+  if (scratch_bytes != 0 && ws_bytes < lib.workspace_bytes(O, K, N, M, T)) scratch_bytes = 0;
+  at::Device here = X->device();
+  if (scratch_bytes != 0) {
+    here = at::Device(at::kCUDA, c10::hip::current_device());
+    if (s != c10::hip::getCurrentHIPStream(here.index()).stream()) return declined();
+  }
   const uint16_t *v = pointer<uint16_t>(values), *xp = pointer<uint16_t>(X);
   const uint32_t* ix = pointer<uint32_t>(indices);
   const float* b = pointer<float>(bias);
@@ -300,6 +310,11 @@ PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
       y.ld = O;
     }
     if (how == 3) return lib.forward_static(v, ix, O, K, N, M, xp, T, x.ld, b, yp, y.ld, code, s);
+    if (scratch_bytes != 0) {
+      const at::Tensor scratch = fresh(here, 1, (int64_t)scratch_bytes, at::kByte);
+      return lib.forward_prepared_scratch(v, ix, O, K, N, M, xp, T, x.ld, b, yp, y.ld, code, ws_ptr, ws_bytes,
+                                          scratch.data_ptr(), scratch_bytes, s);
+    }
     if (how == 1) return lib.forward_prepared(v, ix, O, K, N, M, xp, T, x.ld, b, yp, y.ld, code, ws_ptr, ws_bytes, s);
     return lib.forward(v, ix, O, K, N, M, xp, T, x.ld, b, yp, y.ld, code, ws_ptr, ws_bytes, s);
   });
@@ -315,14 +330,17 @@ PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
 PyObject* bind(PyObject*, PyObject* args) {
   PyObject *table, *raise, *find;
   if (!PyArg_ParseTuple(args, "O!OO", &PyDict_Type, &table, &raise, &find)) return nullptr;
-  Library l;
-  struct { const char* name; void* slot; } slots[] = {
+  Library l = {};
+  struct { const char* name; void* slot; bool optional = false; } slots[] = {
       {"nm_prune", &l.prune}, {"nm_prune_scored", &l.prune_scored}, {"nm_pack", &l.pack}, {"nm_unpack", &l.unpack},
       {"nm_linear_forward", &l.forward}, {"nm_linear_forward_prepared", &l.forward_prepared},
       {"nm_linear_forward_static", &l.forward_static}, {"nm_spmm_workspace_bytes", &l.workspace_bytes},
-      {"nm_values_bytes", &l.values_bytes}, {"nm_index_bytes", &l.index_bytes}};
+      {"nm_values_bytes", &l.values_bytes}, {"nm_index_bytes", &l.index_bytes},
+      {"nm_linear_forward_prepared_scratch", &l.forward_prepared_scratch, true},
+      {"nm_prepared_scratch_bytes", &l.prepared_scratch_bytes, true}};
   for (auto& e : slots) {
     PyObject* address = PyDict_GetItemString(table, e.name);
+    if (address == nullptr && e.optional) continue;
     void* p = address ? PyLong_AsVoidPtr(address) : nullptr;
     if (p == nullptr) {
       if (!PyErr_Occurred()) PyErr_Format(PyExc_KeyError, "%s", e.name);

@@ -52,14 +52,21 @@ def test_products_leave_the_workspace_alone(T, K, O, N, M):
 def test_two_streams_share_a_prepared_layer(T, K, O, N, M):
     v, i, ws, Xs, expected = layer(T, K, O, N, M, 2)
     streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    named = [[torch.zeros_like(y) for _ in range(10)] for y in expected]
     torch.cuda.synchronize()
     outs = [[], []]
-    for _ in range(10):
+    for turn in range(10):
         for n, s in enumerate(streams):
             with torch.cuda.stream(s):
                 outs[n].append(nm.nm_linear_forward_prepared(v, i, K, N, M, Xs[n], ws))
+            if turn % 2:
+                nm.nm_linear_forward_prepared(v, i, K, N, M, Xs[n], ws, out=named[n][turn], stream=s)
+            else:
+                nm.nm_linear_forward_prepared_batched([(v, i, K, N, M, Xs[n], ws, None, named[n][turn])], stream=s)
     torch.cuda.synchronize()
     for got, y in zip(outs, expected):
+        assert all(torch.equal(g, y) for g in got)
+    for got, y in zip(named, expected):
         assert all(torch.equal(g, y) for g in got)
 
 
