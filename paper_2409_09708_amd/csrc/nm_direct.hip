@@ -8,7 +8,7 @@
 // K / 64 steps.  So a block is small (768 out-features are 24 of them per 64 tokens), all four waves decode, the loads
 // of two spans of 256 reduction positions are in flight in registers while a third is multiplied, and a span has one
 // barrier; in blocks of 16 or 32 tokens four spans share one (launch_level).  Which products it takes is decided in nm_spmm.hip
-// (direct_takes).  In a graph, pre-pass and product before: 768 -> 1000 at 4:8 and 8 tokens 9.4 -> 4.6 us, 3072 -> 768 at
+// (direct_form).  In a graph, pre-pass and product before: 768 -> 1000 at 4:8 and 8 tokens 9.4 -> 4.6 us, 3072 -> 768 at
 // 1:4 16.4 -> 9.4, 1024 -> 4096 at 4:8 16.3 -> 6.0.
 //
 // Two summation orders, so that a product is the same bytes whichever kernel of its route computes it:
@@ -18,6 +18,8 @@
 //                   and the odd runs of 8 positions
 #include "nm_launch.h"
 #include "nm_mma.h"
+
+#include <type_traits>
 
 namespace nm {
 namespace {
@@ -33,6 +35,7 @@ struct DirectArgs {
   int64_t ldx, ldy;
   int32_t O, K, T;
   int32_t out_bf16, pieces;  // pieces: rows of Y are made of aligned runs of four outputs
+  int32_t rows16;            // rows of Y in whole aligned 16-byte pieces
 };
 
 template <int N, int M, int TOKS>
@@ -316,6 +319,341 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// The same for more tokens: blocks of 64 out-features x 128 tokens on eight waves, in the tiled kernel's summation order.
+// Against the pre-pass and the tiled kernel it saves a launch (about 4 us) and the weight's way through memory, and it decodes the
+// weight once per 128 tokens: it wins while its blocks are one round or two on the chip and the reduction is not long (the choice is
+// nm_spmm.hip's).  A whole call in a graph, before and after: 1576 x 1024 -> 1024 at 2:8 11.1 -> 8.9 us, 788 x 768 -> 2304 at 1:8 11.2 ->
+// 7.4, 6304 x 256 -> 256 7.2 -> 4.9, 1579 x 1000 -> 1001 in fp32 13.3 -> 11.4; 2048 tokens x 3072 -> 768, which stays with the two, would lose.
+// What bounds it: a span of 128 reduction positions brings 40 KB into a unit, 0.4 us at the 100 GB/s that a unit gets, and
+// moves 137 KB through its LDS; it takes 0.5 us at 1:16 and 0.59 at 2:8.  So the loads of two spans are in flight, the lanes decode in
+// registers (2-byte LDS writes per kept value: 9.4 us for the 8.9 above), and two whole spans at a time run without conditions.
+// Slower: four waves of 64 x 32 (12.0), half the waves bringing and half multiplying (10.3), activations straight from
+// memory into the operand registers (12.8: rows 2 KB apart share the first-level cache's lines).
+// ---------------------------------------------------------------------------------------------
+template <int N, int M>
+struct WideCfg {
+  static constexpr int ROWS = 64, TOKS = 128, STEPS = 2;   // of a block; 64-wide steps per span
+  static constexpr int NW = 8, NT = NW * 64;
+  static constexpr int WO = 2, WT = 4;                     // waves along out-features, along tokens
+  static constexpr int OT = ROWS / 16 / WO, TT = TOKS / 16 / WT;
+  static constexpr bool SPARSE = N <= 2 && N < M;
+  static constexpr int B = log2_of(M);
+  static constexpr int VPC = 16 / M * N;
+  static constexpr int BITS = VPC * B;
+  static constexpr int WORDS = 32 % BITS == 0 ? 1 : 2;
+  static constexpr int VW = (VPC + 1) / 2;
+  static constexpr int PIECES = TOKS * STEPS * 8 / NT;     // of X, per lane and span; of the weight a chunk of 16
+  static constexpr int X_STEP = TOKS * 128, X_SPAN = STEPS * X_STEP;
+  static constexpr int A_ROWB = SPARSE ? 64 : 128;
+  static constexpr int A_STEP = ROWS * A_ROWB, S_STEP = SPARSE ? ROWS * 8 : 0;
+  static constexpr int SPAN = X_SPAN + STEPS * (A_STEP + S_STEP);
+  static constexpr int LDS_BYTES = 2 * SPAN;
+  static_assert(NT == ROWS * STEPS * 4 && NW * wave_tile_slice_bytes<OT, 4>() <= LDS_BYTES && LDS_BYTES <= 160 * 1024, "LDS budget");
+};
+
+template <int N, int M>
+struct WideLoads {
+  using C = WideCfg<N, M>;
+  uint32_t v[C::VW], f[C::WORDS];
+  u32x4_t x[C::PIECES];
+};
+
+// The 2:4 operand of 16 weights, in registers: a run of four owns two 16-bit slots, its first kept value in the first one and a
+// second one in the second, free slots zero; four selector bits per run.  v: the kept values in pairs, fields: their positions.
+template <int N, int M>
+__device__ __forceinline__ void sparse_piece(const uint32_t* v, uint32_t fields, u32x4_t& piece, uint32_t& sel) {
+  if constexpr (M == 4) {  // 1:4: a value per run, always in its first slot
+    piece = u32x4_t{v[0] & 0xFFFFu, v[0] >> 16, v[1] & 0xFFFFu, v[1] >> 16};
+    const uint32_t four = fields & 0xFFu, pairs = (four | (four << 4)) & 0x0F0Fu;
+    sel = (pairs | (pairs << 2)) & 0x3333u;
+  } else if constexpr (M == 8) {  // two groups of two runs
+    sel = 0;
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      if constexpr (N == 1) {
+        const uint32_t pos = (fields >> (3 * g)) & 7u, value = (v[0] >> (16 * g)) & 0xFFFFu;
+        piece[2 * g] = pos & 4u ? 0u : value;
+        piece[2 * g + 1] = pos & 4u ? value : 0u;
+        sel |= (pos & 3u) << (8 * g + (pos & 4u));
+      } else {
+        const uint32_t p0 = (fields >> (6 * g)) & 7u, p1 = (fields >> (6 * g + 3)) & 7u;
+        const bool upper = p0 & 4u, same = ((p0 ^ p1) & 4u) == 0;
+        const uint32_t first = v[g] & 0xFFFFu, second = v[g] >> 16;
+        piece[2 * g] = same ? (upper ? 0u : v[g]) : (upper ? second : first);
+        piece[2 * g + 1] = same ? (upper ? v[g] : 0u) : (upper ? first : second);
+        sel |= ((p0 & 3u) << (p0 & 4u) | (p1 & 3u) << ((p1 & 4u) + (same ? 2u : 0u))) << (8 * g);
+      }
+    }
+  } else {  // one group of four runs
+    const uint32_t p0 = fields & 15u, first = v[0] & 0xFFFFu;
+    if constexpr (N == 1) {
+#pragma unroll
+      for (uint32_t r = 0; r < 4; ++r) piece[r] = (p0 >> 2) == r ? first : 0u;
+      sel = (p0 & 3u) << (p0 & 12u);
+    } else {
+      const uint32_t p1 = (fields >> 4) & 15u;
+      const bool same = ((p0 ^ p1) & 12u) == 0;
+      const uint32_t second = same ? v[0] & 0xFFFF0000u : v[0] >> 16;
+#pragma unroll
+      for (uint32_t r = 0; r < 4; ++r) piece[r] = ((p0 >> 2) == r ? first : 0u) | ((p1 >> 2) == r ? second : 0u);
+      sel = (p0 & 3u) << (p0 & 12u) | (p1 & 3u) << ((p1 & 12u) + (same ? 2u : 0u));
+    }
+  }
+}
+
+template <int N, int M, bool WHOLE>
+__global__ void __launch_bounds__(512) nm_direct_wide_kernel(const DirectArgs a) {
+  using C = WideCfg<N, M>;
+  using Loads = WideLoads<N, M>;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r16 = lane & 15, kb = lane >> 4;
+  const int wo = wave % C::WO, wt = wave / C::WO;
+  const int o0 = (int)blockIdx.x * C::ROWS, t0 = (int)blockIdx.y * C::TOKS;
+  const int nk = (a.K + 63) >> 6, spans = (nk + C::STEPS - 1) / C::STEPS;
+  const int64_t nf = (int64_t)a.K / M * N;
+  const int64_t nw = (nf * C::B + 31) / 32;
+
+  // Where a lane's chunk and pieces of span 0 lie; rows past the last out-feature or token re-read the last one (never stored).
+  // A span ends on a word of the index stream or in the middle of one: `par` is the span's parity.
+  const int row = tid >> 3, chunk = tid & 7;
+  const int64_t o_row = o0 + row < a.O ? o0 + row : a.O - 1;
+  const bf16_t* const v_at = a.values + o_row * nf + chunk * C::VPC;
+  const uint32_t* const f_at = a.indices + o_row * nw;
+  uint32_t x_off[C::PIECES];
+  const unsigned char* x_base = reinterpret_cast<const unsigned char*>(a.X + (int64_t)t0 * a.ldx);
+#pragma unroll
+  for (int i = 0; i < C::PIECES; ++i) {
+    int t = (tid >> 4) + C::NT / 16 * i;
+    if (t0 + t >= a.T) t = a.T - 1 - t0;
+    x_off[i] = (uint32_t)t * (uint32_t)(a.ldx * 2) + (uint32_t)(tid & 15) * 16;
+  }
+  constexpr int SPAN_BITS = 8 * C::BITS;
+  auto field_at = [&](auto par) { return (decltype(par)::value * SPAN_BITS % 32) + chunk * C::BITS; };  // in bits, from the word the span begins in
+  auto load_run = [](const bf16_t* src, auto count, uint32_t* out) {  // `count` values at an address aligned to them
+    constexpr int n = decltype(count)::value;
+    if constexpr (n % 8 == 0) {
+#pragma unroll
+      for (int i = 0; i < n / 2; i += 4) {
+        const uint4 q = *reinterpret_cast<const uint4*>(src + 2 * i);
+        out[i] = q.x; out[i + 1] = q.y; out[i + 2] = q.z; out[i + 3] = q.w;
+      }
+    } else if constexpr (n % 4 == 0) {
+#pragma unroll
+      for (int i = 0; i < n / 2; i += 2) {
+        const uint2 q = *reinterpret_cast<const uint2*>(src + 2 * i);
+        out[i] = q.x; out[i + 1] = q.y;
+      }
+    } else if constexpr (n % 2 == 0) {
+#pragma unroll
+      for (int i = 0; i < n / 2; ++i) out[i] = *reinterpret_cast<const uint32_t*>(src + 2 * i);
+    } else {
+#pragma unroll
+      for (int i = 0; i < n; ++i) out[i / 2] = i & 1 ? out[i / 2] | ((uint32_t)src[i] << 16) : (uint32_t)src[i];
+    }
+  };
+  // The loads of a span carry no condition, so that the compiler counts them and a span waits for its own and not for those of
+  // the next one (with conditions it drains them all: a round trip to memory per span).  What lies past K is fetched from the
+  // span's first positions instead and cleared on its way into LDS; past the last span the last one is fetched again.
+  auto fetch = [&](Loads& d, int span, auto par) {
+    const int k_left = a.K - span * 128;  // reduction positions from the span on
+    const int64_t word0 = (int64_t)span * SPAN_BITS >> 5;
+    const bool in = chunk * 16 < k_left, half_in = chunk * 16 + 8 < k_left;
+    const bf16_t* src = v_at + (int64_t)span * (8 * C::VPC) - (in ? 0 : chunk * C::VPC);
+    if constexpr (WHOLE) {
+      load_run(src, std::integral_constant<int, C::VPC>{}, d.v);
+    } else {  // K % 16 == 8: rows begin on half a chunk, and the last chunk may be half of one
+      constexpr int HALF = C::VPC / 2;
+      const bf16_t* second = src + (half_in ? HALF : 0);
+      if constexpr (HALF % 2 == 0) {
+        load_run(src, std::integral_constant<int, HALF>{}, d.v);
+        load_run(second, std::integral_constant<int, HALF>{}, d.v + HALF / 2);
+      } else {
+#pragma unroll
+        for (int i = 0; i < C::VW; ++i) d.v[i] = 0;
+#pragma unroll
+        for (int j = 0; j < C::VPC; ++j) d.v[j / 2] |= (uint32_t)(j < HALF ? src[j] : second[j - HALF]) << (16 * (j & 1));
+      }
+    }
+    const int64_t word = in ? word0 + (field_at(par) >> 5) : 0;
+    d.f[0] = f_at[word];
+    if constexpr (C::WORDS == 2) d.f[1] = f_at[word + 1 < nw ? word + 1 : word];
+    const unsigned char* x = x_base + (int64_t)span * 256;
+    const uint32_t back = (tid & 15) * 8 < k_left ? 0u : (uint32_t)(tid & 15) * 16;
+#pragma unroll
+    for (int i = 0; i < C::PIECES; ++i) d.x[i] = *reinterpret_cast<const u32x4_t*>(x + (x_off[i] - back));
+  };
+  auto clear_past = [&](Loads& d, int span) {  // the last span, where K ends inside it
+    const int k_left = a.K - span * 128;
+#pragma unroll
+    for (int j = 0; j < C::VPC; ++j)
+      if (chunk * 16 + (j < C::VPC / 2 ? 0 : 8) >= k_left) d.v[j / 2] &= j & 1 ? 0xFFFFu : 0xFFFF0000u;
+    if ((tid & 15) * 8 >= k_left)
+#pragma unroll
+      for (int i = 0; i < C::PIECES; ++i) d.x[i] = u32x4_t{0, 0, 0, 0};
+  };
+  // a span into its LDS buffer, the weight decoded; 16-byte pieces of a row are XOR-swizzled with the row
+  auto put = [&](Loads& d, int span, unsigned char* buf, auto par, auto whole_span) {
+    if constexpr (!decltype(whole_span)::value)
+      if (a.K - span * 128 < 128) clear_past(d, span);
+    const int step = chunk >> 2, c = chunk & 3;
+    uint32_t fields = d.f[0] >> (field_at(par) & 31);
+    if constexpr (C::WORDS == 2) fields = __builtin_amdgcn_alignbit(d.f[1], d.f[0], field_at(par) & 31);
+    unsigned char* at = buf + C::X_SPAN + step * C::A_STEP + row * C::A_ROWB;
+    if constexpr (C::SPARSE) {
+      u32x4_t piece;
+      uint32_t sel;
+      sparse_piece<N, M>(d.v, fields, piece, sel);
+      *reinterpret_cast<u32x4_t*>(at + (c ^ ((row >> 1) & 3)) * 16) = piece;
+      *reinterpret_cast<uint16_t*>(buf + C::X_SPAN + C::STEPS * C::A_STEP + step * C::S_STEP + (row >> 5) * 256 + (row & 15) * 16 +
+                                   c * 4 + ((row >> 4) & 1) * 2) = (uint16_t)sel;
+    } else {
+      const int key = row & 7;
+      *reinterpret_cast<u32x4_t*>(at + ((2 * c) ^ key) * 16) = u32x4_t{0, 0, 0, 0};
+      *reinterpret_cast<u32x4_t*>(at + ((2 * c + 1) ^ key) * 16) = u32x4_t{0, 0, 0, 0};
+      // (the index fields of groups past K may be anything: their values, zero, stay inside their groups)
+#pragma unroll
+      for (int j = 0; j < C::VPC; ++j) {
+        const uint32_t pos = (uint32_t)(j / N * M) + ((fields >> (C::B * j)) & (uint32_t)(M - 1));
+        *reinterpret_cast<uint16_t*>(at + (((2 * c + (pos >> 3)) ^ key) * 16) + (pos & 7) * 2) = (uint16_t)(d.v[j / 2] >> (16 * (j & 1)));
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < C::PIECES; ++i) {
+      const int t = (tid >> 4) + C::NT / 16 * i, p = tid & 15;
+      *reinterpret_cast<u32x4_t*>(buf + (p >> 3) * C::X_STEP + t * 128 + (((p & 7) ^ (t & 7)) * 16)) = d.x[i];
+    }
+  };
+
+  f32x4_t acc[C::OT][C::TT];
+  const int o_wave = o0 + wo * C::OT * 16;
+#pragma unroll
+  for (int i = 0; i < C::OT; ++i) {
+    f32x4_t b = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    if (a.bias != nullptr)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (o_wave + 16 * i + kb * 4 + e < a.O) b[e] = a.bias[o_wave + 16 * i + kb * 4 + e];
+#pragma unroll
+    for (int j = 0; j < C::TT; ++j) acc[i][j] = b;
+  }
+
+  auto multiply = [&](const unsigned char* buf, int steps) {
+#pragma unroll
+    for (int st = 0; st < C::STEPS; ++st) {
+      if (st >= steps) break;
+      const unsigned char* x = buf + st * C::X_STEP + (wt * C::TT * 16 + r16) * 128;
+      const unsigned char* w = buf + C::X_SPAN + st * C::A_STEP + (wo * C::OT * 16 + r16) * C::A_ROWB;
+      const int xk = r16 & 7;
+      if constexpr (C::SPARSE) {
+        u32x4_t af[C::OT];
+        int sel[C::OT / 2];
+        u32x8_t b[C::TT];
+#pragma unroll
+        for (int i = 0; i < C::OT; ++i) af[i] = *reinterpret_cast<const u32x4_t*>(w + i * 16 * C::A_ROWB + (kb ^ ((r16 >> 1) & 3)) * 16);
+#pragma unroll
+        for (int i = 0; i < C::OT / 2; ++i)
+          sel[i] = (int)*reinterpret_cast<const uint32_t*>(buf + C::X_SPAN + C::STEPS * C::A_STEP + st * C::S_STEP +
+                                                           (wo * C::OT / 2 + i) * 256 + r16 * 16 + kb * 4);
+#pragma unroll
+        for (int j = 0; j < C::TT; ++j) {
+          const u32x4_t lo = *reinterpret_cast<const u32x4_t*>(x + j * 2048 + ((kb ^ xk) * 16));
+          const u32x4_t hi = *reinterpret_cast<const u32x4_t*>(x + j * 2048 + (((4 + kb) ^ xk) * 16));
+          b[j] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        }
+#pragma unroll
+        for (int j = 0; j < C::TT; ++j) {
+#pragma unroll
+          for (int i = 0; i < C::OT; i += 2) {
+            acc[i][j] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(__builtin_bit_cast(bf16x8_t, af[i]), __builtin_bit_cast(bf16x16_t, b[j]), acc[i][j], sel[i / 2], 0, 0);
+            acc[i + 1][j] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(__builtin_bit_cast(bf16x8_t, af[i + 1]), __builtin_bit_cast(bf16x16_t, b[j]), acc[i + 1][j], sel[i / 2], 0, 1);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int at = ((4 * h + kb) ^ xk) * 16;
+          u32x4_t af[C::OT], b[C::TT];
+#pragma unroll
+          for (int i = 0; i < C::OT; ++i) af[i] = *reinterpret_cast<const u32x4_t*>(w + i * 16 * C::A_ROWB + at);
+#pragma unroll
+          for (int j = 0; j < C::TT; ++j) b[j] = *reinterpret_cast<const u32x4_t*>(x + j * 2048 + at);
+#pragma unroll
+          for (int j = 0; j < C::TT; ++j)
+#pragma unroll
+            for (int i = 0; i < C::OT; ++i)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, af[i]), __builtin_bit_cast(bf16x8_t, b[j]), acc[i][j], 0, 0, 0);
+        }
+      }
+    }
+  };
+
+  // Two register sets and two LDS buffers, as in the kernel above.
+  constexpr std::integral_constant<int, 0> p0{};
+  constexpr std::integral_constant<int, 1> p1{};
+  Loads even, odd;
+  const int last = spans - 1;
+  fetch(even, 0, p0);
+  fetch(odd, last < 1 ? 0 : 1, p1);  // (a span of the other parity is fetched in vain, past the end: its fields are not used)
+  int span = 0;
+  for (; a.K - span * 128 >= 256; span += 2) {  // two whole spans: no conditions, so that a span's decoding and the products interleave
+    put(even, span, smem, p0, std::true_type{});
+    fetch(even, span + 2 <= last ? span + 2 : last, p0);
+    __syncthreads();
+    multiply(smem, C::STEPS);
+    put(odd, span + 1, smem + C::SPAN, p1, std::true_type{});
+    fetch(odd, span + 3 <= last ? span + 3 : last, p1);
+    __syncthreads();
+    multiply(smem + C::SPAN, C::STEPS);
+  }
+  if (span < spans) {
+    put(even, span, smem, p0, std::false_type{});
+    __syncthreads();
+    multiply(smem, nk - span * C::STEPS);
+    if (span + 1 < spans) {
+      put(odd, span + 1, smem + C::SPAN, p1, std::false_type{});
+      __syncthreads();
+      multiply(smem + C::SPAN, nk - (span + 1) * C::STEPS);
+    }
+  }
+
+  const int64_t row0 = t0 + wt * C::TT * 16, col0 = o_wave;
+  if (a.K & 63) {  // sums that ended as NaN again by the definition, as the ragged form of the tiled kernel has it
+    uint32_t which = 0;  // bit 4 (i TT + j) + e
+    static_assert(C::OT * C::TT <= 8, "one bit per sum");
+#pragma unroll
+    for (int i = 0; i < C::OT; ++i)
+#pragma unroll
+      for (int j = 0; j < C::TT; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) which |= (__builtin_isnan(acc[i][j][e]) ? 1u : 0u) << (4 * (i * C::TT + j) + e);
+    for (; which != 0; which &= which - 1) {
+      const int bit = __ffs(which) - 1;
+      const int64_t t = row0 + (bit >> 2) % C::TT * 16 + r16, o = col0 + (bit >> 2) / C::TT * 16 + kb * 4 + (bit & 3);
+      if (t >= a.T || o >= a.O) continue;
+      const float y = gather_output(a.values, a.indices, a.K, N, M, a.X + t * a.ldx, a.bias, o);
+#pragma unroll
+      for (int i = 0; i < C::OT; ++i)
+#pragma unroll
+        for (int j = 0; j < C::TT; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (bit == 4 * (i * C::TT + j) + e) acc[i][j][e] = y;
+    }
+  }
+  __syncthreads();  // every wave is done with the buffers
+  auto get = [&](int i, int j) { return __builtin_bit_cast(u32x4_t, acc[i][j]); };
+  unsigned char* slice = smem + wave * wave_tile_slice_bytes<C::OT, 4>();
+  if (a.rows16) {
+    if (a.out_bf16) write_wave_tile_pieces<C::OT, C::TT, 2>(slice, lane, get, a.Y, a.ldy, row0, col0, a.T, a.O);
+    else write_wave_tile_pieces<C::OT, C::TT, 4>(slice, lane, get, a.Y, a.ldy, row0, col0, a.T, a.O);
+  } else {
+    if (a.out_bf16) write_wave_tile_rows<C::OT, C::TT, 2>(slice, lane, get, a.Y, a.ldy, row0, col0, a.T, a.O);
+    else write_wave_tile_rows<C::OT, C::TT, 4>(slice, lane, get, a.Y, a.ldy, row0, col0, a.T, a.O);
+  }
+}
+
 template <int N, int M, int TOKS, bool PACKED>
 hipError_t launch_tokens(const DirectArgs& g, hipStream_t s) {
   using C = DirectCfg<N, M, TOKS>;
@@ -352,6 +690,24 @@ hipError_t launch_level(const DirectArgs& g, hipStream_t s) {
   return launch_tokens<N, M, 64, PACKED>(g, s);
 }
 
+template <int N, int M, bool WHOLE>
+hipError_t launch_wide(const DirectArgs& g, hipStream_t s) {
+  using C = WideCfg<N, M>;
+  auto kern = nm_direct_wide_kernel<N, M, WHOLE>;
+  static PerDeviceOnce lds_limit;
+  if (hipError_t e = raise_dynamic_lds_limit(kern, C::LDS_BYTES, lds_limit); e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)((g.O + C::ROWS - 1) / C::ROWS), (unsigned)((g.T + C::TOKS - 1) / C::TOKS)), dim3(C::NT),
+                     C::LDS_BYTES, s, g);
+  return hipGetLastError();
+}
+
+template <int N, int M>
+hipError_t launch_wide_level(const DirectArgs& g, hipStream_t s) {
+  if constexpr (M < 16)
+    if (g.K % 16) return launch_wide<N, M, false>(g, s);
+  return launch_wide<N, M, true>(g, s);
+}
+
 }  // namespace
 
 // The levels whose packed form the matrix instructions cannot read as it lies and whose 16 weights have at most 32 bits
@@ -365,14 +721,25 @@ bool direct_level(int N, int M) {
 }
 
 // The caller has checked the operands (K % 64 == 0, or K % 16 == 0 in the tiled kernel's order; 16-byte aligned X rows and
-// values, sizes as the tiled kernel's).
-hipError_t launch_direct(const SpmmArgs& a, bool packed_order, hipStream_t s) {
+// values, sizes as the tiled kernel's).  wide: blocks of 64 out-features x 128 tokens, the tiled kernel's order only, and K % 8 == 0 is
+// enough (at M = 16 K is a multiple of 16 anyway).
+hipError_t launch_direct(const SpmmArgs& a, bool packed_order, bool wide, hipStream_t s) {
   DirectArgs g;
   g.values = a.values; g.indices = a.indices; g.X = a.X; g.bias = a.bias; g.Y = a.Y;
   g.ldx = a.ldx; g.ldy = a.ldy;
   g.O = (int32_t)a.O; g.K = (int32_t)a.K; g.T = (int32_t)a.T;
   g.out_bf16 = a.out_bf16;
   g.pieces = (a.O % 4 == 0) && (a.ldy % 4 == 0) && ((uintptr_t)a.Y & (a.out_bf16 ? 7u : 15u)) == 0;
+  const int per_piece = a.out_bf16 ? 8 : 4;
+  g.rows16 = (a.O % per_piece == 0) && (a.ldy % per_piece == 0) && ((uintptr_t)a.Y & 15u) == 0;
+  if (wide) {
+    switch (a.N * 32 + a.M) {
+#define X(n, m) case n * 32 + m: return launch_wide_level<n, m>(g, s);
+      X(1, 4) X(3, 4) X(1, 8) X(2, 8) X(3, 8) X(4, 8) X(1, 16) X(2, 16) X(4, 16)
+#undef X
+      default: return hipErrorInvalidValue;
+    }
+  }
   switch (a.N * 32 + a.M) {
 #define X(n, m)                                                                              \
   case n * 32 + m:                                                                           \

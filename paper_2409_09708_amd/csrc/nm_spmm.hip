@@ -2245,21 +2245,48 @@ static bool packed_path(const SpmmArgs& a) {
 // Its sums are those of the tiled kernel; a layer that the persistent kernel or a cut reduction would sum in another
 // order stays there.
 constexpr TileModel kDirectModel[2] = {{32, 64, 3.81, 0.130, 0.57, 1.09}, {32, 64, 3.22, 0.117, 0.85, 0.68}};  // [2:4 form]
-static bool direct_takes(int64_t O, int64_t K, int N, int M, int64_t T, int pick) {
-  const bool sparse_form = N <= 2;
-  if (pick == 0 || !direct_level(N, M) || split_count(O, K, T, sparse_form) != 1) return false;
-  const int64_t blocks = ((O + 31) / 32) * ((T + 63) / 64);
-  if ((T + 63) / 64 > 65535 || blocks > (1 << 20)) return false;  // (a grid's second dimension)
-  double two = 1e30;
-  for (const TileModel& m : kTileModel[sparse_form])
-    if (const double e = tile_estimate(m, O, K, T); e < two) two = e;
-  two += 3.85 + (sparse_form ? 0.49 : 0.85) * 1e-6 * (double)((O + 255) / 256 * 256) * (double)K;
-  return tile_estimate(kDirectModel[sparse_form], O, K, T) < two;
+// Its second form, blocks of 64 out-features x 128 tokens, takes what is beyond the first one's few rounds and still not worth the two
+// launches: spans of 128 reduction positions, and of a block's span and its write-out the parts that grow with the kept
+// values of 16 weights and with the bytes of an output.  Fitted on 3200 shapes (40 .. 8000 tokens, 64 .. 4096 deep and wide, whole and
+// ragged, in a graph) with an rms of 8 %, but for the smallest, which take 4.5 us where the model has 3.7.  It has to be a fifth
+// faster than the first form, whose estimate is the rougher one; up to 64 tokens half its block would be empty, and a reduction of
+// 3072 and more, whose spans cost more than the tiled kernel's steps, it never won.  With it those calls take 0.935 of the time on average (the best
+// route of each 0.922), a third of them 5 % less or better, 18 of 3200 5 % more: 551 x 256 -> 129 at 4:8 stays with the first form
+// (4.2 us, 5.7), 788 x 768 -> 2304 at 1:8 7.4 and 11.2 in two launches, 1576 x 3072 -> 768 at 2:8 17.5 in two and 22.8.
+struct WideModel {
+  double start, span, kept, epi, byte, busy;
+};
+constexpr WideModel kWideModel[2] = {{1.30, 0.650, 0.029, 1.24, 0.12, 0.29}, {1.55, 0.572, 0.016, 1.18, 0.092, 0.37}};  // [2:4 form]
+static double wide_estimate(int64_t O, int64_t K, int N, int M, int64_t T, bool out_bf16) {
+  const WideModel& m = kWideModel[N <= 2];
+  const double tiles = (double)((O + 63) / 64) * (double)((T + 127) / 128);
+  const double full = (double)(int64_t)(tiles / kModelUnits), rest = tiles - full * kModelUnits;
+  const double block = (double)((K + 127) / 128) * (m.span + m.kept * (double)(16 / M * N)) + m.epi + m.byte * (out_bf16 ? 2.0 : 4.0);
+  const double e = m.start + block * (full * (1.0 + m.busy) + (rest > 0 ? 1.0 + m.busy * rest / kModelUnits : 0.0));
+  return e < 4.5 ? 4.5 : e;
 }
 
-// A ragged reduction of whole 16-weight chunks is decoded likewise (210 x 144 -> 332 at 1:16 8.5 us in two launches, 4.4 here).
-static bool direct_takes_ragged(int64_t O, int64_t K, int N, int M, int64_t T) {
-  return K % 16 == 0 && direct_takes(O, padded_k(K), N, M, T, 2);
+enum DirectForm { DIRECT_NONE, DIRECT_FIRST, DIRECT_WIDE };
+static DirectForm direct_form(int64_t O, int64_t K, int N, int M, int64_t T, bool out_bf16, int pick) {
+  const bool sparse_form = N <= 2;
+  const int64_t steps_k = padded_k(K);
+  if (pick == 0 || !direct_level(N, M) || split_count(O, steps_k, T, sparse_form) != 1) return DIRECT_NONE;
+  const int64_t blocks = ((O + 31) / 32) * ((T + 63) / 64);
+  if ((T + 63) / 64 > 65535 || blocks > (1 << 20)) return DIRECT_NONE;  // (a grid's second dimension)
+  double two = 1e30;
+  for (const TileModel& m : kTileModel[sparse_form])
+    if (const double e = tile_estimate(m, O, steps_k, T); e < two) two = e;
+  two += 3.85 + (sparse_form ? 0.49 : 0.85) * 1e-6 * (double)((O + 255) / 256 * 256) * (double)steps_k;
+  const double first = K % 16 == 0 ? tile_estimate(kDirectModel[sparse_form], O, steps_k, T) : 1e30;
+  if (T > 64 && K < 3072)
+    if (const double e = wide_estimate(O, K, N, M, T, out_bf16); e < 0.8 * first && e < two) return DIRECT_WIDE;
+  return first < two ? DIRECT_FIRST : DIRECT_NONE;
+}
+
+// A ragged reduction is decoded likewise, of whole 16-weight chunks (210 x 144 -> 332 at 1:16 8.5 us in two launches, 4.4 here) or of
+// eight more, which the second form takes.
+static DirectForm direct_form_ragged(int64_t O, int64_t K, int N, int M, int64_t T, bool out_bf16) {
+  return K % 8 == 0 ? direct_form(O, K, N, M, T, out_bf16, 2) : DIRECT_NONE;
 }
 
 // A call without a workspace takes it up to four rounds of blocks, and at one block of tokens in any case; beyond, it would
@@ -2286,9 +2313,10 @@ hipError_t launch_spmm(const SpmmArgs& a, hipStream_t s, bool* workspace_short, 
   if (!tiles_ok(a.K, a.X, a.ldx, a.values, a.indices, a.O, a.T)) {
     // without the workspace the gather kernel reads the packed layout itself
     const bool ragged = copy_fits && (a.K % 64 != 0 || tiles_ok(a.K, nullptr, a.K, a.values, a.indices, a.O, a.T));
-    if (ragged && prepare && product && a.K % 64 != 0 && aligned_to(a.X, 16) && a.ldx % 8 == 0 && aligned_to(a.values, 16) &&
-        direct_takes_ragged(a.O, a.K, a.N, a.M, a.T))
-      return launch_direct(a, false, s);
+    if (ragged && prepare && product && a.K % 64 != 0 && aligned_to(a.X, 16) && a.ldx % 8 == 0 && aligned_to(a.values, 16))
+      if (const DirectForm f = direct_form_ragged(a.O, a.K, a.N, a.M, a.T, a.out_bf16);
+          f == DIRECT_FIRST || (f == DIRECT_WIDE && a.ldx <= (1 << 22)))
+        return launch_direct(a, false, f == DIRECT_WIDE, s);
     if (ragged && prepare) {
       hipError_t e = launch_stream_prepass(a, sparse_form, s);
       if (e != hipSuccess) return e;
@@ -2302,14 +2330,16 @@ hipError_t launch_spmm(const SpmmArgs& a, hipStream_t s, bool* workspace_short, 
     if (!packed_path(a)) {
       *workspace_short = true;
     } else if (product) {
-      if (direct_takes_packed(a.O, a.T)) return launch_direct(a, true, s);
+      if (direct_takes_packed(a.O, a.T)) return launch_direct(a, true, false, s);
       const SpmmArgs* one = &a;
       return launch_fewtok(&one, 1, s);
     }
     return hipSuccess;
   }
   const int pick = pick_tile(a.O, a.K, a.T, sparse_form);
-  if (prepare && product && direct_takes(a.O, a.K, a.N, a.M, a.T, pick)) return launch_direct(a, false, s);
+  if (prepare && product)
+    if (const DirectForm f = direct_form(a.O, a.K, a.N, a.M, a.T, a.out_bf16, pick); f != DIRECT_NONE)
+      return launch_direct(a, false, f == DIRECT_WIDE, s);
   GemmArgs g;
   fill_gemm_args(a, form, sparse_form, &g);
   if (prepare && form == FORM_STREAM) {
@@ -2322,19 +2352,24 @@ hipError_t launch_spmm(const SpmmArgs& a, hipStream_t s, bool* workspace_short, 
 }
 
 // Not in the public header, for tests: the kernel that a product of aligned operands takes at one layer's shape and, for
-// the tiled and the persistent one, its tile (out-features, tokens, LDS stages).
+// the tiled and the persistent one and the second form of the one that decodes itself (bfloat16 output), its tile
+// (out-features, tokens, LDS stages).
 // call: 0 the weight is prepared in the same call, 1 it has been, 2 there is no workspace.
 extern "C" int32_t nm_internal_product_route(int32_t call, int64_t O, int64_t K, int32_t N, int32_t M, int64_t T, int32_t* tile) {
   enum { ROUTE_GENERAL, ROUTE_TILED, ROUTE_PERSISTENT, ROUTE_RAGGED, ROUTE_DIRECT, ROUTE_FEWTOK };
   const bool sparse_form = N <= 2 && N < M;
+  auto direct = [&](DirectForm f) {
+    if (f == DIRECT_WIDE) { tile[0] = 64; tile[1] = 128; tile[2] = 2; }
+    return f != DIRECT_NONE;
+  };
   if (K % 64) {
     if (call == 2 || !ragged_shape(O, K, T)) return ROUTE_GENERAL;
-    return call == 0 && direct_takes_ragged(O, K, N, M, T) ? ROUTE_DIRECT : ROUTE_RAGGED;
+    return call == 0 && direct(direct_form_ragged(O, K, N, M, T, true)) ? ROUTE_DIRECT : ROUTE_RAGGED;
   }
   const int pick = pick_tile(O, K, T, sparse_form);
   if (call == 2 && spmm_operand_workspace_bytes(O, K, N, M, T) != 0)
     return !fewtok_shape(O, K, N, M, T) ? -1 : direct_takes_packed(O, T) ? ROUTE_DIRECT : ROUTE_FEWTOK;
-  if (call == 0 && direct_takes(O, K, N, M, T, pick)) return ROUTE_DIRECT;
+  if (call == 0 && direct(direct_form(O, K, N, M, T, true, pick))) return ROUTE_DIRECT;
   if (pick == 0) {
     tile[0] = 256;
     tile[1] = nm_internal_stream_tile(0, sparse_form, O, T, sparse_form ? K / 64 : K / 32, &tile[2]);
