@@ -4,12 +4,14 @@
 // out-features into LDS as the operand of the matrix instructions and multiplies it with up to 64 tokens.
 //
 // What bounds it: latency.  768 -> 1000 at 4:8 and 8 tokens is 1.3 MB, under 1 us of HBM time; what takes time is one
-// round trip to memory, decoding 16 weights per lane and pass (a 2-byte LDS write per kept value), and a serial chain of
-// K / 64 steps.  So a block is small (768 out-features are 24 of them per 64 tokens), all four waves decode, the loads
-// of two spans of 256 reduction positions are in flight in registers while a third is multiplied, and a span has one
-// barrier; in blocks of 16 or 32 tokens four spans share one (launch_level).  Which products it takes is decided in nm_spmm.hip
-// (direct_form).  In a graph, pre-pass and product before: 768 -> 1000 at 4:8 and 8 tokens 9.4 -> 4.6 us, 3072 -> 768 at
-// 1:4 16.4 -> 9.4, 1024 -> 4096 at 4:8 16.3 -> 6.0.
+// round trip to memory, decoding 16 weights per lane and pass (the 2:4 operand in registers, the dense one with a 2-byte LDS write
+// per kept value), and a serial chain of K / 64 steps.  So a block is small (768 out-features are 24 of them per 64 tokens), all
+// four waves decode, the loads of two spans of 256 reduction positions are in flight in registers while a third is multiplied,
+// none of them under a condition (which would make every span wait for the next one's), and a span has one
+// barrier; in blocks of 16 or 32 tokens four spans share one (launch_level).  Conditions and 2-byte writes everywhere, before: 197 tokens x
+// 768 -> 768 at 1:4 5.5 us, now 4.95; 32 x 2048 -> 1024 at 4:8 10.5 and 8.8; 16 x 4096 -> 32768 at 4:8 75 and 55.  Which products it takes is decided in nm_spmm.hip
+// (direct_form).  In a graph, pre-pass and product before: 768 -> 1000 at 4:8 and 8 tokens 9.4 -> 3.7 us, 16 x 3072 ->
+// 16384 at 4:16, where the weight's 100 MB would be read and written once more, 20.5.
 //
 // Two summation orders, so that a product is the same bytes whichever kernel of its route computes it:
 //   PACKED = false  the tiled kernel's (nm_spmm.hip): the sum starts from the bias; the dense instruction takes the
@@ -24,7 +26,7 @@
 namespace nm {
 namespace {
 
-constexpr int kRows = 32, kSteps = 4;  // of a block: out-features, 64-wide steps per span; TOKS: its tokens, 64, 32 or 16
+constexpr int kSteps = 4;  // 64-wide steps per span.  Of a block: TOKS tokens, 64, 32 or 16, ROWS out-features, 32 or 16
 
 struct DirectArgs {
   const bf16_t* values;
@@ -38,7 +40,54 @@ struct DirectArgs {
   int32_t rows16;            // rows of Y in whole aligned 16-byte pieces
 };
 
-template <int N, int M, int TOKS>
+// The 2:4 operand of 16 weights into its 16 bytes of LDS; returns its selectors, four bits per run.  A run of four owns two 16-bit
+// slots, its first kept value in the first one and a second one in the second, free slots zero.  v: the kept values in pairs, fields:
+// their positions.  Put together in registers, but for 1:16, whose one value is cheaper as a 2-byte write over the zeros.
+template <int N, int M>
+__device__ __forceinline__ uint32_t put_sparse_piece(unsigned char* at, const uint32_t* v, uint32_t fields) {
+  u32x4_t piece = u32x4_t{0, 0, 0, 0};
+  uint32_t sel = 0;
+  if constexpr (M == 4) {  // 1:4: a value per run, always in its first slot
+    piece = u32x4_t{v[0] & 0xFFFFu, v[0] >> 16, v[1] & 0xFFFFu, v[1] >> 16};
+    const uint32_t four = fields & 0xFFu, pairs = (four | (four << 4)) & 0x0F0Fu;
+    sel = (pairs | (pairs << 2)) & 0x3333u;
+  } else if constexpr (M == 8) {  // two groups of two runs
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      if constexpr (N == 1) {
+        const uint32_t pos = (fields >> (3 * g)) & 7u, value = (v[0] >> (16 * g)) & 0xFFFFu;
+        piece[2 * g] = pos & 4u ? 0u : value;
+        piece[2 * g + 1] = pos & 4u ? value : 0u;
+        sel |= (pos & 3u) << (8 * g + (pos & 4u));
+      } else {
+        const uint32_t p0 = (fields >> (6 * g)) & 7u, p1 = (fields >> (6 * g + 3)) & 7u;
+        const bool upper = p0 & 4u, same = ((p0 ^ p1) & 4u) == 0;
+        const uint32_t first = v[g] & 0xFFFFu, second = v[g] >> 16;
+        piece[2 * g] = same ? (upper ? 0u : v[g]) : (upper ? second : first);
+        piece[2 * g + 1] = same ? (upper ? v[g] : 0u) : (upper ? first : second);
+        sel |= ((p0 & 3u) << (p0 & 4u) | (p1 & 3u) << ((p1 & 4u) + (same ? 2u : 0u))) << (8 * g);
+      }
+    }
+  } else {  // one group of four runs
+    const uint32_t p0 = fields & 15u;
+    if constexpr (N == 1) {
+      *reinterpret_cast<u32x4_t*>(at) = piece;
+      *reinterpret_cast<uint16_t*>(at + (p0 & 12u)) = (uint16_t)v[0];
+      return (p0 & 3u) << (p0 & 12u);
+    } else {
+      const uint32_t p1 = (fields >> 4) & 15u, first = v[0] & 0xFFFFu;
+      const bool same = ((p0 ^ p1) & 12u) == 0;
+      const uint32_t second = same ? v[0] & 0xFFFF0000u : v[0] >> 16;
+#pragma unroll
+      for (uint32_t r = 0; r < 4; ++r) piece[r] = ((p0 >> 2) == r ? first : 0u) | ((p1 >> 2) == r ? second : 0u);
+      sel = (p0 & 3u) << (p0 & 12u) | (p1 & 3u) << ((p1 & 12u) + (same ? 2u : 0u));
+    }
+  }
+  *reinterpret_cast<u32x4_t*>(at) = piece;
+  return sel;
+}
+
+template <int N, int M, int TOKS, int ROWS>
 struct DirectCfg {
   static constexpr int X_STEP = TOKS * 128, X_SPAN = kSteps * X_STEP;  // bytes of the activations of a step, of a span
   static constexpr int SETS = TOKS == 64 ? 2 : 4;      // spans in flight
@@ -48,7 +97,8 @@ struct DirectCfg {
   static constexpr int BITS = VPC * B;                 // their index fields
   static constexpr int WORDS = 32 % BITS == 0 ? 1 : 2;  // 32-bit words those may lie in
   static constexpr int A_ROWB = SPARSE ? 64 : 128;     // bytes of a weight row per step
-  static constexpr int A_STEP = kRows * A_ROWB;
+  static constexpr int A_STEP = ROWS * A_ROWB;
+  static constexpr int CHUNKS = ROWS / 16;             // 16-weight chunks of a lane per span
   static constexpr int S_STEP = SPARSE ? 256 : 0;      // a selector word per pair of rows and lane group
   static constexpr int SPAN = X_SPAN + kSteps * (A_STEP + S_STEP);
   static constexpr int LDS_BYTES = SETS * SPAN;
@@ -56,91 +106,100 @@ struct DirectCfg {
   static_assert(BITS <= 32 && LDS_BYTES <= 160 * 1024, "chunk fields and LDS budget");
 };
 
-// What a lane brings of a span: the packed form of two 16-weight chunks and TOKS / 8 16-byte pieces of X.
-template <int N, int M, int TOKS>
+// What a lane brings of a span: the packed form of its 16-weight chunks and TOKS / 8 16-byte pieces of X.
+template <int N, int M, int TOKS, int ROWS>
 struct DirectLoads {
-  using C = DirectCfg<N, M, TOKS>;
-  uint32_t v[2][C::VW], f[2][C::WORDS];
+  using C = DirectCfg<N, M, TOKS, ROWS>;
+  uint32_t v[C::CHUNKS][C::VW], f[C::CHUNKS][C::WORDS];
   u32x4_t x[TOKS / 8];
 };
 
-template <int N, int M, int TOKS, bool PACKED>
+template <int N, int M, int TOKS, int ROWS, bool PACKED>
 __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
-  using C = DirectCfg<N, M, TOKS>;
-  using Loads = DirectLoads<N, M, TOKS>;
+  using C = DirectCfg<N, M, TOKS, ROWS>;
+  using Loads = DirectLoads<N, M, TOKS, ROWS>;
+  static_assert(ROWS == 32 || (ROWS == 16 && TOKS == 16), "blocks");
   constexpr int kXStep = C::X_STEP, kXSpan = C::X_SPAN;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r16 = lane & 15, kb = lane >> 4;
-  const int o0 = (int)blockIdx.x * kRows, t0 = (int)blockIdx.y * TOKS;
+  const int o0 = (int)blockIdx.x * ROWS, t0 = (int)blockIdx.y * TOKS;
   const int nk = (a.K + 63) >> 6, spans = (nk + kSteps - 1) / kSteps;  // a last step may be short (K % 16 == 0)
   const int64_t nf = (int64_t)a.K / M * N;
   const int64_t nw = (nf * C::B + 31) / 32;
 
-  // a lane's chunks are tid and tid + 256 of the span's 32 rows x 16, its pieces of X tid + 256 i of TOKS rows x 32
+  // a lane's chunks are tid and tid + 256 of the span's rows x 16, its pieces of X tid + 256 i of TOKS rows x 32; rows past the
+  // last out-feature or token re-read the last one (never stored)
+  const int chunk = tid & 15;
+  const bf16_t* v_at[C::CHUNKS];
+  const uint32_t* f_at[C::CHUNKS];
+  const bf16_t* x_at[TOKS / 8];
+#pragma unroll
+  for (int u = 0; u < C::CHUNKS; ++u) {
+    const int o = o0 + (tid >> 4) + 16 * u;
+    const int64_t row = o < a.O ? o : a.O - 1;
+    v_at[u] = a.values + row * nf + chunk * C::VPC;
+    f_at[u] = a.indices + row * nw;
+  }
+#pragma unroll
+  for (int i = 0; i < TOKS / 8; ++i) {
+    const int t = t0 + (tid >> 5) + 8 * i;
+    x_at[i] = a.X + (int64_t)(t < a.T ? t : a.T - 1) * a.ldx + (tid & 31) * 8;
+  }
+  // No load carries a condition: the compiler then counts them, and a span waits for its own loads and not for the next one's too.
+  // What lies past K is fetched from the span's first positions instead and cleared on its way into LDS.
   auto fetch = [&](Loads& d, int span) {
+    const int k_left = a.K - span * 256;
+    const bool in = chunk * 16 < k_left;
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int o = o0 + (tid >> 4) + 16 * u, c = span * 16 + (tid & 15);
+    for (int u = 0; u < C::CHUNKS; ++u) {
+      const bf16_t* src = v_at[u] + (int64_t)span * (16 * C::VPC) - (in ? 0 : chunk * C::VPC);
+      if constexpr (C::VPC % 8 == 0) {
+        const uint4 q = *reinterpret_cast<const uint4*>(src);
+        d.v[u][0] = q.x; d.v[u][1] = q.y; d.v[u][2] = q.z; d.v[u][3] = q.w;
+      } else if constexpr (C::VPC % 4 == 0) {
 #pragma unroll
-      for (int i = 0; i < C::VW; ++i) d.v[u][i] = 0;
-#pragma unroll
-      for (int i = 0; i < C::WORDS; ++i) d.f[u][i] = 0;
-      if (o < a.O && c * 16 < a.K) {  // rows past O and chunks past K are zero
-        const bf16_t* src = a.values + o * nf + (int64_t)c * C::VPC;
-        if constexpr (C::VPC % 8 == 0) {
-          const uint4 q = *reinterpret_cast<const uint4*>(src);
-          d.v[u][0] = q.x; d.v[u][1] = q.y; d.v[u][2] = q.z; d.v[u][3] = q.w;
-        } else if constexpr (C::VPC % 4 == 0) {
-#pragma unroll
-          for (int i = 0; i < C::VW; i += 2) {
-            const uint2 q = *reinterpret_cast<const uint2*>(src + 2 * i);
-            d.v[u][i] = q.x; d.v[u][i + 1] = q.y;
-          }
-        } else if constexpr (C::VPC % 2 == 0) {
-#pragma unroll
-          for (int i = 0; i < C::VW; ++i) d.v[u][i] = *reinterpret_cast<const uint32_t*>(src + 2 * i);
-        } else {
-          d.v[u][0] = src[0];
+        for (int i = 0; i < C::VW; i += 2) {
+          const uint2 q = *reinterpret_cast<const uint2*>(src + 2 * i);
+          d.v[u][i] = q.x; d.v[u][i + 1] = q.y;
         }
-        const int64_t w = ((int64_t)c * C::BITS) >> 5;
-        d.f[u][0] = a.indices[o * nw + w];
-        if constexpr (C::WORDS == 2) {
-          if (w + 1 < nw) d.f[u][1] = a.indices[o * nw + w + 1];
-        }
+      } else if constexpr (C::VPC % 2 == 0) {
+#pragma unroll
+        for (int i = 0; i < C::VW; ++i) d.v[u][i] = *reinterpret_cast<const uint32_t*>(src + 2 * i);
+      } else {
+        d.v[u][0] = src[0];
       }
+      const int64_t word = (int64_t)(span * 16 + (in ? chunk : 0)) * C::BITS >> 5;
+      d.f[u][0] = f_at[u][word];
+      if constexpr (C::WORDS == 2) d.f[u][1] = f_at[u][word + 1 < nw ? word + 1 : word];
     }
+    const int back = (tid & 31) * 8 < k_left ? 0 : (tid & 31) * 8;
 #pragma unroll
-    for (int i = 0; i < TOKS / 8; ++i) {
-      const int t = t0 + (tid >> 5) + 8 * i, k = span * 256 + (tid & 31) * 8;
-      d.x[i] = u32x4_t{0, 0, 0, 0};
-      if (t < a.T && k < a.K) d.x[i] = *reinterpret_cast<const u32x4_t*>(a.X + t * a.ldx + k);
-    }
+    for (int i = 0; i < TOKS / 8; ++i) d.x[i] = *reinterpret_cast<const u32x4_t*>(x_at[i] + (int64_t)span * 256 - back);
   };
   // the same into the span's LDS buffer, the weight decoded.  16-byte pieces of a row are XOR-swizzled with the row.
-  auto put = [&](const Loads& d, int span, unsigned char* buf) {
+  auto put = [&](Loads& d, int span, unsigned char* buf) {
+    const int k_left = a.K - span * 256;
+    if (k_left < 256) {  // the last span
+      if (chunk * 16 >= k_left)
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int row = (tid >> 4) + 16 * u, step = (tid & 15) >> 2, c = tid & 3;
-      uint64_t fields = d.f[u][0];
-      if constexpr (C::WORDS == 2)
-        fields = (fields | (uint64_t)d.f[u][1] << 32) >> (((uint32_t)(span * 16 + (tid & 15)) * C::BITS) & 31);
-      else
-        fields >>= ((uint32_t)(tid & 15) * C::BITS) & 31;  // a span starts on a word
+        for (int u = 0; u < C::CHUNKS; ++u)
+#pragma unroll
+          for (int i = 0; i < C::VW; ++i) d.v[u][i] = 0;
+      if ((tid & 31) * 8 >= k_left)
+#pragma unroll
+        for (int i = 0; i < TOKS / 8; ++i) d.x[i] = u32x4_t{0, 0, 0, 0};
+    }
+#pragma unroll
+    for (int u = 0; u < C::CHUNKS; ++u) {
+      const int row = (tid >> 4) + 16 * u, step = chunk >> 2, c = chunk & 3;
+      // (at six bits a chunk, where a span ends inside a word, sixteen chunks are three words: every span starts on one)
+      const uint32_t shift = ((uint32_t)chunk * C::BITS) & 31;
+      uint32_t fields = d.f[u][0] >> shift;
+      if constexpr (C::WORDS == 2) fields = __builtin_amdgcn_alignbit(d.f[u][1], d.f[u][0], shift);
       unsigned char* at = buf + kXSpan + step * C::A_STEP + row * C::A_ROWB;
       if constexpr (C::SPARSE) {
-        // the 2:4 form: the first kept value of a run of four in slot 2 run, a second one in slot 2 run + 1
-        at += (c ^ ((row >> 1) & 3)) * 16;
-        *reinterpret_cast<u32x4_t*>(at) = u32x4_t{0, 0, 0, 0};
-        uint32_t sel = 0, prev = 0xFFFFFFFFu;
-#pragma unroll
-        for (int j = 0; j < C::VPC; ++j) {
-          const uint32_t pos = (uint32_t)(j / N * M) + ((uint32_t)(fields >> (C::B * j)) & (uint32_t)(M - 1));
-          const uint32_t run = pos >> 2, second = run == prev ? 1u : 0u;
-          prev = run;
-          *reinterpret_cast<uint16_t*>(at + 4 * run + 2 * second) = (uint16_t)(d.v[u][j / 2] >> (16 * (j & 1)));
-          sel |= (pos & 3u) << (4 * run + 2 * second);
-        }
+        const uint32_t sel = put_sparse_piece<N, M>(at + (c ^ ((row >> 1) & 3)) * 16, d.v[u], fields);
         *reinterpret_cast<uint16_t*>(buf + kXSpan + kSteps * C::A_STEP + step * C::S_STEP + (row & 15) * 16 + c * 4 +
                                      (row >> 4) * 2) = (uint16_t)sel;
       } else {
@@ -149,7 +208,7 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
         *reinterpret_cast<u32x4_t*>(at + ((2 * c + 1) ^ key) * 16) = u32x4_t{0, 0, 0, 0};
 #pragma unroll
         for (int j = 0; j < C::VPC; ++j) {
-          const uint32_t pos = (uint32_t)(j / N * M) + ((uint32_t)(fields >> (C::B * j)) & (uint32_t)(M - 1));
+          const uint32_t pos = (uint32_t)(j / N * M) + ((fields >> (C::B * j)) & (uint32_t)(M - 1));
           *reinterpret_cast<uint16_t*>(at + (((2 * c + (pos >> 3)) ^ key) * 16) + (pos & 7) * 2) =
               (uint16_t)(d.v[u][j / 2] >> (16 * (j & 1)));
         }
@@ -164,7 +223,8 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
 
   f32x4_t acc[2];
   // a lane holds out-features o_lane + 16 i .. + 3 of token r16 of its wave's 16; in blocks of 16 or 32 tokens a wave holds one
-  // block of 16 out-features (acc[0]), the lower one in the even waves
+  // block of 16 out-features (acc[0]) of the tokens `wave_t`, the lower one in the even waves
+  const int half = ROWS == 32 ? wave & 1 : 0, wave_t = ROWS == 32 ? wave >> 1 : wave;
   const int o_lane = o0 + kb * 4;
   auto bias_of = [&](int i) {
     f32x4_t b = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -175,7 +235,7 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
     return b;
   };
 #pragma unroll
-  for (int i = 0; i < 2; ++i) acc[i] = PACKED ? f32x4_t{0.f, 0.f, 0.f, 0.f} : bias_of(TOKS == 64 ? i : wave & 1);
+  for (int i = 0; i < 2; ++i) acc[i] = PACKED ? f32x4_t{0.f, 0.f, 0.f, 0.f} : bias_of(TOKS == 64 ? i : half);
 
   auto multiply = [&](const unsigned char* buf, int span) {
     const int steps = nk - span * kSteps < kSteps ? nk - span * kSteps : kSteps;
@@ -212,8 +272,8 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
 
   // The same for one block of out-features, in the same order.
   auto multiply_block = [&](const unsigned char* buf, int span) {
-    const unsigned char* x = buf + ((wave >> 1) * 16 + r16) * 128;
-    const unsigned char* w = buf + kXSpan + ((wave & 1) * 16 + r16) * C::A_ROWB;
+    const unsigned char* x = buf + (wave_t * 16 + r16) * 128;
+    const unsigned char* w = buf + kXSpan + (half * 16 + r16) * C::A_ROWB;
     const int xk = r16 & 7;
     auto one = [&](int st) {
       if constexpr (C::SPARSE) {
@@ -223,7 +283,7 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
         const u32x4_t hi = *reinterpret_cast<const u32x4_t*>(x + st * kXStep + (((4 + kb) ^ xk) * 16));
         const u32x8_t b = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
         acc[0] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(__builtin_bit_cast(bf16x8_t, a0), __builtin_bit_cast(bf16x16_t, b), acc[0],
-                                                           (int)(sel >> (16 * (wave & 1))), 0, 0);
+                                                           (int)(sel >> (16 * half)), 0, 0);
       } else {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -248,23 +308,40 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
     // that every wave reaches only after it has multiplied the first.
     Loads even, odd;
     fetch(even, 0);
-    if (spans > 1) fetch(odd, 1);
-    for (int span = 0; span < spans; span += 2) {
+    fetch(odd, spans > 1 ? 1 : 0);
+    int span = 0;
+    for (; span + 3 < spans; span += 2) {
       put(even, span, smem);
-      if (span + 2 < spans) fetch(even, span + 2);
+      fetch(even, span + 2);
       __syncthreads();
       multiply(smem, span);
-      if (span + 1 < spans) {
-        put(odd, span + 1, smem + C::SPAN);
-        if (span + 3 < spans) fetch(odd, span + 3);
-        __syncthreads();
-        multiply(smem + C::SPAN, span + 1);
-      }
+      put(odd, span + 1, smem + C::SPAN);
+      fetch(odd, span + 3);
+      __syncthreads();
+      multiply(smem + C::SPAN, span + 1);
+    }
+    if (span + 2 < spans) {  // three are left
+      put(even, span, smem);
+      fetch(even, span + 2);
+      __syncthreads();
+      multiply(smem, span);
+      put(odd, span + 1, smem + C::SPAN);
+      __syncthreads();
+      multiply(smem + C::SPAN, span + 1);
+      span += 2;
+    }
+    put(even, span, smem);
+    __syncthreads();
+    multiply(smem, span);
+    if (span + 1 < spans) {
+      put(odd, span + 1, smem + C::SPAN);
+      __syncthreads();
+      multiply(smem + C::SPAN, span + 1);
     }
   } else {
     // Four spans at a time, all their loads in flight together and one barrier for them.
     Loads d[4];
-    const bool stored = (wave >> 1) * 16 < TOKS && t0 + (wave >> 1) * 16 < a.T;  // some token of this wave's 16 is
+    const bool stored = wave_t * 16 < TOKS && t0 + wave_t * 16 < a.T;  // some token of this wave's 16 is
     auto fetch_four = [&](int first) {
 #pragma unroll
       for (int u = 0; u < 4; ++u)
@@ -287,13 +364,13 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
     if (!stored) return;
   }
 
-  const int t = t0 + (TOKS == 64 ? wave : wave >> 1) * 16 + r16;
+  const int t = t0 + (TOKS == 64 ? wave : wave_t) * 16 + r16;
   if (t >= a.T) return;
 #pragma unroll
   for (int i = 0; i < (TOKS == 64 ? 2 : 1); ++i) {
-    const int o = o_lane + 16 * (TOKS == 64 ? i : wave & 1);
+    const int o = o_lane + 16 * (TOKS == 64 ? i : half);
     if (o >= a.O) continue;
-    f32x4_t y = PACKED ? acc[i] + bias_of(TOKS == 64 ? i : wave & 1) : acc[i];
+    f32x4_t y = PACKED ? acc[i] + bias_of(TOKS == 64 ? i : half) : acc[i];
     if (a.K & 63) {  // a sum that ended as NaN again by the definition, as the ragged form of the tiled kernel has it
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -359,49 +436,6 @@ struct WideLoads {
   u32x4_t x[C::PIECES];
 };
 
-// The 2:4 operand of 16 weights, in registers: a run of four owns two 16-bit slots, its first kept value in the first one and a
-// second one in the second, free slots zero; four selector bits per run.  v: the kept values in pairs, fields: their positions.
-template <int N, int M>
-__device__ __forceinline__ void sparse_piece(const uint32_t* v, uint32_t fields, u32x4_t& piece, uint32_t& sel) {
-  if constexpr (M == 4) {  // 1:4: a value per run, always in its first slot
-    piece = u32x4_t{v[0] & 0xFFFFu, v[0] >> 16, v[1] & 0xFFFFu, v[1] >> 16};
-    const uint32_t four = fields & 0xFFu, pairs = (four | (four << 4)) & 0x0F0Fu;
-    sel = (pairs | (pairs << 2)) & 0x3333u;
-  } else if constexpr (M == 8) {  // two groups of two runs
-    sel = 0;
-#pragma unroll
-    for (int g = 0; g < 2; ++g) {
-      if constexpr (N == 1) {
-        const uint32_t pos = (fields >> (3 * g)) & 7u, value = (v[0] >> (16 * g)) & 0xFFFFu;
-        piece[2 * g] = pos & 4u ? 0u : value;
-        piece[2 * g + 1] = pos & 4u ? value : 0u;
-        sel |= (pos & 3u) << (8 * g + (pos & 4u));
-      } else {
-        const uint32_t p0 = (fields >> (6 * g)) & 7u, p1 = (fields >> (6 * g + 3)) & 7u;
-        const bool upper = p0 & 4u, same = ((p0 ^ p1) & 4u) == 0;
-        const uint32_t first = v[g] & 0xFFFFu, second = v[g] >> 16;
-        piece[2 * g] = same ? (upper ? 0u : v[g]) : (upper ? second : first);
-        piece[2 * g + 1] = same ? (upper ? v[g] : 0u) : (upper ? first : second);
-        sel |= ((p0 & 3u) << (p0 & 4u) | (p1 & 3u) << ((p1 & 4u) + (same ? 2u : 0u))) << (8 * g);
-      }
-    }
-  } else {  // one group of four runs
-    const uint32_t p0 = fields & 15u, first = v[0] & 0xFFFFu;
-    if constexpr (N == 1) {
-#pragma unroll
-      for (uint32_t r = 0; r < 4; ++r) piece[r] = (p0 >> 2) == r ? first : 0u;
-      sel = (p0 & 3u) << (p0 & 12u);
-    } else {
-      const uint32_t p1 = (fields >> 4) & 15u;
-      const bool same = ((p0 ^ p1) & 12u) == 0;
-      const uint32_t second = same ? v[0] & 0xFFFF0000u : v[0] >> 16;
-#pragma unroll
-      for (uint32_t r = 0; r < 4; ++r) piece[r] = ((p0 >> 2) == r ? first : 0u) | ((p1 >> 2) == r ? second : 0u);
-      sel = (p0 & 3u) << (p0 & 12u) | (p1 & 3u) << ((p1 & 12u) + (same ? 2u : 0u));
-    }
-  }
-}
-
 template <int N, int M, bool WHOLE>
 __global__ void __launch_bounds__(512) nm_direct_wide_kernel(const DirectArgs a) {
   using C = WideCfg<N, M>;
@@ -455,7 +489,7 @@ __global__ void __launch_bounds__(512) nm_direct_wide_kernel(const DirectArgs a)
   };
   // The loads of a span carry no condition, so that the compiler counts them and a span waits for its own and not for those of
   // the next one (with conditions it drains them all: a round trip to memory per span).  What lies past K is fetched from the
-  // span's first positions instead and cleared on its way into LDS; past the last span the last one is fetched again.
+  // span's first positions instead and cleared on its way into LDS.
   auto fetch = [&](Loads& d, int span, auto par) {
     const int k_left = a.K - span * 128;  // reduction positions from the span on
     const int64_t word0 = (int64_t)span * SPAN_BITS >> 5;
@@ -502,10 +536,7 @@ __global__ void __launch_bounds__(512) nm_direct_wide_kernel(const DirectArgs a)
     if constexpr (C::WORDS == 2) fields = __builtin_amdgcn_alignbit(d.f[1], d.f[0], field_at(par) & 31);
     unsigned char* at = buf + C::X_SPAN + step * C::A_STEP + row * C::A_ROWB;
     if constexpr (C::SPARSE) {
-      u32x4_t piece;
-      uint32_t sel;
-      sparse_piece<N, M>(d.v, fields, piece, sel);
-      *reinterpret_cast<u32x4_t*>(at + (c ^ ((row >> 1) & 3)) * 16) = piece;
+      const uint32_t sel = put_sparse_piece<N, M>(at + (c ^ ((row >> 1) & 3)) * 16, d.v, fields);
       *reinterpret_cast<uint16_t*>(buf + C::X_SPAN + C::STEPS * C::A_STEP + step * C::S_STEP + (row >> 5) * 256 + (row & 15) * 16 +
                                    c * 4 + ((row >> 4) & 1) * 2) = (uint16_t)sel;
     } else {
@@ -593,29 +624,36 @@ __global__ void __launch_bounds__(512) nm_direct_wide_kernel(const DirectArgs a)
   constexpr std::integral_constant<int, 0> p0{};
   constexpr std::integral_constant<int, 1> p1{};
   Loads even, odd;
-  const int last = spans - 1;
   fetch(even, 0, p0);
-  fetch(odd, last < 1 ? 0 : 1, p1);  // (a span of the other parity is fetched in vain, past the end: its fields are not used)
+  fetch(odd, spans > 1 ? 1 : 0, p1);  // (a span of the other parity is fetched in vain, not used)
   int span = 0;
-  for (; a.K - span * 128 >= 256; span += 2) {  // two whole spans: no conditions, so that a span's decoding and the products interleave
+  for (; span + 3 < spans; span += 2) {  // two whole spans: no conditions, so that a span's decoding and the products interleave
     put(even, span, smem, p0, std::true_type{});
-    fetch(even, span + 2 <= last ? span + 2 : last, p0);
+    fetch(even, span + 2, p0);
     __syncthreads();
     multiply(smem, C::STEPS);
     put(odd, span + 1, smem + C::SPAN, p1, std::true_type{});
-    fetch(odd, span + 3 <= last ? span + 3 : last, p1);
+    fetch(odd, span + 3, p1);
     __syncthreads();
     multiply(smem + C::SPAN, C::STEPS);
   }
-  if (span < spans) {
-    put(even, span, smem, p0, std::false_type{});
+  if (span + 2 < spans) {  // three are left, two of them whole
+    put(even, span, smem, p0, std::true_type{});
+    fetch(even, span + 2, p0);
     __syncthreads();
-    multiply(smem, nk - span * C::STEPS);
-    if (span + 1 < spans) {
-      put(odd, span + 1, smem + C::SPAN, p1, std::false_type{});
-      __syncthreads();
-      multiply(smem + C::SPAN, nk - (span + 1) * C::STEPS);
-    }
+    multiply(smem, C::STEPS);
+    put(odd, span + 1, smem + C::SPAN, p1, std::true_type{});
+    __syncthreads();
+    multiply(smem + C::SPAN, C::STEPS);
+    span += 2;
+  }
+  put(even, span, smem, p0, std::false_type{});
+  __syncthreads();
+  multiply(smem, nk - span * C::STEPS);
+  if (span + 1 < spans) {
+    put(odd, span + 1, smem + C::SPAN, p1, std::false_type{});
+    __syncthreads();
+    multiply(smem + C::SPAN, nk - (span + 1) * C::STEPS);
   }
 
   const int64_t row0 = t0 + wt * C::TT * 16, col0 = o_wave;
@@ -654,39 +692,39 @@ __global__ void __launch_bounds__(512) nm_direct_wide_kernel(const DirectArgs a)
   }
 }
 
-template <int N, int M, int TOKS, bool PACKED>
+template <int N, int M, int TOKS, bool PACKED, int ROWS = 32>
 hipError_t launch_tokens(const DirectArgs& g, hipStream_t s) {
-  using C = DirectCfg<N, M, TOKS>;
-  auto kern = nm_direct_kernel<N, M, TOKS, PACKED>;
+  using C = DirectCfg<N, M, TOKS, ROWS>;
+  auto kern = nm_direct_kernel<N, M, TOKS, ROWS, PACKED>;
   static PerDeviceOnce lds_limit;
   if (hipError_t e = raise_dynamic_lds_limit(kern, C::LDS_BYTES, lds_limit); e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)((g.O + kRows - 1) / kRows), (unsigned)((g.T + TOKS - 1) / TOKS)), dim3(256),
+  hipLaunchKernelGGL(kern, dim3((unsigned)((g.O + ROWS - 1) / ROWS), (unsigned)((g.T + TOKS - 1) / TOKS)), dim3(256),
                      C::LDS_BYTES, s, g);
   return hipGetLastError();
 }
 
+// Blocks of 16 tokens: of 16 out-features, which halves what a lane decodes before the first product, while each has a unit to itself,
+// and where several passes of four spans follow one another; of 32 for a wide shallow weight, whose blocks of 16 are many and mostly
+// start and end.  32 and 16 (in a graph): 8 tokens x 768 -> 1000 at 4:8 4.25 and 3.74 us, 16 x 1024 -> 768 at 1:16 4.14 and 3.63, 1 x 4096
+// -> 16384 at 4:8 35.1 and 29.2, 16 x 2048 -> 8192 at 4:8 9.5 and 8.2; 16 x 1024 -> 8192 at 4:8 5.06 and 5.22, -> 16384 at 1:8 5.2 and 6.6.
+template <int N, int M, bool PACKED>
+hipError_t launch_sixteen(const DirectArgs& g, hipStream_t s) {
+  if (g.O <= 16 * 256 || g.K > 1024) return launch_tokens<N, M, 16, PACKED, 16>(g, s);
+  return launch_tokens<N, M, 16, PACKED>(g, s);
+}
+
 // Up to 16 tokens a block of 64 would bring, store and skip rows of zeros, and its two spans in flight make two round trips of
-// K = 768: 768 -> 1000 at 4:8 and 8 tokens 5.8 -> 4.6 us, 3072 -> 768 at 1:4 12.6 -> 9.4, 16 tokens x
-// 1024 -> 4096 at 4:8 7.0 -> 6.0, one token x 256 -> 128 at 2:8 3.1 -> 2.8 (in a graph).  Up to 32 the same holds for the dense
-// form (24 tokens x 768 -> 1000 at 4:8 5.8 -> 5.2, 20 x 2048 -> 2048 at 4:16 10.3 -> 8.8); the 2:4 form, with half the matrix
-// instructions and LDS reads per step, gains nothing on average (32 x 768 -> 768 at 1:4 5.0 and 4.9, x 768 -> 3072 at 1:16 4.7
-// and 4.8).  In the dense form this holds while round trips bound the launch.  A large weight is bound by what its blocks pull in and
-// decode, and there the longer run of a block of 64 is the faster one, the earlier the more tokens there are.  The limits are in
-// kept values, where the two cross at 4:8, 4:16, 3:8 and 3:4: 32 tokens x 2048 -> 4096 at 4:8 (4 M) 12.1 us in blocks of 64 and 11.2,
-// x 3072 -> 16384 (25 M) 31.6 and 35.2; 28 tokens x 3072 -> 6144 (9 M) 16.7 and 16.0, x 3072 -> 16384 31.4 and 32.4; up to 24 tokens a
-// weight beyond the memory-side cache (24 tokens x 8192 -> 32768, 134 M, 150 and 177).  At 3:4 the two waves that multiply in a block
-// of 16 hold up a large weight (16 tokens x 3072 -> 8192, 19 M: 19.0 in blocks of 64, 20.8 in blocks of 16, 18.5 in blocks of 32).
+// K = 768; up to 32 tokens the same holds for blocks of 32 while round trips bound the launch (in blocks of 64 and of 32, in a graph:
+// 20 tokens x 768 -> 1000 at 2:8 5.3 and 4.8 us, at 4:8 5.5 and 4.6, 32 x 3072 -> 3072 at 1:8 11.7 and 10.4, x 2048 -> 4096 at 4:8 10.6 and
+// 9.0, x 1024 -> 32768 at 1:8 19.2 and 16.7).  A large weight is bound by what its blocks pull in and decode, and there the longer run of
+// a block of 64 is the faster one.  The limits are in kept values, near where the two cross: 2:4 form 32 x 2048 -> 8192 at 2:8
+// (4 M) 9.3 and 8.8, x 3072 -> 16384 (12 M) 23.8 and 25.0, x 4096 -> 32768 (32 M) 56.9 and 63.0; dense form 32 x 3072 -> 8192 at 4:8
+// (12 M) 14.6 and 14.2, 3072 -> 16384 (24 M) 27.8 and 28.1, 20 x 4096 -> 16384 (32 M) 35.4 and 37.8.
 template <int N, int M, bool PACKED>
 hipError_t launch_level(const DirectArgs& g, hipStream_t s) {
-  if constexpr (N <= 2) {
-    if (g.T <= 16) return launch_tokens<N, M, 16, PACKED>(g, s);
-  } else {
-    const int64_t kept = (int64_t)g.O * (g.K / M * N), full = 1 << 24;
-    if (kept < (g.T <= 24 ? 6 * full : g.T <= 28 ? full : g.T <= 32 ? full / 2 : 0)) {
-      if (g.T <= 16 && (M > 4 || kept < full)) return launch_tokens<N, M, 16, PACKED>(g, s);
-      return launch_tokens<N, M, 32, PACKED>(g, s);
-    }
-  }
+  if (g.T <= 16) return launch_sixteen<N, M, PACKED>(g, s);
+  const int64_t kept = (int64_t)g.O * (g.K / M * N);
+  if (g.T <= 32 && kept < (N <= 2 ? 1 << 23 : 1 << 24)) return launch_tokens<N, M, 32, PACKED>(g, s);
   return launch_tokens<N, M, 64, PACKED>(g, s);
 }
 
