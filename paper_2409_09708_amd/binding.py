@@ -230,7 +230,7 @@ def _native():
     loader = importlib.machinery.ExtensionFileLoader("_nm_calls", path)
     calls = importlib.util.module_from_spec(importlib.util.spec_from_loader("_nm_calls", loader))
     loader.exec_module(calls)
-    calls.bind({name: ctypes.cast(getattr(lib, name), c_void_p).value for name in EXPORTS}, _check, _workspace)
+    calls.bind({name: ctypes.cast(getattr(lib, name), c_void_p).value for name in EXPORTS}, _check, _workspace, _WORKSPACES)
     _CALLS = calls
     return calls
 
@@ -744,6 +744,9 @@ def nm_backward_input_workspace_bytes(O: int, K: int, T: int) -> int:
 
 def nm_linear_backward_input(Ws, dY, out_dtype=None, out=None, workspace=None, stream=None):
     """dX = dY * Ws for the masked dense weight Ws [O, K] and dY [T, O]; float32 (default) or bfloat16 [T, K]."""
+    done = (_CALLS or _native()).backward_input(Ws, dY, out_dtype, out, workspace, stream)
+    if done is not NotImplemented:
+        return done
     torch = _torch()
     _need(Ws, torch.bfloat16, "Ws")
     _need(dY, torch.bfloat16, "dY")
@@ -768,6 +771,9 @@ def nm_backward_weight_workspace_bytes(O: int, K: int, T: int) -> int:
 
 def nm_linear_backward_weight(dY, X, mask=None, out_dtype=None, out=None, workspace=None, stream=None):
     """dW = dY^T * X, with pruned positions zeroed when the step's mask words are given; [O, K]."""
+    done = (_CALLS or _native()).backward_weight(dY, X, mask, out_dtype, out, workspace, stream)
+    if done is not NotImplemented:
+        return done
     torch = _torch()
     _need(dY, torch.bfloat16, "dY")
     _need(X, torch.bfloat16, "X")
@@ -861,6 +867,10 @@ def nm_linear_forward_i8(Wq, mask, N: int, M: int, Xq, x_scale: float = 1.0, w_s
                          out=None, workspace=None, stream=None, _prepared=False):
     """Y = x_scale * w_scale[o] * (Xq . (Wq (.) m)^T) + bias from int8 operands: float32 (default), bfloat16, or
     the exact int32 sums (out dtype int32)."""
+    done = (_CALLS or _native()).forward_i8(Wq, mask, None, N, M, Xq, x_scale, w_scale, bias, out_dtype, out, workspace, stream,
+                                            int(_prepared))
+    if done is not NotImplemented:
+        return done
     torch = _torch()
     O, K, ldw = _i8_weight(Wq, mask)
     _need(Xq, torch.int8, "Xq")
@@ -936,6 +946,10 @@ def nm_i8_prepare_packed(values, indices, K: int, N: int, M: int, T: int, worksp
 def nm_linear_forward_i8_packed(values, indices, K: int, N: int, M: int, Xq, x_scale: float = 1.0, w_scale=None, bias=None,
                                 out_dtype=None, out=None, workspace=None, stream=None, _prepared=False):
     """nm_linear_forward_i8 with the weight in its compressed form."""
+    done = (_CALLS or _native()).forward_i8(values, indices, K, N, M, Xq, x_scale, w_scale, bias, out_dtype, out, workspace, stream,
+                                            int(_prepared))
+    if done is not NotImplemented:
+        return done
     torch = _torch()
     O = _i8_packed(values, indices)
     _need(Xq, torch.int8, "Xq")

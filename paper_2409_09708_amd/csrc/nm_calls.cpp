@@ -5,7 +5,9 @@
 // knows the other forms that are accepted and names what is wrong with the ones that are not.  Nothing is kept
 // between calls.
 // Measured per call: the projection above 7.3 -> 4.1 us; 768 -> 1000 at 4:8 on 8 tokens, plain, 8.2 -> 6.2 (5.0 with a kernel
-// that has become faster since); the twelve calls and sixteen allocations that compress a block by scores and expand it 94 -> 63.
+// that has become faster since); the twelve calls and sixteen allocations that compress a block by scores and expand it 94 -> 63. The training
+// products and the int8 layer on small operands: dX 7.2 -> 4.0 us, dW (two launches) 11 -> 8, a prepared int8 call 7.5 -> 3.6; a plain
+// call, whose scratch is looked up in the table that Python keeps, 4.0 -> 3.5.  (A launch alone takes the host 3.0 to 3.5.)
 #include <Python.h>
 
 #include <ATen/PythonTorchFunctionTLS.h>
@@ -41,9 +43,20 @@ struct Library {
   // may be missing: a prepared layer is then multiplied uncut
   decltype(&nm_linear_forward_prepared_scratch) forward_prepared_scratch;
   decltype(&nm_prepared_scratch_bytes) prepared_scratch_bytes;
+  // may be missing: those calls are then declined
+  decltype(&nm_linear_backward_input) backward_input;
+  decltype(&nm_linear_backward_weight) backward_weight;
+  decltype(&nm_backward_input_workspace_bytes) backward_input_bytes;
+  decltype(&nm_backward_weight_workspace_bytes) backward_weight_bytes;
+  decltype(&nm_linear_forward_i8) i8;
+  decltype(&nm_linear_forward_i8_prepared) i8_prepared;
+  decltype(&nm_linear_forward_i8_packed) i8_packed;
+  decltype(&nm_linear_forward_i8_packed_prepared) i8_packed_prepared;
+  decltype(&nm_i8_workspace_bytes) i8_bytes;
 } lib;
 PyObject* raise_status;    // raises NmError for a status that is not NM_OK
 PyObject* find_workspace;  // the scratch tensor of a device and stream
+PyObject* workspaces;      // where find_workspace keeps them: (device type, index, stream) -> tensor; may be missing
 
 PyObject* declined() { Py_RETURN_NOTIMPLEMENTED; }
 
@@ -138,6 +151,84 @@ PyObject* result(int32_t st, PyObject* value) {  // steals value
 at::Tensor fresh(at::Device device, int64_t rows, int64_t cols, at::ScalarType type) {
   return at::empty({rows, cols}, at::TensorOptions().dtype(type).device(device));
 }
+
+// The workspace of a call: the given tensor, or the scratch of its device and stream, held until the call has returned.
+struct Workspace {
+  THPObjectPtr found;
+  void* ptr = nullptr;
+  size_t bytes = 0;
+};
+enum Take { TAKEN, DECLINED, FAILED };
+Take given_workspace(PyObject* given, Workspace* w) {
+  if (given == Py_None) return TAKEN;
+  const at::Tensor* ws = nullptr;
+  if (!THPVariable_CheckExact(given) || !(ws = &THPVariable_Unpack(given))->is_cuda() || !ws->has_storage()) return DECLINED;
+  w->ptr = ws->data_ptr();
+  w->bytes = ws->nbytes();
+  return TAKEN;
+}
+// `like`: the tensor on whose device it lies (asking Python for it takes 0.7 us, reading its table 0.1)
+Take scratch_workspace(size_t need, PyObject* like, PyObject* stream, void* s, Workspace* w) {
+  if (workspaces != nullptr) {
+    THPObjectPtr key(Py_BuildValue("(snK)", "cuda", (Py_ssize_t)THPVariable_Unpack(like).device().index(), (unsigned long long)(uintptr_t)s));
+    if (!key) return FAILED;
+    PyObject* kept = PyDict_GetItemWithError(workspaces, key.get());
+    if (kept == nullptr && PyErr_Occurred()) return FAILED;
+    if (kept != nullptr) {
+      Py_INCREF(kept);
+      w->found = THPObjectPtr(kept);
+      if (given_workspace(kept, w) == TAKEN && w->bytes >= need) return TAKEN;
+    }
+  }
+  THPObjectPtr device(PyObject_GetAttrString(like, "device"));
+  if (!device) return FAILED;
+  w->found = THPObjectPtr(PyObject_CallFunction(find_workspace, "nOO", (Py_ssize_t)need, device.get(), stream));
+  return w->found ? given_workspace(w->found.get(), w) : FAILED;
+}
+
+// The output of a call: `given` (out), or made on the device of its operands in the type asked for (out_dtype).
+struct Output {
+  PyObject* given;
+  at::Tensor made;
+  at::ScalarType type;
+  int64_t rows, cols, ld;
+  void* ptr;
+  int32_t code;
+  bool read(PyObject* dtype, PyObject* out, int64_t r, int64_t c, bool i32) {
+    given = out;
+    rows = r;
+    cols = c;
+    type = at::kFloat;
+    if (out != Py_None) {
+      const at::Tensor* t = nullptr;
+      Matrix m;
+      if (!plain(out, at::kBFloat16, &t) && !plain(out, at::kFloat, &t) && !(i32 && plain(out, at::kInt, &t))) return false;
+      if (!matrix(*t, &m) || m.rows != r || m.cols != c) return false;
+      type = t->scalar_type();
+      ld = m.ld;
+      ptr = t->data_ptr();
+    } else if (dtype != Py_None) {
+      if (!THPDtype_Check(dtype)) return false;
+      type = reinterpret_cast<THPDtype*>(dtype)->scalar_type;
+    }
+    if (type == at::kFloat) code = NM_OUT_F32;
+    else if (type == at::kBFloat16) code = NM_OUT_BF16;
+    else if (i32 && type == at::kInt) code = NM_OUT_I32;
+    else return false;
+    return true;
+  }
+  void make(at::Device device) {  // (without the interpreter lock)
+    if (given != Py_None) return;
+    made = fresh(device, rows, cols, type);
+    ptr = made.data_ptr();
+    ld = cols;
+  }
+  PyObject* take() {
+    if (given == Py_None) return THPVariable_Wrap(std::move(made));
+    Py_INCREF(given);
+    return given;
+  }
+};
 
 // prune(W, N, M, W_masked, stream)
 PyObject* prune(PyObject*, PyObject* const* a, Py_ssize_t n) {
@@ -237,7 +328,7 @@ PyObject* unpack(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // from the packed format, 3 on the library's fixed scratch
 PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
   HANDLE_TH_ERRORS
-  const at::Tensor *values, *indices, *X, *bias = nullptr, *out = nullptr, *ws = nullptr;
+  const at::Tensor *values, *indices, *X, *bias = nullptr, *out = nullptr;
   int64_t K, how;
   int32_t N, M;
   Matrix x, y;
@@ -265,30 +356,19 @@ PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     code = type == at::kFloat ? NM_OUT_F32 : NM_OUT_BF16;
   }
   if (!stream_of(a[10], &s)) return declined();
-  THPObjectPtr found;  // a workspace looked up here, held until the call has returned
-  void* ws_ptr = nullptr;
-  size_t ws_bytes = 0;
+  Workspace ws;
   if (how != 3) {
-    PyObject* given = a[9];
-    if (given == Py_None && how != 2) {
+    if (a[9] == Py_None && how != 2) {
       const size_t need = lib.workspace_bytes(O, K, N, M, T);
       if (need != 0 && how == 1) return declined();  // (refused, or a ragged reduction without its copy)
-      if (need != 0) {
-        PyObject* device = PyObject_GetAttrString(a[5], "device");
-        if (device == nullptr) return nullptr;
-        found = PyObject_CallFunction(find_workspace, "nNO", (Py_ssize_t)need, device, a[10]);
-        if (!found) return nullptr;
-        given = found.get();
-      }
-    }
-    if (given != Py_None) {
-      if (!THPVariable_CheckExact(given) || !(ws = &THPVariable_Unpack(given))->is_cuda() || !ws->has_storage()) {
-        return declined();
-      }
-      ws_ptr = ws->data_ptr();
-      ws_bytes = ws->nbytes();
+      if (need != 0)
+        if (const Take t = scratch_workspace(need, a[5], a[10], s, &ws); t != TAKEN) return t == DECLINED ? declined() : nullptr;
+    } else if (given_workspace(a[9], &ws) != TAKEN) {
+      return declined();
     }
   }
+  void* const ws_ptr = ws.ptr;
+  const size_t ws_bytes = ws.bytes;
   // partial sums of a prepared layer that is cut along K: scratch of the call, allocated on its stream, so that the memory goes to
   // later work of that stream only.  (Not for a workspace of the operand part alone, which asks for the uncut product.)
   size_t scratch_bytes = how == 1 && lib.prepared_scratch_bytes ? lib.prepared_scratch_bytes(O, K, N, M, T) : 0;
@@ -326,10 +406,115 @@ PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
   END_HANDLE_TH_ERRORS
 }
 
-// bind(addresses by name, raise_status, find_workspace)
+// backward_input(Ws, dY, out_dtype, out, workspace, stream)
+PyObject* backward_input(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
+  const at::Tensor *W, *dY;
+  Matrix w, dy;
+  Output y;
+  void* s;
+  if (n != 6 || lib.backward_input == nullptr || lib.backward_input_bytes == nullptr || observed() || !plain(a[0], at::kBFloat16, &W) ||
+      !matrix(*W, &w) || !plain(a[1], at::kBFloat16, &dY) || !matrix(*dY, &dy) || dy.cols != w.rows ||
+      !y.read(a[2], a[3], dy.rows, w.cols, false) || !stream_of(a[5], &s))
+    return declined();
+  Workspace ws;
+  const size_t need = a[4] == Py_None ? lib.backward_input_bytes(w.rows, w.cols, dy.rows) : 0;
+  if (const Take t = need != 0 ? scratch_workspace(need, a[1], a[5], s, &ws) : given_workspace(a[4], &ws); t != TAKEN)
+    return t == DECLINED ? declined() : nullptr;
+  const uint16_t *wp = pointer<uint16_t>(W), *dyp = pointer<uint16_t>(dY);
+  const at::Device device = dY->device();
+  const int32_t st = unlocked([&] {
+    y.make(device);
+    return lib.backward_input(wp, w.rows, w.cols, w.ld, dyp, dy.rows, dy.ld, y.ptr, y.ld, y.code, ws.ptr, ws.bytes, s);
+  });
+  return result(st, y.take());
+  END_HANDLE_TH_ERRORS
+}
+
+// backward_weight(dY, X, mask, out_dtype, out, workspace, stream)
+PyObject* backward_weight(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
+  const at::Tensor *dY, *X, *mask = nullptr;
+  Matrix dy, x;
+  Output y;
+  void* s;
+  if (n != 7 || lib.backward_weight == nullptr || lib.backward_weight_bytes == nullptr || observed() || !plain(a[0], at::kBFloat16, &dY) ||
+      !matrix(*dY, &dy) || !plain(a[1], at::kBFloat16, &X) || !matrix(*X, &x) || x.rows != dy.rows)
+    return declined();
+  if (a[2] != Py_None && (!plain(a[2], at::kInt, &mask) || !whole(*mask) || mask->size(0) != dy.cols || mask->size(1) != (x.cols + 31) / 32))
+    return declined();
+  if (!y.read(a[3], a[4], dy.cols, x.cols, false) || !stream_of(a[6], &s)) return declined();
+  Workspace ws;
+  const size_t need = a[5] == Py_None ? lib.backward_weight_bytes(dy.cols, x.cols, dy.rows) : 0;
+  if (const Take t = need != 0 ? scratch_workspace(need, a[0], a[6], s, &ws) : given_workspace(a[5], &ws); t != TAKEN)
+    return t == DECLINED ? declined() : nullptr;
+  const uint16_t *dyp = pointer<uint16_t>(dY), *xp = pointer<uint16_t>(X);
+  const uint32_t* mp = pointer<uint32_t>(mask);
+  const at::Device device = dY->device();
+  const int32_t st = unlocked([&] {
+    y.make(device);
+    return lib.backward_weight(dyp, dy.rows, dy.cols, dy.ld, xp, x.cols, x.ld, mp, y.ptr, y.ld, y.code, ws.ptr, ws.bytes, s);
+  });
+  return result(st, y.take());
+  END_HANDLE_TH_ERRORS
+}
+
+bool per_feature(PyObject* obj, int64_t O, const float** out) {
+  const at::Tensor* t = nullptr;
+  if (obj != Py_None && (!plain(obj, at::kFloat, &t) || t->numel() != O || !t->is_contiguous())) return false;
+  *out = pointer<float>(t);
+  return true;
+}
+
+// forward_i8(Wq, mask, None, N, M, Xq, x_scale, w_scale, bias, out_dtype, out, workspace, stream, prepared), or values, indices and K
+// in the first three places
+PyObject* forward_i8(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
+  const at::Tensor *W, *words, *X;
+  Matrix w, x;
+  int64_t K, prepared;
+  int32_t N, M;
+  Output y;
+  const float *scale, *bias;
+  void* s;
+  if (n != 14 || lib.i8_bytes == nullptr || observed() || !plain(a[0], at::kChar, &W) || !plain(a[1], at::kInt, &words) ||
+      !whole(*words) || !matrix(*W, &w) || !level(a[3], a[4], &N, &M) || !plain(a[5], at::kChar, &X) || !matrix(*X, &x) ||
+      !integer(a[13], 0, 1, &prepared))
+    return declined();
+  const bool packed = a[2] != Py_None;
+  if (packed ? !W->is_contiguous() || !integer(a[2], 1, 1ll << 40, &K)
+             : words->size(0) != w.rows || words->size(1) != ((K = w.cols) + 31) / 32)
+    return declined();
+  const int64_t O = w.rows, T = x.rows;
+  if (x.cols != K || !per_feature(a[7], O, &scale) || !per_feature(a[8], O, &bias) || !y.read(a[9], a[10], T, O, true)) return declined();
+  float x_scale;
+  if (PyFloat_CheckExact(a[6])) x_scale = (float)PyFloat_AS_DOUBLE(a[6]);
+  else return declined();
+  if (!stream_of(a[12], &s)) return declined();
+  Workspace ws;
+  const size_t need = a[11] == Py_None ? lib.i8_bytes(O, K, N, M, T) : 0;
+  if (need != 0 && prepared) return declined();  // (refused)
+  if (const Take t = need != 0 ? scratch_workspace(need, a[5], a[12], s, &ws) : given_workspace(a[11], &ws); t != TAKEN)
+    return t == DECLINED ? declined() : nullptr;
+  const auto dense_call = prepared ? lib.i8_prepared : lib.i8;
+  const auto packed_call = prepared ? lib.i8_packed_prepared : lib.i8_packed;
+  if (packed ? packed_call == nullptr : dense_call == nullptr) return declined();
+  const int8_t *wp = pointer<int8_t>(W), *xp = pointer<int8_t>(X);
+  const uint32_t* mp = pointer<uint32_t>(words);
+  const at::Device device = X->device();
+  const int32_t st = unlocked([&] {
+    y.make(device);
+    if (packed) return packed_call(wp, mp, O, K, N, M, xp, T, x.ld, x_scale, scale, bias, y.ptr, y.ld, y.code, ws.ptr, ws.bytes, s);
+    return dense_call(wp, O, K, w.ld, mp, N, M, xp, T, x.ld, x_scale, scale, bias, y.ptr, y.ld, y.code, ws.ptr, ws.bytes, s);
+  });
+  return result(st, y.take());
+  END_HANDLE_TH_ERRORS
+}
+
+// bind(addresses by name, raise_status, find_workspace[, where that keeps its tensors])
 PyObject* bind(PyObject*, PyObject* args) {
-  PyObject *table, *raise, *find;
-  if (!PyArg_ParseTuple(args, "O!OO", &PyDict_Type, &table, &raise, &find)) return nullptr;
+  PyObject *table, *raise, *find, *kept = nullptr;
+  if (!PyArg_ParseTuple(args, "O!OO|O!", &PyDict_Type, &table, &raise, &find, &PyDict_Type, &kept)) return nullptr;
   Library l = {};
   struct { const char* name; void* slot; bool optional = false; } slots[] = {
       {"nm_prune", &l.prune}, {"nm_prune_scored", &l.prune_scored}, {"nm_pack", &l.pack}, {"nm_unpack", &l.unpack},
@@ -337,7 +522,12 @@ PyObject* bind(PyObject*, PyObject* args) {
       {"nm_linear_forward_static", &l.forward_static}, {"nm_spmm_workspace_bytes", &l.workspace_bytes},
       {"nm_values_bytes", &l.values_bytes}, {"nm_index_bytes", &l.index_bytes},
       {"nm_linear_forward_prepared_scratch", &l.forward_prepared_scratch, true},
-      {"nm_prepared_scratch_bytes", &l.prepared_scratch_bytes, true}};
+      {"nm_prepared_scratch_bytes", &l.prepared_scratch_bytes, true},
+      {"nm_linear_backward_input", &l.backward_input, true}, {"nm_linear_backward_weight", &l.backward_weight, true},
+      {"nm_backward_input_workspace_bytes", &l.backward_input_bytes, true},
+      {"nm_backward_weight_workspace_bytes", &l.backward_weight_bytes, true}, {"nm_linear_forward_i8", &l.i8, true},
+      {"nm_linear_forward_i8_prepared", &l.i8_prepared, true}, {"nm_linear_forward_i8_packed", &l.i8_packed, true},
+      {"nm_linear_forward_i8_packed_prepared", &l.i8_packed_prepared, true}, {"nm_i8_workspace_bytes", &l.i8_bytes, true}};
   for (auto& e : slots) {
     PyObject* address = PyDict_GetItemString(table, e.name);
     if (address == nullptr && e.optional) continue;
@@ -353,6 +543,8 @@ PyObject* bind(PyObject*, PyObject* args) {
   Py_XSETREF(raise_status, raise);
   Py_INCREF(find);
   Py_XSETREF(find_workspace, find);
+  Py_XINCREF(kept);
+  Py_XSETREF(workspaces, kept);
   Py_RETURN_NONE;
 }
 
@@ -363,6 +555,9 @@ PyMethodDef methods[] = {
     {"pack", (PyCFunction)(void (*)())pack, METH_FASTCALL, nullptr},
     {"unpack", (PyCFunction)(void (*)())unpack, METH_FASTCALL, nullptr},
     {"forward", (PyCFunction)(void (*)())forward, METH_FASTCALL, nullptr},
+    {"backward_input", (PyCFunction)(void (*)())backward_input, METH_FASTCALL, nullptr},
+    {"backward_weight", (PyCFunction)(void (*)())backward_weight, METH_FASTCALL, nullptr},
+    {"forward_i8", (PyCFunction)(void (*)())forward_i8, METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_nm_calls", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
