@@ -352,6 +352,10 @@ int32_t nm_linear_forward_prepared_batched_scratch(const nm_forward_desc* descs,
  *       workspace scratch of nm_backward_input_workspace_bytes(O, K, T) bytes, 256-byte aligned (large layers:
  *                 the weight is first written transposed in matrix-core operand order, then the product is
  *                 the forward one); NULL allowed when that size is 0.  Contents undefined afterwards.
+ *   nm_linear_backward_input_scratch
+ *                 the same, for a caller that brings nm_backward_input_scratch_bytes(O, K, T) bytes: small layers
+ *                 whose product pays for the transposed copy take it too.  With less they run as
+ *                 nm_linear_backward_input does (the same sums).  Concurrent calls need distinct workspaces.
  *   nm_linear_backward_weight   dW[o, k] = m[o, k] * sum_t dY[t, o] * X[t, k], fp32 accumulation.
  *       dY   in   [T, O], ld ldy            X    in   [T, K], ld ldx
  *       mask in   mask words of the step as nm_prune writes them ([O, ceil(K/32)]); pruned positions receive
@@ -372,6 +376,10 @@ size_t nm_backward_weight_workspace_bytes(int64_t O, int64_t K, int64_t T);
 int32_t nm_linear_backward_input(const nm_bf16* Ws, int64_t O, int64_t K, int64_t ldw, const nm_bf16* dY,
                                  int64_t T, int64_t ldy, void* dX, int64_t ldx, int32_t out_dtype,
                                  void* workspace, size_t workspace_bytes, void* stream);
+size_t nm_backward_input_scratch_bytes(int64_t O, int64_t K, int64_t T);
+int32_t nm_linear_backward_input_scratch(const nm_bf16* Ws, int64_t O, int64_t K, int64_t ldw, const nm_bf16* dY,
+                                         int64_t T, int64_t ldy, void* dX, int64_t ldx, int32_t out_dtype,
+                                         void* workspace, size_t workspace_bytes, void* stream);
 int32_t nm_linear_backward_weight(const nm_bf16* dY, int64_t T, int64_t O, int64_t ldy, const nm_bf16* X,
                                   int64_t K, int64_t ldx, const uint32_t* mask, void* dW, int64_t lddw,
                                   int32_t out_dtype, void* workspace, size_t workspace_bytes, void* stream);

@@ -33,7 +33,7 @@ EXPORTS = (
     "nm_linear_forward_i8_packed_prepared",
     "nm_rank_bytes", "nm_rank", "nm_rank_batched", "nm_rank_mask", "nm_pack_ranked", "nm_pack_ranked_batched", "nm_pack_prepare_batched",
     "nm_config_cost", "nm_sample_config",
-    "nm_backward_input_workspace_bytes", "nm_backward_weight_workspace_bytes", "nm_linear_backward_input", "nm_linear_backward_weight",
+    "nm_backward_input_workspace_bytes", "nm_backward_weight_workspace_bytes", "nm_linear_backward_input", "nm_backward_input_scratch_bytes", "nm_linear_backward_input_scratch", "nm_linear_backward_weight",
     "nm_linear_forward_prepared_batched", "nm_prepared_scratch_bytes", "nm_linear_forward_prepared_scratch",
     "nm_prepared_batched_scratch_bytes", "nm_linear_forward_prepared_batched_scratch", "nm_prune_scored", "nm_i8_workspace_bytes", "nm_linear_forward_i8", "nm_i8_prepare", "nm_linear_forward_i8_prepared",
 )
@@ -175,10 +175,14 @@ def load_library() -> ctypes.CDLL:
     lib.nm_backward_weight_workspace_bytes.restype = c_size_t
     lib.nm_backward_weight_workspace_bytes.argtypes = [c_int64, c_int64, c_int64]
     lib.nm_linear_backward_input.restype = c_int32
+    lib.nm_backward_input_scratch_bytes.restype = c_size_t
+    lib.nm_backward_input_scratch_bytes.argtypes = [c_int64, c_int64, c_int64]
     lib.nm_backward_input_workspace_bytes.restype = c_size_t
     lib.nm_backward_input_workspace_bytes.argtypes = [c_int64, c_int64, c_int64]
     lib.nm_linear_backward_input.argtypes = [c_void_p, c_int64, c_int64, c_int64, c_void_p, c_int64, c_int64, c_void_p,
                                              c_int64, c_int32, c_void_p, c_size_t, c_void_p]
+    lib.nm_linear_backward_input_scratch.restype = c_int32
+    lib.nm_linear_backward_input_scratch.argtypes = lib.nm_linear_backward_input.argtypes
     lib.nm_linear_backward_weight.restype = c_int32
     lib.nm_linear_backward_weight.argtypes = [c_void_p, c_int64, c_int64, c_int64, c_void_p, c_int64, c_int64, c_void_p,
                                               c_void_p, c_int64, c_int32, c_void_p, c_size_t, c_void_p]
@@ -755,13 +759,16 @@ def nm_linear_backward_input(Ws, dY, out_dtype=None, out=None, workspace=None, s
     if OY != O:
         raise ValueError("dY must be [T, O]")
     out, ldx, code = _out_matrix(out, out_dtype, T, K, dY, "dX")
+    lib = load_library()
+    fn = lib.nm_linear_backward_input  # (which leaves a workspace alone that it can do without)
     if workspace is None:
-        need = nm_backward_input_workspace_bytes(O, K, T)
+        need = lib.nm_backward_input_scratch_bytes(O, K, T)
         if need:
             workspace = _workspace(need, dY.device, stream)
+            fn = lib.nm_linear_backward_input_scratch
     ws_ptr, ws_bytes = _scratch(workspace)
-    _check(load_library().nm_linear_backward_input(Ws.data_ptr(), O, K, ldw, dY.data_ptr(), T, ldy, out.data_ptr(), ldx,
-                                                   code, ws_ptr, ws_bytes, _stream_handle(stream)))
+    _check(fn(Ws.data_ptr(), O, K, ldw, dY.data_ptr(), T, ldy, out.data_ptr(), ldx, code, ws_ptr, ws_bytes,
+              _stream_handle(stream)))
     return out
 
 

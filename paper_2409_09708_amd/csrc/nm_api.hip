@@ -377,9 +377,9 @@ size_t nm_backward_input_workspace_bytes(int64_t O, int64_t K, int64_t T) {
   return nm::backward_input_workspace_bytes(O, K, T);
 }
 
-int32_t nm_linear_backward_input(const nm_bf16* Ws, int64_t O, int64_t K, int64_t ldw, const nm_bf16* dY, int64_t T,
-                                 int64_t ldy, void* dX, int64_t ldx, int32_t out_dtype, void* workspace,
-                                 size_t workspace_bytes, void* stream) {
+namespace {
+int32_t backward_input(const nm_bf16* Ws, int64_t O, int64_t K, int64_t ldw, const nm_bf16* dY, int64_t T, int64_t ldy, void* dX,
+                       int64_t ldx, int32_t out_dtype, void* workspace, size_t workspace_bytes, void* stream, bool optional) {
   if (!Ws || !dY || !dX) return NM_ERR_NULL;
   if (O <= 0 || K <= 0 || T <= 0 || O > (int64_t)1 << 31 || K > (int64_t)1 << 31 || T > (int64_t)1 << 31)
     return NM_ERR_SHAPE;
@@ -388,9 +388,27 @@ int32_t nm_linear_backward_input(const nm_bf16* Ws, int64_t O, int64_t K, int64_
   if (!aligned(Ws, 2) || !aligned(dY, 2) || !aligned(dX, out_dtype == NM_OUT_F32 ? 4 : 2)) return NM_ERR_ALIGN;
   bool workspace_short = false;
   hipError_t e = nm::launch_backward_input(Ws, O, K, ldw, dY, T, ldy, dX, ldx, out_dtype == NM_OUT_BF16, workspace,
-                                           workspace_bytes, (hipStream_t)stream, &workspace_short);
+                                           workspace_bytes, (hipStream_t)stream, optional, &workspace_short);
   if (workspace_short) return NM_ERR_WORKSPACE;
   return device_status(e);
+}
+}  // namespace
+
+int32_t nm_linear_backward_input(const nm_bf16* Ws, int64_t O, int64_t K, int64_t ldw, const nm_bf16* dY, int64_t T,
+                                 int64_t ldy, void* dX, int64_t ldx, int32_t out_dtype, void* workspace,
+                                 size_t workspace_bytes, void* stream) {
+  return backward_input(Ws, O, K, ldw, dY, T, ldy, dX, ldx, out_dtype, workspace, workspace_bytes, stream, false);
+}
+
+size_t nm_backward_input_scratch_bytes(int64_t O, int64_t K, int64_t T) {
+  if (O <= 0 || K <= 0 || T <= 0) return 0;
+  return nm::backward_input_scratch_bytes(O, K, T);
+}
+
+int32_t nm_linear_backward_input_scratch(const nm_bf16* Ws, int64_t O, int64_t K, int64_t ldw, const nm_bf16* dY, int64_t T,
+                                         int64_t ldy, void* dX, int64_t ldx, int32_t out_dtype, void* workspace,
+                                         size_t workspace_bytes, void* stream) {
+  return backward_input(Ws, O, K, ldw, dY, T, ldy, dX, ldx, out_dtype, workspace, workspace_bytes, stream, true);
 }
 
 int32_t nm_linear_backward_weight(const nm_bf16* dY, int64_t T, int64_t O, int64_t ldy, const nm_bf16* X, int64_t K,

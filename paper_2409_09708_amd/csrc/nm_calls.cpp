@@ -46,7 +46,8 @@ struct Library {
   // may be missing: those calls are then declined
   decltype(&nm_linear_backward_input) backward_input;
   decltype(&nm_linear_backward_weight) backward_weight;
-  decltype(&nm_backward_input_workspace_bytes) backward_input_bytes;
+  decltype(&nm_linear_backward_input_scratch) backward_input_scratch;
+  decltype(&nm_backward_input_scratch_bytes) backward_input_bytes;
   decltype(&nm_backward_weight_workspace_bytes) backward_weight_bytes;
   decltype(&nm_linear_forward_i8) i8;
   decltype(&nm_linear_forward_i8_prepared) i8_prepared;
@@ -413,7 +414,7 @@ PyObject* backward_input(PyObject*, PyObject* const* a, Py_ssize_t n) {
   Matrix w, dy;
   Output y;
   void* s;
-  if (n != 6 || lib.backward_input == nullptr || lib.backward_input_bytes == nullptr || observed() || !plain(a[0], at::kBFloat16, &W) ||
+  if (n != 6 || lib.backward_input == nullptr || lib.backward_input_scratch == nullptr || lib.backward_input_bytes == nullptr || observed() || !plain(a[0], at::kBFloat16, &W) ||
       !matrix(*W, &w) || !plain(a[1], at::kBFloat16, &dY) || !matrix(*dY, &dy) || dy.cols != w.rows ||
       !y.read(a[2], a[3], dy.rows, w.cols, false) || !stream_of(a[5], &s))
     return declined();
@@ -425,7 +426,8 @@ PyObject* backward_input(PyObject*, PyObject* const* a, Py_ssize_t n) {
   const at::Device device = dY->device();
   const int32_t st = unlocked([&] {
     y.make(device);
-    return lib.backward_input(wp, w.rows, w.cols, w.ld, dyp, dy.rows, dy.ld, y.ptr, y.ld, y.code, ws.ptr, ws.bytes, s);
+    const auto call = need != 0 ? lib.backward_input_scratch : lib.backward_input;  // (a given workspace is left alone that is not required)
+    return call(wp, w.rows, w.cols, w.ld, dyp, dy.rows, dy.ld, y.ptr, y.ld, y.code, ws.ptr, ws.bytes, s);
   });
   return result(st, y.take());
   END_HANDLE_TH_ERRORS
@@ -524,7 +526,8 @@ PyObject* bind(PyObject*, PyObject* args) {
       {"nm_linear_forward_prepared_scratch", &l.forward_prepared_scratch, true},
       {"nm_prepared_scratch_bytes", &l.prepared_scratch_bytes, true},
       {"nm_linear_backward_input", &l.backward_input, true}, {"nm_linear_backward_weight", &l.backward_weight, true},
-      {"nm_backward_input_workspace_bytes", &l.backward_input_bytes, true},
+      {"nm_linear_backward_input_scratch", &l.backward_input_scratch, true},
+      {"nm_backward_input_scratch_bytes", &l.backward_input_bytes, true},
       {"nm_backward_weight_workspace_bytes", &l.backward_weight_bytes, true}, {"nm_linear_forward_i8", &l.i8, true},
       {"nm_linear_forward_i8_prepared", &l.i8_prepared, true}, {"nm_linear_forward_i8_packed", &l.i8_packed, true},
       {"nm_linear_forward_i8_packed_prepared", &l.i8_packed_prepared, true}, {"nm_i8_workspace_bytes", &l.i8_bytes, true}};

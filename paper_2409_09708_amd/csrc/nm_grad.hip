@@ -593,22 +593,31 @@ extern "C" int32_t nm_internal_weight_grad_plan(int64_t O, int64_t K, int64_t T,
 }
 
 size_t backward_input_workspace_bytes(int64_t O, int64_t K, int64_t T) {
-  return dense_transposed_workspace_bytes(O, K, T);
+  bool required = false;
+  const size_t need = dense_transposed_workspace_bytes(O, K, T, &required);
+  return required ? need : 0;
+}
+size_t backward_input_scratch_bytes(int64_t O, int64_t K, int64_t T) {
+  bool required = false;
+  return dense_transposed_workspace_bytes(O, K, T, &required);
 }
 
 hipError_t launch_backward_input(const bf16_t* Ws, int64_t O, int64_t K, int64_t ldw, const bf16_t* dY, int64_t T,
                                  int64_t ldy, void* dX, int64_t ldx, int out_bf16, void* workspace,
-                                 size_t workspace_bytes, hipStream_t s, bool* workspace_short) {
+                                 size_t workspace_bytes, hipStream_t s, bool optional, bool* workspace_short) {
   *workspace_short = false;
   // Large layers: dX = dY * Ws is the forward product of a layer whose weight is Ws^T, so once the weight has
   // been written transposed into stream order (a pass over the weight only) the persistent dense kernel of the
-  // forward path computes it.
-  const size_t need = backward_input_workspace_bytes(O, K, T);
-  if (need) {
-    if (workspace == nullptr || workspace_bytes < need || !aligned_to(workspace, 256)) {
-      *workspace_short = true;
-      return hipSuccess;
-    }
+  // forward path computes it.  Small ones whose copy is worth its while take the tiled kernel of that path, where the
+  // caller has brought the scratch for it (optional).
+  bool required = false;
+  const size_t need = dense_transposed_workspace_bytes(O, K, T, &required);
+  const bool there = workspace != nullptr && workspace_bytes >= need && aligned_to(workspace, 256);
+  if (required && !there) {
+    *workspace_short = true;
+    return hipSuccess;
+  }
+  if (need && there && (required || optional)) {
     bool taken = false;
     hipError_t e = launch_dense_transposed(Ws, O, K, ldw, dY, T, ldy, dX, ldx, out_bf16, workspace, workspace_bytes, s,
                                            &taken);

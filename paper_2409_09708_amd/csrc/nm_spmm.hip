@@ -2123,8 +2123,27 @@ static bool dense_transposed_takes(int64_t R, int64_t I, int64_t T) {
   const double pass = R > 192 ? 2.5 + 0.25 * weight_mb : 1.3;
   return stream_estimate(kStreamModel[0][0], I, T, R / 32) + pass <= tiled_estimate(I, T, R / 64, 0.5) * (R == 64 ? 0.7 : 1.0);
 }
-size_t dense_transposed_workspace_bytes(int64_t R, int64_t I, int64_t T) {
-  if (!dense_transposed_takes(R, I, T)) return 0;
+
+// What the persistent kernel does not take, few tokens above all, the tiled kernel multiplies from the same copy where the two are
+// estimated faster (by a fifth where the result is four times as wide as the reduction is long) than nm_grad.hip's kernel, whose
+// tiles of 128 x 256 are a handful of blocks then, each with the whole reduction in a row, 0.32 us per 32 positions.  Tokens x
+// reduction -> width: 197 x 3072 -> 768 37 -> 17.7 us, x 768 -> 768 13.9 -> 9.0, 1576 x 4096 -> 1024 50.5 -> 27.5; 394 x 768 -> 3072, 13.2 us,
+// would take 15.2.  Over 865 shapes (1 to 20000 tokens, 64 .. 4096 wide and deep, in a graph) such calls take 0.735 of the time on
+// average (the better of the two 0.72), 4 of them 5 % more; the sums are the same bits.  The copy is optional: without the
+// workspace for it the call runs as it did.  The constants are fitted on the same shapes (rms 5 % for the one kernel, 10 % for the two).
+static bool dense_transposed_tiles(int64_t R, int64_t I, int64_t T) {
+  if (R % 64 || R > (1 << 22) || I > (1 << 24) || T >= (1ll << 31) || dense_transposed_takes(R, I, T)) return false;
+  const double weight_mb = (double)((I + 255) / 256 * 256) * (double)R * 2e-6;
+  double tiles = 1e30;
+  for (const TileModel& m : kTileModel[0])
+    if (const double e = tile_estimate(m, I, R, T); e < tiles) tiles = e;
+  constexpr TileModel kGrad = {256, 128, 2.92, 0.638, 1.56, 0.81};  // (a step of 64; its 256-wide side runs along the tokens)
+  return tiles + 2.74 + 0.615 * weight_mb < (I >= 4 * R ? 0.8 : 0.95) * tile_estimate(kGrad, T, R, I);
+}
+// *required: the layer is the persistent kernel's, and a call without the workspace is refused.
+size_t dense_transposed_workspace_bytes(int64_t R, int64_t I, int64_t T, bool* required) {
+  *required = dense_transposed_takes(R, I, T);
+  if (!*required && !dense_transposed_tiles(R, I, T)) return 0;
   return (size_t)(((I + 255) / 256) * 256) * (size_t)R * 2;
 }
 
@@ -2132,7 +2151,8 @@ hipError_t launch_dense_transposed(const bf16_t* Ws, int64_t R, int64_t I, int64
                                    int64_t ldq, void* Out, int64_t ldo, int out_bf16, void* workspace,
                                    size_t workspace_bytes, hipStream_t s, bool* taken) {
   *taken = false;
-  const size_t need = dense_transposed_workspace_bytes(R, I, T);
+  bool persistent = false;
+  const size_t need = dense_transposed_workspace_bytes(R, I, T, &persistent);
   const int per_piece = out_bf16 ? 8 : 4;
   if (!need || workspace == nullptr || workspace_bytes < need || !aligned_to(workspace, 256)) return hipSuccess;
   if (!aligned_to(Q, 16) || (ldq % 8) || !aligned_to(Ws, 2) || (ldo % per_piece) || !aligned_to(Out, 16) || (I % per_piece))
@@ -2152,7 +2172,7 @@ hipError_t launch_dense_transposed(const bf16_t* Ws, int64_t R, int64_t I, int64
   g.n_o_tiles = g.n_t_tiles = 0;
   g.out_bf16 = (uint8_t)out_bf16; g.vec_store = 1; g.stream_form = 1; g.splits = 1; g.partial = nullptr;
   *taken = true;
-  return dispatch_gemm<false>(g, 0, s);
+  return dispatch_gemm<false>(g, persistent ? 0 : ((I + 127) / 128) * ((T + 127) / 128) < 64 ? 3 : 2, s);
 }
 
 #define NM_FOR_EACH_LEVEL(X)                                                                         \
