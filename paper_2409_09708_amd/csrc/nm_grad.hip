@@ -425,6 +425,236 @@ nm_tgemm_kernel(const TGemmArgs a) {
   }
 }
 
+// dW of a short reduction in one launch.  A block walks the whole reduction of a tile of 128 x 128 and adds the sums of its
+// ranges itself, range by range (pair by pair) in the order in which grad_reduce_kernel adds the partial tiles: the same bits,
+// without the partial tiles (up to 64 MB written and read back, whatever the layer) and without the second launch, which bound the
+// short reductions.  The smaller tile makes twice the blocks of them, as nothing else spreads the work.  A step of 32 tokens takes
+// 0.29 us: LDS moves 64 KB in it (0.21 at its 128 bytes a cycle), the matrix instructions take half of that.  Eight waves of 64 x 32
+// and fragments read one step ahead: with one wave of 64 x 64 on each SIMD nothing covers a range's additions and the waits, and a step
+// takes 0.38; with eight stages instead of four it is no faster.  us, f32 gradients, before and now: 20 tokens x 768 -> 2304
+// 11.7 and 5.6, 197 x 768 -> 2304 15.3 and 8.8, 394 x 1024 -> 4096 29.6 and 11.9, 788 x 768 -> 3072 27.2 and 15.9, 1576 x 768 -> 2304
+// 28.3 and 21.0.
+struct SCfg {
+  static constexpr int WI = 2, WJ = 4, IT = 4, JT = 2;
+  static constexpr int NW = WI * WJ, NT = NW * 64;
+  static constexpr int BI = WI * IT * 16, BJ = WJ * JT * 16;
+  static constexpr int RS = 32, STAGES = 4;
+  static constexpr int ROWB = BI * 2, P_BYTES = RS * BI * 2, Q_BYTES = RS * BJ * 2;  // (rows of both operands are 256 bytes)
+  static constexpr int STAGE = P_BYTES + Q_BYTES, LDS_BYTES = STAGES * STAGE;
+  static constexpr int P_PW = P_BYTES / 1024 / NW, Q_PW = Q_BYTES / 1024 / NW, LPW = P_PW + Q_PW;
+  static constexpr int MMA = IT * JT;
+  static_assert(BI == BJ && RS == TCfg::RS && LDS_BYTES <= 160 * 1024 && STAGES * LPW < 64, "one block of 160 KiB at most");
+};
+
+template <bool PAIRED>
+__global__ void __launch_bounds__(SCfg::NT, 2)
+nm_wgrad_kernel(const TGemmArgs a, const uint32_t* __restrict__ mask) {
+  using C = SCfg;
+  constexpr int IT = C::IT, JT = C::JT, STAGES = C::STAGES;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+  const int n_tiles = a.n_i_tiles * a.n_j_tiles;
+  const int per_xcd = (n_tiles + 7) >> 3;
+  const int tile = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);  // an XCD's tiles share rows of Q
+  if (tile >= n_tiles) return;
+  const int64_t i0 = (int64_t)(tile % a.n_i_tiles) * C::BI, j0 = (int64_t)(tile / a.n_i_tiles) * C::BJ;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wi = wave % C::WI, wj = wave / C::WI, c16 = lane & 15, kb = lane >> 4;
+
+  // loads of a stage, as in the kernel above: columns past the edge re-read the last piece, rows past R the last row (and are cleared)
+  int row[C::P_PW];
+  uint32_t p_col[C::P_PW], q_col[C::P_PW], p_voff[C::P_PW], q_voff[C::P_PW];
+  static_assert(C::P_PW == C::Q_PW, "one set of rows");
+  const int64_t p_last = (a.I - i0) / 8 - 1, q_last = (a.J - j0) / 8 - 1;
+  const uint32_t ldp2 = (uint32_t)(a.ldp * 2), ldq2 = (uint32_t)(a.ldq * 2);
+#pragma unroll
+  for (int d = 0; d < C::P_PW; ++d) {
+    int piece;
+    strided_load_place<C::ROWB>(wave + d * C::NW, lane, &row[d], &piece);
+    p_col[d] = (uint32_t)((piece > p_last ? (int)p_last : piece) * 16);
+    q_col[d] = (uint32_t)((piece > q_last ? (int)q_last : piece) * 16);
+    p_voff[d] = (uint32_t)row[d] * ldp2 + p_col[d];
+    q_voff[d] = (uint32_t)row[d] * ldq2 + q_col[d];
+  }
+  const int steps = (int)((a.R + C::RS - 1) / C::RS);
+  const int last_rows = (int)(a.R - (int64_t)(steps - 1) * C::RS);  // of the last step
+  const unsigned char* fp = reinterpret_cast<const unsigned char*>(a.P + i0);
+  const unsigned char* fq = reinterpret_cast<const unsigned char*>(a.Q + j0);
+  const int64_t p_step = (int64_t)C::RS * a.ldp * 2, q_step = (int64_t)C::RS * a.ldq * 2;
+  auto issue_one = [&](auto d_tag, uniform_ptr_t up, uniform_ptr_t uq, uint32_t lds) {
+    constexpr int d = decltype(d_tag)::value;
+    if constexpr (d < C::P_PW) dma16(up, p_voff[d], lds + (uint32_t)((wave + d * C::NW) * 1024));
+    else dma16(uq, q_voff[d - C::P_PW], lds + (uint32_t)(C::P_BYTES + (wave + (d - C::P_PW) * C::NW) * 1024));
+  };
+  // the last step's missing rows are fetched from its last one
+  auto clamp_rows = [&]() {
+#pragma unroll
+    for (int d = 0; d < C::P_PW; ++d)
+      if (row[d] >= last_rows) {
+        p_voff[d] = (uint32_t)(last_rows - 1) * ldp2 + p_col[d];
+        q_voff[d] = (uint32_t)(last_rows - 1) * ldq2 + q_col[d];
+      }
+  };
+  auto issue_stage = [&](int s, int buf) {
+    if (s == steps - 1) clamp_rows();
+    const uniform_ptr_t up = make_uniform(fp + s * p_step), uq = make_uniform(fq + s * q_step);
+    const uint32_t lds = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)buf * C::STAGE);
+    [&]<int... D>(std::integer_sequence<int, D...>) {
+      (issue_one(std::integral_constant<int, D>{}, up, uq, lds), ...);
+    }(std::make_integer_sequence<int, C::LPW>{});
+  };
+
+  // the mask words of this lane's outputs: rows j, 64 columns; in flight under the reduction
+  const int64_t row0 = j0 + wj * JT * 16, col0 = i0 + wi * IT * 16;
+  uint32_t word[JT][IT / 2];
+  const int64_t nw = (a.I + 31) / 32;
+#pragma unroll
+  for (int j = 0; j < JT; ++j)
+#pragma unroll
+    for (int h = 0; h < IT / 2; ++h) {
+      const int64_t jj = row0 + j * 16 + c16, w = (col0 >> 5) + h;
+      word[j][h] = !mask ? ~0u : mask[(jj < a.J ? jj : a.J - 1) * nw + (w < nw ? w : nw - 1)];
+    }
+
+  // A step's fragments are read under the matrix instructions of the step before.
+  f32x4_t acc[IT][JT], sum[IT][JT], first[PAIRED ? IT : 1][PAIRED ? JT : 1];
+  u32x4_t pf[2][IT], qf[2][JT];
+  const int share = steps / a.splits, extra = steps % a.splits;
+  int range = 0, left = share + (0 < extra ? 1 : 0);
+  bool fresh = true;  // the next step begins a range
+  auto end_range = [&]() {  // the sums of `range` are complete
+    auto each = [&](auto f) {
+#pragma unroll
+      for (int q = 0; q < C::MMA; ++q) f(q / JT, q % JT);
+    };
+    if constexpr (PAIRED) {
+      if (range & 1) each([&](int i, int j) { acc[i][j] = first[i][j] + acc[i][j]; });
+      else if (range + 1 < a.splits) each([&](int i, int j) { first[i][j] = acc[i][j]; });
+    }
+    if (!PAIRED || (range & 1) || range + 1 == a.splits) {
+      if (range < (PAIRED ? 2 : 1)) each([&](int i, int j) { sum[i][j] = acc[i][j]; });
+      else each([&](int i, int j) { sum[i][j] += acc[i][j]; });
+    }
+    ++range;
+    left = share + (range < extra ? 1 : 0);
+    fresh = true;
+  };
+  auto read_frags = [&](auto set_tag, int buf) {
+    constexpr int S = decltype(set_tag)::value;
+    const unsigned char* base = smem + buf * C::STAGE;
+#pragma unroll
+    for (int i = 0; i < IT; ++i) pf[S][i] = read_transposed<C::ROWB>(base, wi * IT + i, c16, kb);
+#pragma unroll
+    for (int j = 0; j < JT; ++j) qf[S][j] = read_transposed<C::ROWB>(base + C::P_BYTES, wj * JT + j, c16, kb);
+  };
+  auto clear_rows = [&](int buf) {  // this wave's own loads have landed: it clears the rows past R that it fetched
+    unsigned char* base = smem + buf * C::STAGE;
+#pragma unroll
+    for (int d = 0; d < C::P_PW; ++d)
+      if (row[d] >= last_rows) {
+        *reinterpret_cast<u32x4_t*>(base + (wave + d * C::NW) * 1024 + lane * 16) = u32x4_t{0, 0, 0, 0};
+        *reinterpret_cast<u32x4_t*>(base + C::P_BYTES + (wave + d * C::NW) * 1024 + lane * 16) = u32x4_t{0, 0, 0, 0};
+      }
+  };
+  auto wait_landed = [&](int ahead) {  // ... a stage after which `ahead` stages have been asked for
+    if (ahead >= 2) wait_loads_outstanding<2 * C::LPW>();
+    else if (ahead == 1) wait_loads_outstanding<C::LPW>();
+    else wait_loads_outstanding<0>();
+  };
+  static_assert(STAGES == 4, "the cases above");
+
+#pragma unroll
+  for (int s = 0; s < STAGES - 1; ++s)
+    if (s < steps) issue_stage(s, s);
+  wait_landed(steps - 1 < STAGES - 2 ? steps - 1 : STAGES - 2);
+  if (steps == 1 && last_rows < C::RS) clear_rows(0);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  read_frags(std::integral_constant<int, 0>{}, 0);
+
+  int buf = 0;
+  // Step ks with fragment set S: stage ks + 1 has landed, everybody has read stage ks - 1 and has stage ks in registers.
+  auto step = [&](auto set_tag, int ks, auto fast_tag) {
+    constexpr int S = decltype(set_tag)::value;
+    constexpr bool FAST = decltype(fast_tag)::value;
+    int next = buf + 1 == STAGES ? 0 : buf + 1;
+    if (FAST) {
+      wait_loads_outstanding<(STAGES - 3) * C::LPW>();
+    } else if (ks + 1 < steps) {
+      wait_landed(steps - 2 - ks < STAGES - 3 ? steps - 2 - ks : STAGES - 3);
+      if (ks + 2 == steps && last_rows < C::RS) clear_rows(next);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    if (FAST || ks + 1 < steps) read_frags(std::integral_constant<int, S ^ 1>{}, next);
+    // the buffer of stage ks - 1, which nobody reads any more
+    const int free_buf = buf == 0 ? STAGES - 1 : buf - 1;
+    uniform_ptr_t up = 0, uq = 0;
+    uint32_t lds = 0;
+    const bool load = FAST || ks + STAGES - 1 < steps;
+    if (load) {
+      if (!FAST && ks + STAGES - 1 == steps - 1) clamp_rows();
+      up = make_uniform(fp + (ks + STAGES - 1) * p_step);
+      uq = make_uniform(fq + (ks + STAGES - 1) * q_step);
+      lds = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)free_buf * C::STAGE);
+    }
+    auto products = [&](auto fresh_tag) {
+      [&]<int... Q>(std::integer_sequence<int, Q...>) {
+        ([&] {
+          constexpr int j = Q / IT, i = j & 1 ? IT - 1 - Q % IT : Q % IT;
+          const f32x4_t c = decltype(fresh_tag)::value ? f32x4_t{0.f, 0.f, 0.f, 0.f} : acc[i][j];
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pf[S][i]),
+                                                              __builtin_bit_cast(bf16x8_t, qf[S][j]), c, 0, 0, 0);
+          if constexpr (Q % 4 == 3 && Q / 4 < C::LPW) {
+            if (load) issue_one(std::integral_constant<int, Q / 4>{}, up, uq, lds);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }(), ...);
+      }(std::make_integer_sequence<int, C::MMA>{});
+    };
+    if (fresh) products(std::true_type{});
+    else products(std::false_type{});
+    fresh = false;
+    buf = next;
+    if (--left == 0) end_range();
+  };
+  // Steady state: a whole stage to load
+  const int n_fast = steps - (STAGES - 1) - (last_rows < C::RS ? 1 : 0);
+  int ks = 0;
+  for (; ks + 1 < n_fast; ks += 2) {
+    step(std::integral_constant<int, 0>{}, ks, std::true_type{});
+    step(std::integral_constant<int, 1>{}, ks + 1, std::true_type{});
+  }
+  for (; ks < steps; ks += 2) {
+    step(std::integral_constant<int, 0>{}, ks, std::false_type{});
+    if (ks + 1 < steps) step(std::integral_constant<int, 1>{}, ks + 1, std::false_type{});
+  }
+
+  // ---- the mask of the step, then as the kernel above
+  if (mask) {
+#pragma unroll
+    for (int j = 0; j < JT; ++j)
+#pragma unroll
+      for (int i = 0; i < IT; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (!((word[j][i / 2] >> (16 * (i & 1) + kb * 4 + e)) & 1u)) sum[i][j][e] = 0.f;
+  }
+  __builtin_amdgcn_s_barrier();  // every wave is done with the operand stages
+  auto get = [&](int i, int j) { return __builtin_bit_cast(u32x4_t, sum[i][j]); };
+  static_assert(C::NW * wave_tile_slice_bytes<IT, 4>() <= C::LDS_BYTES, "write-out slices");
+  unsigned char* slice = smem + wave * wave_tile_slice_bytes<IT, 4>();
+  if (a.vec_store) {
+    if (a.out_bf16) write_wave_tile_pieces<IT, JT, 2>(slice, lane, get, a.out, a.ldo, row0, col0, a.J, a.I);
+    else write_wave_tile_pieces<IT, JT, 4>(slice, lane, get, a.out, a.ldo, row0, col0, a.J, a.I);
+  } else if (a.out_bf16) {
+    write_wave_tile_rows<IT, JT, 2>(slice, lane, get, a.out, a.ldo, row0, col0, a.J, a.I);
+  } else {
+    write_wave_tile_rows<IT, JT, 4>(slice, lane, get, a.out, a.ldo, row0, col0, a.J, a.I);
+  }
+}
+
 // Sum of the partial tiles (of a range, or of a pair of ranges: `planes` of them for each tile) in order, the mask of the step
 // (bit k % 32 of word k / 32 of row o; NULL = every weight receives its gradient) and the rounding.  One lane per accumulator of
 // the tile kernel.  Bound by reading the partial tiles, and by its launch (72 tiles in 4 planes, 47 MB in all, 8.3 us; 12.2 with
@@ -533,6 +763,16 @@ hipError_t launch_tgemm(TGemmArgs g, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <bool PAIRED>
+hipError_t launch_wgrad(const TGemmArgs& g, const uint32_t* mask, hipStream_t s) {
+  auto kern = nm_wgrad_kernel<PAIRED>;
+  static PerDeviceOnce lds_limit;
+  if (hipError_t e = raise_dynamic_lds_limit(kern, SCfg::LDS_BYTES, lds_limit); e != hipSuccess) return e;
+  const unsigned grid = (unsigned)((g.n_i_tiles * g.n_j_tiles + 7) / 8 * 8);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(SCfg::NT), SCfg::LDS_BYTES, s, g, mask);
+  return hipGetLastError();
+}
+
 // Ranges of the token reduction of dW.  Two blocks fit a compute unit, 512 at once on a 256-unit chip; the
 // smallest count that fills at least 90 % of a whole number of such rounds is taken (else the fullest), with
 // at least four steps per range where the reduction is long enough.
@@ -581,7 +821,32 @@ bool weight_grad_paired(const WeightGradPlan& p, int64_t T) {
 // Partial tiles of a tile: one per pair, and the last of an odd number of ranges by itself.
 int weight_grad_planes(const WeightGradPlan& p, int64_t T) { return weight_grad_paired(p, T) ? (p.splits + 1) / 2 : p.splits; }
 
+// Whether one launch takes the whole reduction (nm_wgrad_kernel) rather than ranges of it to many blocks and the sum over them.
+// Times in us, least squares over 1230 shapes of 1 to 16000 tokens and 64 to 9000 features (rms 6 and 10 %).  One launch: the steps
+// of a tile one after another, in rounds of one tile to a compute unit, and the output.  Two: the steps of a range, in rounds of 512
+// blocks, and the partial tiles.  Single ranges, many, on 257 to 431 blocks write them partly under the others' arithmetic (0.85).
+// 1.0 us and 5 % are left for the two launches.  With them the one launch takes 0.97 of the time or less wherever it is chosen, and of
+// the 29 % that always choosing right would save 28.5 are had.  us, two launches and one, near the border: 394 x 256 -> 256 9.1
+// and 9.9 (two), 394 x 768 -> 768 13.2 and 9.5; 788 x 256 -> 256 9.9 and 13.3 (two), 788 x 768 -> 768 17.1 and 13.8; 1576 x 768 -> 2304
+// 28.3 and 21.0, 3152 x 768 -> 2304 30.3 and 36.9 (two).
+bool weight_grad_one_launch(const WeightGradPlan& p, int64_t O, int64_t K, int64_t T) {
+  const int64_t steps = (T + TCfg::RS - 1) / TCfg::RS, tiles = (int64_t)p.n_i_tiles * p.n_j_tiles, blocks = tiles * p.splits;
+  const int64_t small = ((K + SCfg::BI - 1) / SCfg::BI) * ((O + SCfg::BJ - 1) / SCfg::BJ);
+  const bool pair = weight_grad_paired(p, T);
+  const double one = 2.8 + (1.66 + 0.325 * (double)steps) * (double)((small + 255) / 256) + 0.009 * (double)small;
+  const double rounds = (double)(pair ? ((blocks + 1) / 2 + 255) / 256 : (blocks + 511) / 512);
+  double two = 6.4 + 0.59 * (double)((steps + p.splits - 1) / p.splits) * rounds + 0.063 * (double)tiles * weight_grad_planes(p, T);
+  if (!pair && p.splits > 8 && blocks > 256) two *= 0.85;
+  return one + 1.0 < 0.95 * two;
+}
+
 }  // namespace
+
+// Not in the public header, for tests: whether the weight gradient of the shape is one launch.
+extern "C" int32_t nm_internal_weight_grad_one_launch(int64_t O, int64_t K, int64_t T) {
+  const WeightGradPlan p = weight_grad_plan(O, K, T);
+  return p.tiles && weight_grad_one_launch(p, O, K, T);
+}
 
 // Not in the public header, for tests: tiles of the weight gradient, ranges of its reduction, and partial tiles of a tile that
 // the sum over them reads (fewer than ranges where they are taken in pairs).  0: another kernel takes the shape.
@@ -673,6 +938,14 @@ hipError_t launch_backward_weight(const bf16_t* dY, int64_t T, int64_t O, int64_
   g.n_i_tiles = p.n_i_tiles; g.n_j_tiles = p.n_j_tiles;
   g.splits = p.splits; g.partial = reinterpret_cast<float*>(workspace);
   const bool pair = weight_grad_paired(p, T);
+  if (weight_grad_one_launch(p, O, K, T)) {
+    g.partial = nullptr;
+    g.out = dW; g.ldo = lddw; g.out_bf16 = out_bf16;
+    g.vec_store = (lddw % (out_bf16 ? 8 : 4) == 0) && aligned_to(dW, 16);  // K % 8 == 0 holds here
+    g.n_i_tiles = (int)((K + SCfg::BI - 1) / SCfg::BI);
+    g.n_j_tiles = (int)((O + SCfg::BJ - 1) / SCfg::BJ);
+    return pair ? launch_wgrad<true>(g, mask, s) : launch_wgrad<false>(g, mask, s);
+  }
   const int planes = weight_grad_planes(p, T);
   hipError_t e = pair ? launch_tgemm<true, true>(g, s) : launch_tgemm<true>(g, s);
   if (e != hipSuccess) return e;
