@@ -210,7 +210,7 @@ struct GemmArgs {
   uint8_t stream_form;  // A (and sel) lie in stream order (the pre-pass's output), else row-major as packed
   uint8_t splits;       // ranges the reduction is cut into (tiled kernel only; 1 = the whole K in one block)
   uint8_t rot;          // tiled kernel: XCD x takes the layer's share number (x + rot) mod 8
-  uint8_t x_align;      // bytes every X row start is a multiple of: 16, 8, 4 or 2 (read by the register-staged form only)
+  uint8_t x_aligned;    // every X row starts on 16 bytes
   // ragged form only: the packed weight itself, for the sums that are computed a second time
   uint8_t N, M;
   const bf16_t* values;
@@ -268,7 +268,7 @@ __device__ __forceinline__ f32x4_t bias_init(const float* bias, int64_t o, int64
 // STREAM: the weight lies in stream order (the pre-pass's output: every 16-row x K-step slice one contiguous,
 // already swizzled kilobyte; selector words interleaved per 32-row pair), else row-major (the packed 2:4 layout
 // or a dense level's values, read as they lie).
-// X_REGS: X travels through registers instead of by asynchronous copies, so that its rows may start anywhere and K
+// X_REGS: the operands travel through registers instead of by asynchronous copies, so that rows of X may start anywhere and K
 // may end anywhere (see the loop); two stages.
 // TAIL: K, a multiple of 8, may end inside the last step (rows of X still start on 16 bytes).  The pieces of that step past K are fetched
 // from its first piece instead (what lies behind a row's end may be no memory at all) and cleared in LDS by the lanes
@@ -496,13 +496,19 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned block, uns
   };
 
   if constexpr (X_REGS) {
-    // Ragged operands.  A lane loads its 16-byte pieces of X with as many loads as the rows' alignment asks for and
-    // writes them to LDS where the asynchronous copies of the other form would put them; past K the piece is zero
-    // (so is the weight there: what lies behind a row's end never enters a sum).  The loads of step ks + 1 leave
-    // before step ks is multiplied and are written to the other buffer after it.  One stage is in flight and a
-    // step drains everything at its barrier, but the two small stages leave room for three blocks per compute unit.
+    // Rows of X that start anywhere, and a K that ends anywhere.  Every operand travels through registers: plain loads, which
+    // need no alignment, DEPTH stages ahead, and written to LDS where the asynchronous copies of the other form put them.  The loads carry no
+    // condition, so that the wait before a stage's write leaves the younger ones in flight: past K a piece is the row's last
+    // eight elements, shifted and cleared on its way to LDS (so is the weight there: what lies behind a row's end never enters a sum);
+    // past the last stage it is that one again.  Bound by the latency of a stage's loads where a unit has one block: with one stage in
+    // flight and its wait in the same step, a step took 0.6 - 0.9 us, now 0.25.  us, before and now: 926 x 2740 -> 96 at 1:4 28.2 and
+    // 13.4, 518 x 2164 -> 528 at 4:4 25.0 and 13.3, 4345 x 3468 -> 128 at 1:4 61.5 and 17.7, 8000 x 516 -> 2052 at 4:4 69.1 and 45.1,
+    // 3000 x 1028 -> 1400 at 3:4 34.0 and 24.7, 969 x 244 -> 3040 at 4:4 8.6 and 7.6.
     static_assert(!X_REGS || (STAGES == 2 && STREAM), "register-staged form");
-    u32x4_t xr[C::X_PW];
+    constexpr int DEPTH = C::LPW <= 4 ? 4 : 2;
+    u32x4_t xr[DEPTH][C::X_PW], ar[DEPTH][C::A_PW];
+    uint32_t sr[DEPTH][C::S_PW > 0 ? C::S_PW : 1];
+    struct __attribute__((packed, aligned(2))) Piece { u32x4_t v; };
     const bf16_t* x_row_ptr[C::X_PW];
     int x_k[C::X_PW];  // the piece's first k inside a step
 #pragma unroll
@@ -511,66 +517,84 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned block, uns
       int64_t row = 8 * j + (lane >> 3);
       x_k[i] = ((lane & 7) ^ (int)(row & 7)) * 8;
       if (row > t_last) row = t_last;
-      x_row_ptr[i] = a.X + (t0 + row) * a.ldx + x_k[i];
+      x_row_ptr[i] = a.X + (t0 + row) * a.ldx;
     }
-    auto fetch_x = [&](int ks) {
-      const int64_t left = a.K - (int64_t)ks * 64;  // elements of the rows from this step on
+    auto fetch = [&](auto set_tag, int ks) {
+      constexpr int S = decltype(set_tag)::value;
+      if (ks >= nk) ks = nk - 1;
 #pragma unroll
       for (int i = 0; i < C::X_PW; ++i) {
-        const bf16_t* src = x_row_ptr[i] + (int64_t)ks * 64;
-        const int n = left - x_k[i] >= 8 ? 8 : (left - x_k[i] > 0 ? (int)(left - x_k[i]) : 0);  // a multiple of 4: K is one
-        u32x4_t v = u32x4_t{0, 0, 0, 0};
-        if (a.x_align == 16) {
-          if (n == 8) v = *reinterpret_cast<const u32x4_t*>(src);
-          else if (n == 4) { const uint2 h = *reinterpret_cast<const uint2*>(src); v[0] = h.x; v[1] = h.y; }
-        } else if (a.x_align == 8) {
-          if (n >= 4) { const uint2 h = *reinterpret_cast<const uint2*>(src); v[0] = h.x; v[1] = h.y; }
-          if (n == 8) { const uint2 h = *reinterpret_cast<const uint2*>(src + 4); v[2] = h.x; v[3] = h.y; }
-        } else if (a.x_align == 4) {
+        const int k = ks * 64 + x_k[i];
+        xr[S][i] = reinterpret_cast<const Piece*>(x_row_ptr[i] + (k <= (int)a.K - 8 ? k : (int)a.K - 8))->v;
+      }
+      const unsigned char* src = reinterpret_cast<const unsigned char*>(a_base + (int64_t)ks * A_STEP);
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (2 * e < n) v[e] = *reinterpret_cast<const uint32_t*>(src + 2 * e);
-        } else {
+      for (int i = 0; i < C::A_PW; ++i) ar[S][i] = *reinterpret_cast<const u32x4_t*>(src + a_voff[i]);
+      if constexpr (SPARSE) {
+        const unsigned char* sel_src = reinterpret_cast<const unsigned char*>(s_base + (int64_t)ks * S_STEP);
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (2 * e < n) v[e] = (uint32_t)src[2 * e] | ((uint32_t)src[2 * e + 1] << 16);
+        for (int i = 0; i < C::S_PW; ++i) sr[S][i] = *reinterpret_cast<const uint32_t*>(sel_src + s_voff[i]);
+      }
+    };
+    auto put = [&](auto set_tag, int ks, int buf) {
+      constexpr int S = decltype(set_tag)::value;
+      unsigned char* base = smem + buf * C::STAGE;
+      if (ks == nk - 1) {
+#pragma unroll
+        for (int i = 0; i < C::X_PW; ++i) {
+          const int n = (int)a.K - (ks * 64 + x_k[i]);  // elements left of the piece; a multiple of 4: K is one
+          const u32x4_t v = xr[S][i];
+          xr[S][i] = n >= 8 ? v : n >= 4 ? u32x4_t{v[2], v[3], 0, 0} : u32x4_t{0, 0, 0, 0};
         }
-        xr[i] = v;
+      }
+#pragma unroll
+      for (int i = 0; i < C::X_PW; ++i) *reinterpret_cast<u32x4_t*>(base + x_dst[i] + lane * 16) = xr[S][i];
+#pragma unroll
+      for (int i = 0; i < C::A_PW; ++i) *reinterpret_cast<u32x4_t*>(base + a_dst[i] + lane * 16) = ar[S][i];
+      if constexpr (SPARSE) {
+#pragma unroll
+        for (int i = 0; i < C::S_PW; ++i) *reinterpret_cast<uint32_t*>(base + s_dst[i] + lane * 4) = sr[S][i];
       }
     };
-    auto put_x = [&](int buf) {
-#pragma unroll
-      for (int i = 0; i < C::X_PW; ++i)
-        *reinterpret_cast<u32x4_t*>(smem + buf * C::STAGE + x_dst[i] + lane * 16) = xr[i];
-    };
-    auto issue_weight = [&](int buf) {
-      [&]<int... D>(std::integer_sequence<int, D...>) {
-        (issue_one(std::integral_constant<int, C::X_PW + D>{}, buf), ...);
-      }(std::make_integer_sequence<int, C::LPW - C::X_PW>{});
-    };
-    auto stage_done = [&]() {
-      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    auto everyone = [&]() {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
     };
-    issue_weight(0);
-    fetch_x(0);
-    put_x(0);
-    stage_done();
-    for (int ks = 0; ks < nk; ++ks) {
-      const int buf = ks & 1;
-      if (ks + 1 < nk) {
-        issue_weight(buf ^ 1);
-        fetch_x(ks + 1);
-      }
+    [&]<int... D>(std::integer_sequence<int, D...>) {
+      (fetch(std::integral_constant<int, D>{}, D), ...);
+    }(std::make_integer_sequence<int, DEPTH>{});
+    put(std::integral_constant<int, 0>{}, 0, 0);
+    // Steps first .. first + DEPTH - 1: stage ks lies in LDS, stages ks + 1 .. ks + DEPTH are on their way.  STEADY: all of them load one.
+    auto round = [&](auto steady, int first) {
+      [&]<int... B>(std::integer_sequence<int, B...>) {
+        ([&] {
+          constexpr bool STEADY = decltype(steady)::value;
+          constexpr int buf = B & 1;
+          using Next = std::integral_constant<int, (B + 1) % DEPTH>;
+          const int ks = first + B;
+          if (!STEADY && ks >= nk) return;
 #pragma unroll
-      for (int h = 0; h < H; ++h) {
-        read_frags(buf, h);
-        multiply(false, 0);
-      }
-      if (ks + 1 < nk) put_x(buf ^ 1);
-      stage_done();
+          for (int h = 0; h < H; ++h) {
+            read_frags(buf, h);
+            multiply(false, 0);
+          }
+          if (!STEADY && ks + 1 == nk) return;
+          put(Next{}, ks + 1, buf ^ 1);
+          if (STEADY || ks + 1 + DEPTH < nk) fetch(Next{}, ks + 1 + DEPTH);
+          everyone();
+        }(), ...);
+      }(std::make_integer_sequence<int, DEPTH>{});
+    };
+    int first = 0;
+    if (nk > 2 * DEPTH) {
+      fetch(std::integral_constant<int, 0>{}, DEPTH);
+      everyone();
+      for (; first + 2 * DEPTH < nk; first += DEPTH) round(std::true_type{}, first);
+    } else {
+      if (DEPTH < nk) fetch(std::integral_constant<int, 0>{}, DEPTH);
+      everyone();
     }
+    for (; first < nk; first += DEPTH) round(std::false_type{}, first);
   } else {
     static_assert(!TAIL || C::X_LOADS % C::NW == 0, "every piece is brought by one lane");
     const int k_tail = (int)(a.K - (int64_t)(nk_all - 1) * 64);  // elements of the last step, 8 .. 64
@@ -2072,9 +2096,12 @@ static hipError_t dispatch_gemm(const GemmArgs& g, int pick, hipStream_t s) {
 }
 
 // The ragged form of the tiled kernel.  K and the rows of X in whole 16-byte pieces: the
-// tile of the aligned form.  A product of 1579 x 1000 -> 1001 at 2:8 takes 9.1 us that way and 15.5 through registers.
-// Other rows: 128 x 128 tiles once there is one for every compute unit, else 64 x 64.  (The gather kernel, which still
-// takes such shapes when there is no workspace: 1096 us.)
+// tile of the aligned form.  A product of 1579 x 1000 -> 1001 at 2:8 takes 8.1 us that way and 10.7 through registers.
+// Other rows: tiles of 128 x 128 or of 64 x 64, a quarter of the work for half the loads.  The large ones take over past 1.3 of them
+// to a unit, and where the steps are eight and more, which is where the loads count, from 208 on, most of which run at once.  64 and
+// 128 (us): 1096 x 196 -> 1572 6.4 and 7.6, 9314 x 276 -> 318 9.7 and 12.4, 18298 x 196 -> 156 (286 tiles of 128) 10.9 and 13.8;
+// 9460 x 1764 -> 324 (222) 34.2 and 26.3, 9545 x 548 -> 354 (225) 14.5 and 12.5, 11269 x 1132 -> 437 (356) 31.6 and 29.6,
+// 29106 x 148 -> 584 25.0 and 18.0.  (The gather kernel, which still takes such shapes when there is no workspace: 1096 us.)
 template <bool SPARSE>
 static hipError_t launch_ragged(GemmArgs g, hipStream_t s) {
   auto go = [&](auto kern, auto cfg, PerDeviceOnce& once) {
@@ -2089,7 +2116,7 @@ static hipError_t launch_ragged(GemmArgs g, hipStream_t s) {
   };
   const int64_t tiles_mid = ((g.O + 127) / 128) * ((g.T + 127) / 128);
   static PerDeviceOnce once[6];
-  if (g.x_align == 16 && g.K % 8 == 0 && g.ldx <= (1 << 22)) {  // (per-lane byte offsets inside a tile stay below 2^32)
+  if (g.x_aligned && g.K % 8 == 0 && g.ldx <= (1 << 22)) {  // (per-lane byte offsets inside a tile stay below 2^32)
     switch (tile_kind(g.O, padded_k(g.K), g.T, SPARSE, tiles_mid < 64 ? 3 : 2)) {
       case TILE_64: return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 2, 2, 3, false>, GemmCfg<SPARSE, 2, 2, 2, 2, 3>{}, once[0]);
       case TILE_128_64: return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 4, 2, 3, false>, GemmCfg<SPARSE, 2, 2, 4, 2, 3>{}, once[1]);
@@ -2097,7 +2124,7 @@ static hipError_t launch_ragged(GemmArgs g, hipStream_t s) {
       default: return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 4, 4, 3, false>, GemmCfg<SPARSE, 2, 2, 4, 4, 3>{}, once[3]);
     }
   }
-  if (tiles_mid >= 256)
+  if (tiles_mid >= 336 || (tiles_mid >= 208 && g.K >= 512))
     return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 4, 4, 2, true>, GemmCfg<SPARSE, 2, 2, 4, 4, 2>{}, once[4]);
   return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 2, 2, 2, true>, GemmCfg<SPARSE, 2, 2, 2, 2, 2>{}, once[5]);
 }
@@ -2209,10 +2236,7 @@ static void fill_gemm_args(const SpmmArgs& a, int form, bool sparse_form, GemmAr
   g->out_bf16 = a.out_bf16;
   g->n_o_tiles = g->n_t_tiles = 0;
   g->rot = 0;
-  {
-    const uintptr_t at = (uintptr_t)a.X | (uintptr_t)(a.ldx * 2);
-    g->x_align = (at & 15) == 0 ? 16 : (at & 7) == 0 ? 8 : (at & 3) == 0 ? 4 : 2;
-  }
+  g->x_aligned = aligned_to(a.X, 16) && a.ldx % 8 == 0;
   // 16-byte pieces of Y rows: every row start and the row end fall on a piece boundary
   const int per_piece = a.out_bf16 ? 8 : 4;
   g->vec_store = (a.ldy % per_piece == 0) && aligned_to(a.Y, 16) && (a.O % per_piece == 0) &&
