@@ -826,7 +826,7 @@ int weight_grad_planes(const WeightGradPlan& p, int64_t T) { return weight_grad_
 // of a tile one after another, in rounds of one tile to a compute unit, and the output.  Two: the steps of a range, in rounds of 512
 // blocks, and the partial tiles.  Single ranges, many, on 257 to 431 blocks write them partly under the others' arithmetic (0.85).
 // 1.0 us and 5 % are left for the two launches.  With them the one launch takes 0.97 of the time or less wherever it is chosen, and of
-// the 29 % that always choosing right would save 28.5 are had.  us, two launches and one, near the border: 394 x 256 -> 256 9.1
+// the 28.7 % that always choosing right would save 28.4 are had.  us, two launches and one, near the border: 394 x 256 -> 256 9.1
 // and 9.9 (two), 394 x 768 -> 768 13.2 and 9.5; 788 x 256 -> 256 9.9 and 13.3 (two), 788 x 768 -> 768 17.1 and 13.8; 1576 x 768 -> 2304
 // 28.3 and 21.0, 3152 x 768 -> 2304 30.3 and 36.9 (two).
 bool weight_grad_one_launch(const WeightGradPlan& p, int64_t O, int64_t K, int64_t T) {
