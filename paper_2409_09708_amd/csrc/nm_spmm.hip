@@ -2310,6 +2310,15 @@ static double wide_estimate(int64_t O, int64_t K, int N, int M, int64_t T, bool 
   return e < 4.5 ? 4.5 : e;
 }
 
+// Many tokens on most of the units, where every unit waits for memory and not for its own chain, are outside of what the estimate
+// was fitted on: of 755 shapes of 1500 to 50000 tokens the two launches won at 4490 x 1216 -> 440 at 1:8 (252 blocks; 13.3 us, 16.2 in one),
+// 8969 x 1096 -> 156 (213; 12.9 and 14.4), 8830 x 416 -> 392 (483; 12.4 and 16.1), 9911 x 80 -> 436 (546; 12.4 and 14.9), the one launch at
+// 1579 x 1000 -> 1001 (208; 13.5 and 11.6), 5222 x 448 -> 312 (205; 8.9 and 7.1), 4003 x 104 -> 832 (416; 9.0 and 7.8).
+static bool wide_in_range(int64_t O, int64_t K, int64_t T) {
+  const int64_t tiles = ((O + 63) / 64) * ((T + 127) / 128), spans = (K + 127) / 128;
+  return tiles <= 192 || T <= 2560 || (tiles <= 256 && spans <= 5) || (tiles <= 512 && spans == 1 && T <= 8192);
+}
+
 enum DirectForm { DIRECT_NONE, DIRECT_FIRST, DIRECT_WIDE };
 static DirectForm direct_form(int64_t O, int64_t K, int N, int M, int64_t T, bool out_bf16, int pick) {
   const bool sparse_form = N <= 2;
@@ -2322,7 +2331,7 @@ static DirectForm direct_form(int64_t O, int64_t K, int N, int M, int64_t T, boo
     if (const double e = tile_estimate(m, O, steps_k, T); e < two) two = e;
   two += 3.85 + (sparse_form ? 0.49 : 0.85) * 1e-6 * (double)((O + 255) / 256 * 256) * (double)steps_k;
   const double first = K % 16 == 0 ? tile_estimate(kDirectModel[sparse_form], O, steps_k, T) : 1e30;
-  if (T > 64 && K < 3072)
+  if (T > 64 && K < 3072 && wide_in_range(O, K, T))
     if (const double e = wide_estimate(O, K, N, M, T, out_bf16); e < 0.8 * first && e < two) return DIRECT_WIDE;
   return first < two ? DIRECT_FIRST : DIRECT_NONE;
 }
