@@ -21,6 +21,7 @@
 #include "nm_launch.h"
 #include "nm_mma.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace nm {
@@ -103,6 +104,8 @@ struct DirectCfg {
   static constexpr int SPAN = X_SPAN + kSteps * (A_STEP + S_STEP);
   static constexpr int LDS_BYTES = SETS * SPAN;
   static constexpr int VW = (VPC + 1) / 2;             // registers of a chunk's values
+  // Word of a row's index stream in which the fields of a chunk begin; `in`: the chunk does not lie past K (else the span's first one's).
+  static constexpr int64_t field_word(int span, int chunk, bool in) { return (int64_t)(span * 16 + (in ? chunk : 0)) * BITS >> 5; }
   static_assert(BITS <= 32 && LDS_BYTES <= 160 * 1024, "chunk fields and LDS budget");
 };
 
@@ -169,7 +172,7 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
       } else {
         d.v[u][0] = src[0];
       }
-      const int64_t word = (int64_t)(span * 16 + (in ? chunk : 0)) * C::BITS >> 5;
+      const int64_t word = C::field_word(span, chunk, in);
       d.f[u][0] = f_at[u][word];
       if constexpr (C::WORDS == 2) d.f[u][1] = f_at[u][word + 1 < nw ? word + 1 : word];
     }
@@ -426,6 +429,16 @@ struct WideCfg {
   static constexpr int A_STEP = ROWS * A_ROWB, S_STEP = SPARSE ? ROWS * 8 : 0;
   static constexpr int SPAN = X_SPAN + STEPS * (A_STEP + S_STEP);
   static constexpr int LDS_BYTES = 2 * SPAN;
+  // A span's index fields begin on a word of the row's stream, or ODD_BITS into one where the span is an odd one.
+  static constexpr int SPAN_BITS = 8 * BITS, ODD_BITS = SPAN_BITS % 32;
+  // The word in which the fields of a chunk begin; `in`: the chunk does not lie past K (else the row's first one).
+  static constexpr int64_t field_word(int span, int begin, int chunk, bool in) {
+    return in ? ((int64_t)span * SPAN_BITS >> 5) + ((begin + chunk * BITS) >> 5) : 0;
+  }
+  // What the second register set holds first: span 1, or span 0 again, not used, where there is no other.  Its fields have to be
+  // asked for where that span has them: with an odd span's place the last row of a single span would be read past its end.
+  static constexpr int second_span(int spans) { return spans > 1 ? 1 : 0; }
+  static constexpr int second_begin(int spans) { return spans > 1 ? ODD_BITS : 0; }
   static_assert(NT == ROWS * STEPS * 4 && NW * wave_tile_slice_bytes<OT, 4>() <= LDS_BYTES && LDS_BYTES <= 160 * 1024, "LDS budget");
 };
 
@@ -450,7 +463,7 @@ __global__ void __launch_bounds__(512) nm_direct_wide_kernel(const DirectArgs a)
   const int64_t nw = (nf * C::B + 31) / 32;
 
   // Where a lane's chunk and pieces of span 0 lie; rows past the last out-feature or token re-read the last one (never stored).
-  // A span ends on a word of the index stream or in the middle of one: `par` is the span's parity.
+  // A span ends on a word of the index stream or in the middle of one: `begin` is where in its first word it begins.
   const int row = tid >> 3, chunk = tid & 7;
   const int64_t o_row = o0 + row < a.O ? o0 + row : a.O - 1;
   const bf16_t* const v_at = a.values + o_row * nf + chunk * C::VPC;
@@ -463,8 +476,6 @@ __global__ void __launch_bounds__(512) nm_direct_wide_kernel(const DirectArgs a)
     if (t0 + t >= a.T) t = a.T - 1 - t0;
     x_off[i] = (uint32_t)t * (uint32_t)(a.ldx * 2) + (uint32_t)(tid & 15) * 16;
   }
-  constexpr int SPAN_BITS = 8 * C::BITS;
-  auto field_at = [&](auto par) { return (decltype(par)::value * SPAN_BITS % 32) + chunk * C::BITS; };  // in bits, from the word the span begins in
   auto load_run = [](const bf16_t* src, auto count, uint32_t* out) {  // `count` values at an address aligned to them
     constexpr int n = decltype(count)::value;
     if constexpr (n % 8 == 0) {
@@ -490,9 +501,8 @@ __global__ void __launch_bounds__(512) nm_direct_wide_kernel(const DirectArgs a)
   // The loads of a span carry no condition, so that the compiler counts them and a span waits for its own and not for those of
   // the next one (with conditions it drains them all: a round trip to memory per span).  What lies past K is fetched from the
   // span's first positions instead and cleared on its way into LDS.
-  auto fetch = [&](Loads& d, int span, auto par) {
+  auto fetch = [&](Loads& d, int span, int begin) {
     const int k_left = a.K - span * 128;  // reduction positions from the span on
-    const int64_t word0 = (int64_t)span * SPAN_BITS >> 5;
     const bool in = chunk * 16 < k_left, half_in = chunk * 16 + 8 < k_left;
     const bf16_t* src = v_at + (int64_t)span * (8 * C::VPC) - (in ? 0 : chunk * C::VPC);
     if constexpr (WHOLE) {
@@ -510,7 +520,7 @@ __global__ void __launch_bounds__(512) nm_direct_wide_kernel(const DirectArgs a)
         for (int j = 0; j < C::VPC; ++j) d.v[j / 2] |= (uint32_t)(j < HALF ? src[j] : second[j - HALF]) << (16 * (j & 1));
       }
     }
-    const int64_t word = in ? word0 + (field_at(par) >> 5) : 0;
+    const int64_t word = C::field_word(span, begin, chunk, in);
     d.f[0] = f_at[word];
     if constexpr (C::WORDS == 2) d.f[1] = f_at[word + 1 < nw ? word + 1 : word];
     const unsigned char* x = x_base + (int64_t)span * 256;
@@ -528,12 +538,13 @@ __global__ void __launch_bounds__(512) nm_direct_wide_kernel(const DirectArgs a)
       for (int i = 0; i < C::PIECES; ++i) d.x[i] = u32x4_t{0, 0, 0, 0};
   };
   // a span into its LDS buffer, the weight decoded; 16-byte pieces of a row are XOR-swizzled with the row
-  auto put = [&](Loads& d, int span, unsigned char* buf, auto par, auto whole_span) {
+  auto put = [&](Loads& d, int span, unsigned char* buf, int begin, auto whole_span) {
     if constexpr (!decltype(whole_span)::value)
       if (a.K - span * 128 < 128) clear_past(d, span);
     const int step = chunk >> 2, c = chunk & 3;
-    uint32_t fields = d.f[0] >> (field_at(par) & 31);
-    if constexpr (C::WORDS == 2) fields = __builtin_amdgcn_alignbit(d.f[1], d.f[0], field_at(par) & 31);
+    const int shift = (begin + chunk * C::BITS) & 31;
+    uint32_t fields = d.f[0] >> shift;
+    if constexpr (C::WORDS == 2) fields = __builtin_amdgcn_alignbit(d.f[1], d.f[0], shift);
     unsigned char* at = buf + C::X_SPAN + step * C::A_STEP + row * C::A_ROWB;
     if constexpr (C::SPARSE) {
       const uint32_t sel = put_sparse_piece<N, M>(at + (c ^ ((row >> 1) & 3)) * 16, d.v, fields);
@@ -621,11 +632,10 @@ __global__ void __launch_bounds__(512) nm_direct_wide_kernel(const DirectArgs a)
   };
 
   // Two register sets and two LDS buffers, as in the kernel above.
-  constexpr std::integral_constant<int, 0> p0{};
-  constexpr std::integral_constant<int, 1> p1{};
+  constexpr int p0 = 0, p1 = C::ODD_BITS;
   Loads even, odd;
   fetch(even, 0, p0);
-  fetch(odd, spans > 1 ? 1 : 0, p1);  // (a span of the other parity is fetched in vain, not used)
+  fetch(odd, C::second_span(spans), C::second_begin(spans));
   int span = 0;
   for (; span + 3 < spans; span += 2) {  // two whole spans: no conditions, so that a span's decoding and the products interleave
     put(even, span, smem, p0, std::true_type{});
@@ -755,6 +765,44 @@ bool direct_level(int N, int M) {
     case 1 * 32 + 4: case 3 * 32 + 4: case 1 * 32 + 8: case 2 * 32 + 8: case 3 * 32 + 8: case 4 * 32 + 8:
     case 1 * 32 + 16: case 2 * 32 + 16: case 4 * 32 + 16: return true;
     default: return false;
+  }
+}
+
+// Words of a row's index stream that the kernels of the level load at a reduction of K, up to the last one of them.
+template <int N, int M>
+static int64_t index_words_reached(bool wide, int64_t K) {
+  const int64_t nw = (K / M * N * log2_of(M) + 31) / 32;
+  const int nk = (int)((K + 63) / 64);
+  int64_t end = 0;
+  auto load = [&](int64_t word, bool two) {
+    end = std::max(end, word + 1);
+    if (two) end = std::max(end, (word + 1 < nw ? word + 1 : word) + 1);
+  };
+  if (wide) {
+    using C = WideCfg<N, M>;
+    const int spans = (nk + C::STEPS - 1) / C::STEPS;
+    auto fetch = [&](int span, int begin) {
+      for (int chunk = 0; chunk < 8; ++chunk)
+        load(C::field_word(span, begin, chunk, chunk * 16 < (int)K - span * 128), C::WORDS == 2);
+    };
+    for (int span = 0; span < spans; ++span) fetch(span, span % 2 ? C::ODD_BITS : 0);
+    fetch(C::second_span(spans), C::second_begin(spans));
+  } else {
+    using C = DirectCfg<N, M, 64, 32>;
+    for (int span = 0; span < (nk + kSteps - 1) / kSteps; ++span)
+      for (int chunk = 0; chunk < 16; ++chunk)
+        load(C::field_word(span, chunk, chunk * 16 < (int)K - span * 256), C::WORDS == 2);
+  }
+  return end;
+}
+
+// Not in the public header, for tests: the above; -1 where the level is not one of these kernels'.
+extern "C" int64_t nm_internal_direct_index_words(int32_t wide, int32_t N, int32_t M, int64_t K) {
+  switch (N * 32 + M) {
+#define X(n, m) case n * 32 + m: return index_words_reached<n, m>(wide != 0, K);
+    X(1, 4) X(3, 4) X(1, 8) X(2, 8) X(3, 8) X(4, 8) X(1, 16) X(2, 16) X(4, 16)
+#undef X
+    default: return -1;
   }
 }
 
