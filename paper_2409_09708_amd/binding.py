@@ -762,10 +762,14 @@ def nm_linear_backward_input(Ws, dY, out_dtype=None, out=None, workspace=None, s
     lib = load_library()
     fn = lib.nm_linear_backward_input  # (which leaves a workspace alone that it can do without)
     if workspace is None:
-        need = lib.nm_backward_input_scratch_bytes(O, K, T)
+        need = lib.nm_backward_input_workspace_bytes(O, K, T)
         if need:
             workspace = _workspace(need, dY.device, stream)
-            fn = lib.nm_linear_backward_input_scratch
+        else:  # a small layer: what it can use is the call's own, so that such calls may overlap and be captured as without it
+            need = lib.nm_backward_input_scratch_bytes(O, K, T)
+            if need:
+                workspace = _own_scratch(need, stream)
+                fn = lib.nm_linear_backward_input_scratch
     ws_ptr, ws_bytes = _scratch(workspace)
     _check(fn(Ws.data_ptr(), O, K, ldw, dY.data_ptr(), T, ldy, out.data_ptr(), ldx, code, ws_ptr, ws_bytes,
               _stream_handle(stream)))

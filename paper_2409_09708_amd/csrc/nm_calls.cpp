@@ -47,7 +47,8 @@ struct Library {
   decltype(&nm_linear_backward_input) backward_input;
   decltype(&nm_linear_backward_weight) backward_weight;
   decltype(&nm_linear_backward_input_scratch) backward_input_scratch;
-  decltype(&nm_backward_input_scratch_bytes) backward_input_bytes;
+  decltype(&nm_backward_input_workspace_bytes) backward_input_bytes;
+  decltype(&nm_backward_input_scratch_bytes) backward_input_scratch_bytes;
   decltype(&nm_backward_weight_workspace_bytes) backward_weight_bytes;
   decltype(&nm_linear_forward_i8) i8;
   decltype(&nm_linear_forward_i8_prepared) i8_prepared;
@@ -151,6 +152,12 @@ PyObject* result(int32_t st, PyObject* value) {  // steals value
 
 at::Tensor fresh(at::Device device, int64_t rows, int64_t cols, at::ScalarType type) {
   return at::empty({rows, cols}, at::TensorOptions().dtype(type).device(device));
+}
+
+// Whether memory allocated now, on the current device, goes to later work of this stream only.
+bool on_current_stream(void* s, at::Device* here) {
+  *here = at::Device(at::kCUDA, c10::hip::current_device());
+  return s == c10::hip::getCurrentHIPStream(here->index()).stream();
 }
 
 // The workspace of a call: the given tensor, or the scratch of its device and stream, held until the call has returned.
@@ -375,10 +382,7 @@ PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
   size_t scratch_bytes = how == 1 && lib.prepared_scratch_bytes ? lib.prepared_scratch_bytes(O, K, N, M, T) : 0;
   if (scratch_bytes != 0 && ws_bytes < lib.workspace_bytes(O, K, N, M, T)) scratch_bytes = 0;
   at::Device here = X->device();
-  if (scratch_bytes != 0) {
-    here = at::Device(at::kCUDA, c10::hip::current_device());
-    if (s != c10::hip::getCurrentHIPStream(here.index()).stream()) return declined();
-  }
+  if (scratch_bytes != 0 && !on_current_stream(s, &here)) return declined();
   const uint16_t *v = pointer<uint16_t>(values), *xp = pointer<uint16_t>(X);
   const uint32_t* ix = pointer<uint32_t>(indices);
   const float* b = pointer<float>(bias);
@@ -414,7 +418,8 @@ PyObject* backward_input(PyObject*, PyObject* const* a, Py_ssize_t n) {
   Matrix w, dy;
   Output y;
   void* s;
-  if (n != 6 || lib.backward_input == nullptr || lib.backward_input_scratch == nullptr || lib.backward_input_bytes == nullptr || observed() || !plain(a[0], at::kBFloat16, &W) ||
+  if (n != 6 || lib.backward_input == nullptr || lib.backward_input_scratch == nullptr || lib.backward_input_bytes == nullptr ||
+      lib.backward_input_scratch_bytes == nullptr || observed() || !plain(a[0], at::kBFloat16, &W) ||
       !matrix(*W, &w) || !plain(a[1], at::kBFloat16, &dY) || !matrix(*dY, &dy) || dy.cols != w.rows ||
       !y.read(a[2], a[3], dy.rows, w.cols, false) || !stream_of(a[5], &s))
     return declined();
@@ -422,12 +427,20 @@ PyObject* backward_input(PyObject*, PyObject* const* a, Py_ssize_t n) {
   const size_t need = a[4] == Py_None ? lib.backward_input_bytes(w.rows, w.cols, dy.rows) : 0;
   if (const Take t = need != 0 ? scratch_workspace(need, a[1], a[5], s, &ws) : given_workspace(a[4], &ws); t != TAKEN)
     return t == DECLINED ? declined() : nullptr;
+  // what a small layer can use: scratch of the call, as the partial sums above.  (A given workspace is left alone that is not required.)
+  const size_t scratch_bytes = need == 0 && a[4] == Py_None ? lib.backward_input_scratch_bytes(w.rows, w.cols, dy.rows) : 0;
+  at::Device here = dY->device();
+  if (scratch_bytes != 0 && !on_current_stream(s, &here)) return declined();
   const uint16_t *wp = pointer<uint16_t>(W), *dyp = pointer<uint16_t>(dY);
   const at::Device device = dY->device();
   const int32_t st = unlocked([&] {
     y.make(device);
-    const auto call = need != 0 ? lib.backward_input_scratch : lib.backward_input;  // (a given workspace is left alone that is not required)
-    return call(wp, w.rows, w.cols, w.ld, dyp, dy.rows, dy.ld, y.ptr, y.ld, y.code, ws.ptr, ws.bytes, s);
+    if (scratch_bytes != 0) {
+      const at::Tensor scratch = fresh(here, 1, (int64_t)scratch_bytes, at::kByte);
+      return lib.backward_input_scratch(wp, w.rows, w.cols, w.ld, dyp, dy.rows, dy.ld, y.ptr, y.ld, y.code, scratch.data_ptr(),
+                                        scratch_bytes, s);
+    }
+    return lib.backward_input(wp, w.rows, w.cols, w.ld, dyp, dy.rows, dy.ld, y.ptr, y.ld, y.code, ws.ptr, ws.bytes, s);
   });
   return result(st, y.take());
   END_HANDLE_TH_ERRORS
@@ -527,7 +540,8 @@ PyObject* bind(PyObject*, PyObject* args) {
       {"nm_prepared_scratch_bytes", &l.prepared_scratch_bytes, true},
       {"nm_linear_backward_input", &l.backward_input, true}, {"nm_linear_backward_weight", &l.backward_weight, true},
       {"nm_linear_backward_input_scratch", &l.backward_input_scratch, true},
-      {"nm_backward_input_scratch_bytes", &l.backward_input_bytes, true},
+      {"nm_backward_input_workspace_bytes", &l.backward_input_bytes, true},
+      {"nm_backward_input_scratch_bytes", &l.backward_input_scratch_bytes, true},
       {"nm_backward_weight_workspace_bytes", &l.backward_weight_bytes, true}, {"nm_linear_forward_i8", &l.i8, true},
       {"nm_linear_forward_i8_prepared", &l.i8_prepared, true}, {"nm_linear_forward_i8_packed", &l.i8_packed, true},
       {"nm_linear_forward_i8_packed_prepared", &l.i8_packed_prepared, true}, {"nm_i8_workspace_bytes", &l.i8_bytes, true}};
