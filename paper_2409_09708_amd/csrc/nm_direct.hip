@@ -39,6 +39,7 @@ struct DirectArgs {
   int32_t O, K, T;
   int32_t out_bf16, pieces;  // pieces: rows of Y are made of aligned runs of four outputs
   int32_t rows16;            // rows of Y in whole aligned 16-byte pieces
+  int32_t again;             // a sum that ended as NaN is computed again by the definition, as the ragged form of the tiled kernel has it
 };
 
 // The 2:4 operand of 16 weights into its 16 bytes of LDS; returns its selectors, four bits per run.  A run of four owns two 16-bit
@@ -374,7 +375,7 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
     const int o = o_lane + 16 * (TOKS == 64 ? i : half);
     if (o >= a.O) continue;
     f32x4_t y = PACKED ? acc[i] + bias_of(TOKS == 64 ? i : half) : acc[i];
-    if (a.K & 63) {  // a sum that ended as NaN again by the definition, as the ragged form of the tiled kernel has it
+    if (a.again) {
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         if (__builtin_isnan(y[e]) && o + e < a.O)
@@ -667,7 +668,7 @@ __global__ void __launch_bounds__(512) nm_direct_wide_kernel(const DirectArgs a)
   }
 
   const int64_t row0 = t0 + wt * C::TT * 16, col0 = o_wave;
-  if (a.K & 63) {  // sums that ended as NaN again by the definition, as the ragged form of the tiled kernel has it
+  if (a.again) {
     uint32_t which = 0;  // bit 4 (i TT + j) + e
     static_assert(C::OT * C::TT <= 8, "one bit per sum");
 #pragma unroll
@@ -808,8 +809,9 @@ extern "C" int64_t nm_internal_direct_index_words(int32_t wide, int32_t N, int32
 
 // The caller has checked the operands (K % 64 == 0, or K % 16 == 0 in the tiled kernel's order; 16-byte aligned X rows and
 // values, sizes as the tiled kernel's).  wide: blocks of 64 out-features x 128 tokens, the tiled kernel's order only, and K % 8 == 0 is
-// enough (at M = 16 K is a multiple of 16 anyway).
-hipError_t launch_direct(const SpmmArgs& a, bool packed_order, bool wide, hipStream_t s) {
+// enough (at M = 16 K is a multiple of 16 anyway).  again: a prepared call multiplies the layer on the ragged form of the tiled
+// kernel also where K % 64 == 0, so what that form does with sums that end as NaN is done here.
+hipError_t launch_direct(const SpmmArgs& a, bool packed_order, bool wide, bool again, hipStream_t s) {
   DirectArgs g;
   g.values = a.values; g.indices = a.indices; g.X = a.X; g.bias = a.bias; g.Y = a.Y;
   g.ldx = a.ldx; g.ldy = a.ldy;
@@ -817,6 +819,7 @@ hipError_t launch_direct(const SpmmArgs& a, bool packed_order, bool wide, hipStr
   g.out_bf16 = a.out_bf16;
   g.pieces = (a.O % 4 == 0) && (a.ldy % 4 == 0) && ((uintptr_t)a.Y & (a.out_bf16 ? 7u : 15u)) == 0;
   const int per_piece = a.out_bf16 ? 8 : 4;
+  g.again = again || a.K % 64 != 0;
   g.rows16 = (a.O % per_piece == 0) && (a.ldy % per_piece == 0) && ((uintptr_t)a.Y & 15u) == 0;
   if (wide) {
     switch (a.N * 32 + a.M) {

@@ -153,9 +153,10 @@ bool fewtok_takes(const SpmmArgs& a);
 hipError_t launch_fewtok(const SpmmArgs* const* layers, int count, hipStream_t s);
 
 // nm_direct.hip: one launch from the packed weight to the product of a few tokens; packed_order: summed as the kernel of
-// nm_fewtok.hip does it, else as the tiled kernel; wide: its blocks of 64 out-features x 128 tokens
+// nm_fewtok.hip does it, else as the tiled kernel; wide: its blocks of 64 out-features x 128 tokens; again: sums that end as NaN once more by the definition (at
+// K % 64 != 0 in any case)
 bool direct_level(int N, int M);
-hipError_t launch_direct(const SpmmArgs& a, bool packed_order, bool wide, hipStream_t s);
+hipError_t launch_direct(const SpmmArgs& a, bool packed_order, bool wide, bool again, hipStream_t s);
 
 // Out[t, i] = sum_r Q[t, r] * Ws[r, i] on the persistent dense product kernel, or the tiled one (weight transposed into stream
 // order in the workspace first; *required: the persistent one's layers); *taken stays false, and nothing is launched, when the shape, the alignment or

@@ -2369,7 +2369,7 @@ hipError_t launch_spmm(const SpmmArgs& a, hipStream_t s, bool* workspace_short, 
     if (ragged && prepare && product && a.K % 64 != 0 && aligned_to(a.X, 16) && a.ldx % 8 == 0 && aligned_to(a.values, 16))
       if (const DirectForm f = direct_form_ragged(a.O, a.K, a.N, a.M, a.T, a.out_bf16);
           f == DIRECT_FIRST || (f == DIRECT_WIDE && a.ldx <= (1 << 22)))
-        return launch_direct(a, false, f == DIRECT_WIDE, s);
+        return launch_direct(a, false, f == DIRECT_WIDE, true, s);
     if (ragged && prepare) {
       hipError_t e = launch_stream_prepass(a, sparse_form, s);
       if (e != hipSuccess) return e;
@@ -2383,24 +2383,25 @@ hipError_t launch_spmm(const SpmmArgs& a, hipStream_t s, bool* workspace_short, 
     if (!packed_path(a)) {
       *workspace_short = true;
     } else if (product) {
-      if (direct_takes_packed(a.O, a.T)) return launch_direct(a, true, false, s);
+      if (direct_takes_packed(a.O, a.T)) return launch_direct(a, true, false, false, s);
       const SpmmArgs* one = &a;
       return launch_fewtok(&one, 1, s);
     }
     return hipSuccess;
   }
   const int pick = pick_tile(a.O, a.K, a.T, sparse_form);
-  if (prepare && product)
-    if (const DirectForm f = direct_form(a.O, a.K, a.N, a.M, a.T, a.out_bf16, pick); f != DIRECT_NONE)
-      return launch_direct(a, false, f == DIRECT_WIDE, s);
   GemmArgs g;
   fill_gemm_args(a, form, sparse_form, &g);
+  const bool unaligned = unaligned_output(a, g, pick);
+  if (prepare && product)
+    if (const DirectForm f = direct_form(a.O, a.K, a.N, a.M, a.T, a.out_bf16, pick); f != DIRECT_NONE)
+      return launch_direct(a, false, f == DIRECT_WIDE, unaligned, s);
   if (prepare && form == FORM_STREAM) {
     hipError_t e = launch_stream_prepass(a, sparse_form, s);
     if (e != hipSuccess) return e;
   }
   if (!product) return hipSuccess;
-  if (unaligned_output(a, g, pick)) return ragged_product();
+  if (unaligned) return ragged_product();
   return sparse_form ? dispatch_gemm<true>(g, pick, s) : dispatch_gemm<false>(g, pick, s);
 }
 
