@@ -364,8 +364,11 @@ int32_t nm_linear_forward_prepared_batched_scratch(const nm_forward_desc* descs,
  *       workspace scratch of nm_backward_weight_workspace_bytes(O, K, T) bytes, 256-byte aligned (the token
  *                 reduction is cut into ranges whose partial sums are added in a fixed order, so results
  *                 repeat bit for bit; the size is that of all ranges, of which a call may leave half
- *                 unused); NULL allowed when that size is 0.  Contents undefined afterwards;
+ *                 unused, and a short reduction all of it); NULL allowed when that size is 0.  Contents undefined afterwards;
  *                 concurrent calls need distinct workspaces.
+ *   nm_linear_backward_weight_scratch
+ *                 the same (the same sums) with nm_backward_weight_scratch_bytes(O, K, T) bytes: none for a short reduction,
+ *                 whose ranges one launch adds on the chip, elsewhere the size above.
  * The matrix-core kernels need 16-byte aligned operands, leading dimensions that are multiples of 8, K % 8 == 0
  * and O % 32 == 0 (dX) or O % 8 == 0 (dW); other shapes run a slower general kernel with the same results.
  * Errors: NM_ERR_NULL, NM_ERR_SHAPE (sizes <= 0, a leading dimension smaller than its row), NM_ERR_DTYPE,
@@ -383,6 +386,10 @@ int32_t nm_linear_backward_input_scratch(const nm_bf16* Ws, int64_t O, int64_t K
 int32_t nm_linear_backward_weight(const nm_bf16* dY, int64_t T, int64_t O, int64_t ldy, const nm_bf16* X,
                                   int64_t K, int64_t ldx, const uint32_t* mask, void* dW, int64_t lddw,
                                   int32_t out_dtype, void* workspace, size_t workspace_bytes, void* stream);
+size_t nm_backward_weight_scratch_bytes(int64_t O, int64_t K, int64_t T);
+int32_t nm_linear_backward_weight_scratch(const nm_bf16* dY, int64_t T, int64_t O, int64_t ldy, const nm_bf16* X,
+                                          int64_t K, int64_t ldx, const uint32_t* mask, void* dW, int64_t lddw,
+                                          int32_t out_dtype, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
  * nm_prune_scored -- Eq. (1) with a saliency supplied by the caller (Section 3.1: rho can be the weight magnitude,

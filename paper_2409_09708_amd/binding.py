@@ -34,6 +34,7 @@ EXPORTS = (
     "nm_rank_bytes", "nm_rank", "nm_rank_batched", "nm_rank_mask", "nm_pack_ranked", "nm_pack_ranked_batched", "nm_pack_prepare_batched",
     "nm_config_cost", "nm_sample_config",
     "nm_backward_input_workspace_bytes", "nm_backward_weight_workspace_bytes", "nm_linear_backward_input", "nm_backward_input_scratch_bytes", "nm_linear_backward_input_scratch", "nm_linear_backward_weight",
+    "nm_backward_weight_scratch_bytes", "nm_linear_backward_weight_scratch",
     "nm_linear_forward_prepared_batched", "nm_prepared_scratch_bytes", "nm_linear_forward_prepared_scratch",
     "nm_prepared_batched_scratch_bytes", "nm_linear_forward_prepared_batched_scratch", "nm_prune_scored", "nm_i8_workspace_bytes", "nm_linear_forward_i8", "nm_i8_prepare", "nm_linear_forward_i8_prepared",
 )
@@ -183,9 +184,13 @@ def load_library() -> ctypes.CDLL:
                                              c_int64, c_int32, c_void_p, c_size_t, c_void_p]
     lib.nm_linear_backward_input_scratch.restype = c_int32
     lib.nm_linear_backward_input_scratch.argtypes = lib.nm_linear_backward_input.argtypes
+    lib.nm_backward_weight_scratch_bytes.restype = c_size_t
+    lib.nm_backward_weight_scratch_bytes.argtypes = [c_int64, c_int64, c_int64]
     lib.nm_linear_backward_weight.restype = c_int32
     lib.nm_linear_backward_weight.argtypes = [c_void_p, c_int64, c_int64, c_int64, c_void_p, c_int64, c_int64, c_void_p,
                                               c_void_p, c_int64, c_int32, c_void_p, c_size_t, c_void_p]
+    lib.nm_linear_backward_weight_scratch.restype = c_int32
+    lib.nm_linear_backward_weight_scratch.argtypes = lib.nm_linear_backward_weight.argtypes
     lib.nm_linear_forward_prepared_batched.restype = c_int32
     lib.nm_linear_forward_prepared_batched.argtypes = [ctypes.POINTER(ForwardDesc), c_int32, c_void_p]
     lib.nm_prepared_batched_scratch_bytes.restype = c_size_t
@@ -794,13 +799,16 @@ def nm_linear_backward_weight(dY, X, mask=None, out_dtype=None, out=None, worksp
         raise ValueError("dY and X must have the same number of rows")
     mask_ptr = None if mask is None else _mask_words(mask, O, K)
     out, lddw, code = _out_matrix(out, out_dtype, O, K, dY, "dW")
+    lib = load_library()
+    fn = lib.nm_linear_backward_weight
     if workspace is None:
-        need = nm_backward_weight_workspace_bytes(O, K, T)
+        need = lib.nm_backward_weight_scratch_bytes(O, K, T)
         if need:
             workspace = _workspace(need, dY.device, stream)
+        fn = lib.nm_linear_backward_weight_scratch
     ws_ptr, ws_bytes = _scratch(workspace)
-    _check(load_library().nm_linear_backward_weight(dY.data_ptr(), T, O, ldy, X.data_ptr(), K, ldx, mask_ptr,
-                                                    out.data_ptr(), lddw, code, ws_ptr, ws_bytes, _stream_handle(stream)))
+    _check(fn(dY.data_ptr(), T, O, ldy, X.data_ptr(), K, ldx, mask_ptr, out.data_ptr(), lddw, code, ws_ptr, ws_bytes,
+              _stream_handle(stream)))
     return out
 
 

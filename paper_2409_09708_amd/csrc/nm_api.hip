@@ -411,9 +411,10 @@ int32_t nm_linear_backward_input_scratch(const nm_bf16* Ws, int64_t O, int64_t K
   return backward_input(Ws, O, K, ldw, dY, T, ldy, dX, ldx, out_dtype, workspace, workspace_bytes, stream, true);
 }
 
-int32_t nm_linear_backward_weight(const nm_bf16* dY, int64_t T, int64_t O, int64_t ldy, const nm_bf16* X, int64_t K,
+namespace {
+int32_t backward_weight(const nm_bf16* dY, int64_t T, int64_t O, int64_t ldy, const nm_bf16* X, int64_t K,
                                   int64_t ldx, const uint32_t* mask, void* dW, int64_t lddw, int32_t out_dtype,
-                                  void* workspace, size_t workspace_bytes, void* stream) {
+                                  void* workspace, size_t workspace_bytes, void* stream, bool used_only) {
   if (!dY || !X || !dW) return NM_ERR_NULL;
   if (O <= 0 || K <= 0 || T <= 0 || O > (int64_t)1 << 31 || K > (int64_t)1 << 31 || T > (int64_t)1 << 31)
     return NM_ERR_SHAPE;
@@ -423,9 +424,27 @@ int32_t nm_linear_backward_weight(const nm_bf16* dY, int64_t T, int64_t O, int64
     return NM_ERR_ALIGN;
   bool workspace_short = false;
   hipError_t e = nm::launch_backward_weight(dY, T, O, ldy, X, K, ldx, mask, dW, lddw, out_dtype == NM_OUT_BF16, workspace,
-                                            workspace_bytes, (hipStream_t)stream, &workspace_short);
+                                            workspace_bytes, (hipStream_t)stream, used_only, &workspace_short);
   if (workspace_short) return NM_ERR_WORKSPACE;
   return device_status(e);
+}
+}  // namespace
+
+int32_t nm_linear_backward_weight(const nm_bf16* dY, int64_t T, int64_t O, int64_t ldy, const nm_bf16* X, int64_t K,
+                                  int64_t ldx, const uint32_t* mask, void* dW, int64_t lddw, int32_t out_dtype,
+                                  void* workspace, size_t workspace_bytes, void* stream) {
+  return backward_weight(dY, T, O, ldy, X, K, ldx, mask, dW, lddw, out_dtype, workspace, workspace_bytes, stream, false);
+}
+
+size_t nm_backward_weight_scratch_bytes(int64_t O, int64_t K, int64_t T) {
+  if (O <= 0 || K <= 0 || T <= 0) return 0;
+  return nm::backward_weight_scratch_bytes(O, K, T);
+}
+
+int32_t nm_linear_backward_weight_scratch(const nm_bf16* dY, int64_t T, int64_t O, int64_t ldy, const nm_bf16* X, int64_t K,
+                                  int64_t ldx, const uint32_t* mask, void* dW, int64_t lddw, int32_t out_dtype,
+                                  void* workspace, size_t workspace_bytes, void* stream) {
+  return backward_weight(dY, T, O, ldy, X, K, ldx, mask, dW, lddw, out_dtype, workspace, workspace_bytes, stream, true);
 }
 
 size_t nm_i8_workspace_bytes(int64_t O, int64_t K, int32_t N, int32_t M, int64_t T) {

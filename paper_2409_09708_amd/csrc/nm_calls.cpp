@@ -49,7 +49,8 @@ struct Library {
   decltype(&nm_linear_backward_input_scratch) backward_input_scratch;
   decltype(&nm_backward_input_workspace_bytes) backward_input_bytes;
   decltype(&nm_backward_input_scratch_bytes) backward_input_scratch_bytes;
-  decltype(&nm_backward_weight_workspace_bytes) backward_weight_bytes;
+  decltype(&nm_linear_backward_weight_scratch) backward_weight_scratch;
+  decltype(&nm_backward_weight_scratch_bytes) backward_weight_scratch_bytes;
   decltype(&nm_linear_forward_i8) i8;
   decltype(&nm_linear_forward_i8_prepared) i8_prepared;
   decltype(&nm_linear_forward_i8_packed) i8_packed;
@@ -453,14 +454,16 @@ PyObject* backward_weight(PyObject*, PyObject* const* a, Py_ssize_t n) {
   Matrix dy, x;
   Output y;
   void* s;
-  if (n != 7 || lib.backward_weight == nullptr || lib.backward_weight_bytes == nullptr || observed() || !plain(a[0], at::kBFloat16, &dY) ||
+  if (n != 7 || lib.backward_weight == nullptr || lib.backward_weight_scratch == nullptr ||
+      lib.backward_weight_scratch_bytes == nullptr || observed() || !plain(a[0], at::kBFloat16, &dY) ||
       !matrix(*dY, &dy) || !plain(a[1], at::kBFloat16, &X) || !matrix(*X, &x) || x.rows != dy.rows)
     return declined();
   if (a[2] != Py_None && (!plain(a[2], at::kInt, &mask) || !whole(*mask) || mask->size(0) != dy.cols || mask->size(1) != (x.cols + 31) / 32))
     return declined();
   if (!y.read(a[3], a[4], dy.cols, x.cols, false) || !stream_of(a[6], &s)) return declined();
   Workspace ws;
-  const size_t need = a[5] == Py_None ? lib.backward_weight_bytes(dy.cols, x.cols, dy.rows) : 0;
+  const size_t need = a[5] == Py_None ? lib.backward_weight_scratch_bytes(dy.cols, x.cols, dy.rows) : 0;
+  const auto call = a[5] == Py_None ? lib.backward_weight_scratch : lib.backward_weight;
   if (const Take t = need != 0 ? scratch_workspace(need, a[0], a[6], s, &ws) : given_workspace(a[5], &ws); t != TAKEN)
     return t == DECLINED ? declined() : nullptr;
   const uint16_t *dyp = pointer<uint16_t>(dY), *xp = pointer<uint16_t>(X);
@@ -468,7 +471,7 @@ PyObject* backward_weight(PyObject*, PyObject* const* a, Py_ssize_t n) {
   const at::Device device = dY->device();
   const int32_t st = unlocked([&] {
     y.make(device);
-    return lib.backward_weight(dyp, dy.rows, dy.cols, dy.ld, xp, x.cols, x.ld, mp, y.ptr, y.ld, y.code, ws.ptr, ws.bytes, s);
+    return call(dyp, dy.rows, dy.cols, dy.ld, xp, x.cols, x.ld, mp, y.ptr, y.ld, y.code, ws.ptr, ws.bytes, s);
   });
   return result(st, y.take());
   END_HANDLE_TH_ERRORS
@@ -542,7 +545,8 @@ PyObject* bind(PyObject*, PyObject* args) {
       {"nm_linear_backward_input_scratch", &l.backward_input_scratch, true},
       {"nm_backward_input_workspace_bytes", &l.backward_input_bytes, true},
       {"nm_backward_input_scratch_bytes", &l.backward_input_scratch_bytes, true},
-      {"nm_backward_weight_workspace_bytes", &l.backward_weight_bytes, true}, {"nm_linear_forward_i8", &l.i8, true},
+      {"nm_linear_backward_weight_scratch", &l.backward_weight_scratch, true},
+      {"nm_backward_weight_scratch_bytes", &l.backward_weight_scratch_bytes, true}, {"nm_linear_forward_i8", &l.i8, true},
       {"nm_linear_forward_i8_prepared", &l.i8_prepared, true}, {"nm_linear_forward_i8_packed", &l.i8_packed, true},
       {"nm_linear_forward_i8_packed_prepared", &l.i8_packed_prepared, true}, {"nm_i8_workspace_bytes", &l.i8_bytes, true}};
   for (auto& e : slots) {

@@ -914,9 +914,15 @@ size_t backward_weight_workspace_bytes(int64_t O, int64_t K, int64_t T) {
   return (size_t)p.splits * (size_t)p.n_i_tiles * (size_t)p.n_j_tiles * (size_t)(TCfg::BI * TCfg::BJ) * sizeof(float);
 }
 
+// (none where one launch adds the ranges itself)
+size_t backward_weight_scratch_bytes(int64_t O, int64_t K, int64_t T) {
+  const WeightGradPlan p = weight_grad_plan(O, K, T);
+  return p.tiles && weight_grad_one_launch(p, O, K, T) ? 0 : backward_weight_workspace_bytes(O, K, T);
+}
+
 hipError_t launch_backward_weight(const bf16_t* dY, int64_t T, int64_t O, int64_t ldy, const bf16_t* X, int64_t K,
                                   int64_t ldx, const uint32_t* mask, void* dW, int64_t lddw, int out_bf16, void* workspace,
-                                  size_t workspace_bytes, hipStream_t s, bool* workspace_short) {
+                                  size_t workspace_bytes, hipStream_t s, bool used_only, bool* workspace_short) {
   *workspace_short = false;
   const WeightGradPlan p = weight_grad_plan(O, K, T);
   const bool tiles = p.tiles && (ldy % 8 == 0) && (ldx % 8 == 0) && aligned_to(dY, 16) && aligned_to(X, 16) &&
@@ -927,8 +933,9 @@ hipError_t launch_backward_weight(const bf16_t* dY, int64_t T, int64_t O, int64_
                        X, K, ldx, mask, dW, lddw, out_bf16);
     return hipGetLastError();
   }
-  const size_t need = backward_weight_workspace_bytes(O, K, T);
-  if (workspace == nullptr || workspace_bytes < need || !aligned_to(workspace, 256)) {
+  const bool one_launch = weight_grad_one_launch(p, O, K, T);
+  const size_t need = used_only && one_launch ? 0 : backward_weight_workspace_bytes(O, K, T);
+  if (need && (workspace == nullptr || workspace_bytes < need || !aligned_to(workspace, 256))) {
     *workspace_short = true;
     return hipSuccess;
   }
@@ -938,7 +945,7 @@ hipError_t launch_backward_weight(const bf16_t* dY, int64_t T, int64_t O, int64_
   g.n_i_tiles = p.n_i_tiles; g.n_j_tiles = p.n_j_tiles;
   g.splits = p.splits; g.partial = reinterpret_cast<float*>(workspace);
   const bool pair = weight_grad_paired(p, T);
-  if (weight_grad_one_launch(p, O, K, T)) {
+  if (one_launch) {
     g.partial = nullptr;
     g.out = dW; g.ldo = lddw; g.out_bf16 = out_bf16;
     g.vec_store = (lddw % (out_bf16 ? 8 : 4) == 0) && aligned_to(dW, 16);  // K % 8 == 0 holds here

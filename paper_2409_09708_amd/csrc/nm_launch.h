@@ -173,10 +173,11 @@ hipError_t launch_backward_input(const bf16_t* Ws, int64_t O, int64_t K, int64_t
                                  int64_t ldy, void* dX, int64_t ldx, int out_bf16, void* workspace,
                                  size_t workspace_bytes, hipStream_t s, bool optional, bool* workspace_short);
 size_t backward_weight_workspace_bytes(int64_t O, int64_t K, int64_t T);
-// *workspace_short is set when the workspace is required but missing, misaligned or too small
+size_t backward_weight_scratch_bytes(int64_t O, int64_t K, int64_t T);  // what of it the kernels use
+// *workspace_short is set when the workspace is required but missing, misaligned or too small (used_only: the above)
 hipError_t launch_backward_weight(const bf16_t* dY, int64_t T, int64_t O, int64_t ldy, const bf16_t* X, int64_t K,
                                   int64_t ldx, const uint32_t* mask, void* dW, int64_t lddw, int out_bf16, void* workspace,
-                                  size_t workspace_bytes, hipStream_t s, bool* workspace_short);
+                                  size_t workspace_bytes, hipStream_t s, bool used_only, bool* workspace_short);
 
 // nm_spmm.hip: the int8 layer on the persistent kernel (operands in stream order, O padded to 256 rows)
 struct StreamI8Args {
