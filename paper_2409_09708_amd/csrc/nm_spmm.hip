@@ -202,20 +202,22 @@ struct GemmArgs {
   const bf16_t* X;
   const float* bias;
   void* Y;
-  float* partial;       // splits > 1: fp32 partial sums [splits][T][O] (rows of O floats), added up by the reduce kernel
+  float* partial = nullptr;  // splits > 1: fp32 partial sums [splits][T][O] (rows of O floats), added up by the reduce kernel
   int64_t O, K, T, ldx, ldy;
   int n_o_tiles, n_t_tiles;
   uint8_t out_bf16;
   uint8_t vec_store;    // Y rows split into whole aligned 16-byte pieces (ldy, O multiples of 8 (bf16) / 4 (fp32))
   uint8_t stream_form;  // A (and sel) lie in stream order (the pre-pass's output), else row-major as packed
-  uint8_t splits;       // ranges the reduction is cut into (tiled kernel only; 1 = the whole K in one block)
-  uint8_t rot;          // tiled kernel: XCD x takes the layer's share number (x + rot) mod 8
-  uint8_t x_aligned;    // every X row starts on 16 bytes
+  uint8_t splits = 1;   // ranges the reduction is cut into (tiled kernel only; 1 = the whole K in one block)
+  uint8_t rot = 0;      // tiled kernel: XCD x takes the layer's share number (x + rot) mod 8
+  uint8_t x_aligned = 0;  // every X row starts on 16 bytes
   // ragged form only: the packed weight itself, for the sums that are computed a second time
-  uint8_t N, M;
-  const bf16_t* values;
-  const uint32_t* indices;
+  uint8_t N = 0, M = 0;
+  const bf16_t* values = nullptr;
+  const uint32_t* indices = nullptr;
 };
+// (a launch that sets only what it knows leaves no share number to chance)
+static_assert([] { GemmArgs g; return g.rot == 0 && g.splits == 1 && g.partial == nullptr && g.values == nullptr; }());
 
 template <bool SPARSE, int WO, int WT, int OT, int TT, int STAGES_>
 struct GemmCfg {
