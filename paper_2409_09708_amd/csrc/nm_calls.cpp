@@ -13,6 +13,7 @@
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
+#include <c10/core/StreamGuard.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
@@ -153,6 +154,15 @@ PyObject* result(int32_t st, PyObject* value) {  // steals value
 
 at::Tensor fresh(at::Device device, int64_t rows, int64_t cols, at::ScalarType type) {
   return at::empty({rows, cols}, at::TensorOptions().dtype(type).device(device));
+}
+
+// Bytes that go to later work of this stream only.
+at::Tensor fresh_on(void* s, at::Device device, int64_t bytes) {
+  const c10::DeviceIndex current = c10::hip::current_device();
+  if (s == c10::hip::getCurrentHIPStream(current).stream()) return fresh(at::Device(at::kCUDA, current), 1, bytes, at::kByte);
+  const c10::StreamGuard on(s == nullptr ? c10::hip::getDefaultHIPStream(device.index()).unwrap()
+                                         : c10::hip::getStreamFromExternal(static_cast<hipStream_t>(s), device.index()).unwrap());
+  return fresh(device, 1, bytes, at::kByte);
 }
 
 // Whether memory allocated now, on the current device, goes to later work of this stream only.
@@ -430,14 +440,12 @@ PyObject* backward_input(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return t == DECLINED ? declined() : nullptr;
   // what a small layer can use: scratch of the call, as the partial sums above.  (A given workspace is left alone that is not required.)
   const size_t scratch_bytes = need == 0 && a[4] == Py_None ? lib.backward_input_scratch_bytes(w.rows, w.cols, dy.rows) : 0;
-  at::Device here = dY->device();
-  if (scratch_bytes != 0 && !on_current_stream(s, &here)) return declined();
   const uint16_t *wp = pointer<uint16_t>(W), *dyp = pointer<uint16_t>(dY);
   const at::Device device = dY->device();
   const int32_t st = unlocked([&] {
     y.make(device);
     if (scratch_bytes != 0) {
-      const at::Tensor scratch = fresh(here, 1, (int64_t)scratch_bytes, at::kByte);
+      const at::Tensor scratch = fresh_on(s, device, (int64_t)scratch_bytes);
       return lib.backward_input_scratch(wp, w.rows, w.cols, w.ld, dyp, dy.rows, dy.ld, y.ptr, y.ld, y.code, scratch.data_ptr(),
                                         scratch_bytes, s);
     }

@@ -71,16 +71,20 @@ def test_a_recorded_product_outlives_larger_calls_on_its_stream(explicit):
 
 
 @pytest.mark.gpu
-def test_two_threads_on_one_stream():
+@pytest.mark.parametrize("named", [False, True])
+def test_two_threads_on_one_stream(named):
+    stream = torch.cuda.Stream() if named else None  # (not the current stream: the scratch is that stream's all the same)
     layers = [layer(197, 768, 3072, 10), layer(65, 768, 2304, 11)]
     want = [nm.nm_linear_backward_input(W, dY, workspace=torch.empty(8, dtype=torch.uint8, device="cuda")) for W, dY in layers]
+    assert binding._CALLS.backward_input(*layers[0], None, None, None, stream) is not NotImplemented
     torch.cuda.synchronize()
     wrong, start = [], threading.Barrier(2)
 
     def work(n):
         W, dY = layers[n]
         start.wait()
-        got = [nm.nm_linear_backward_input(W, dY) for _ in range(300)]
+        got = [nm.nm_linear_backward_input(W, dY, stream=stream) for _ in range(300)]
+        torch.cuda.synchronize()
         wrong.append(sum(not torch.equal(y, want[n]) for y in got))
 
     threads = [threading.Thread(target=work, args=(n,)) for n in (0, 1)]
