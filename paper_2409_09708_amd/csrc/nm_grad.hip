@@ -920,11 +920,12 @@ size_t backward_weight_scratch_bytes(int64_t O, int64_t K, int64_t T) {
   return p.tiles && weight_grad_one_launch(p, O, K, T) ? 0 : backward_weight_workspace_bytes(O, K, T);
 }
 
-hipError_t launch_backward_weight(const bf16_t* dY, int64_t T, int64_t O, int64_t ldy, const bf16_t* X, int64_t K,
-                                  int64_t ldx, const uint32_t* mask, void* dW, int64_t lddw, int out_bf16, void* workspace,
-                                  size_t workspace_bytes, hipStream_t s, bool used_only, bool* workspace_short) {
+// need: bytes of the workspace without which the call is refused (0 only with one_launch)
+static hipError_t launch_weight_grad(const WeightGradPlan& p, bool one_launch, size_t need, const bf16_t* dY, int64_t T, int64_t O,
+                                     int64_t ldy, const bf16_t* X, int64_t K, int64_t ldx, const uint32_t* mask, void* dW,
+                                     int64_t lddw, int out_bf16, void* workspace, size_t workspace_bytes, hipStream_t s,
+                                     bool* workspace_short) {
   *workspace_short = false;
-  const WeightGradPlan p = weight_grad_plan(O, K, T);
   const bool tiles = p.tiles && (ldy % 8 == 0) && (ldx % 8 == 0) && aligned_to(dY, 16) && aligned_to(X, 16) &&
                      ldx <= (1 << 22) && ldy <= (1 << 22);
   if (!tiles) {
@@ -933,8 +934,6 @@ hipError_t launch_backward_weight(const bf16_t* dY, int64_t T, int64_t O, int64_
                        X, K, ldx, mask, dW, lddw, out_bf16);
     return hipGetLastError();
   }
-  const bool one_launch = weight_grad_one_launch(p, O, K, T);
-  const size_t need = used_only && one_launch ? 0 : backward_weight_workspace_bytes(O, K, T);
   if (need && (workspace == nullptr || workspace_bytes < need || !aligned_to(workspace, 256))) {
     *workspace_short = true;
     return hipSuccess;
@@ -960,6 +959,27 @@ hipError_t launch_backward_weight(const bf16_t* dY, int64_t T, int64_t O, int64_
   hipLaunchKernelGGL(grad_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, g.partial, planes,
                      p.n_i_tiles * p.n_j_tiles, p.n_i_tiles, K, O, mask, dW, lddw, out_bf16);
   return hipGetLastError();
+}
+
+hipError_t launch_backward_weight(const bf16_t* dY, int64_t T, int64_t O, int64_t ldy, const bf16_t* X, int64_t K,
+                                  int64_t ldx, const uint32_t* mask, void* dW, int64_t lddw, int out_bf16, void* workspace,
+                                  size_t workspace_bytes, hipStream_t s, bool used_only, bool* workspace_short) {
+  const WeightGradPlan p = weight_grad_plan(O, K, T);
+  const size_t need = used_only ? backward_weight_scratch_bytes(O, K, T) : backward_weight_workspace_bytes(O, K, T);
+  return launch_weight_grad(p, p.tiles && weight_grad_one_launch(p, O, K, T), need, dY, T, O, ldy, X, K, ldx, mask, dW, lddw, out_bf16,
+                            workspace, workspace_bytes, s, workspace_short);
+}
+
+// Not in the public header, for tests: dW in two launches also where one is chosen.  Arguments as nm_linear_backward_weight has checked
+// them; 0, or -1 where the workspace is too small or a launch fails.
+extern "C" int32_t nm_internal_weight_grad_two_launches(const bf16_t* dY, int64_t T, int64_t O, int64_t ldy, const bf16_t* X, int64_t K,
+                                                        int64_t ldx, const uint32_t* mask, float* dW, int64_t lddw, void* workspace,
+                                                        size_t workspace_bytes, hipStream_t s) {
+  bool workspace_short = false;
+  const WeightGradPlan p = weight_grad_plan(O, K, T);
+  const hipError_t e = launch_weight_grad(p, false, backward_weight_workspace_bytes(O, K, T), dY, T, O, ldy, X, K, ldx, mask, dW, lddw, 0,
+                                          workspace, workspace_bytes, s, &workspace_short);
+  return e == hipSuccess && !workspace_short ? 0 : -1;
 }
 
 }  // namespace nm
