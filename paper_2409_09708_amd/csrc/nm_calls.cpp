@@ -13,8 +13,9 @@
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
-#include <c10/core/StreamGuard.h>
+#include <c10/core/DeviceGuard.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
+#include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
@@ -156,14 +157,19 @@ at::Tensor fresh(at::Device device, int64_t rows, int64_t cols, at::ScalarType t
   return at::empty({rows, cols}, at::TensorOptions().dtype(type).device(device));
 }
 
-// Bytes that go to later work of this stream only.
-at::Tensor fresh_on(void* s, at::Device device, int64_t bytes) {
-  const c10::DeviceIndex current = c10::hip::current_device();
-  if (s == c10::hip::getCurrentHIPStream(current).stream()) return fresh(at::Device(at::kCUDA, current), 1, bytes, at::kByte);
-  const c10::StreamGuard on(s == nullptr ? c10::hip::getDefaultHIPStream(device.index()).unwrap()
-                                         : c10::hip::getStreamFromExternal(static_cast<hipStream_t>(s), device.index()).unwrap());
-  return fresh(device, 1, bytes, at::kByte);
-}
+// Bytes that go to later work of this stream only, and back to it when the call has been issued.  Taken from the allocator without a
+// tensor around them.
+struct Scratch {
+  void* ptr;
+  Scratch(void* s, at::Device device, size_t bytes) {
+    const c10::DeviceIndex current = c10::hip::current_device();
+    c10::OptionalDeviceGuard on;
+    if (device.index() != current && s != c10::hip::getCurrentHIPStream(current).stream()) on.reset_device(device);
+    ptr = c10::hip::HIPCachingAllocator::raw_alloc_with_stream(bytes, static_cast<hipStream_t>(s));
+  }
+  Scratch(const Scratch&) = delete;
+  ~Scratch() { c10::hip::HIPCachingAllocator::raw_delete(ptr); }
+};
 
 // Whether memory allocated now, on the current device, goes to later work of this stream only.
 bool on_current_stream(void* s, at::Device* here) {
@@ -445,9 +451,8 @@ PyObject* backward_input(PyObject*, PyObject* const* a, Py_ssize_t n) {
   const int32_t st = unlocked([&] {
     y.make(device);
     if (scratch_bytes != 0) {
-      const at::Tensor scratch = fresh_on(s, device, (int64_t)scratch_bytes);
-      return lib.backward_input_scratch(wp, w.rows, w.cols, w.ld, dyp, dy.rows, dy.ld, y.ptr, y.ld, y.code, scratch.data_ptr(),
-                                        scratch_bytes, s);
+      const Scratch scratch(s, device, scratch_bytes);
+      return lib.backward_input_scratch(wp, w.rows, w.cols, w.ld, dyp, dy.rows, dy.ld, y.ptr, y.ld, y.code, scratch.ptr, scratch_bytes, s);
     }
     return lib.backward_input(wp, w.rows, w.cols, w.ld, dyp, dy.rows, dy.ld, y.ptr, y.ld, y.code, ws.ptr, ws.bytes, s);
   });
