@@ -309,38 +309,45 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
 
   if constexpr (TOKS == 64) {
     // Two register sets and two LDS buffers.  A buffer is written again two spans later: between the two lies a barrier
-    // that every wave reaches only after it has multiplied the first.
+    // that every wave reaches only after it has multiplied the first.  A single span goes by itself: the loads of a second one,
+    // unused, took 0.2 to 0.4 us.
     Loads even, odd;
     fetch(even, 0);
-    fetch(odd, spans > 1 ? 1 : 0);
-    int span = 0;
-    for (; span + 3 < spans; span += 2) {
+    if (spans == 1) {
+      put(even, 0, smem);
+      __syncthreads();
+      multiply(smem, 0);
+    } else {
+      fetch(odd, 1);
+      int span = 0;
+      for (; span + 3 < spans; span += 2) {
+        put(even, span, smem);
+        fetch(even, span + 2);
+        __syncthreads();
+        multiply(smem, span);
+        put(odd, span + 1, smem + C::SPAN);
+        fetch(odd, span + 3);
+        __syncthreads();
+        multiply(smem + C::SPAN, span + 1);
+      }
+      if (span + 2 < spans) {  // three are left
+        put(even, span, smem);
+        fetch(even, span + 2);
+        __syncthreads();
+        multiply(smem, span);
+        put(odd, span + 1, smem + C::SPAN);
+        __syncthreads();
+        multiply(smem + C::SPAN, span + 1);
+        span += 2;
+      }
       put(even, span, smem);
-      fetch(even, span + 2);
       __syncthreads();
       multiply(smem, span);
-      put(odd, span + 1, smem + C::SPAN);
-      fetch(odd, span + 3);
-      __syncthreads();
-      multiply(smem + C::SPAN, span + 1);
-    }
-    if (span + 2 < spans) {  // three are left
-      put(even, span, smem);
-      fetch(even, span + 2);
-      __syncthreads();
-      multiply(smem, span);
-      put(odd, span + 1, smem + C::SPAN);
-      __syncthreads();
-      multiply(smem + C::SPAN, span + 1);
-      span += 2;
-    }
-    put(even, span, smem);
-    __syncthreads();
-    multiply(smem, span);
-    if (span + 1 < spans) {
-      put(odd, span + 1, smem + C::SPAN);
-      __syncthreads();
-      multiply(smem + C::SPAN, span + 1);
+      if (span + 1 < spans) {
+        put(odd, span + 1, smem + C::SPAN);
+        __syncthreads();
+        multiply(smem + C::SPAN, span + 1);
+      }
     }
   } else {
     // Four spans at a time, all their loads in flight together and one barrier for them.
@@ -436,10 +443,6 @@ struct WideCfg {
   static constexpr int64_t field_word(int span, int begin, int chunk, bool in) {
     return in ? ((int64_t)span * SPAN_BITS >> 5) + ((begin + chunk * BITS) >> 5) : 0;
   }
-  // What the second register set holds first: span 1, or span 0 again, not used, where there is no other.  Its fields have to be
-  // asked for where that span has them: with an odd span's place the last row of a single span would be read past its end.
-  static constexpr int second_span(int spans) { return spans > 1 ? 1 : 0; }
-  static constexpr int second_begin(int spans) { return spans > 1 ? ODD_BITS : 0; }
   static_assert(NT == ROWS * STEPS * 4 && NW * wave_tile_slice_bytes<OT, 4>() <= LDS_BYTES && LDS_BYTES <= 160 * 1024, "LDS budget");
 };
 
@@ -636,35 +639,41 @@ __global__ void __launch_bounds__(512) nm_direct_wide_kernel(const DirectArgs a)
   constexpr int p0 = 0, p1 = C::ODD_BITS;
   Loads even, odd;
   fetch(even, 0, p0);
-  fetch(odd, C::second_span(spans), C::second_begin(spans));
-  int span = 0;
-  for (; span + 3 < spans; span += 2) {  // two whole spans: no conditions, so that a span's decoding and the products interleave
-    put(even, span, smem, p0, std::true_type{});
-    fetch(even, span + 2, p0);
+  if (spans == 1) {
+    put(even, 0, smem, p0, std::false_type{});
     __syncthreads();
-    multiply(smem, C::STEPS);
-    put(odd, span + 1, smem + C::SPAN, p1, std::true_type{});
-    fetch(odd, span + 3, p1);
+    multiply(smem, nk);
+  } else {
+    fetch(odd, 1, p1);
+    int span = 0;
+    for (; span + 3 < spans; span += 2) {  // two whole spans: no conditions, so that a span's decoding and the products interleave
+      put(even, span, smem, p0, std::true_type{});
+      fetch(even, span + 2, p0);
+      __syncthreads();
+      multiply(smem, C::STEPS);
+      put(odd, span + 1, smem + C::SPAN, p1, std::true_type{});
+      fetch(odd, span + 3, p1);
+      __syncthreads();
+      multiply(smem + C::SPAN, C::STEPS);
+    }
+    if (span + 2 < spans) {  // three are left, two of them whole
+      put(even, span, smem, p0, std::true_type{});
+      fetch(even, span + 2, p0);
+      __syncthreads();
+      multiply(smem, C::STEPS);
+      put(odd, span + 1, smem + C::SPAN, p1, std::true_type{});
+      __syncthreads();
+      multiply(smem + C::SPAN, C::STEPS);
+      span += 2;
+    }
+    put(even, span, smem, p0, std::false_type{});
     __syncthreads();
-    multiply(smem + C::SPAN, C::STEPS);
-  }
-  if (span + 2 < spans) {  // three are left, two of them whole
-    put(even, span, smem, p0, std::true_type{});
-    fetch(even, span + 2, p0);
-    __syncthreads();
-    multiply(smem, C::STEPS);
-    put(odd, span + 1, smem + C::SPAN, p1, std::true_type{});
-    __syncthreads();
-    multiply(smem + C::SPAN, C::STEPS);
-    span += 2;
-  }
-  put(even, span, smem, p0, std::false_type{});
-  __syncthreads();
-  multiply(smem, nk - span * C::STEPS);
-  if (span + 1 < spans) {
-    put(odd, span + 1, smem + C::SPAN, p1, std::false_type{});
-    __syncthreads();
-    multiply(smem + C::SPAN, nk - (span + 1) * C::STEPS);
+    multiply(smem, nk - span * C::STEPS);
+    if (span + 1 < spans) {
+      put(odd, span + 1, smem + C::SPAN, p1, std::false_type{});
+      __syncthreads();
+      multiply(smem + C::SPAN, nk - (span + 1) * C::STEPS);
+    }
   }
 
   const int64_t row0 = t0 + wt * C::TT * 16, col0 = o_wave;
@@ -787,7 +796,6 @@ static int64_t index_words_reached(bool wide, int64_t K) {
         load(C::field_word(span, begin, chunk, chunk * 16 < (int)K - span * 128), C::WORDS == 2);
     };
     for (int span = 0; span < spans; ++span) fetch(span, span % 2 ? C::ODD_BITS : 0);
-    fetch(C::second_span(spans), C::second_begin(spans));
   } else {
     using C = DirectCfg<N, M, 64, 32>;
     for (int span = 0; span < (nk + kSteps - 1) / kSteps; ++span)
