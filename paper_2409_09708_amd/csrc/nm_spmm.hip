@@ -270,12 +270,12 @@ __device__ __forceinline__ f32x4_t bias_init(const float* bias, int64_t o, int64
 // STREAM: the weight lies in stream order (the pre-pass's output: every 16-row x K-step slice one contiguous,
 // already swizzled kilobyte; selector words interleaved per 32-row pair), else row-major (the packed 2:4 layout
 // or a dense level's values, read as they lie).
-// X_REGS: the operands travel through registers instead of by asynchronous copies, so that rows of X may start anywhere and K
-// may end anywhere (see the loop); two stages.
+// X_REGS: not 0: the operands travel through registers instead of by asynchronous copies, so that rows of X may start anywhere and K
+// may end anywhere, loaded that many stages ahead (2 or 4; see the loop); two stages of LDS.
 // TAIL: K, a multiple of 8, may end inside the last step (rows of X still start on 16 bytes).  The pieces of that step past K are fetched
 // from its first piece instead (what lies behind a row's end may be no memory at all) and cleared in LDS by the lanes
 // that brought them, so they never enter a sum.
-template <bool SPARSE, int WO, int WT, int OT, int TT, int STAGES, bool STREAM, bool X_REGS = false, bool TAIL = false>
+template <bool SPARSE, int WO, int WT, int OT, int TT, int STAGES, bool STREAM, int X_REGS = 0, bool TAIL = false>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned block, unsigned char* smem) {
   using C = GemmCfg<SPARSE, WO, WT, OT, TT, STAGES>;
   static_assert(!STREAM || (OT % 2 == 0 && C::BO % 32 == 0 && 256 % C::BO == 0), "stream order: whole 32-row pairs inside one 256-row tile");
@@ -497,17 +497,19 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned block, uns
     else wait_loads_outstanding<0>();
   };
 
-  if constexpr (X_REGS) {
+  if constexpr (X_REGS != 0) {
     // Rows of X that start anywhere, and a K that ends anywhere.  Every operand travels through registers: plain loads, which
-    // need no alignment, DEPTH stages ahead, and written to LDS where the asynchronous copies of the other form put them.  The loads carry no
+    // need no alignment, X_REGS stages ahead, and written to LDS where the asynchronous copies of the other form put them.  The loads carry no
     // condition, so that the wait before a stage's write leaves the younger ones in flight: past K a piece is the row's last
     // eight elements, shifted and cleared on its way to LDS (so is the weight there: what lies behind a row's end never enters a sum);
     // past the last stage it is that one again.  Bound by the latency of a stage's loads where a unit has one block: with one stage in
-    // flight and its wait in the same step, a step took 0.6 - 0.9 us, now 0.25.  us, before and now: 926 x 2740 -> 96 at 1:4 28.2 and
-    // 13.4, 518 x 2164 -> 528 at 4:4 25.0 and 13.3, 4345 x 3468 -> 128 at 1:4 61.5 and 17.7, 8000 x 516 -> 2052 at 4:4 69.1 and 45.1,
-    // 3000 x 1028 -> 1400 at 3:4 34.0 and 24.7, 969 x 244 -> 3040 at 4:4 8.6 and 7.6.
-    static_assert(!X_REGS || (STAGES == 2 && STREAM), "register-staged form");
-    constexpr int DEPTH = C::LPW <= 4 ? 4 : 2;
+    // flight and its wait in the same step, a step took 0.6 - 0.9 us, now 0.25.  Where units have several, the registers of further stages
+    // cost blocks: two stages, and four only for long reductions of the dense form on few tiles (518 x 2164 -> 528 at 4:4 12.5 us, 13.0 with
+    // two; 10403 x 100 -> 279 at 4:4 in the small tiles 9.3 with four, 7.3 with two).  Products, us, one stage in flight and now: 926 x 2740
+    // -> 96 at 1:4 27.5 and 12.3, 518 x 2164 -> 528 24.3 and 12.5, 4345 x 3468 -> 128 at 1:4 61.0 and 15.6, 8000 x 516 -> 2052 at 4:4
+    // 69.5 and 40.3, 3000 x 1028 -> 1400 at 3:4 31.0 and 21.6, 969 x 244 -> 3040 at 4:4 7.6 and 6.8, 35674 x 84 -> 2697 at 2:4 82.6 and 88.0.
+    static_assert(STAGES == 2 && STREAM && X_REGS % 2 == 0, "register-staged form");
+    constexpr int DEPTH = X_REGS;
     u32x4_t xr[DEPTH][C::X_PW], ar[DEPTH][C::A_PW];
     uint32_t sr[DEPTH][C::S_PW > 0 ? C::S_PW : 1];
     struct __attribute__((packed, aligned(2))) Piece { u32x4_t v; };
@@ -686,7 +688,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, unsigned block, uns
     write_wave_tile_rows<OT, TT, 4>(smem + wave * wave_tile_slice_bytes<OT, 4>(), lane, get, out_ptr, out_ld, row0, col0, a.T, a.O);
   }
 
-  if constexpr (X_REGS || TAIL) {
+  if constexpr (X_REGS != 0 || TAIL) {
     // The shapes of the ragged form are the gather kernel's when there is no workspace, and an infinity or NaN among the
     // activations must not change a product by the way it was computed: a zero of the padded weight makes NaN of it
     // where the gather skips it.  Sums that ended as NaN are computed again by the definition.  The test is one
@@ -731,11 +733,11 @@ nm_gemm_kernel(const GemmArgs a) {
 
 // Any K, any alignment of X and Y: the weight in stream order (K padded with zeros to whole steps), X by asynchronous
 // copies where its rows are whole 16-byte pieces, else through registers.
-template <bool SPARSE, int WO, int WT, int OT, int TT, int STAGES, bool X_REGS>
+template <bool SPARSE, int WO, int WT, int OT, int TT, int STAGES, int X_REGS>
 __global__ void __launch_bounds__(WO * WT * 64)
 nm_gemm_ragged_kernel(const GemmArgs a) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  gemm_tile<SPARSE, WO, WT, OT, TT, STAGES, true, X_REGS, !X_REGS>(a, blockIdx.x, smem);
+  gemm_tile<SPARSE, WO, WT, OT, TT, STAGES, true, X_REGS, X_REGS == 0>(a, blockIdx.x, smem);
 }
 
 // The tiles of many small layers in one launch, whatever their operand form and weight order: products of a few
@@ -2097,13 +2099,40 @@ static hipError_t dispatch_gemm(const GemmArgs& g, int pick, hipStream_t s) {
   }
 }
 
+// Tiles of the ragged form where X travels through registers: 64 x 64, or, from 150 of them on, 128 x 128 where those are estimated
+// faster.  The blocks of a unit's list run `at_once` of them together; `share` is what the units' number of blocks adds beyond whole lists.
+// Fitted on 24800 shapes (60 to 40000 tokens, 72 .. 4096 deep and wide); the choice takes 1.002 of the better tile's time on average, 1.7 %
+// of the shapes lose more than 5 %.  (Two thresholds on the tiles, 208 and 336, took 1.042.)  64 and 128, us: 7410 x 84 -> 1317 at 2:4 in
+// bfloat16 13.5 and 17.8, 18048 x 476 -> 159 at 3:4 in float32 12.1 and 17.2; 9906 x 1932 -> 648 at 1:4 41.6 and 31.8, 35674 x 84 -> 2697 at
+// 2:4 in float32 122 and 94.
+struct RaggedModel {
+  double start, step, epi[2], busy, byte, share;  // epi: [bfloat16]; byte: a MB of output
+  int at_once;
+};
+constexpr RaggedModel kRaggedModel[2][2] = {  // [2:4 form][128 x 128]
+    {{4.25, 0.284, {0.325, 0.499}, 0.639, 0.065, 0, 4}, {5.14, 0.628, {0.96, 2.61}, 0.556, 0.112, 0.083, 2}},
+    {{4.22, 0.244, {0.52, 0.685}, 0.541, 0.045, 0, 4}, {4.72, 0.477, {1.41, 2.98}, 0.504, 0.082, 0.065, 2}}};
+static double ragged_estimate(bool sparse_form, bool large, int64_t O, int64_t K, int64_t T, bool out_bf16) {
+  const RaggedModel& m = kRaggedModel[sparse_form][large];
+  const int64_t side = large ? 128 : 64, tiles = ((O + side - 1) / side) * ((T + side - 1) / side);
+  const int64_t list = ((tiles + 7) / 8 + 31) / 32, rest = list % m.at_once;  // blocks of a unit; of those, past the last full set
+  const double steps = (double)((K + 63) / 64);
+  return m.start + (steps * m.step + m.epi[out_bf16]) * ((double)(list / m.at_once) * (1.0 + m.busy * (m.at_once - 1)) +
+                                                         (rest ? 1.0 + m.busy * (double)(rest - 1) : 0.0)) +
+         m.byte * 1e-6 * (double)O * (double)T * (out_bf16 ? 2.0 : 4.0) + m.share * steps * (double)tiles / kModelUnits;
+}
+static int ragged_tile(bool sparse_form, int64_t O, int64_t K, int64_t T, bool out_bf16) {
+  if (((O + 127) / 128) * ((T + 127) / 128) < 150) return 64;
+  return ragged_estimate(sparse_form, true, O, K, T, out_bf16) < ragged_estimate(sparse_form, false, O, K, T, out_bf16) ? 128 : 64;
+}
+// Not in the public header, for tests.
+extern "C" int32_t nm_internal_ragged_tile(int32_t sparse_form, int64_t O, int64_t K, int64_t T, int32_t out_bf16) {
+  return ragged_tile(sparse_form != 0, O, K, T, out_bf16 != 0);
+}
+
 // The ragged form of the tiled kernel.  K and the rows of X in whole 16-byte pieces: the
 // tile of the aligned form.  A product of 1579 x 1000 -> 1001 at 2:8 takes 8.1 us that way and 10.7 through registers.
-// Other rows: tiles of 128 x 128 or of 64 x 64, a quarter of the work for half the loads.  The large ones take over past 1.3 of them
-// to a unit, and where the steps are eight and more, which is where the loads count, from 208 on, most of which run at once.  64 and
-// 128 (us): 1096 x 196 -> 1572 6.4 and 7.6, 9314 x 276 -> 318 9.7 and 12.4, 18298 x 196 -> 156 (286 tiles of 128) 10.9 and 13.8;
-// 9460 x 1764 -> 324 (222) 34.2 and 26.3, 9545 x 548 -> 354 (225) 14.5 and 12.5, 11269 x 1132 -> 437 (356) 31.6 and 29.6,
-// 29106 x 148 -> 584 25.0 and 18.0.  (The gather kernel, which still takes such shapes when there is no workspace: 1096 us.)
+// Other rows: ragged_tile's choice.  (The gather kernel, which still takes such shapes when there is no workspace: 1096 us.)
 template <bool SPARSE>
 static hipError_t launch_ragged(GemmArgs g, hipStream_t s) {
   auto go = [&](auto kern, auto cfg, PerDeviceOnce& once) {
@@ -2117,18 +2146,20 @@ static hipError_t launch_ragged(GemmArgs g, hipStream_t s) {
     return hipGetLastError();
   };
   const int64_t tiles_mid = ((g.O + 127) / 128) * ((g.T + 127) / 128);
-  static PerDeviceOnce once[6];
+  static PerDeviceOnce once[7];
   if (g.x_aligned && g.K % 8 == 0 && g.ldx <= (1 << 22)) {  // (per-lane byte offsets inside a tile stay below 2^32)
     switch (tile_kind(g.O, padded_k(g.K), g.T, SPARSE, tiles_mid < 64 ? 3 : 2)) {
-      case TILE_64: return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 2, 2, 3, false>, GemmCfg<SPARSE, 2, 2, 2, 2, 3>{}, once[0]);
-      case TILE_128_64: return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 4, 2, 3, false>, GemmCfg<SPARSE, 2, 2, 4, 2, 3>{}, once[1]);
-      case TILE_128_TWO: return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 4, 4, 2, false>, GemmCfg<SPARSE, 2, 2, 4, 4, 2>{}, once[2]);
-      default: return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 4, 4, 3, false>, GemmCfg<SPARSE, 2, 2, 4, 4, 3>{}, once[3]);
+      case TILE_64: return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 2, 2, 3, 0>, GemmCfg<SPARSE, 2, 2, 2, 2, 3>{}, once[0]);
+      case TILE_128_64: return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 4, 2, 3, 0>, GemmCfg<SPARSE, 2, 2, 4, 2, 3>{}, once[1]);
+      case TILE_128_TWO: return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 4, 4, 2, 0>, GemmCfg<SPARSE, 2, 2, 4, 4, 2>{}, once[2]);
+      default: return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 4, 4, 3, 0>, GemmCfg<SPARSE, 2, 2, 4, 4, 3>{}, once[3]);
     }
   }
-  if (tiles_mid >= 336 || (tiles_mid >= 208 && g.K >= 512))
-    return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 4, 4, 2, true>, GemmCfg<SPARSE, 2, 2, 4, 4, 2>{}, once[4]);
-  return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 2, 2, 2, true>, GemmCfg<SPARSE, 2, 2, 2, 2, 2>{}, once[5]);
+  if (ragged_tile(SPARSE, g.O, g.K, g.T, g.out_bf16 != 0) == 128)
+    return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 4, 4, 2, 2>, GemmCfg<SPARSE, 2, 2, 4, 4, 2>{}, once[4]);
+  if constexpr (!SPARSE)
+    if (tiles_mid < 64 && g.K >= 1280) return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 2, 2, 2, 4>, GemmCfg<SPARSE, 2, 2, 2, 2, 2>{}, once[6]);
+  return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 2, 2, 2, 2>, GemmCfg<SPARSE, 2, 2, 2, 2, 2>{}, once[5]);
 }
 
 static hipError_t launch_general(const SpmmArgs& a, hipStream_t s) {
