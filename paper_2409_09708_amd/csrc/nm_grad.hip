@@ -867,6 +867,12 @@ size_t backward_input_scratch_bytes(int64_t O, int64_t K, int64_t T) {
   return dense_transposed_workspace_bytes(O, K, T, &required);
 }
 
+// Not in the public header, for tests: whether dX of aligned operands multiplies a transposed copy where its scratch is brought.
+extern "C" int32_t nm_internal_backward_input_copies(int64_t O, int64_t K, int64_t T, int32_t out_bf16) {
+  bool required = false;
+  return dense_transposed_workspace_bytes(O, K, T, &required) != 0 && (required || dense_transposed_pays(O, K, T, out_bf16 != 0));
+}
+
 hipError_t launch_backward_input(const bf16_t* Ws, int64_t O, int64_t K, int64_t ldw, const bf16_t* dY, int64_t T,
                                  int64_t ldy, void* dX, int64_t ldx, int out_bf16, void* workspace,
                                  size_t workspace_bytes, hipStream_t s, bool optional, bool* workspace_short) {
@@ -882,14 +888,14 @@ hipError_t launch_backward_input(const bf16_t* Ws, int64_t O, int64_t K, int64_t
     *workspace_short = true;
     return hipSuccess;
   }
-  if (need && there && (required || optional)) {
+  const bool tiles = (O % 32 == 0) && (K % 8 == 0) && (ldw % 8 == 0) && (ldy % 8 == 0) && aligned_to(Ws, 16) &&
+                     aligned_to(dY, 16) && K <= (1 << 24) && T <= (1ll << 31) && ldw <= (1 << 22) && ldy <= (1 << 22);
+  if (need && there && (required || (optional && (!tiles || dense_transposed_pays(O, K, T, out_bf16))))) {
     bool taken = false;
     hipError_t e = launch_dense_transposed(Ws, O, K, ldw, dY, T, ldy, dX, ldx, out_bf16, workspace, workspace_bytes, s,
                                            &taken);
     if (e != hipSuccess || taken) return e;
   }
-  const bool tiles = (O % 32 == 0) && (K % 8 == 0) && (ldw % 8 == 0) && (ldy % 8 == 0) && aligned_to(Ws, 16) &&
-                     aligned_to(dY, 16) && K <= (1 << 24) && T <= (1ll << 31) && ldw <= (1 << 22) && ldy <= (1 << 22);
   if (!tiles) {
     if (T * K > 0x7FFFFFFFll * 256) return hipErrorInvalidValue;
     hipLaunchKernelGGL(backward_input_general_kernel, dim3((unsigned)((T * K + 255) / 256)), dim3(256), 0, s, Ws, O, K, ldw,

@@ -162,6 +162,7 @@ hipError_t launch_direct(const SpmmArgs& a, bool packed_order, bool wide, bool a
 // order in the workspace first; *required: the persistent one's layers); *taken stays false, and nothing is launched, when the shape, the alignment or
 // the workspace do not allow it.
 size_t dense_transposed_workspace_bytes(int64_t R, int64_t I, int64_t T, bool* required);
+bool dense_transposed_pays(int64_t R, int64_t I, int64_t T, int out_bf16);  // of layers that do not require it, against nm_grad.hip's kernel
 hipError_t launch_dense_transposed(const bf16_t* Ws, int64_t R, int64_t I, int64_t ldw, const bf16_t* Q, int64_t T,
                                    int64_t ldq, void* Out, int64_t ldo, int out_bf16, void* workspace,
                                    size_t workspace_bytes, hipStream_t s, bool* taken);

@@ -2200,6 +2200,22 @@ static bool dense_transposed_tiles(int64_t R, int64_t I, int64_t T) {
   constexpr TileModel kGrad = {256, 128, 2.92, 0.638, 1.56, 0.81};  // (a step of 64; its 256-wide side runs along the tokens)
   return tiles + 2.74 + 0.615 * weight_mb < (I >= 4 * R ? 0.8 : 0.95) * tile_estimate(kGrad, T, R, I);
 }
+
+// Of these, with the output type known: what the one kernel writes in bfloat16 takes it up to a sixth less, and many tokens cost the two
+// launches their way through memory as well, which the estimates above do not see.  Fitted on 10400 shapes that they chose (rms 3 and
+// 2 % for the one kernel, 8 % for the two).  On the estimates above alone 62 (float32) and 98 (bfloat16) of them lost more than 3 % against
+// the one kernel, up to 25; now 8 and 25.  One kernel and two launches, us: 1576 x 768 -> 2048 in bfloat16 13.9 and 15.7, 7205 x 576
+// -> 1600 20.6 and 25.1, 13056 x 1792 -> 640 in float32 33.4 and 41.8; 1576 x 4096 -> 1024 in bfloat16 51.4 and 26.7.
+bool dense_transposed_pays(int64_t R, int64_t I, int64_t T, int out_bf16) {
+  const double weight_mb = (double)((I + 255) / 256 * 256) * (double)R * 2e-6;
+  double tiles = 1e30;
+  for (const TileModel& m : kTileModel[0])
+    if (const double e = tile_estimate(m, I, R, T); e < tiles) tiles = e;
+  const double two = 3.62 + 0.487 * weight_mb + 0.89 * tiles + 0.047e-6 * (double)T * (double)R +
+                     (out_bf16 ? 0.855e-6 : 1.585e-6) * (double)T * (double)I;
+  constexpr TileModel kGrad[2] = {{256, 128, 5.34, 0.656, 0, 0.276}, {256, 128, 4.65, 0.654, 0, 0.316}};  // [bfloat16]
+  return two < tile_estimate(kGrad[out_bf16], T, R, I) + (out_bf16 ? 0.388e-6 : 1.13e-6) * (double)T * (double)I;
+}
 // *required: the layer is the persistent kernel's, and a call without the workspace is refused.
 size_t dense_transposed_workspace_bytes(int64_t R, int64_t I, int64_t T, bool* required) {
   *required = dense_transposed_takes(R, I, T);
