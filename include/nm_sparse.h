@@ -356,6 +356,10 @@ int32_t nm_linear_forward_prepared_batched_scratch(const nm_forward_desc* descs,
  *                 the same, for a caller that brings nm_backward_input_scratch_bytes(O, K, T) bytes: small layers
  *                 whose product pays for the transposed copy take it too.  With less they run as
  *                 nm_linear_backward_input does (the same sums).  Concurrent calls need distinct workspaces.
+ *   nm_backward_input_scratch_pays
+ *                 whether that scratch is worth bringing to a call on the stream: 0 where the call would leave it alone, and where the
+ *                 one launch without it takes the device less time than two launches take the host (which counts unless the stream
+ *                 is being captured); else 1.
  *   nm_linear_backward_weight   dW[o, k] = m[o, k] * sum_t dY[t, o] * X[t, k], fp32 accumulation.
  *       dY   in   [T, O], ld ldy            X    in   [T, K], ld ldx
  *       mask in   mask words of the step as nm_prune writes them ([O, ceil(K/32)]); pruned positions receive
@@ -380,6 +384,7 @@ int32_t nm_linear_backward_input(const nm_bf16* Ws, int64_t O, int64_t K, int64_
                                  int64_t T, int64_t ldy, void* dX, int64_t ldx, int32_t out_dtype,
                                  void* workspace, size_t workspace_bytes, void* stream);
 size_t nm_backward_input_scratch_bytes(int64_t O, int64_t K, int64_t T);
+int32_t nm_backward_input_scratch_pays(int64_t O, int64_t K, int64_t T, int32_t out_dtype, void* stream);
 int32_t nm_linear_backward_input_scratch(const nm_bf16* Ws, int64_t O, int64_t K, int64_t ldw, const nm_bf16* dY,
                                          int64_t T, int64_t ldy, void* dX, int64_t ldx, int32_t out_dtype,
                                          void* workspace, size_t workspace_bytes, void* stream);

@@ -33,7 +33,7 @@ EXPORTS = (
     "nm_linear_forward_i8_packed_prepared",
     "nm_rank_bytes", "nm_rank", "nm_rank_batched", "nm_rank_mask", "nm_pack_ranked", "nm_pack_ranked_batched", "nm_pack_prepare_batched",
     "nm_config_cost", "nm_sample_config",
-    "nm_backward_input_workspace_bytes", "nm_backward_weight_workspace_bytes", "nm_linear_backward_input", "nm_backward_input_scratch_bytes", "nm_linear_backward_input_scratch", "nm_linear_backward_weight",
+    "nm_backward_input_workspace_bytes", "nm_backward_weight_workspace_bytes", "nm_linear_backward_input", "nm_backward_input_scratch_bytes", "nm_backward_input_scratch_pays", "nm_linear_backward_input_scratch", "nm_linear_backward_weight",
     "nm_backward_weight_scratch_bytes", "nm_linear_backward_weight_scratch",
     "nm_linear_forward_prepared_batched", "nm_prepared_scratch_bytes", "nm_linear_forward_prepared_scratch",
     "nm_prepared_batched_scratch_bytes", "nm_linear_forward_prepared_batched_scratch", "nm_prune_scored", "nm_i8_workspace_bytes", "nm_linear_forward_i8", "nm_i8_prepare", "nm_linear_forward_i8_prepared",
@@ -178,6 +178,8 @@ def load_library() -> ctypes.CDLL:
     lib.nm_linear_backward_input.restype = c_int32
     lib.nm_backward_input_scratch_bytes.restype = c_size_t
     lib.nm_backward_input_scratch_bytes.argtypes = [c_int64, c_int64, c_int64]
+    lib.nm_backward_input_scratch_pays.restype = c_int32
+    lib.nm_backward_input_scratch_pays.argtypes = [c_int64, c_int64, c_int64, c_int32, c_void_p]
     lib.nm_backward_input_workspace_bytes.restype = c_size_t
     lib.nm_backward_input_workspace_bytes.argtypes = [c_int64, c_int64, c_int64]
     lib.nm_linear_backward_input.argtypes = [c_void_p, c_int64, c_int64, c_int64, c_void_p, c_int64, c_int64, c_void_p,

@@ -405,6 +405,11 @@ size_t nm_backward_input_scratch_bytes(int64_t O, int64_t K, int64_t T) {
   return nm::backward_input_scratch_bytes(O, K, T);
 }
 
+int32_t nm_backward_input_scratch_pays(int64_t O, int64_t K, int64_t T, int32_t out_dtype, void* stream) {
+  if (O <= 0 || K <= 0 || T <= 0) return 0;
+  return nm::backward_input_scratch_pays(O, K, T, out_dtype == NM_OUT_BF16, (hipStream_t)stream);
+}
+
 int32_t nm_linear_backward_input_scratch(const nm_bf16* Ws, int64_t O, int64_t K, int64_t ldw, const nm_bf16* dY, int64_t T,
                                          int64_t ldy, void* dX, int64_t ldx, int32_t out_dtype, void* workspace,
                                          size_t workspace_bytes, void* stream) {

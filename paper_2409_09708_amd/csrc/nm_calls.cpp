@@ -51,6 +51,7 @@ struct Library {
   decltype(&nm_linear_backward_input_scratch) backward_input_scratch;
   decltype(&nm_backward_input_workspace_bytes) backward_input_bytes;
   decltype(&nm_backward_input_scratch_bytes) backward_input_scratch_bytes;
+  decltype(&nm_backward_input_scratch_pays) backward_input_scratch_pays;
   decltype(&nm_linear_backward_weight_scratch) backward_weight_scratch;
   decltype(&nm_backward_weight_scratch_bytes) backward_weight_scratch_bytes;
   decltype(&nm_linear_forward_i8) i8;
@@ -436,7 +437,7 @@ PyObject* backward_input(PyObject*, PyObject* const* a, Py_ssize_t n) {
   Output y;
   void* s;
   if (n != 6 || lib.backward_input == nullptr || lib.backward_input_scratch == nullptr || lib.backward_input_bytes == nullptr ||
-      lib.backward_input_scratch_bytes == nullptr || observed() || !plain(a[0], at::kBFloat16, &W) ||
+      lib.backward_input_scratch_bytes == nullptr || lib.backward_input_scratch_pays == nullptr || observed() || !plain(a[0], at::kBFloat16, &W) ||
       !matrix(*W, &w) || !plain(a[1], at::kBFloat16, &dY) || !matrix(*dY, &dy) || dy.cols != w.rows ||
       !y.read(a[2], a[3], dy.rows, w.cols, false) || !stream_of(a[5], &s))
     return declined();
@@ -445,7 +446,8 @@ PyObject* backward_input(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (const Take t = need != 0 ? scratch_workspace(need, a[1], a[5], s, &ws) : given_workspace(a[4], &ws); t != TAKEN)
     return t == DECLINED ? declined() : nullptr;
   // what a small layer can use: scratch of the call, as the partial sums above.  (A given workspace is left alone that is not required.)
-  const size_t scratch_bytes = need == 0 && a[4] == Py_None ? lib.backward_input_scratch_bytes(w.rows, w.cols, dy.rows) : 0;
+  const size_t scratch_bytes = need == 0 && a[4] == Py_None && lib.backward_input_scratch_pays(w.rows, w.cols, dy.rows, y.code, s)
+                                   ? lib.backward_input_scratch_bytes(w.rows, w.cols, dy.rows) : 0;
   const uint16_t *wp = pointer<uint16_t>(W), *dyp = pointer<uint16_t>(dY);
   const at::Device device = dY->device();
   const int32_t st = unlocked([&] {
@@ -558,6 +560,7 @@ PyObject* bind(PyObject*, PyObject* args) {
       {"nm_linear_backward_input_scratch", &l.backward_input_scratch, true},
       {"nm_backward_input_workspace_bytes", &l.backward_input_bytes, true},
       {"nm_backward_input_scratch_bytes", &l.backward_input_scratch_bytes, true},
+      {"nm_backward_input_scratch_pays", &l.backward_input_scratch_pays, true},
       {"nm_linear_backward_weight_scratch", &l.backward_weight_scratch, true},
       {"nm_backward_weight_scratch_bytes", &l.backward_weight_scratch_bytes, true}, {"nm_linear_forward_i8", &l.i8, true},
       {"nm_linear_forward_i8_prepared", &l.i8_prepared, true}, {"nm_linear_forward_i8_packed", &l.i8_packed, true},

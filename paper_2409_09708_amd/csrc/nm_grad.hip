@@ -867,6 +867,25 @@ size_t backward_input_scratch_bytes(int64_t O, int64_t K, int64_t T) {
   return dense_transposed_workspace_bytes(O, K, T, &required);
 }
 
+// A call that is launched by itself takes the host 7.4 to 8.0 us with the two launches and the scratch (5.9 without the scratch on the
+// fastest host seen).  A reduction of up to 256 on one round of blocks takes the one kernel less: us a call, one and two, 4 x 256 -> 256
+// in float32 7.0 and 7.9, in bfloat16 6.5 and 7.9, 1576 x 256 -> 256 in bfloat16 7.3 and 7.5 (in float32 8.6 and 7.5, which copies);
+// at 320 4 tokens in float32 take 7.8 and 7.6.  In a graph only the device counts: 4 x 256 -> 256 7.0 and 5.3.
+bool backward_input_scratch_pays(int64_t O, int64_t K, int64_t T, int out_bf16, hipStream_t s) {
+  bool required = false;
+  if (dense_transposed_workspace_bytes(O, K, T, &required) == 0) return false;
+  if (required) return true;
+  if (!dense_transposed_pays(O, K, T, out_bf16)) return false;
+  const int64_t tiles = ((K + TCfg::BI - 1) / TCfg::BI) * ((T + TCfg::BJ - 1) / TCfg::BJ);
+  if (O > 256 || tiles > 256 || !(out_bf16 || T <= 64)) return true;
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (s != nullptr && hipStreamIsCapturing(s, &status) != hipSuccess) {
+    (void)hipGetLastError();  // (a later launch does not report it)
+    status = hipStreamCaptureStatusNone;
+  }
+  return status == hipStreamCaptureStatusActive;
+}
+
 // Not in the public header, for tests: whether dX of aligned operands multiplies a transposed copy where its scratch is brought.
 extern "C" int32_t nm_internal_backward_input_copies(int64_t O, int64_t K, int64_t T, int32_t out_bf16) {
   bool required = false;

@@ -170,6 +170,7 @@ hipError_t launch_dense_transposed(const bf16_t* Ws, int64_t R, int64_t I, int64
 // nm_grad.hip: training products of a layer.  Ws is the masked dense weight [O, K].
 size_t backward_input_workspace_bytes(int64_t O, int64_t K, int64_t T);  // the part that is required
 size_t backward_input_scratch_bytes(int64_t O, int64_t K, int64_t T);    // with what small layers can use
+bool backward_input_scratch_pays(int64_t O, int64_t K, int64_t T, int out_bf16, hipStream_t s);
 hipError_t launch_backward_input(const bf16_t* Ws, int64_t O, int64_t K, int64_t ldw, const bf16_t* dY, int64_t T,
                                  int64_t ldy, void* dX, int64_t ldx, int out_bf16, void* workspace,
                                  size_t workspace_bytes, hipStream_t s, bool optional, bool* workspace_short);

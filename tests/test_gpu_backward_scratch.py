@@ -90,3 +90,35 @@ def test_two_threads_on_one_stream(named):
     threads = [threading.Thread(target=work, args=(n,)) for n in (0, 1)]
     [t.start() for t in threads], [t.join() for t in threads]
     assert wrong == [0, 0]
+
+
+def test_when_the_scratch_is_worth_bringing():
+    lib = binding.load_library()
+    for T, O, K, f32, bf16 in ((197, 3072, 768, 1, 1), (4, 256, 256, 0, 0), (64, 256, 64, 0, 0), (65, 256, 64, 1, 0), (788, 256, 768, 1, 0),
+                               (1, 384, 64, 1, 1), (12608, 2304, 768, 1, 1), (1576, 768, 2048, 0, 0), (4, 32, 64, 0, 0), (0, 256, 256, 0, 0)):
+        assert [lib.nm_backward_input_scratch_pays(O, K, T, dtype, None) for dtype in (0, 1)] == [f32, bf16], (T, O, K)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("T,K,O,alone", [(4, 256, 256, 0), (64, 64, 256, 0), (197, 768, 3072, 1)])
+def test_launches_of_a_call_and_of_a_recorded_one(T, K, O, alone, dtype):
+    W, dY = layer(T, K, O, 20)
+    out, recorded = (torch.zeros(T, K, dtype=dtype, device="cuda") for _ in range(2))
+    call = lambda y: nm.nm_linear_backward_input(W, dY, out=y)
+    call(out)
+    allocations = lambda: torch.cuda.memory_stats()["allocation.all.allocated"]
+    before = allocations()
+    call(out)
+    assert allocations() - before == alone  # the copy's scratch: two launches
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(graph, stream=side):
+        before = allocations()
+        call(recorded)
+        assert allocations() - before == 1
+    for _ in range(3):
+        recorded.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(recorded, out)
