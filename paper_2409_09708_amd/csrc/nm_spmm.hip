@@ -2100,34 +2100,40 @@ static hipError_t dispatch_gemm(const GemmArgs& g, int pick, hipStream_t s) {
 }
 
 // Tiles of the ragged form where X travels through registers: 64 x 64, or, from 150 of them on, 128 x 128 where those are estimated
-// faster.  The blocks of a unit's list run `at_once` of them together; `share` is what the units' number of blocks adds beyond whole lists.
-// Fitted on 24800 shapes (60 to 40000 tokens, 72 .. 4096 deep and wide); the choice takes 1.002 of the better tile's time on average, 1.7 %
-// of the shapes lose more than 5 %.  (Two thresholds on the tiles, 208 and 336, took 1.042.)  64 and 128, us: 7410 x 84 -> 1317 at 2:4 in
-// bfloat16 13.5 and 17.8, 18048 x 476 -> 159 at 3:4 in float32 12.1 and 17.2; 9906 x 1932 -> 648 at 1:4 41.6 and 31.8, 35674 x 84 -> 2697 at
-// 2:4 in float32 122 and 94.
+// faster.  The blocks of a unit's list run `at_once` of them together; `share` is what the units' number of blocks adds beyond whole
+// lists.  `pieces`: rows of Y in whole aligned 16-byte pieces; without, a large tile's write-out is most of a short reduction.  Fitted on
+// 24800 shapes (60 to 40000 tokens, 72 .. 4096 deep and wide; rms 5 and 6 %); the choice takes 1.0015 of the better tile's time on
+// average, 1.1 % of the shapes lose more than 5 %.  (Two thresholds on the tiles, 208 and 336, took 1.042.)  64 and 128, us: 7410 x 84 ->
+// 1317 at 2:4 in bfloat16 13.5 and 17.8, 18048 x 476 -> 159 at 3:4 in float32 12.1 and 17.2; 33413 x 140 -> 1896 at 2:4 in bfloat16 51.5
+// and 41.5, 9906 x 1932 -> 648 at 1:4 41.6 and 31.8, 35674 x 84 -> 2697 at 2:4 in float32 122 and 94.
 struct RaggedModel {
-  double start, step, epi[2], busy, byte, share;  // epi: [bfloat16]; byte: a MB of output
+  double start, step, busy, share;
+  double byte[2];    // a MB of output: [pieces]
+  double epi[2][2];  // [bfloat16][pieces]
   int at_once;
 };
 constexpr RaggedModel kRaggedModel[2][2] = {  // [2:4 form][128 x 128]
-    {{4.25, 0.284, {0.325, 0.499}, 0.639, 0.065, 0, 4}, {5.14, 0.628, {0.96, 2.61}, 0.556, 0.112, 0.083, 2}},
-    {{4.22, 0.244, {0.52, 0.685}, 0.541, 0.045, 0, 4}, {4.72, 0.477, {1.41, 2.98}, 0.504, 0.082, 0.065, 2}}};
-static double ragged_estimate(bool sparse_form, bool large, int64_t O, int64_t K, int64_t T, bool out_bf16) {
+    {{4.20, 0.284, 0.643, 0, {0.047, 0.082}, {{0.449, 0.160}, {0.576, 0.115}}, 4},
+     {4.78, 0.620, 0.549, 0.101, {0.075, 0.135}, {{1.792, 0.264}, {3.139, 0.109}}, 2}},
+    {{4.23, 0.244, 0.536, 0, {0.051, 0.046}, {{0.535, 0.422}, {0.715, 0.297}}, 4},
+     {4.37, 0.470, 0.499, 0.077, {0.054, 0.094}, {{2.177, 0.912}, {3.492, 0.528}}, 2}}};
+static double ragged_estimate(bool sparse_form, bool large, int64_t O, int64_t K, int64_t T, bool out_bf16, bool pieces) {
   const RaggedModel& m = kRaggedModel[sparse_form][large];
   const int64_t side = large ? 128 : 64, tiles = ((O + side - 1) / side) * ((T + side - 1) / side);
   const int64_t list = ((tiles + 7) / 8 + 31) / 32, rest = list % m.at_once;  // blocks of a unit; of those, past the last full set
   const double steps = (double)((K + 63) / 64);
-  return m.start + (steps * m.step + m.epi[out_bf16]) * ((double)(list / m.at_once) * (1.0 + m.busy * (m.at_once - 1)) +
-                                                         (rest ? 1.0 + m.busy * (double)(rest - 1) : 0.0)) +
-         m.byte * 1e-6 * (double)O * (double)T * (out_bf16 ? 2.0 : 4.0) + m.share * steps * (double)tiles / kModelUnits;
+  return m.start + (steps * m.step + m.epi[out_bf16][pieces]) * ((double)(list / m.at_once) * (1.0 + m.busy * (m.at_once - 1)) +
+                                                                 (rest ? 1.0 + m.busy * (double)(rest - 1) : 0.0)) +
+         m.byte[pieces] * 1e-6 * (double)O * (double)T * (out_bf16 ? 2.0 : 4.0) + m.share * steps * (double)tiles / kModelUnits;
 }
-static int ragged_tile(bool sparse_form, int64_t O, int64_t K, int64_t T, bool out_bf16) {
+static int ragged_tile(bool sparse_form, int64_t O, int64_t K, int64_t T, bool out_bf16, bool pieces) {
   if (((O + 127) / 128) * ((T + 127) / 128) < 150) return 64;
-  return ragged_estimate(sparse_form, true, O, K, T, out_bf16) < ragged_estimate(sparse_form, false, O, K, T, out_bf16) ? 128 : 64;
+  auto estimate = [&](bool large) { return ragged_estimate(sparse_form, large, O, K, T, out_bf16, pieces); };
+  return estimate(true) < estimate(false) ? 128 : 64;
 }
 // Not in the public header, for tests.
-extern "C" int32_t nm_internal_ragged_tile(int32_t sparse_form, int64_t O, int64_t K, int64_t T, int32_t out_bf16) {
-  return ragged_tile(sparse_form != 0, O, K, T, out_bf16 != 0);
+extern "C" int32_t nm_internal_ragged_tile(int32_t sparse_form, int64_t O, int64_t K, int64_t T, int32_t out_bf16, int32_t pieces) {
+  return ragged_tile(sparse_form != 0, O, K, T, out_bf16 != 0, pieces != 0);
 }
 
 // The ragged form of the tiled kernel.  K and the rows of X in whole 16-byte pieces: the
@@ -2155,7 +2161,7 @@ static hipError_t launch_ragged(GemmArgs g, hipStream_t s) {
       default: return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 4, 4, 3, 0>, GemmCfg<SPARSE, 2, 2, 4, 4, 3>{}, once[3]);
     }
   }
-  if (ragged_tile(SPARSE, g.O, g.K, g.T, g.out_bf16 != 0) == 128)
+  if (ragged_tile(SPARSE, g.O, g.K, g.T, g.out_bf16 != 0, g.vec_store != 0) == 128)
     return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 4, 4, 2, 2>, GemmCfg<SPARSE, 2, 2, 4, 4, 2>{}, once[4]);
   if constexpr (!SPARSE)
     if (tiles_mid < 64 && g.K >= 1280) return go(nm_gemm_ragged_kernel<SPARSE, 2, 2, 2, 2, 2, 4>, GemmCfg<SPARSE, 2, 2, 2, 2, 2>{}, once[6]);

@@ -13,13 +13,15 @@ from test_gpu_ragged import layer
 
 def tile(T, K, O, N, dtype):
     i64 = ctypes.c_int64
-    return load_library().nm_internal_ragged_tile(int(N <= 2), i64(O), i64(K), i64(T), int(dtype == torch.bfloat16))
+    bf16 = dtype == torch.bfloat16
+    return load_library().nm_internal_ragged_tile(int(N <= 2), i64(O), i64(K), i64(T), int(bf16), int(O % (8 if bf16 else 4) == 0))
 
 
 # (one list of blocks per unit more for the small tiles; 208 to 336 and past 512 large ones, where those are the second round that is
-# nearly empty; outputs of half the memory-side cache)
+# nearly empty; rows of the output in whole pieces)
 @pytest.mark.parametrize("T,K,O,N,dtype,want", [
     (7410, 84, 1317, 2, torch.bfloat16, 64), (6053, 76, 1774, 2, torch.bfloat16, 64), (10403, 100, 279, 4, torch.float32, 64),
+    (33413, 140, 1896, 2, torch.bfloat16, 128), (6061, 116, 6096, 2, torch.bfloat16, 128),
     (9545, 548, 354, 1, torch.float32, 64), (35674, 84, 2697, 2, torch.float32, 128), (15713, 444, 1188, 3, torch.float32, 128),
     (9460, 1764, 324, 1, torch.float32, 128), (926, 2740, 96, 1, torch.bfloat16, 64)])
 def test_choice(T, K, O, N, dtype, want):
