@@ -6,8 +6,9 @@
 // between calls.
 // Measured per call: the projection above 7.3 -> 4.1 us; 768 -> 1000 at 4:8 on 8 tokens, plain, 8.2 -> 6.2 (5.0 with a kernel
 // that has become faster since); the twelve calls and sixteen allocations that compress a block by scores and expand it 94 -> 63. The training
-// products and the int8 layer on small operands: dX 7.2 -> 4.0 us, dW (two launches) 11 -> 8, a prepared int8 call 7.5 -> 3.6; a plain
-// call, whose scratch is looked up in the table that Python keeps, 4.0 -> 3.5.  (A launch alone takes the host 3.0 to 3.5.)
+// products and the int8 layer on small operands: dX in one launch 7.2 -> 4.0 us (in two, with scratch of the call's own, 7.5 to 8.0), dW
+// in two launches 11 -> 8, a prepared int8 call 7.5 -> 3.6; a plain call, whose scratch is looked up in the table that Python keeps,
+// 4.0 -> 3.5.  (A launch alone takes the host 3.0 to 3.5; all of these vary by a quarter from host to host.)
 #include <Python.h>
 
 #include <ATen/PythonTorchFunctionTLS.h>

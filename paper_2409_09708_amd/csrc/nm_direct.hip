@@ -1,17 +1,18 @@
 // One launch from the packed weight to the product of a few tokens.  A call that brings a packed weight and no prepared
 // copy of it otherwise runs the stream-order pre-pass over the weight and then the tiled kernel; at up to a few dozen
-// tokens the pre-pass is the longer of the two and its output is read once.  Here a block decodes the weight of its 32
-// out-features into LDS as the operand of the matrix instructions and multiplies it with up to 64 tokens.
+// tokens the pre-pass is the longer of the two and its output is read once.  Here a block decodes the weight of its 32 or 16
+// out-features into LDS as the operand of the matrix instructions and multiplies it with up to 64 tokens; a second form, further
+// down, takes 64 out-features and 128 tokens.
 //
 // What bounds it: latency.  768 -> 1000 at 4:8 and 8 tokens is 1.3 MB, under 1 us of HBM time; what takes time is one
 // round trip to memory, decoding 16 weights per lane and pass (the 2:4 operand in registers, the dense one with a 2-byte LDS write
 // per kept value), and a serial chain of K / 64 steps.  So a block is small (768 out-features are 24 of them per 64 tokens), all
-// four waves decode, the loads of two spans of 256 reduction positions are in flight in registers while a third is multiplied,
-// none of them under a condition (which would make every span wait for the next one's), and a span has one
-// barrier; in blocks of 16 or 32 tokens four spans share one (launch_level).  Conditions and 2-byte writes everywhere, before: 197 tokens x
-// 768 -> 768 at 1:4 5.5 us, now 4.95; 32 x 2048 -> 1024 at 4:8 10.5 and 8.8; 16 x 4096 -> 32768 at 4:8 75 and 55.  Which products it takes is decided in nm_spmm.hip
-// (direct_form).  In a graph, pre-pass and product before: 768 -> 1000 at 4:8 and 8 tokens 9.4 -> 3.7 us, 16 x 3072 ->
-// 16384 at 4:16, where the weight's 100 MB would be read and written once more, 20.5.
+// four waves decode, the loads of two spans of 256 reduction positions are in flight in registers while a third is multiplied, and a
+// span has one barrier; in blocks of 16 or 32 tokens four spans, those that there are, share one (launch_level).  No load of a span is
+// under a condition of its own, which would make the span wait for the next one's.  With such conditions, and with 2-byte writes
+// everywhere: 197 tokens x 768 -> 768 at 1:4 5.4 us, now 4.9; 32 x 2048 -> 1024 at 4:8 10.4 and 8.7; 16 x 4096 -> 32768 at 4:8 75.7 and 54.8.
+// Which products it takes is decided in nm_spmm.hip (direct_form).  In a graph, pre-pass and product, and here: 768 -> 1000 at 4:8 and 8
+// tokens 8.1 and 3.7 us, 16 x 3072 -> 16384 at 4:16, where the weight's 100 MB are read and written once more, 41.7 and 19.2.
 //
 // Two summation orders, so that a product is the same bytes whichever kernel of its route computes it:
 //   PACKED = false  the tiled kernel's (nm_spmm.hip): the sum starts from the bias; the dense instruction takes the
@@ -411,13 +412,14 @@ __global__ void __launch_bounds__(256) nm_direct_kernel(const DirectArgs a) {
 // The same for more tokens: blocks of 64 out-features x 128 tokens on eight waves, in the tiled kernel's summation order.
 // Against the pre-pass and the tiled kernel it saves a launch (about 4 us) and the weight's way through memory, and it decodes the
 // weight once per 128 tokens: it wins while its blocks are one round or two on the chip and the reduction is not long (the choice is
-// nm_spmm.hip's).  A whole call in a graph, before and after: 1576 x 1024 -> 1024 at 2:8 11.1 -> 8.9 us, 788 x 768 -> 2304 at 1:8 11.2 ->
-// 7.4, 6304 x 256 -> 256 7.2 -> 4.9, 1579 x 1000 -> 1001 in fp32 13.3 -> 11.4; 2048 tokens x 3072 -> 768, which stays with the two, would lose.
+// nm_spmm.hip's).  A whole call in a graph, the two launches and here: 1576 x 1024 -> 1024 at 2:8 10.7 and 8.4 us, 788 x 768 -> 2304 at 1:8 10.8
+// and 6.9, 6304 x 256 -> 256 at 1:8 6.7 and 4.3, 1579 x 1000 -> 1001 in fp32 12.6 and 11.2; 2048 tokens x 3072 -> 768, which stays with the
+// two, would lose.
 // What bounds it: a span of 128 reduction positions brings 40 KB into a unit, 0.4 us at the 100 GB/s that a unit gets, and
-// moves 137 KB through its LDS; it takes 0.5 us at 1:16 and 0.59 at 2:8.  So the loads of two spans are in flight, the lanes decode in
-// registers (2-byte LDS writes per kept value: 9.4 us for the 8.9 above), and two whole spans at a time run without conditions.
-// Slower: four waves of 64 x 32 (12.0), half the waves bringing and half multiplying (10.3), activations straight from
-// memory into the operand registers (12.8: rows 2 KB apart share the first-level cache's lines).
+// moves 137 KB through its LDS; it takes 0.5 us at 1:16 and 0.59 at 2:8 (LDS busy for 0.37 of a unit's cycles, matrix pipes for 0.1).  So the loads of two spans are in flight, the lanes decode in
+// registers, and two whole spans at a time run without conditions.  Slower, 1576 x 1024 -> 1024 on the card where this took 8.9: 2-byte LDS
+// writes per kept value (9.4), four waves of 64 x 32 (12.0), half the waves bringing and half multiplying (10.3), activations straight
+// from memory into the operand registers (12.8: rows 2 KB apart share the first-level cache's lines).
 // ---------------------------------------------------------------------------------------------
 template <int N, int M>
 struct WideCfg {

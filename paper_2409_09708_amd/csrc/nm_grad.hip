@@ -429,11 +429,13 @@ nm_tgemm_kernel(const TGemmArgs a) {
 // ranges itself, range by range (pair by pair) in the order in which grad_reduce_kernel adds the partial tiles: the same bits,
 // without the partial tiles (up to 64 MB written and read back, whatever the layer) and without the second launch, which bound the
 // short reductions.  The smaller tile makes twice the blocks of them, as nothing else spreads the work.  A step of 32 tokens takes
-// 0.29 us: LDS moves 64 KB in it (0.21 at its 128 bytes a cycle), the matrix instructions take half of that.  Eight waves of 64 x 32
+// 0.29 us, some 610 cycles, and keeps nothing busy: at 1576 x 768 -> 2304 the fragments hold LDS for 0.22 of a unit's cycles (48 KB a
+// step, and 16 KB of copies beside them), the matrix pipes run for 0.26, and the waves, one block of them to a unit, are stalled at a
+// wait for 0.35 of their time and wait to issue for 0.28: what bounds it is the chain of a step, barrier, reads, products.  Eight waves of 64 x 32
 // and fragments read one step ahead: with one wave of 64 x 64 on each SIMD nothing covers a range's additions and the waits, and a step
-// takes 0.38; with eight stages instead of four it is no faster.  us, f32 gradients, before and now: 20 tokens x 768 -> 2304
-// 11.7 and 5.6, 197 x 768 -> 2304 15.3 and 8.8, 394 x 1024 -> 4096 29.6 and 11.9, 788 x 768 -> 3072 27.2 and 15.9, 1576 x 768 -> 2304
-// 28.3 and 21.0.
+// takes 0.38; with eight stages instead of four it is no faster.  us, f32 gradients, in two launches and here: 20 tokens x 768 -> 2304
+// 10.8 and 4.9, 197 x 768 -> 2304 13.9 and 7.2, 394 x 1024 -> 4096 28.5 and 11.3, 788 x 768 -> 3072 28.2 and 13.7, 1576 x 768 -> 2304
+// 27.6 and 21.3.
 struct SCfg {
   static constexpr int WI = 2, WJ = 4, IT = 4, JT = 2;
   static constexpr int NW = WI * WJ, NT = NW * 64;

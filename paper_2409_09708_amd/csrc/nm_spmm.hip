@@ -2137,7 +2137,7 @@ extern "C" int32_t nm_internal_ragged_tile(int32_t sparse_form, int64_t O, int64
 }
 
 // The ragged form of the tiled kernel.  K and the rows of X in whole 16-byte pieces: the
-// tile of the aligned form.  A product of 1579 x 1000 -> 1001 at 2:8 takes 8.1 us that way and 10.7 through registers.
+// tile of the aligned form.  A product of 1579 x 1000 -> 1001 at 2:8 takes 8.0 us that way and 11.0 through registers.
 // Other rows: ragged_tile's choice.  (The gather kernel, which still takes such shapes when there is no workspace: 1096 us.)
 template <bool SPARSE>
 static hipError_t launch_ragged(GemmArgs g, hipStream_t s) {
@@ -2193,10 +2193,11 @@ static bool dense_transposed_takes(int64_t R, int64_t I, int64_t T) {
 // What the persistent kernel does not take, few tokens above all, the tiled kernel multiplies from the same copy where the two are
 // estimated faster (by a fifth where the result is four times as wide as the reduction is long) than nm_grad.hip's kernel, whose
 // tiles of 128 x 256 are a handful of blocks then, each with the whole reduction in a row, 0.32 us per 32 positions.  Tokens x
-// reduction -> width: 197 x 3072 -> 768 37 -> 17.7 us, x 768 -> 768 13.9 -> 9.0, 1576 x 4096 -> 1024 50.5 -> 27.5; 394 x 768 -> 3072, 13.2 us,
-// would take 15.2.  Over 865 shapes (1 to 20000 tokens, 64 .. 4096 wide and deep, in a graph) such calls take 0.735 of the time on
-// average (the better of the two 0.72), 4 of them 5 % more; the sums are the same bits.  The copy is optional: without the
-// workspace for it the call runs as it did.  The constants are fitted on the same shapes (rms 5 % for the one kernel, 10 % for the two).
+// reduction -> width, float32: 197 x 3072 -> 768 37.1 -> 17.2 us, x 768 -> 768 13.5 -> 8.6, 1576 x 4096 -> 1024 52.4 -> 27.3; 394 x 768 ->
+// 3072, 14.1 us, would take 15.2.  The sums are the same bits.  The copy is optional: without the workspace for it the
+// call runs as it did.  The constants are fitted on 865 shapes of 1 to 20000 tokens, 64 .. 4096 wide and deep, float32 (rms 5 % for the one
+// kernel, 10 % for the two); of 10400 other shapes that this chose the two launches take 0.55 of the one kernel's time on average (0.57
+// in bfloat16).
 static bool dense_transposed_tiles(int64_t R, int64_t I, int64_t T) {
   if (R % 64 || R > (1 << 22) || I > (1 << 24) || T >= (1ll << 31) || dense_transposed_takes(R, I, T)) return false;
   const double weight_mb = (double)((I + 255) / 256 * 256) * (double)R * 2e-6;
@@ -2335,12 +2336,12 @@ static bool packed_path(const SpmmArgs& a) {
 
 // A call that prepares and multiplies in one takes the kernel that decodes the weight itself (nm_direct.hip) where its
 // estimate is below the pre-pass and the tiled kernel together.  It decodes the weight once per 64 tokens, so it wins as
-// long as its blocks of 32 out-features x 64 tokens are few rounds on the chip, later for a shallow weight.  Both fitted on
-// 3000 shapes per form (64 .. 16384 deep, 64 .. 49152 wide, 1 .. 1000 tokens, in a graph); with blocks of 64 tokens the route
-// it picks cost 1 % on average over the better of the two.  Up to 32 tokens the kernel may take smaller blocks, 0.44 - 1.0 of
-// the time (launch_level there), which the estimate does not know: near the border such a call still goes to the two launches.
-// Pre-pass and product against it: 768 -> 1000 at 4:8 and 8 tokens 9.4 and 4.9 us, 768 -> 768 at 394 tokens 9.2 and 6.3;
-// 2048 -> 16384 at 1:8 and 208 tokens 33.4 and 68.9, which stays with the two.
+// long as its blocks of 32 out-features x 64 tokens are few rounds on the chip, later for a shallow weight.  Both estimates were fitted on
+// 3000 shapes per form (64 .. 16384 deep, 64 .. 49152 wide, 1 .. 1000 tokens, in a graph) when the loads of blocks of 64 tokens still
+// carried conditions, and they know neither the smaller blocks of up to 32 tokens (launch_level there) nor the faster loads.  They still
+// choose well between the two: over 47300 shapes (1 .. 50000 tokens, 64 .. 8192 deep, 64 .. 24576 wide, both output types) the choice takes
+// 1.003 of the better one's time on average, 1.9 % of the shapes lose more than 5 %.  Pre-pass and product against it: 768 -> 1000 at
+// 4:8 and 8 tokens 8.1 and 3.7 us, 768 -> 768 at 394 tokens 9.0 and 5.8, 1024 -> 4096 at 197 tokens 17.4 and 9.6.
 // Its sums are those of the tiled kernel; a layer that the persistent kernel or a cut reduction would sum in another
 // order stays there.
 constexpr TileModel kDirectModel[2] = {{32, 64, 3.81, 0.130, 0.57, 1.09}, {32, 64, 3.22, 0.117, 0.85, 0.68}};  // [2:4 form]
@@ -2348,10 +2349,12 @@ constexpr TileModel kDirectModel[2] = {{32, 64, 3.81, 0.130, 0.57, 1.09}, {32, 6
 // launches: spans of 128 reduction positions, and of a block's span and its write-out the parts that grow with the kept
 // values of 16 weights and with the bytes of an output.  Fitted on 3200 shapes (40 .. 8000 tokens, 64 .. 4096 deep and wide, whole and
 // ragged, in a graph) with an rms of 8 %, but for the smallest, which take 4.5 us where the model has 3.7.  It has to be a fifth
-// faster than the first form, whose estimate is the rougher one; up to 64 tokens half its block would be empty, and a reduction of
-// 3072 and more, whose spans cost more than the tiled kernel's steps, it never won.  With it those calls take 0.935 of the time on average (the best
-// route of each 0.922), a third of them 5 % less or better, 18 of 3200 5 % more: 551 x 256 -> 129 at 4:8 stays with the first form
-// (4.2 us, 5.7), 788 x 768 -> 2304 at 1:8 7.4 and 11.2 in two launches, 1576 x 3072 -> 768 at 2:8 17.5 in two and 22.8.
+// faster than the first form, whose estimate is the rougher one.  Where it is chosen it takes 0.73 of the better other route's time on
+// average (8400 of 60500 shapes as above), 0.5 % of them lose more than 5 %: 551 x 256 -> 129 at 4:8 stays with the first form
+// (3.6 us, 5.7), 788 x 768 -> 2304 at 1:8 6.9 and 10.8 in two launches, 1576 x 3072 -> 768 at 2:8 17.4 in two and 22.8.
+// It is not asked up to 64 tokens, where half its block would be empty, nor for reductions of 3072 and more, which it was not fitted on;
+// both leave something: 42 x 2232 -> 16032 at 4:8 takes 41 us in two launches and would take 22, 204 x 3968 -> 7488 at 4:16 52 and 29.
+// Of all 60500 shapes 10 % are more than 5 % from their best route, 1.02 of its time on average.
 struct WideModel {
   double start, span, kept, epi, byte, busy;
 };
