@@ -605,8 +605,8 @@ def _workspace(nbytes: int, device, stream=None):
     key = (device.type, index, handle)
     ws = _WORKSPACES.get(key)
     if ws is None or ws.numel() < nbytes:
-        if ws is not None and handle:
-            ws.record_stream(torch.cuda.ExternalStream(handle, device=index))
+        if ws is not None:
+            ws.record_stream(torch.cuda.ExternalStream(handle, device=index) if handle else torch.cuda.default_stream(index))
         ws = torch.empty((max(nbytes, 1 << 20),), dtype=torch.uint8, device=device)
         _WORKSPACES[key] = ws
     return ws
